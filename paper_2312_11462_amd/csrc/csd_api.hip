@@ -132,7 +132,7 @@ static int32_t create_impl(csd_model *mod, const void *const *weights, hipStream
     }
     int32_t rc;
     if ((rc = csd_pack_weights(mod, weights, st)) != CSD_OK) return rc;
-    if (mod->mfma && (rc = csd_gemm_setup()) != CSD_OK) return rc;
+    if (mod->mfma && ((rc = csd_gemm_setup()) != CSD_OK || (rc = csd_tall_setup()) != CSD_OK)) return rc;
 
     const int m_pad = (mod->m_max + 15) / 16 * 16;
     int wmax = d > F ? d : F;
@@ -153,8 +153,15 @@ static int32_t create_impl(csd_model *mod, const void *const *weights, hipStream
         for (int i = 0; i < 4; i++) mod->x_plane[i] = (size_t)m_pad * widths[i];
         if ((rc = csd_chain_setup()) != CSD_OK) return rc;
     }
-    // the per-call scratch is one block, carved the same way wherever it lives
     void *p;
+    if (mod->mfma && c.arch == 1) {
+        const long long enc_rows = (long long)c.max_batch * c.enc_len;
+        mod->enc_act_rows = (int)((enc_rows < CSD_CROSS_ROWS ? enc_rows : CSD_CROSS_ROWS) + 15) / 16 * 16;
+        CSD_HIP(hipMalloc(&p, (size_t)2 * 2 * mod->enc_act_rows * d));
+        mod->allocs.push_back(p);
+        mod->enc_act = p;
+    }
+    // the per-call scratch is one block, carved the same way wherever it lives
     CSD_HIP(hipMalloc(&p, csd_scratch_carve(mod, nullptr, nullptr)));
     mod->allocs.push_back(p);
     ScratchPtrs sp;

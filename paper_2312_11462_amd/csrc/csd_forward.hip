@@ -68,7 +68,7 @@ __global__ void k_copy_cols(const T *__restrict__ src, int K, int N_src, T *__re
 // barriers.
 template <int NT, int MT, int U>
 __global__ __launch_bounds__(512) void k_gemm_ws(const u32x4 *__restrict__ Wp, const bf16_t *__restrict__ act, size_t plane,
-                                                 int mtp, float *__restrict__ part, int M, int Mtot, int K, int N, int S) {
+                                                 int mtp, float *__restrict__ part, int M, int K, int N, int S) {
     extern __shared__ __align__(16) char wg_smem[];
     constexpr int CH = U * MT * 2 * 64;                      // 16-byte fragments per chunk
     static_assert(CH % 256 == 0, "chunk must divide over the staging waves");
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(512) void k_gemm_ws(const u32x4 *__restrict__ Wp, c
 #pragma unroll
                 for (int j = 0; j < NT; j++)
                     if (tv[j]) {
-                        float *o = part + ((size_t)s * Mtot + row) * N + (size_t)(tile0 + j) * 16 + 4 * g;
+                        float *o = part + ((size_t)s * M + row) * N + (size_t)(tile0 + j) * 16 + 4 * g;
                         *reinterpret_cast<f32x4 *>(o) = acc[mt][j];
                     }
             }
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(512) void k_gemm_ws(const u32x4 *__restrict__ Wp, c
 // its matrix instructions), and nothing goes through LDS that only one wave needs.
 template <int CT, int RW, int U>
 __global__ __launch_bounds__(512) void k_gemm_rs(const u32x4 *__restrict__ Wp, const bf16_t *__restrict__ act, size_t plane,
-                                                 int mtp, float *__restrict__ part, int M, int Mtot, int K, int N, int S) {
+                                                 int mtp, float *__restrict__ part, int M, int K, int N, int S) {
     extern __shared__ __align__(16) char wg_smem[];
     constexpr int CH = U * CT * 64;                          // 16-byte weight fragments (per lane) of a chunk
     constexpr int ST = CH / 256;                             // staging loads per staging thread and chunk
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(512) void k_gemm_rs(const u32x4 *__restrict__ Wp, c
 #pragma unroll
                 for (int ct = 0; ct < CT; ct++)
                     if (tile0 + ct < n_tiles) {
-                        float *o = part + ((size_t)s * Mtot + row) * N + (size_t)(tile0 + ct) * 16 + 4 * g;
+                        float *o = part + ((size_t)s * M + row) * N + (size_t)(tile0 + ct) * 16 + 4 * g;
                         *reinterpret_cast<f32x4 *>(o) = acc[r][ct];
                     }
             }
@@ -685,42 +685,38 @@ ProfScope::~ProfScope() {
 
 #define WG_U_MAX 4      /* k-steps per chunk of the workgroup-tiled GEMMs */
 template <int MT>
-static int32_t launch_gemm_ws_mt(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int Mtot, int S,
+static int32_t launch_gemm_ws_mt(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int S,
                                  int groups, hipStream_t st) {
     const size_t lds = (size_t)2 * WG_U_MAX * MT * 2 * 64 * 16;      // allowed at csd_gemm_setup
     hipLaunchKernelGGL((k_gemm_ws<1, MT, WG_U_MAX>), dim3(groups * S), dim3(512), lds, st, reinterpret_cast<const u32x4 *>(w.data),
-                       act, plane, mtp, part, M, Mtot, w.K, w.N, S);
+                       act, plane, mtp, part, M, w.K, w.N, S);
     return CSD_OK;
 }
 
-// Blocks of up to 32 rows (of Mtot in the call): one column tile per wave, 64 columns per workgroup; K is split
+// Blocks of up to 32 rows: one column tile per wave, 64 columns per workgroup; K is split
 // until there are two workgroups per compute unit: the light workgroups share a compute unit, and two per unit stream
 // faster than one (measured: 3.84 -> 3.69 ms per step at 6 rows of the 7B shape; beyond 512 the partial sums cost
 // more).  Two column tiles per wave, 128 columns per workgroup, were slower here (4.02 against 3.86 ms at 6 rows,
-// 5.83 against 5.68 ms at 24 rows of batch 8).  *S_io: the number of K splits, chosen here when 0 (later row chunks
-// of the same call must use the same).
-static int32_t launch_gemm_ws(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int Mtot, int *S_io,
+// 5.83 against 5.68 ms at 24 rows of batch 8).  *S_used: the number of K splits.
+static int32_t launch_gemm_ws(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int *S_used,
                               hipStream_t st) {
     const int n_tiles = w.N / 16, KS = w.K / 32, groups = (n_tiles + 3) / 4;
-    int S = *S_io;
-    if (S == 0) {
-        S = 1;
-        while (groups * S < 512 && S * 2 <= w.S && KS / (S * 2) >= 2 * WG_U_MAX) S *= 2;
-        *S_io = S;
-    }
+    int S = 1;
+    while (groups * S < 512 && S * 2 <= w.S && KS / (S * 2) >= 2 * WG_U_MAX) S *= 2;
+    *S_used = S;
     switch ((M + 15) / 16) {
-    case 1: return launch_gemm_ws_mt<1>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
-    case 2: return launch_gemm_ws_mt<2>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
+    case 1: return launch_gemm_ws_mt<1>(w, act, plane, mtp, part, M, S, groups, st);
+    case 2: return launch_gemm_ws_mt<2>(w, act, plane, mtp, part, M, S, groups, st);
     default: return CSD_ESHAPE;       // taller blocks take the row-split form
     }
 }
 
 template <int CT, int RW>
-static int32_t launch_gemm_rs_t(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int Mtot, int S,
+static int32_t launch_gemm_rs_t(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int S,
                                 int groups, hipStream_t st) {
     const size_t lds = (size_t)2 * WG_U_MAX * CT * 64 * 16;          // allowed at csd_gemm_setup
     hipLaunchKernelGGL((k_gemm_rs<CT, RW, WG_U_MAX>), dim3(groups * S), dim3(512), lds, st, reinterpret_cast<const u32x4 *>(w.data),
-                       act, plane, mtp, part, M, Mtot, w.K, w.N, S);
+                       act, plane, mtp, part, M, w.K, w.N, S);
     return CSD_OK;
 }
 
@@ -730,23 +726,22 @@ static int32_t launch_gemm_rs_t(const GemmW &w, const bf16_t *act, size_t plane,
 // compute unit as the shape allows, the wider workgroup winning a tie (it reads the activation rows less often).
 // Measured per launch at 128 rows of the 7B shape, against 16 tiles and 128 workgroups for every matrix: QKV 40.6 ->
 // 33.1 us (12 tiles, 4 splits, 256 workgroups), O and down 30.6 -> 23.6 (8, 8, 256), gate|up 57.2 -> 49.1 (11, 2, 252).
-static int rs_splits(int groups, int KS, int Mtot, int N, size_t part_floats) {
+static int rs_splits(int groups, int KS, int M, int N, size_t part_floats) {
     int S = 1;
-    while (groups * (S + 1) <= 256 && S < 8 && KS / (S + 1) >= 2 * WG_U_MAX && (size_t)(S + 1) * Mtot * N <= part_floats) S++;
+    while (groups * (S + 1) <= 256 && S < 8 && KS / (S + 1) >= 2 * WG_U_MAX && (size_t)(S + 1) * M * N <= part_floats) S++;
     return S;
 }
-// rows: the rows of this launch (33 to 144), Mtot: the rows of the whole call (the partial-sum buffer holds S x Mtot x N
-// floats), S_fixed: the number of splits when an earlier row chunk of the call has chosen it, else 0.
-static void rs_plan(int N, int K, int rows, int Mtot, size_t part_floats, int S_fixed, int *ct_out, int *S_out) {
+// rows: 33 to 144; the partial-sum buffer holds S x rows x N floats.
+static void rs_plan(int N, int K, int rows, size_t part_floats, int *ct_out, int *S_out) {
     const int n_tiles = N / 16, KS = K / 32, MT = (rows + 15) / 16;
     const int rw = MT <= 8 ? 2 : 3;          // row tiles per compute wave: waves past the block's rows only pass the barriers
     static const int cts2[] = {16, 12, 11, 8, 6, 0}, cts3[] = {8, 6, 0};
     const int *cts = rw == 2 ? cts2 : cts3;
-    int ct = cts[0], S = S_fixed;
+    int ct = cts[0], S = 1;
     double best = -1.0;
     for (int i = 0; cts[i]; i++) {
         const int groups = (n_tiles + cts[i] - 1) / cts[i];
-        const int s = S_fixed ? S_fixed : rs_splits(groups, KS, Mtot, N, part_floats);
+        const int s = rs_splits(groups, KS, rows, N, part_floats);
         const int wgs = groups * s;
         const double fill = (double)wgs / (256.0 * ((wgs + 255) / 256));
         if (fill > best) best = fill, ct = cts[i], S = s;
@@ -758,28 +753,28 @@ int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats,
     if (!ct || !S) return CSD_ENULL;
     if (N <= 0 || K <= 0 || N % 16 || K % 32 || rows < 1 || rows > 144) return CSD_EINVAL;
     int c = 0, s = 0;
-    rs_plan(N, K, rows, rows, part_floats, 0, &c, &s);
+    rs_plan(N, K, rows, part_floats, &c, &s);
     *ct = c;
     *S = s;
     return CSD_OK;
 }
 static int32_t launch_gemm_rs(const csd_model *mod, const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M,
-                              int Mtot, int *S_io, hipStream_t st) {
+                              int *S_used, hipStream_t st) {
     const int n_tiles = w.N / 16, MT = (M + 15) / 16;
     const int rw = MT <= 8 ? 2 : 3;
     int ct = 0, S = 0;
-    rs_plan(w.N, w.K, M, Mtot, mod->part_floats, *S_io, &ct, &S);
-    *S_io = S;
+    rs_plan(w.N, w.K, M, mod->part_floats, &ct, &S);
+    *S_used = S;
     const int groups = (n_tiles + ct - 1) / ct;
     if (rw == 2) switch (ct) {
-        case 16: return launch_gemm_rs_t<16, 2>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
-        case 12: return launch_gemm_rs_t<12, 2>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
-        case 11: return launch_gemm_rs_t<11, 2>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
-        case 8: return launch_gemm_rs_t<8, 2>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
-        default: return launch_gemm_rs_t<6, 2>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
+        case 16: return launch_gemm_rs_t<16, 2>(w, act, plane, mtp, part, M, S, groups, st);
+        case 12: return launch_gemm_rs_t<12, 2>(w, act, plane, mtp, part, M, S, groups, st);
+        case 11: return launch_gemm_rs_t<11, 2>(w, act, plane, mtp, part, M, S, groups, st);
+        case 8: return launch_gemm_rs_t<8, 2>(w, act, plane, mtp, part, M, S, groups, st);
+        default: return launch_gemm_rs_t<6, 2>(w, act, plane, mtp, part, M, S, groups, st);
     }
-    if (MT <= 12) return ct == 8 ? launch_gemm_rs_t<8, 3>(w, act, plane, mtp, part, M, Mtot, S, groups, st)
-                                : launch_gemm_rs_t<6, 3>(w, act, plane, mtp, part, M, Mtot, S, groups, st);
+    if (MT <= 12) return ct == 8 ? launch_gemm_rs_t<8, 3>(w, act, plane, mtp, part, M, S, groups, st)
+                                : launch_gemm_rs_t<6, 3>(w, act, plane, mtp, part, M, S, groups, st);
     return CSD_ESHAPE;
 }
 
@@ -808,23 +803,18 @@ int32_t csd_gemm_setup() {
     return CSD_OK;
 }
 
-// act: M rows of width w.K in the path's activation form; part: [S][M][w.N] with S (<= w.S) returned in *S_used
-static int32_t run_gemm(csd_model *mod, const GemmW &w, const void *act, int M, int *S_used, hipStream_t st) {
+// act: M rows of width w.K in the path's activation form (MFMA models: planes `plane` elements apart); part: [S][M][w.N] with
+// S (<= w.S) returned in *S_used
+static int32_t run_gemm(csd_model *mod, const GemmW &w, const void *act, size_t plane, int M, int *S_used, hipStream_t st) {
     ProfScope ps(mod, st, CSD_PROF_GEMM);
     *S_used = w.S;
     if (mod->mfma) {
-        // up to 144 rows in one launch, more in chunks of 128 rows that share the number of K splits
         *S_used = 0;
-        const int step = M <= 144 ? M : 128;
-        for (int row0 = 0; row0 < M; row0 += step) {
-            const int rows = M - row0 < step ? M - row0 : step;
-            const bf16_t *a = (const bf16_t *)act + (size_t)(row0 / 16) * 512;   // row tile row0 / 16 of every k-step
-            float *p = mod->part + (size_t)row0 * w.N;
-            const int32_t rc = rows >= mod->gemm_rs_min_rows
-                                   ? launch_gemm_rs(mod, w, a, mod->act_plane, mod->act_mtp, p, rows, M, S_used, st)
-                                   : launch_gemm_ws(w, a, mod->act_plane, mod->act_mtp, p, rows, M, S_used, st);
-            if (rc != CSD_OK) return rc;
-        }
+        const bf16_t *a = (const bf16_t *)act;
+        const int32_t rc = M >= CSD_TALL_MIN_ROWS ? csd_tall_part(mod, w, a, plane, M, S_used, st)
+                           : M >= mod->gemm_rs_min_rows ? launch_gemm_rs(mod, w, a, plane, mod->act_mtp, mod->part, M, S_used, st)
+                                                        : launch_gemm_ws(w, a, plane, mod->act_mtp, mod->part, M, S_used, st);
+        if (rc != CSD_OK) return rc;
     } else if (mod->cfg.dtype == CSD_DTYPE_BF16) {
         hipLaunchKernelGGL((k_gemm_simple<bf16_t>), dim3((w.N + 255) / 256), dim3(256), 0, st, (const bf16_t *)w.data,
                            (const float *)act, mod->part, M, w.K, w.N);
@@ -846,16 +836,22 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
     const csd_model_cfg &c = mod->cfg;
     const int M = B * m, d = c.d_model, F = c.d_ffn, hd = mod->hd, V = c.vocab, L = c.n_layers;
     const KvGeom geo = geom(mod);
-    TA *act = (TA *)mod->act;
     TA *qb = (TA *)mod->qbuf;
-    const int lda = d > F ? (d > hd ? d : hd) : (F > hd ? F : hd);   // rows of `act` are reused at several widths
-    (void)lda;
+    // the input rows of the four GEMMs of a layer: one buffer reused at several widths, or, where GEMMs with their epilogue
+    // inside read one while they write the next, the four of the small-block forward
+    const bool fused = sizeof(TA) == 2 && csd_tall_fused(mod, M);
+    TA *x[4];
+    size_t xp[4];
+    for (int i = 0; i < 4; i++) {
+        x[i] = (TA *)(fused ? mod->x[i] : mod->act);
+        xp[i] = fused ? mod->x_plane[i] : mod->act_plane;
+    }
     const float scale = 1.0f / sqrtf((float)c.head_dim);
     int S_g = 1;            // K splits the last GEMM wrote partial sums for
     {
         ProfScope ps(mod, st, CSD_PROF_OTHER);
         hipLaunchKernelGGL((k_embed_norm<TW, TA>), dim3(M), dim3(256), 0, st, tokens, (const TW *)mod->embed, V, d,
-                           mod->layers[0].attn_norm, c.rms_eps, mod->h, act, d, mod->act_plane, mod->act_mtp, mod->rstd);
+                           mod->layers[0].attn_norm, c.rms_eps, mod->h, x[0], d, xp[0], mod->act_mtp, mod->rstd);
         CSD_LAUNCH_CHECK();
     }
     if (mod->trace) CSD_HIP(hipMemcpyAsync(mod->trace, mod->h, sizeof(float) * (size_t)M * d, hipMemcpyDeviceToDevice, st));
@@ -868,8 +864,13 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
     for (int l = 0; l < L; l++) {
         const LayerW &lw = mod->layers[l];
         int32_t rc;
-        if ((rc = run_gemm(mod, lw.qkv, act, M, &S_g, st)) != CSD_OK) return rc;
-        {
+        if (fused) {
+            ProfScope ps(mod, st, CSD_PROF_GEMM);
+            if ((rc = csd_tall_qkv(mod, lw.qkv, (const bf16_t *)x[0], xp[0], M, m, l, geo, kv, cache_len, c.rope_theta > 0.f ? mod->rope : nullptr,
+                                   st)) != CSD_OK)
+                return rc;
+        } else {
+            if ((rc = run_gemm(mod, lw.qkv, x[0], xp[0], M, &S_g, st)) != CSD_OK) return rc;
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             hipLaunchKernelGGL((k_fix_qkv<TA, TC>), dim3(M, c.n_heads), dim3(64), 0, st, mod->part, S_g, M, m,
                                cache_len, geo, l, c.rope_theta > 0.f ? mod->rope : nullptr, qb, mod->q_plane, (TC *)kv, mod->rstd);
@@ -878,34 +879,37 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
         AttnMode am;
         if (mod->tree_call) am.anc = mod->tree_anc;
         if (mod->mfma_attn) {
-            if ((rc = csd_attn_mfma_enqueue(mod, geo, kv, cache_len, B, m, l, scale, am, st)) != CSD_OK) return rc;
+            if ((rc = csd_attn_mfma_enqueue(mod, geo, kv, cache_len, B, m, l, scale, am, st, (bf16_t *)x[1], xp[1])) != CSD_OK) return rc;
         } else {
             ProfScope ps(mod, st, CSD_PROF_ATTN);
             const size_t lds = sizeof(float) * (size_t)(c.head_dim + mod->seq_pad);
             hipLaunchKernelGGL((k_attn_simple<TA, TC>), dim3(M, c.n_heads), dim3(64), lds, st, qb, m, cache_len, geo, l,
-                               (const TC *)kv, scale, mod->q_plane, act, hd, mod->act_plane, mod->act_mtp, am);
+                               (const TC *)kv, scale, mod->q_plane, x[1], hd, xp[1], mod->act_mtp, am);
             CSD_LAUNCH_CHECK();
         }
-        if ((rc = run_gemm(mod, lw.o, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.o, x[1], xp[1], M, &S_g, st)) != CSD_OK) return rc;
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             hipLaunchKernelGGL((k_residual_norm<TA>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, lw.ffn_norm,
-                               c.rms_eps, mod->h, act, d, mod->act_plane, mod->act_mtp, mod->rstd);
+                               c.rms_eps, mod->h, x[2], d, xp[2], mod->act_mtp, mod->rstd);
             CSD_LAUNCH_CHECK();
         }
-        if ((rc = run_gemm(mod, lw.gu, act, M, &S_g, st)) != CSD_OK) return rc;
-        {
+        if (fused) {
+            ProfScope ps(mod, st, CSD_PROF_GEMM);
+            if ((rc = csd_tall_gu(mod, lw.gu, (const bf16_t *)x[2], xp[2], M, (bf16_t *)x[3], xp[3], 0, st)) != CSD_OK) return rc;
+        } else {
+            if ((rc = run_gemm(mod, lw.gu, x[2], xp[2], M, &S_g, st)) != CSD_OK) return rc;
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             hipLaunchKernelGGL((k_fix_gu<TA>), dim3((F + 255) / 256, M), dim3(256), 0, st, mod->part, S_g, M, F,
-                               mod->mfma ? 1 : 0, act, F, mod->act_plane, mod->act_mtp, 0, mod->rstd);
+                               mod->mfma ? 1 : 0, x[3], F, xp[3], mod->act_mtp, 0, mod->rstd);
             CSD_LAUNCH_CHECK();
         }
-        if ((rc = run_gemm(mod, lw.down, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.down, x[3], xp[3], M, &S_g, st)) != CSD_OK) return rc;
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             const float *g = (l + 1 < L) ? mod->layers[l + 1].attn_norm : mod->final_norm;
             hipLaunchKernelGGL((k_residual_norm<TA>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, g,
-                               c.rms_eps, mod->h, act, d, mod->act_plane, mod->act_mtp, mod->rstd);
+                               c.rms_eps, mod->h, x[0], d, xp[0], mod->act_mtp, mod->rstd);
             CSD_LAUNCH_CHECK();
         }
         if (mod->trace)
@@ -913,7 +917,11 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
                                    hipMemcpyDeviceToDevice, st));
     }
     int32_t rc;
-    if ((rc = run_gemm(mod, mod->lm, act, M, &S_g, st)) != CSD_OK) return rc;
+    if (fused) {
+        ProfScope ps(mod, st, CSD_PROF_GEMM);
+        return csd_tall_logits(mod, mod->lm, (const bf16_t *)x[0], xp[0], M, logits, st);
+    }
+    if ((rc = run_gemm(mod, mod->lm, x[0], xp[0], M, &S_g, st)) != CSD_OK) return rc;
     {
         ProfScope ps(mod, st, CSD_PROF_OTHER);
         hipLaunchKernelGGL(k_fix_logits, dim3((V + 255) / 256, M), dim3(256), 0, st, mod->part, S_g, M, V, logits, mod->rstd);
@@ -974,7 +982,7 @@ static int32_t forward_t5(csd_model *mod, void *kv, const int32_t *tokens, const
     if (mod->trace) CSD_HIP(hipMemcpyAsync(mod->trace, mod->h, sizeof(float) * (size_t)M * d, hipMemcpyDeviceToDevice, st));
     for (int l = 0; l < L; l++) {
         const LayerW &lw = mod->layers[l];
-        if ((rc = run_gemm(mod, lw.qkv, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.qkv, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             hipLaunchKernelGGL((k_fix_qkv<TA, TC>), dim3(M, c.n_heads), dim3(64), 0, st, mod->part, S_g, M, m, cache_len,
@@ -982,9 +990,9 @@ static int32_t forward_t5(csd_model *mod, void *kv, const int32_t *tokens, const
             CSD_LAUNCH_CHECK();
         }
         if ((rc = attention_any<TA, TC>(mod, geo, kv, cache_len, B, m, l, 1.0f, self_mode, st)) != CSD_OK) return rc;
-        if ((rc = run_gemm(mod, lw.o, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.o, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
         if ((rc = resid_norm(lw.o, lw.cross_norm)) != CSD_OK) return rc;
-        if ((rc = run_gemm(mod, lw.cq, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.cq, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             hipLaunchKernelGGL((k_fix_plain<TA>), dim3((hd + 255) / 256, M), dim3(256), 0, st, mod->part, S_g, M, hd, qb, hd,
@@ -992,22 +1000,22 @@ static int32_t forward_t5(csd_model *mod, void *kv, const int32_t *tokens, const
             CSD_LAUNCH_CHECK();
         }
         if ((rc = attention_any<TA, TC>(mod, cgeo, kv_cross, cache_len, B, m, l, 1.0f, cross_mode, st)) != CSD_OK) return rc;
-        if ((rc = run_gemm(mod, lw.co, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.co, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
         if ((rc = resid_norm(lw.co, lw.ffn_norm)) != CSD_OK) return rc;
-        if ((rc = run_gemm(mod, lw.gu, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.gu, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             hipLaunchKernelGGL((k_fix_gu<TA>), dim3((F + 255) / 256, M), dim3(256), 0, st, mod->part, S_g, M, F,
                                mod->mfma ? 1 : 0, act, F, mod->act_plane, mod->act_mtp, 1, mod->rstd);
             CSD_LAUNCH_CHECK();
         }
-        if ((rc = run_gemm(mod, lw.down, act, M, &S_g, st)) != CSD_OK) return rc;
+        if ((rc = run_gemm(mod, lw.down, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
         if ((rc = resid_norm(lw.down, (l + 1 < L) ? mod->layers[l + 1].attn_norm : mod->final_norm)) != CSD_OK) return rc;
         if (mod->trace)
             CSD_HIP(hipMemcpyAsync(mod->trace + (size_t)(l + 1) * M * d, mod->h, sizeof(float) * (size_t)M * d,
                                    hipMemcpyDeviceToDevice, st));
     }
-    if ((rc = run_gemm(mod, mod->lm, act, M, &S_g, st)) != CSD_OK) return rc;
+    if ((rc = run_gemm(mod, mod->lm, act, mod->act_plane, M, &S_g, st)) != CSD_OK) return rc;
     {
         ProfScope ps(mod, st, CSD_PROF_OTHER);
         hipLaunchKernelGGL(k_fix_logits, dim3((V + 255) / 256, M), dim3(256), 0, st, mod->part, S_g, M, V, logits, mod->rstd);
@@ -1023,8 +1031,30 @@ static int32_t cross_init_typed(csd_model *mod, void *kv, const float *enc_out, 
     const int d = c.d_model, hd = mod->hd, E = c.enc_len;
     const KvGeom cgeo = cross_geom(mod);
     TC *kvc = (TC *)((char *)kv + csd_self_kv_bytes(mod));
-    const int chunk = mod->m_max;       // the activation and partial-sum buffers hold this many rows
     int32_t rc;
+    if constexpr (sizeof(TA) == 2) {
+        // the rows of all sequences follow each other: as many per pass over the matrices as the row buffer holds, keys and
+        // values written by the GEMM itself (in chunks of the 8 rows of a decoder block, 512 rows took 64 passes: 40 ms at the
+        // T5-XXL shape)
+        const int total = B * E, step = mod->enc_act_rows, mtp = step / 16;
+        const size_t plane = (size_t)step * d;
+        for (int row0 = 0; row0 < total; row0 += step) {
+            const int rows = total - row0 < step ? total - row0 : step;
+            {
+                ProfScope ps(mod, st, CSD_PROF_OTHER);
+                hipLaunchKernelGGL((k_rows_to_act<TA>), dim3((unsigned)(((size_t)rows * d + 255) / 256)), dim3(256), 0, st,
+                                   enc_out + (size_t)row0 * d, rows, d, (TA *)mod->enc_act, d, plane, mtp);
+                CSD_LAUNCH_CHECK();
+            }
+            for (int l = 0; l < c.n_layers; l++) {
+                ProfScope ps(mod, st, CSD_PROF_GEMM);
+                if ((rc = csd_tall_cross(mod, mod->layers[l].ckv, (const bf16_t *)mod->enc_act, plane, mtp, rows, row0, l, cgeo, kvc, st)) != CSD_OK)
+                    return rc;
+            }
+        }
+        return CSD_OK;
+    }
+    const int chunk = mod->m_max;       // the activation and partial-sum buffers hold this many rows
     int S_g = 1;
     for (int b = 0; b < B; b++)
         for (int row0 = 0; row0 < E; row0 += chunk) {
@@ -1038,7 +1068,7 @@ static int32_t cross_init_typed(csd_model *mod, void *kv, const float *enc_out, 
             }
             for (int l = 0; l < c.n_layers; l++) {
                 const LayerW &lw = mod->layers[l];
-                if ((rc = run_gemm(mod, lw.ckv, mod->act, rows, &S_g, st)) != CSD_OK) return rc;
+                if ((rc = run_gemm(mod, lw.ckv, mod->act, 0, rows, &S_g, st)) != CSD_OK) return rc;
                 ProfScope ps(mod, st, CSD_PROF_OTHER);
                 hipLaunchKernelGGL((k_fix_cross_kv<TC>), dim3((hd + 255) / 256, rows), dim3(256), 0, st, mod->part, S_g, rows,
                                    cgeo, l, b, row0, kvc);

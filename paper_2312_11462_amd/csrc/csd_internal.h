@@ -250,6 +250,8 @@ struct csd_model {
     unsigned *tail_cnt = nullptr;        // [max_batch] arrival counters of that review: zero between launches
     // arch 1
     int enc_pad = 0;                 // encoder rows padded to 64
+    void *enc_act = nullptr;         // MFMA models: planes of the encoder rows being projected (setup, not per-call scratch)
+    int enc_act_rows = 0;            // rows they hold
     float *rel_bias = nullptr;       // [32][H] fp32
     int32_t *rel_bucket = nullptr;   // [128] bucket of distance n (n >= 127 shares the last entry)
     float *rel_bias_hd = nullptr;    // [H][128]: rel_bias[rel_bucket[n]][h]
@@ -298,6 +300,19 @@ int32_t csd_chain_setup();
 bool csd_chain_eligible(const csd_model *mod, int32_t B, int32_t m);
 int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int32_t B, int32_t m,
                           float *logits, hipStream_t st);
+// csd_tall.hip: GEMMs over more rows than k_gemm_rs takes, partial sums or with the epilogue inside
+#define CSD_TALL_MIN_ROWS 145
+#define CSD_CROSS_ROWS 512       /* encoder rows that csd_cross_kv_init projects per pass over a layer's matrix */
+int32_t csd_tall_setup();
+bool csd_tall_fused(const csd_model *mod, int M);
+int32_t csd_tall_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st);
+int32_t csd_tall_qkv(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int m, int layer, const KvGeom &geo,
+                     void *kv, const int32_t *cache_len, const float2 *rope, hipStream_t st);
+int32_t csd_tall_gu(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, bf16_t *out, size_t out_plane, int gelu,
+                    hipStream_t st);
+int32_t csd_tall_logits(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, float *logits, hipStream_t st);
+int32_t csd_tall_cross(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int mtp, int M, int row0, int layer,
+                       const KvGeom &geo, void *kv_cross, hipStream_t st);
 // csd_accept.hip
 int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int32_t V, float temperature,
                             hipStream_t st);

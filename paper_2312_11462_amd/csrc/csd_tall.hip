@@ -1,0 +1,337 @@
+// GEMM for blocks of more rows than csd_chain.hip and k_gemm_rs take (a new prompt in large blocks, the encoder rows of
+// an arch 1 prompt): tiles of up to 192 columns x 128 rows per workgroup, both operands through LDS.
+//
+// With hundreds of rows the matrix instructions bound a launch (two activation planes: 4 * M * N * K operations), so what
+// counts is how little has to move per matrix instruction.  Four waves share a tile as a 2 x 2 grid; a wave owns CTW column
+// tiles x RTW row tiles of 16 and reads each of its CTW + 2 * RTW operand fragments of a k-step once from LDS for
+// 2 * CTW * RTW matrix instructions.  Fragments are 1 KB of consecutive memory on both sides (weights pre-tiled,
+// activations in fragment order), so a stage is brought in by direct loads to LDS, one instruction per fragment, lanes
+// placed in operand order; NST stages of one k-step are in flight or in use.  A wave holds the fragments of the running
+// k-step in registers and reads the next one's between its matrix instructions; one workgroup barrier per k-step.
+// Row blocks of one column group go to one compute die, which then fetches those weights once.
+// 7B shape, 512 rows, against four launches of the row-split form over 128 rows each: QKV 122 -> 81 us (1.27 PFLOP/s, both
+// planes counted), gate|up 188 -> 146, down 111 -> 79, O 57 -> 34, LM head 254 -> 223; with the loads of the main loop
+// switched off 57-68 us for QKV, so it is bound by the operand traffic into LDS beside the matrix instructions.
+#include "csd_epilogue.h"
+
+enum { EPI_PART = 4, EPI_CROSS = 5 };       // besides the epilogues of csd_epilogue.h
+
+struct TallArgs {
+    ChainGemm g;
+    int n_tiles, S, rblocks;
+    float *part;              // EPI_PART: partial sums [S][M][16 n_tiles]
+    const float *rstd;        // [M] scale of the folded norm (EPI_QKV, EPI_GU, EPI_LOGITS)
+    int enc_len, row0;        // EPI_CROSS: row r of the launch is encoder row (row0 + r) % enc_len of sequence (row0 + r) / enc_len
+};
+
+typedef __attribute__((address_space(3))) void *lds_void;
+
+// 16 bytes per lane from a buffer straight to LDS: lane l's go to d + 16 l
+template <int AUX>
+__device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, lds_void d, int voff, int soff) {
+#ifdef __HIP_DEVICE_COMPILE__                // (the host pass does not know the 16-byte form)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, d, 16, voff, soff, 0, AUX);
+#endif
+}
+// At most V vector memory operations still outstanding, and no LDS read.
+template <int V>
+__device__ __forceinline__ void wait_loads() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((V & 15) | ((V >> 4) << 14) | 0x0070);
+}
+// The barrier alone: lds_sync()'s fences would wait for every direct load to LDS still in flight.  What makes it safe is the
+// wait in front of it: every wave has seen its own loads of the stage that is read next arrive, and has the fragments
+// it read from the stage that is overwritten next in registers.
+__device__ __forceinline__ void stage_barrier() {
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// EPI_CROSS: keys | values of the encoder rows into the cross-attention part of the cache
+__device__ __forceinline__ void cross_epilogue(const TallArgs &A, const f32x4 &v, int row, int T, int g) {
+    const ChainGemm &P = A.g;
+    if (row >= P.M) return;
+    const int r = A.row0 + row, b = r / A.enc_len, pos = r % A.enc_len;
+    const bool is_v = T >= P.hd / 16;
+    const int j = (is_v ? T - P.hd / 16 : T) * 16 + 4 * g, hh = j / P.dh, x = j % P.dh;
+    if (!is_v) {
+        u32x2 k;
+        k[0] = pack_bf16x2(v[0], v[1]);
+        k[1] = pack_bf16x2(v[2], v[3]);
+        *reinterpret_cast<u32x2 *>(P.kv + kv_k_off(P.geo, P.layer, b, hh) + (size_t)pos * P.dh + x) = k;
+    } else {
+        bf16_t *vc = P.kv + kv_v_off(P.geo, P.layer, b, hh);
+#pragma unroll
+        for (int i = 0; i < 4; i++) vc[kv_v_idx(P.geo, x + i, pos)] = f32_to_bf16(v[i]);
+    }
+}
+
+template <int CTW, int RTW, int NST, int EPI>
+__global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
+    extern __shared__ __align__(16) char tall_smem[];
+    constexpr int WF = 2 * CTW, NF = WF + 4 * RTW;               // fragments of a stage: W tiles, then [plane][row tile]
+    constexpr int PW = (NF + 3) / 4;                             // per wave: fragments w, w + 4, ... (the last one again past the end)
+    const ChainGemm &P = A.g;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // workgroups go to the eight compute dies round-robin: consecutive tiles to the workgroups of one die
+    const int per_die = gridDim.x >> 3, rest = gridDim.x & 7, die = blockIdx.x & 7;
+    const int wg = die * per_die + (die < rest ? die : rest) + (blockIdx.x >> 3);
+    const int rb = wg % A.rblocks, s = (wg / A.rblocks) % A.S, grp = wg / (A.rblocks * A.S);
+    const int ks0 = (int)((long long)P.KS * s / A.S), ks1 = (int)((long long)P.KS * (s + 1) / A.S);
+    const int tile0 = grp * WF, rt0 = rb * 2 * RTW;
+    const __amdgpu_buffer_rsrc_t rw = ch_rsrc(P.Wp, (size_t)P.wbytes), ra = ch_rsrc(P.a, (size_t)2 * P.a_plane_bytes);
+    // Tiles and row tiles past the end are read as the last one (their sums are not stored), k-steps past the slice likewise:
+    // every address is inside the matrix, and every wave issues PW loads per stage, so the waits can count them.
+    int base[PW], step[PW];
+#pragma unroll
+    for (int i = 0; i < PW; i++) {
+        const int f = min(i * 4 + w, NF - 1);
+        if (f < WF) {
+            base[i] = min(tile0 + f, A.n_tiles - 1) * P.KS * 1024;
+            step[i] = 1024;
+        } else {
+            const int a = f - WF;
+            base[i] = a / (2 * RTW) * P.a_plane_bytes + min(rt0 + a % (2 * RTW), P.mtp - 1) * 1024;
+            step[i] = P.mtp * 1024;
+        }
+    }
+    const int vw = lane * 16, va = (4 * (lane & 15) + (lane >> 4)) * 16;     // see act_tiled_idx
+    auto load_stage = [&](int ks, int buf) {
+        const int k = min(ks, ks1 - 1);
+#pragma unroll
+        for (int i = 0; i < PW; i++) {
+            const int f = min(i * 4 + w, NF - 1);
+            const lds_void d = (lds_void)(tall_smem + (buf * NF + f) * 1024);
+            if (f < WF)
+                lds_load16<0>(rw, d, vw, base[i] + k * step[i]);
+            else
+                lds_load16<0>(ra, d, va, base[i] + k * step[i]);
+        }
+    };
+    const int wc = w & 1, wr = w >> 1;
+    f32x4 acc[RTW][CTW];
+#pragma unroll
+    for (int r = 0; r < RTW; r++)
+#pragma unroll
+        for (int c = 0; c < CTW; c++) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 0; p < NST; p++) load_stage(ks0 + p, p);
+    const u32x4 *L = reinterpret_cast<const u32x4 *>(tall_smem) + lane;
+    const int wo = wc * CTW * 64, ao = (WF + wr * RTW) * 64;     // this wave's W tiles and (hi) row tiles of a stage
+    u32x4 fa[2][2][RTW], fw[2][CTW];                             // [k-step parity]
+    wait_loads<(NST - 1) * PW>();
+    stage_barrier();
+#pragma unroll
+    for (int p = 0; p < 2; p++)
+#pragma unroll
+        for (int r = 0; r < RTW; r++) fa[0][p][r] = L[ao + (p * 2 * RTW + r) * 64];
+#pragma unroll
+    for (int c = 0; c < CTW; c++) fw[0][c] = L[wo + c * 64];
+    int cur = 0, nxt = 1;
+    // k-step K with its fragments in set PAR: the stage behind it has arrived, its own stage is free for k-step K + NST
+#define TALL_STEP(PAR, K)                                                                                             \
+    {                                                                                                                 \
+        wait_loads<(NST - 2) * PW>();                                                                                 \
+        stage_barrier();                                                                                              \
+        load_stage((K) + NST, cur);                                                                                   \
+        const u32x4 *Ln = L + nxt * NF * 64;                                                                          \
+        _Pragma("unroll") for (int c = 0; c < CTW; c++) {                                                             \
+            fw[1 - (PAR)][c] = Ln[wo + c * 64];                                                                       \
+            _Pragma("unroll") for (int a = 0; a < 2 * RTW; a++) if (a * CTW / (2 * RTW) == c)                         \
+                fa[1 - (PAR)][a / RTW][a % RTW] = Ln[ao + (a / RTW * 2 * RTW + a % RTW) * 64];                        \
+            _Pragma("unroll") for (int p = 0; p < 2; p++) _Pragma("unroll") for (int r = 0; r < RTW; r++)             \
+                acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[PAR][c]),           \
+                                                                    __builtin_bit_cast(bf16x8, fa[PAR][p][r]), acc[r][c], 0, 0, 0); \
+            __builtin_amdgcn_sched_barrier(0);                                                                        \
+        }                                                                                                             \
+        cur = nxt;                                                                                                    \
+        nxt = nxt + 1 == NST ? 0 : nxt + 1;                                                                           \
+    }
+    int k = ks0;
+    for (; k + 1 < ks1; k += 2) {
+        TALL_STEP(0, k)
+        TALL_STEP(1, k + 1)
+    }
+    if (k < ks1) TALL_STEP(0, k)
+#undef TALL_STEP
+    wait_loads<0>();                                             // nothing may land in this LDS after the workgroup has ended
+
+    const int t = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < RTW; r++) {
+        const int row = (rt0 + wr * RTW + r) * 16 + t;
+        const bool valid = row < P.M;
+        float rs = 1.f;
+        if (EPI != EPI_PART && EPI != EPI_CROSS) rs = valid ? A.rstd[row] : 0.f;
+        EpiIn E;
+        E.hcur = E.gcur = f32x4{0.f, 0.f, 0.f, 0.f};
+        E.pos = EPI == EPI_QKV && valid ? P.cache_len[row / P.m] + row % P.m : -1;
+        constexpr int UT = EPI == EPI_GU ? 2 : 1;
+#pragma unroll
+        for (int c = 0; c < CTW; c += UT) {
+            const int T = tile0 + wc * CTW + c;
+            if (T >= A.n_tiles) break;                           // uniform
+            if constexpr (EPI == EPI_PART) {
+                if (valid) *reinterpret_cast<f32x4 *>(A.part + (((size_t)s * P.M + row) * A.n_tiles + T) * 16 + 4 * g) = acc[r][c];
+            } else if constexpr (EPI == EPI_CROSS) {
+                cross_epilogue(A, acc[r][c], row, T, g);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; i++) E.cs[i] = float2{1.f, 0.f};
+                if (EPI == EPI_QKV && P.rope && valid && T < 2 * (P.hd / 16)) {
+                    const int ti = T % (P.hd / 16) % (P.dh / 16);
+#pragma unroll
+                    for (int i = 0; i < 4; i++) E.cs[i] = P.rope[(size_t)row * (P.dh / 2) + 8 * ti + 4 * (g & 1) + i];
+                }
+                f32x4 v[UT];
+#pragma unroll
+                for (int i = 0; i < UT; i++) v[i] = acc[r][c + i] * rs;
+                gemm_epilogue<EPI>(P, v, E, row, T, g);
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------- host driver
+
+#define TALL_RTW 4            /* 128 rows per workgroup */
+
+template <int CTW, int NST>
+static constexpr int tall_lds() { return NST * (2 * CTW + 4 * TALL_RTW) * 1024; }
+
+template <int CTW, int NST, int EPI>
+static hipError_t tall_allow_lds() {
+    return hipFuncSetAttribute((const void *)k_gemm_tall<CTW, TALL_RTW, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               tall_lds<CTW, NST>());
+}
+
+int32_t csd_tall_setup() {
+#define TALL_ALLOW(EPI)                         \
+    CSD_HIP((tall_allow_lds<4, 4, EPI>()));     \
+    CSD_HIP((tall_allow_lds<6, 3, EPI>()));     \
+    CSD_HIP((tall_allow_lds<6, 2, EPI>()));
+    TALL_ALLOW(EPI_PART)
+    TALL_ALLOW(EPI_CROSS)
+    TALL_ALLOW(EPI_QKV)
+    TALL_ALLOW(EPI_GU)
+    TALL_ALLOW(EPI_LOGITS)
+#undef TALL_ALLOW
+    return CSD_OK;
+}
+
+// Column tiles per wave and K splits: the pair with the shortest launch by a model fitted to measurements at the 7B shape
+// (512 rows).  A k-step of a workgroup takes 0.07 us * (CTW + 2) where every compute unit holds one workgroup, or two of them
+// twice that; a split's partial sums are written and read back at about 4 TB/s.  QKV 6 tiles per wave (256 workgroups, 81 us;
+// 4: 384 workgroups, 107), gate|up 6 (460, 146 us; 4: 688, 162), O and down 4 tiles and 2 splits (256; without
+// a split O takes 58 us against 34).  max_splits = 1 where the epilogue runs in the kernel.
+static void tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats, int *ctw_out, int *S_out) {
+    const int rblocks = ((M + 15) / 16 + 2 * TALL_RTW - 1) / (2 * TALL_RTW);
+    double best = 1e30;
+    *ctw_out = 6;
+    *S_out = 1;
+    for (int ctw = 6; ctw >= 4; ctw -= 2) {
+        const int groups = (n_tiles + 2 * ctw - 1) / (2 * ctw);
+        for (int S = 1; S <= max_splits; S++) {
+            if (S > 1 && (KS / S < 6 || (size_t)S * M * n_tiles * 16 > part_floats)) break;
+            const long long wgs = (long long)groups * rblocks * S;
+            const double rounds = (double)((wgs + 255) / 256);
+            const double us = rounds * (ctw + 2) * ((KS + S - 1) / S) * 0.07 + (max_splits > 1 ? S * 8.0 * M * n_tiles * 16 / 4e6 : 0.0);
+            if (us < best) best = us, *ctw_out = ctw, *S_out = S;
+        }
+    }
+}
+
+template <int EPI>
+static int32_t tall_launch(TallArgs &A, int max_splits, size_t part_floats, hipStream_t st) {
+    int ctw;
+    tall_plan(A.n_tiles, A.g.KS, A.g.M, max_splits, part_floats, &ctw, &A.S);
+    A.rblocks = ((A.g.M + 15) / 16 + 2 * TALL_RTW - 1) / (2 * TALL_RTW);
+    const int grid = (A.n_tiles + 2 * ctw - 1) / (2 * ctw) * A.rblocks * A.S;
+#define TALL_LAUNCH(CTW, NST) \
+    hipLaunchKernelGGL((k_gemm_tall<CTW, TALL_RTW, NST, EPI>), dim3(grid), dim3(256), (tall_lds<CTW, NST>()), st, A)
+    // with more workgroups than compute units two of them share one (two stages each), which evens out the last round:
+    // gate|up 146 us against 155 with three stages and one workgroup at a time; at 256 workgroups 117 against 81
+    if (ctw == 4)
+        TALL_LAUNCH(4, 4);
+    else if (grid > 256)
+        TALL_LAUNCH(6, 2);
+    else
+        TALL_LAUNCH(6, 3);
+#undef TALL_LAUNCH
+    CSD_LAUNCH_CHECK();
+    return CSD_OK;
+}
+
+static TallArgs tall_args(const csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int mtp, int M) {
+    TallArgs A{};
+    A.g.Wp = (const u32x4 *)w.data;
+    A.g.KS = w.K / 32;
+    A.g.wbytes = (int)((size_t)w.K * w.N * 2);
+    A.g.a = a;
+    A.g.a_plane_bytes = (int)(plane * 2);
+    A.g.mtp = mtp;
+    A.g.M = M;
+    A.g.hd = mod->hd;
+    A.g.dh = mod->cfg.head_dim;
+    A.n_tiles = w.N / 16;
+    A.rstd = mod->rstd;
+    return A;
+}
+
+int32_t csd_tall_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st) {
+    TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
+    A.part = mod->part;
+    const int32_t rc = tall_launch<EPI_PART>(A, w.S < 8 ? w.S : 8, mod->part_floats, st);
+    *S_used = A.S;
+    return rc;
+}
+
+bool csd_tall_fused(const csd_model *mod, int M) {
+    // the cache appends of the epilogue address a layer's keys, or values, through one 32-bit offset
+    const size_t layer_kv = (size_t)mod->cfg.max_batch * mod->cfg.n_heads * mod->seq_pad * mod->cfg.head_dim * 2;
+    return mod->chain_on && M >= CSD_TALL_MIN_ROWS && layer_kv < (1ull << 31);
+}
+
+int32_t csd_tall_qkv(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int m, int layer, const KvGeom &geo,
+                     void *kv, const int32_t *cache_len, const float2 *rope, hipStream_t st) {
+    TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
+    A.g.m = m;
+    A.g.layer = layer;
+    A.g.geo = geo;
+    A.g.kv = (bf16_t *)kv;
+    A.g.cache_len = cache_len;
+    A.g.rope = rope;
+    A.g.q = (bf16_t *)mod->qbuf;
+    A.g.q_plane_bytes = (int)(mod->q_plane * 2);
+    return tall_launch<EPI_QKV>(A, 1, 0, st);
+}
+
+int32_t csd_tall_gu(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, bf16_t *out, size_t out_plane, int gelu,
+                    hipStream_t st) {
+    TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
+    A.g.out = out;
+    A.g.out_plane_bytes = (int)(out_plane * 2);
+    A.g.gelu = gelu;
+    return tall_launch<EPI_GU>(A, 1, 0, st);
+}
+
+int32_t csd_tall_logits(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, float *logits, hipStream_t st) {
+    TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
+    A.g.logits = logits;
+    A.g.V = w.N;
+    return tall_launch<EPI_LOGITS>(A, 1, 0, st);
+}
+
+int32_t csd_tall_cross(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int mtp, int M, int row0, int layer,
+                       const KvGeom &geo, void *kv_cross, hipStream_t st) {
+    TallArgs A = tall_args(mod, w, a, plane, mtp, M);
+    A.enc_len = mod->cfg.enc_len;
+    A.row0 = row0;
+    A.g.layer = layer;
+    A.g.geo = geo;
+    A.g.kv = (bf16_t *)kv_cross;
+    return tall_launch<EPI_CROSS>(A, 1, 0, st);
+}

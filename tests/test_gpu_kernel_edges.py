@@ -40,3 +40,51 @@ def test_bigram_fit_tables(P, n, text):
         want = O.bigram_fit(s, vocab, default.numpy())
     got = P.bigram_fit(torch.from_numpy(s).cuda(), vocab, default.cuda().clone())
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+BF = I.ModelShape("edge_dh64", 0, "bf16", 2, 256, 4, 64, 512, 1024)
+BF128 = I.ModelShape("edge_dh128", 0, "bf16", 2, 256, 2, 128, 480, 1040)
+
+
+@pytest.mark.parametrize("shape", [BF, BF128], ids=["dh64", "dh128"])
+@pytest.mark.parametrize("B,m", [(1, 145), (1, 256), (1, 257), (2, 100), (3, 173)])
+def test_tall_blocks(P, shape, B, m):
+    """The GEMMs over many rows: one row more than the row-split form takes, whole and ragged 128-row blocks, rows of several
+    sequences in one row tile, column tiles that do not fill a workgroup.  Tolerances: the project's (bf16)."""
+    from gpu_util import make_pair, prefill_both, tol_ok
+    gm, om = make_pair(shape, 17, B, 40 + m, m, std=0.05)
+    toks = I.token_ids(B * (m + 30), shape.vocab, 17, 1).reshape(B, m + 30)
+    prefill_both(gm, om, toks[:, :30], 15)
+    cl = np.asarray([30 - 7 * b for b in range(B)], np.int32)
+    block = np.stack([toks[b, cl[b]:cl[b] + m].numpy() for b in range(B)]).astype(np.int32)
+    tr = torch.zeros((shape.n_layers + 1, B * m, shape.d_model), dtype=torch.float32, device="cuda")
+    gm.set_trace(tr)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    gm.set_trace(None)
+    ref, otr = om.verify_block(block, cl, trace=True)
+    for l in range(shape.n_layers + 1):
+        g = tr.cpu().numpy()[l, :m].astype(np.float64)
+        assert np.linalg.norm(g - otr[l]) < 5e-3 * np.linalg.norm(otr[l])
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), ref, 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+    for b in range(B):
+        for got, want in zip(gm.kv_read(1, b, 0, int(cl[b]) + m), om.kv_read(1, b, 0, int(cl[b]) + m)):
+            ok, err = tol_ok(got.cpu().numpy().astype(np.float64), want, 2e-2, 1e-2)
+            assert ok, f"cache rows of sequence {b}: max abs err {err}"
+
+
+@pytest.mark.parametrize("B,enc_len", [(1, 1), (1, 31), (1, 130), (2, 300), (3, 171)])
+def test_cross_projection_rows(P, B, enc_len):
+    """Encoder rows of several sequences in one pass: a single row, ragged row tiles and row blocks, sequences that cross the
+    limit of 512 rows per pass."""
+    from gpu_util import make_pair, tol_ok
+    shape = I.ModelShape("edge_t5", 1, "bf16", 2, 256, 4, 64, 512, 1024, rms_eps=1e-6, enc_len=enc_len)
+    gm, om = make_pair(shape, 29, B, 32, 8, std=0.05)
+    enc = I.encoder_output(shape, B, 29)
+    gm.cross_kv_init(enc.cuda())
+    om.cross_kv_init(enc.numpy())
+    block = I.token_ids(B * 5, shape.vocab, 29, 1).reshape(B, 5).numpy().astype(np.int32)
+    cl = np.zeros(B, np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
