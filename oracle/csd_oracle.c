@@ -422,7 +422,7 @@ static int32_t verify_rows(csdo_model *mod, double *kv, const int32_t *tokens, c
     double *vv = (double *)malloc(sizeof(double) * (size_t)m * hd);
     double *o = (double *)malloc(sizeof(double) * (size_t)m * hd);
     double *t1 = (double *)malloc(sizeof(double) * (size_t)m * (F > d ? F : d));
-    double *t2 = (double *)malloc(sizeof(double) * (size_t)m * F);
+    double *t2 = (double *)malloc(sizeof(double) * (size_t)m * (F > d ? F : d));
     double *sc = (double *)malloc(sizeof(double) * (size_t)c->max_seq);
     int *depth = (int *)malloc(sizeof(int) * (size_t)m);
     unsigned char *sees = (unsigned char *)malloc((size_t)m * m);   /* sees[i*m + j]: block row j is row i or above it */
