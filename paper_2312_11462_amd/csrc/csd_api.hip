@@ -123,6 +123,8 @@ static int32_t create_impl(csd_model *mod, const void *const *weights, hipStream
     mod->mfma_attn = mod->mfma && (c.head_dim == 64 || c.head_dim == 128) && !env_is("CSD_ATTN", "generic");
     const int keys_pad = mod->seq_pad > mod->enc_pad ? mod->seq_pad : mod->enc_pad;
     if (!mod->mfma_attn && sizeof(float) * (size_t)(c.head_dim + keys_pad) > 64 * 1024) return CSD_ESHAPE;
+    int32_t rc;
+    if (!mod->mfma_attn && (rc = csd_attn_simple_setup()) != CSD_OK) return rc;
     {
         // the GEMM kernels address a matrix through one buffer descriptor with 32-bit offsets
         const size_t esz = c.dtype == CSD_DTYPE_BF16 ? 2 : 4;
@@ -130,7 +132,6 @@ static int32_t create_impl(csd_model *mod, const void *const *weights, hipStream
         for (size_t n : mats)
             if (n * esz >= ((size_t)1 << 31)) return CSD_ESHAPE;
     }
-    int32_t rc;
     if ((rc = csd_pack_weights(mod, weights, st)) != CSD_OK) return rc;
     if (mod->mfma && ((rc = csd_gemm_setup()) != CSD_OK || (rc = csd_tall_setup()) != CSD_OK)) return rc;
 

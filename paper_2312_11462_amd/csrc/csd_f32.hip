@@ -6,7 +6,7 @@
 // the tiny shape, K = 64 and 256); here K is split over the eight waves of a workgroup, a wave requests eight rows of its
 // slice at once, the eight partial sums meet in LDS, and whatever follows a GEMM (rotary embedding and cache append, residual
 // sum, gated activation, the scale of the folded norm) runs on them in the same kernel, which computes the norm of its input
-// rows along the way: five launches per layer of about 4 us each.  Tiny shape, verify step: 364 -> 75 us.
+// rows along the way: five launches per layer of 3 to 6 us.  Tiny shape, verify step: 363 -> 67 us.
 #include <cmath>
 
 #include "csd_internal.h"

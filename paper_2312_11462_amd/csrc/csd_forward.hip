@@ -352,26 +352,6 @@ __global__ __launch_bounds__(512) void k_gemm_rs(const u32x4 *__restrict__ Wp, c
     }
 }
 
-// Generic GEMM (fp32 models and the debugging path): one thread per output column, fp32
-// activations [M][K], row-major weights [K][N]; writes partial plane 0.
-template <typename TW>
-__global__ __launch_bounds__(256) void k_gemm_simple(const TW *__restrict__ W, const float *__restrict__ act,
-                                                     float *__restrict__ part, int M, int K, int N) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    for (int r0 = 0; r0 < M; r0 += 8) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        const int rn = min(8, M - r0);
-        for (int k = 0; k < K; k++) {
-            const float w = to_f32<TW>(W[(size_t)k * N + n]);
-#pragma unroll
-            for (int r = 0; r < 8; r++)
-                if (r < rn) acc[r] = fmaf(act[(size_t)(r0 + r) * K + k], w, acc[r]);
-        }
-        for (int r = 0; r < rn; r++) part[(size_t)(r0 + r) * N + n] = acc[r];
-    }
-}
-
 // ------------------------------------------------------------------------------- epilogues
 
 // h[r] = E[token[r]];  a[r] = h[r] * g and rstd[r] = 1 / sqrt(mean(h[r]^2) + eps): the norm is folded around the
@@ -590,19 +570,21 @@ __global__ __launch_bounds__(256) void k_rows_to_act(const float *__restrict__ s
     store_act<TA>(a, plane, (int)(idx / d), (int)(idx % d), lda, mtp, src[idx]);
 }
 
-// Generic causal block attention: one wave per (block row, head).  Scores of the visible cache
-// rows 0..pos go through LDS; softmax in fp32 with max subtraction; o = sum_j p_j V_j.
+// Generic causal block attention: one workgroup per (block row, head).  Scores of the visible cache rows 0..pos go
+// through LDS; softmax in fp32 with max subtraction; o = sum_j p_j V_j with the keys dealt over 256 / dh groups of threads
+//.
+#define AS_THREADS 256
 template <typename TA, typename TC>
-__global__ __launch_bounds__(64) void k_attn_simple(const TA *__restrict__ q, int m, const int32_t *__restrict__ cache_len,
+__global__ __launch_bounds__(AS_THREADS) void k_attn_simple(const TA *__restrict__ q, int m, const int32_t *__restrict__ cache_len,
                                                     KvGeom geo, int layer, const TC *__restrict__ kv, float scale,
                                                     size_t qplane, TA *__restrict__ out, int ldo, size_t plane, int mtp,
                                                     AttnMode mode) {
-    extern __shared__ float sm[];
+    extern __shared__ float red[];      // [16]
     const int r = blockIdx.x, hh = blockIdx.y;
     const int b = r / m, i = r % m;
     const int dh = geo.dh, hd = geo.H * dh;
-    float *qs = sm;           // [dh]
-    float *sc = sm + dh;      // [nk]
+    float *sm = red + 16, *qs = sm;     // [dh]
+    float *sc = sm + dh;                // [nk]
     const int qpos = mode.fixed_nk > 0 ? 0 : cache_len[b] + i;
     int nk = mode.fixed_nk > 0 ? mode.fixed_nk : qpos + 1;
     nk = max(1, min(nk, geo.seq_pad));
@@ -610,13 +592,13 @@ __global__ __launch_bounds__(64) void k_attn_simple(const TA *__restrict__ q, in
     const int t0 = qpos - i;
     const TC *kc = kv + kv_k_off(geo, layer, b, hh);
     const TC *vc = kv + kv_v_off(geo, layer, b, hh);
-    for (int x = threadIdx.x; x < dh; x += 64) {
+    for (int x = threadIdx.x; x < dh; x += AS_THREADS) {
         const size_t qi = (size_t)r * hd + hh * dh + x;
         qs[x] = to_f32<TA>(q[qi]) + (sizeof(TA) == 2 ? to_f32<TA>(q[qi + qplane]) : 0.f);
     }
     __syncthreads();
     float mx = -INFINITY;
-    for (int j = threadIdx.x; j < nk; j += 64) {
+    for (int j = threadIdx.x; j < nk; j += AS_THREADS) {
         float s = 0.f;
         for (int x = 0; x < dh; x++) s = fmaf(qs[x], to_f32<TC>(kc[(size_t)j * dh + x]), s);
         s *= scale;
@@ -625,21 +607,34 @@ __global__ __launch_bounds__(64) void k_attn_simple(const TA *__restrict__ q, in
         sc[j] = s;
         mx = fmaxf(mx, s);
     }
-    mx = wave_max(mx);
+    mx = block_max(mx, red);
     float z = 0.f;
-    for (int j = threadIdx.x; j < nk; j += 64) {
+    for (int j = threadIdx.x; j < nk; j += AS_THREADS) {
         const float e = expf(sc[j] - mx);
         sc[j] = e;
         z += e;
     }
-    z = wave_sum(z);
-    __syncthreads();
+    z = block_sum(z, red);                                   // (its barriers also show every thread the weights)
     const float rz = 1.0f / z;
-    for (int x = threadIdx.x; x < dh; x += 64) {
+    const int groups = dh < AS_THREADS ? AS_THREADS / dh : 1;
+    const int g = dh < AS_THREADS ? (int)threadIdx.x / dh : 0;           // threads past the last whole group: no keys
+    for (int x = dh < AS_THREADS ? (int)threadIdx.x % dh : (int)threadIdx.x; x < dh; x += AS_THREADS) {
         float o = 0.f;
-        for (int j = 0; j < nk; j++) o = fmaf(sc[j], to_f32<TC>(vc[kv_v_idx(geo, x, j)]), o);
-        store_act<TA>(out, plane, r, hh * dh + x, ldo, mtp, o * rz);
+        for (int j = g; g < groups && j < nk; j += groups) o = fmaf(sc[j], to_f32<TC>(vc[kv_v_idx(geo, x, j)]), o);
+        if (groups > 1) {                                    // every thread comes here once: dh < AS_THREADS
+            __syncthreads();                                 // the weights have been read
+            sm[threadIdx.x] = o;
+            __syncthreads();
+            if (g > 0) break;
+            for (int i2 = 1; i2 < groups; i2++) o += sm[i2 * dh + x];
+        }
+        if (g == 0) store_act<TA>(out, plane, r, hh * dh + x, ldo, mtp, o * rz);
     }
+}
+// dynamic LDS: the query and the scores, or one partial output per thread; and what block_max / block_sum need
+static size_t attn_simple_lds(int dh, int keys_pad) {
+    const int n = dh + keys_pad > AS_THREADS ? dh + keys_pad : AS_THREADS;
+    return sizeof(float) * (size_t)(n + 16);
 }
 
 // cache row import / export in canonical [n][H*dh] fp32 form
@@ -815,12 +810,8 @@ static int32_t run_gemm(csd_model *mod, const GemmW &w, const void *act, size_t 
                            : M >= mod->gemm_rs_min_rows ? launch_gemm_rs(mod, w, a, plane, mod->act_mtp, mod->part, M, S_used, st)
                                                         : launch_gemm_ws(w, a, plane, mod->act_mtp, mod->part, M, S_used, st);
         if (rc != CSD_OK) return rc;
-    } else if (mod->cfg.dtype == CSD_DTYPE_BF16) {
-        hipLaunchKernelGGL((k_gemm_simple<bf16_t>), dim3((w.N + 255) / 256), dim3(256), 0, st, (const bf16_t *)w.data,
-                           (const float *)act, mod->part, M, w.K, w.N);
     } else {
-        hipLaunchKernelGGL((k_gemm_simple<float>), dim3((w.N + 255) / 256), dim3(256), 0, st, (const float *)w.data,
-                           (const float *)act, mod->part, M, w.K, w.N);
+        return csd_f32_part(mod, w, (const float *)act, M, st);
     }
     CSD_LAUNCH_CHECK();
     return CSD_OK;
@@ -882,8 +873,7 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
             if ((rc = csd_attn_mfma_enqueue(mod, geo, kv, cache_len, B, m, l, scale, am, st, (bf16_t *)x[1], xp[1])) != CSD_OK) return rc;
         } else {
             ProfScope ps(mod, st, CSD_PROF_ATTN);
-            const size_t lds = sizeof(float) * (size_t)(c.head_dim + mod->seq_pad);
-            hipLaunchKernelGGL((k_attn_simple<TA, TC>), dim3(M, c.n_heads), dim3(64), lds, st, qb, m, cache_len, geo, l,
+            hipLaunchKernelGGL((k_attn_simple<TA, TC>), dim3(M, c.n_heads), dim3(AS_THREADS), attn_simple_lds(c.head_dim, mod->seq_pad), st, qb, m, cache_len, geo, l,
                                (const TC *)kv, scale, mod->q_plane, x[1], hd, xp[1], mod->act_mtp, am);
             CSD_LAUNCH_CHECK();
         }
@@ -939,11 +929,26 @@ static int32_t attention_any(csd_model *mod, const KvGeom &geo, const void *kvba
                              int layer, float scale, const AttnMode &mode, hipStream_t st) {
     if (mod->mfma_attn) return csd_attn_mfma_enqueue(mod, geo, kvbase, cache_len, B, m, layer, scale, mode, st);
     ProfScope ps(mod, st, CSD_PROF_ATTN);
-    const size_t lds = sizeof(float) * (size_t)(mod->cfg.head_dim + geo.seq_pad);
-    hipLaunchKernelGGL((k_attn_simple<TA, TC>), dim3(B * m, mod->cfg.n_heads), dim3(64), lds, st, (const TA *)mod->qbuf, m,
+    hipLaunchKernelGGL((k_attn_simple<TA, TC>), dim3(B * m, mod->cfg.n_heads), dim3(AS_THREADS),
+                       attn_simple_lds(mod->cfg.head_dim, geo.seq_pad), st, (const TA *)mod->qbuf, m,
                        cache_len, geo, layer, (const TC *)kvbase, scale, mod->q_plane, (TA *)mod->act, mod->hd, mod->act_plane,
                        mod->act_mtp, mode);
     CSD_LAUNCH_CHECK();
+    return CSD_OK;
+}
+
+int32_t csd_attn_simple_f32(csd_model *mod, const KvGeom &geo, const float *kv, const int32_t *cache_len, int B, int m, int layer,
+                            float scale, const AttnMode &mode, hipStream_t st) {
+    return attention_any<float, float>(mod, geo, kv, cache_len, B, m, layer, scale, mode, st);
+}
+
+// At model creation: next to the scores of the longest sequence that is accepted (64 KB with the query) the generic
+// attention needs a few words more than the default limit of dynamic LDS.
+int32_t csd_attn_simple_setup() {
+    const int n = 64 * 1024 + 16 * (int)sizeof(float);
+    CSD_HIP(hipFuncSetAttribute((const void *)k_attn_simple<float, float>, hipFuncAttributeMaxDynamicSharedMemorySize, n));
+    CSD_HIP(hipFuncSetAttribute((const void *)k_attn_simple<float, bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, n));
+    CSD_HIP(hipFuncSetAttribute((const void *)k_attn_simple<bf16_t, bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, n));
     return CSD_OK;
 }
 
@@ -1097,8 +1102,7 @@ int32_t csd_forward_enqueue(csd_model *mod, void *kv, const int32_t *tokens, con
         if (mod->mfma) return forward_t5<bf16_t, bf16_t, bf16_t>(mod, kv, tokens, cache_len, B, m, logits, st);
         return forward_t5<bf16_t, float, bf16_t>(mod, kv, tokens, cache_len, B, m, logits, st);
     }
-    if (mod->cfg.dtype == CSD_DTYPE_FP32)
-        return forward_typed<float, float, float>(mod, kv, tokens, cache_len, B, m, logits, st);
+    if (mod->cfg.dtype == CSD_DTYPE_FP32) return csd_f32_enqueue(mod, kv, tokens, cache_len, B, m, logits, st);
     if (mod->mfma) return forward_typed<bf16_t, bf16_t, bf16_t>(mod, kv, tokens, cache_len, B, m, logits, st);
     return forward_typed<bf16_t, float, bf16_t>(mod, kv, tokens, cache_len, B, m, logits, st);
 }

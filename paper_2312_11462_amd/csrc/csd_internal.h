@@ -300,6 +300,13 @@ int32_t csd_chain_setup();
 bool csd_chain_eligible(const csd_model *mod, int32_t B, int32_t m);
 int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int32_t B, int32_t m,
                           float *logits, hipStream_t st);
+int32_t csd_attn_simple_setup();    // models on the generic attention, at creation
+int32_t csd_attn_simple_f32(csd_model *mod, const KvGeom &geo, const float *kv, const int32_t *cache_len, int B, int m, int layer,
+                            float scale, const AttnMode &mode, hipStream_t st);
+// csd_f32.hip: forward of fp32 models (arch 0); the GEMM of models that are not on the matrix cores (partial plane 0)
+int32_t csd_f32_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int32_t B, int32_t m,
+                        float *logits, hipStream_t st);
+int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int M, hipStream_t st);
 // csd_tall.hip: GEMMs over more rows than k_gemm_rs takes, partial sums or with the epilogue inside
 #define CSD_TALL_MIN_ROWS 145
 #define CSD_CROSS_ROWS 512       /* encoder rows that csd_cross_kv_init projects per pass over a layer's matrix */

@@ -88,3 +88,36 @@ def test_cross_projection_rows(P, B, enc_len):
     lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
     ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
     assert ok, f"max abs err {err}"
+
+
+@pytest.mark.parametrize("dims", [(48, 3, 16, 100, 301), (64, 4, 16, 256, 512), (33, 3, 2, 65, 70), (40, 1, 130, 7, 129), (300, 5, 64, 90, 65)],
+                         ids=lambda d: "-".join(map(str, d)))
+@pytest.mark.parametrize("B,m,t", [(1, 1, 1), (2, 4, 30), (1, 9, 400), (3, 17, 63)])
+def test_fp32_forward(P, dims, B, m, t):
+    """The fp32 GEMMs (K slices shorter than a turn, ragged column groups and rotary pairs, rows across workgroups) and the
+    generic attention (heads narrower and wider than the groups of its threads, few and many keys)."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    d, H, dh, F, V = dims
+    shape = I.ModelShape("edge_fp32", 0, "fp32", 2, d, H, dh, F, V)
+    gm, om = make_pair(shape, 31, B, t + m + 3, m, std=0.1)
+    import_synthetic_kv(gm, om, shape, t, 31, B=B)
+    block = I.token_ids(B * m, V, 31, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([max(0, t - 5 * b) for b in range(B)], np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 1e-4, 1e-4)
+    assert ok, f"max abs err {err}"
+    for b in range(B):
+        for got, want in zip(gm.kv_read(1, b, 0, int(cl[b]) + m), om.kv_read(1, b, 0, int(cl[b]) + m)):
+            assert tol_ok(got.cpu().numpy().astype(np.float64), want, 1e-4, 1e-4)[0]
+
+
+def test_generic_attention_longest_sequence(P):
+    """The longest sequence that a model on the generic attention accepts: 64 KB of scores and query."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_long", 0, "fp32", 1, 64, 1, 64, 32, 40)
+    gm, om = make_pair(shape, 3, 1, 16384 - 64, 2, std=0.1)
+    import_synthetic_kv(gm, om, shape, 16300, 3)
+    block, cl = np.asarray([[5, 9]], np.int32), np.asarray([16300], np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 1e-4, 1e-4)
+    assert ok, f"max abs err {err}"
