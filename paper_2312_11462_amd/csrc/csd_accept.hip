@@ -332,18 +332,21 @@ int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int
 // in a record; the last workgroup of a sequence to arrive (a counter) picks the first failing row.  No
 // probability is written unless the caller asks for it, rows are read once, and nothing waits on anything.
 //
-// Wave w holds tokens [4096 w, 4096 w + 4096), and in it lane l holds the 4-token groups at 256 j + 4 l, j = 0..15:
+// Wave w holds 64 * RR_PER consecutive tokens, and in it lane l holds the 4-token groups at 256 j + 4 l:
 // every load is a contiguous kilobyte per wave, and token order is (wave, j, lane, position in the group), which
 // is the order the draw's running sum follows.  The result is that of k_softmax + k_accept bit for bit (exact sums
-// on both sides).  V <= RR_THREADS * RR_PER; 512 threads, so that a thread may hold its 64 values and more in registers.
+// on both sides).  V <= RR_THREADS * RR_PER_MAX; 512 threads, so that a thread may hold its 64 values and more in registers.
 // raw: greedy review with lenience 1, which compares token ids of the arg max of the logits themselves.
+// RR_PER: values per thread, 64, or 16 or 4 for a vocabulary that fits: the work on a thread's values is what the kernel is
+// bound by, padding included (V = 512: 16.8 us with 64 values, 6.5 with 4).
 #define RR_THREADS 512
-#define RR_PER 64
+#define RR_PER_MAX 64
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
+template <int RR_PER>
 __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
     const float *__restrict__ logits, float *__restrict__ probs, unsigned long long *__restrict__ recs,
     unsigned *__restrict__ counters, float inv_t, const float *__restrict__ q, const uint8_t *__restrict__ q_onehot,
@@ -474,9 +477,22 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             }
             unsigned long long Z = 0ull, before = 0ull, wave_total = 0ull;
             for (int pass = 0; pass < 2; pass++) {
+                // weights are at most lenience <= 256, so the high parts of four (at most 2^28 each) and the low parts of
+                // all (at most 2^20 each) add up in 32 bits
                 unsigned long long mine = 0ull;
+                uint32_t sl = 0;
 #pragma unroll
-                for (int i = 0; i < RR_PER; i++) mine += fixed40_small(val[i]);     // weights are at most lenience <= 256
+                for (int j = 0; j < NG; j++) {
+                    uint32_t sh = 0;
+#pragma unroll
+                    for (int c = 0; c < 4; c++) {
+                        uint32_t h, l;
+                        fixed40_parts(val[4 * j + c], h, l);
+                        sh += h, sl += l;
+                    }
+                    mine += sh;
+                }
+                mine = (mine << 20) + sl;
                 wave_total = wave_sum_u64(mine);
                 __syncthreads();
                 if (lane == 0) red64[wv] = wave_total;
@@ -580,7 +596,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
 
 // the kernel takes whole 16-byte groups of four tokens
 bool csd_review_rows_fits(const float *logits, const float *probs, const float *q, int32_t V) {
-    return V % 4 == 0 && V <= RR_THREADS * RR_PER && (uintptr_t)logits % 16 == 0 && (uintptr_t)probs % 16 == 0 &&
+    return V % 4 == 0 && V <= RR_THREADS * RR_PER_MAX && (uintptr_t)logits % 16 == 0 && (uintptr_t)probs % 16 == 0 &&
            (uintptr_t)q % 16 == 0;
 }
 
@@ -591,9 +607,17 @@ int32_t csd_review_rows_enqueue(const float *logits, float *probs, unsigned long
     if (B <= 0) return CSD_OK;
     if (!csd_review_rows_fits(logits, probs, q, V)) return CSD_ESHAPE;
     const int32_t raw = mode == CSD_MODE_GREEDY && !(lenience > 1.0f);
-    hipLaunchKernelGGL(k_review_rows, dim3(k + 1, B), dim3(RR_THREADS), 0, st, logits, probs, recs, counters,
-                       1.0f / (temperature > 0.f ? temperature : 1.0f), q, q_onehot, draft, draft_stride, u_acc, u_samp, k, V,
-                       lenience, mode, raw, n_accepted, next_token);
+#define RR_LAUNCH(PER)                                                                                                     \
+    hipLaunchKernelGGL((k_review_rows<PER>), dim3(k + 1, B), dim3(RR_THREADS), 0, st, logits, probs, recs, counters,        \
+                       1.0f / (temperature > 0.f ? temperature : 1.0f), q, q_onehot, draft, draft_stride, u_acc, u_samp, k, \
+                       V, lenience, mode, raw, n_accepted, next_token)
+    if (V <= RR_THREADS * 4)
+        RR_LAUNCH(4);
+    else if (V <= RR_THREADS * 16)
+        RR_LAUNCH(16);
+    else
+        RR_LAUNCH(RR_PER_MAX);
+#undef RR_LAUNCH
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }

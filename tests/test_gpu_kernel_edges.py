@@ -121,3 +121,47 @@ def test_generic_attention_longest_sequence(P):
     lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
     ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 1e-4, 1e-4)
     assert ok, f"max abs err {err}"
+
+
+@pytest.mark.parametrize("arch,dh", [(0, 64), (0, 128), (1, 64), (1, 128)])
+@pytest.mark.parametrize("max_seq,B,m,t", [(64, 1, 1, 1), (64, 2, 8, 31), (192, 1, 16, 128), (448, 2, 5, 443), (512, 1, 1, 0), (576, 1, 7, 512),
+                                           (832, 2, 3, 829), (896, 1, 4, 600)])
+def test_small_block_attention(P, arch, dh, max_seq, B, m, t):
+    """The attention of blocks of up to 16 rows on either side of the cache lengths where one workgroup per head gives way to
+    chunks: one tile and less, a tile per wave and one key more, waves without a tile, several turns, a full cache."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_attn", arch, "bf16", 1, 256, 2, dh, 256, 512, rms_eps=1e-6 if arch else 1e-5,
+                         enc_len=max(1, min(t, 520)) if arch else 0)
+    gm, om = make_pair(shape, 37, B, max_seq, m, std=0.05)
+    if t:
+        import_synthetic_kv(gm, om, shape, t, 37, B=B)
+    if arch:
+        enc = I.encoder_output(shape, B, 37)
+        gm.cross_kv_init(enc.cuda())
+        om.cross_kv_init(enc.numpy())
+    block = I.token_ids(B * m, shape.vocab, 37, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([max(0, t - 40 * b) for b in range(B)], np.int32)
+    assert gm.path(B, m) == 1
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+
+
+@pytest.mark.parametrize("V", [4, 512, 2048, 2052, 8192, 8196, 32768])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_review_of_all_rows_equals_softmax_then_accept(P, V, mode):
+    """Vocabularies at the limits of the values a thread holds: the fused review decides as the two kernels, bit for bit."""
+    shape = I.ModelShape("edge_review", 0, "fp32", 1, 16, 1, 16, 16, V)
+    gm = P.Model(shape, I.make_weights(shape, 41, device="cuda", std=0.3), max_batch=2, max_seq=16, max_block=6)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    block = torch.randint(0, V, (2, 6), generator=g, device="cuda", dtype=torch.int32)
+    cl = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for dense in (False, True):
+        q = torch.softmax(torch.randn((2, 5, V), generator=g, device="cuda"), -1) if dense else None
+        ua, us = torch.rand((2, 5), generator=g, device="cuda"), torch.rand(2, generator=g, device="cuda")
+        probs = torch.empty((2, 6, V), device="cuda")
+        n, x = gm.verify_accept(block, cl, ua, us, q=q, mode=mode, probs=probs)
+        lg, p = gm.verify_block(block, cl, want_probs=True)
+        n2, x2 = P.accept(lg if mode else p, q, block[:, 1:].contiguous(), ua, us, mode=mode)
+        assert torch.equal(n, n2) and torch.equal(x, x2)
+        assert torch.equal(probs, p)
