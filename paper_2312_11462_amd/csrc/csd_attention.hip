@@ -29,8 +29,14 @@ __device__ __forceinline__ u32x4 attn_load(const bf16_t *p) {
 // A small grid (few sequences and heads) is bound by the chain of memory round trips of each wave, not by
 // bandwidth: with PRE = 4 a wave has its whole 128-key chunk in flight at once (at the price of registers,
 // i.e. of waves per SIMD, which such a grid does not fill anyway).
-template <int DH, int PRE, bool ONCE>
-__global__ __launch_bounds__(64) void k_attn_mfma(const bf16_t *__restrict__ q, size_t qplane, int m, int row_tiles,
+//
+// MODE: what a score needs besides the causal mask, compiled apart because the instructions per score are what a wave with many
+// keys is bound by.  Rows of the block's early row tiles see few of its keys: keys past the last one a row tile sees are left
+// out (a 512-row block over an empty cache: half of the work), a tile that every row sees whole is not masked, and the output is
+// rescaled only where a maximum has moved.  512 rows of the 7B shape, mean over cached lengths 0 and 512: 48.5 -> 33.6 us.
+enum { ATT_PLAIN = 0, ATT_BIAS = 1, ATT_TREE = 2 };
+template <int DH, int PRE, bool ONCE, int MODE>
+__global__ __launch_bounds__(64, PRE == 1 && (MODE == ATT_PLAIN || DH == 64) ? 3 : 1) void k_attn_mfma(const bf16_t *__restrict__ q, size_t qplane, int m, int row_tiles,
                                                   const int32_t *__restrict__ cache_len, KvGeom geo, int layer,
                                                   const bf16_t *__restrict__ kv, float scale, float *__restrict__ part,
                                                   int chunks_max, int chunk_keys, AttnMode mode) {
@@ -43,7 +49,8 @@ __global__ __launch_bounds__(64) void k_attn_mfma(const bf16_t *__restrict__ q, 
     const int hd = geo.H * DH;
     const bool causal = mode.fixed_nk <= 0;
     const int t = causal ? cache_len[b] : 0;
-    const int nk = max(0, min(causal ? t + m : mode.fixed_nk, geo.seq_pad));   // cache rows in play for this block
+    const int nk_all = max(0, min(causal ? t + m : mode.fixed_nk, geo.seq_pad));   // cache rows in play for this block
+    const int nk = causal && MODE != ATT_TREE ? min(nk_all, t + rt * 16 + 16) : nk_all;   // ... for this row tile
     float *po = part + ((((size_t)b * geo.H + hh) * chunks_max + c) * row_tiles + rt) * 16 * PS;
     float *pr = po + (size_t)col * PS;
     const int key0 = c * chunk_keys;
@@ -56,7 +63,7 @@ __global__ __launch_bounds__(64) void k_attn_mfma(const bf16_t *__restrict__ q, 
     }
     const int row = rt * 16 + col;                           // this lane's block row
     const int qpos = t + row;                                // it sees cache rows 0..qpos
-    const unsigned long long anc_row = (mode.anc && row < m) ? mode.anc[b * m + row] : 0ull;
+    const unsigned long long anc_row = (MODE == ATT_TREE && row < m) ? mode.anc[b * m + row] : 0ull;
     u32x4 qf[DH / 32][2];                                    // hi and lo planes of the query
 #pragma unroll
     for (int s = 0; s < DH / 32; s++) {
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(64) void k_attn_mfma(const bf16_t *__restrict__ q, 
             const int kb = key0 + (sub0 + p) * 32;
 #pragma unroll
             for (int j = 0; j < 8; j++) bias[p][j] = 0.f;
-            if (mode.bias_hd && kb < nk && sub0 + p < chunk_keys / 32) {     // uniform; fetched with the tile, ahead of its scores
+            if (MODE == ATT_BIAS && kb < nk && sub0 + p < chunk_keys / 32) {     // uniform; fetched with the tile, ahead of its scores
 #pragma unroll
                 for (int j = 0; j < 8; j++)
                     bias[p][j] = mode.bias_hd[hh * 128 + min(max(qpos - (kb + 8 * g + j), 0), 127)];
@@ -127,53 +134,65 @@ __global__ __launch_bounds__(64) void k_attn_mfma(const bf16_t *__restrict__ q, 
                                                                     __builtin_bit_cast(bf16x8, qf[s][1]), sT[T], 0, 0, 0);
                 }
             }
+            // (uniform) every row of the tile sees all 32 keys
+            const bool whole = MODE != ATT_TREE && kb + 32 <= nk && (!causal || kb + 31 <= t + rt * 16);
             float sv[8];
             float mx = -INFINITY;
 #pragma unroll
             for (int j = 0; j < 8; j++) {
-                const int key = kb + 8 * g + j;
-                float s = sT[j >> 2][j & 3] * scale;
-                const bool seen = (mode.anc ? tree_sees(anc_row, key, t) : (!causal || key <= qpos)) && key < nk;
-                s += bias[p][j];                             // 0 without a bias table; unseen keys are masked next
-                sv[j] = seen ? s : -INFINITY;
-                mx = fmaxf(mx, sv[j]);
+                sv[j] = sT[j >> 2][j & 3] * scale;
+                if (MODE == ATT_BIAS) sv[j] += bias[p][j];   // unseen keys are masked next
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            if (!whole) {
+#pragma unroll
+                for (int j = 0; j < 8; j++) {
+                    const int key = kb + 8 * g + j;
+                    const bool seen = (MODE == ATT_TREE ? tree_sees(anc_row, key, t) : (!causal || key <= qpos)) && key < nk;
+                    sv[j] = seen ? sv[j] : -INFINITY;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 8; j++) mx = fmaxf(mx, sv[j]);
+            mx = groups_max(mx);
             const float mnew = fmaxf(mrun, mx);
-            const float alpha = (mnew == -INFINITY) ? 1.0f : expf(mrun - mnew);
+            const float msafe = mnew == -INFINITY ? 0.f : mnew;              // (no key seen so far: every weight is e^-inf)
+            const float alpha = expf(mrun - msafe);
             float pv[8];
             float psum = 0.f;
 #pragma unroll
             for (int j = 0; j < 8; j++) {
-                pv[j] = (sv[j] == -INFINITY) ? 0.f : expf(sv[j] - mnew);
+                pv[j] = expf(sv[j] - msafe);
                 psum += pv[j];
             }
-            psum += __shfl_xor(psum, 16, 64);
-            psum += __shfl_xor(psum, 32, 64);
-            lrun = lrun * alpha + psum;
+            lrun = lrun * alpha + psum;                      // of this lane's keys; the lane groups are added up at the end
             mrun = mnew;
+            const bool rescale = __any(alpha != 1.0f);       // (uniform)
             u32x4 pf, pl;                                    // hi and lo planes of the probabilities
 #pragma unroll
             for (int w = 0; w < 4; w++) {
-                const bf16_t h0 = f32_to_bf16(pv[2 * w]), h1 = f32_to_bf16(pv[2 * w + 1]);
-                pf[w] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-                pl[w] = (uint32_t)f32_to_bf16(pv[2 * w] - bf16_to_f32(h0)) |
-                        ((uint32_t)f32_to_bf16(pv[2 * w + 1] - bf16_to_f32(h1)) << 16);
+                const uint32_t hpk = pack_bf16x2(pv[2 * w], pv[2 * w + 1]);
+                pf[w] = hpk;
+                pl[w] = pack_bf16x2(pv[2 * w] - __uint_as_float(hpk << 16), pv[2 * w + 1] - __uint_as_float(hpk & 0xFFFF0000u));
             }
-            const bool tail = kb + 32 > nk;                  // rows past nk may hold anything: zero them
+            if (kb + 32 > nk) {                              // (uniform) rows past nk may hold anything: zero them
+                uint32_t keep[4];
+#pragma unroll
+                for (int w = 0; w < 4; w++) {
+                    const int k0 = kb + 8 * g + 2 * w;
+                    keep[w] = (k0 < nk ? 0x0000FFFFu : 0u) | (k0 + 1 < nk ? 0xFFFF0000u : 0u);
+                }
+#pragma unroll
+                for (int dt = 0; dt < DH / 16; dt++)
+#pragma unroll
+                    for (int w = 0; w < 4; w++) vfr[p][dt][w] &= keep[w];
+            }
+            if (rescale) {
+#pragma unroll
+                for (int dt = 0; dt < DH / 16; dt++) oacc[dt] = oacc[dt] * alpha;
+            }
 #pragma unroll
             for (int dt = 0; dt < DH / 16; dt++) {
-                u32x4 vf = vfr[p][dt];
-                if (tail) {
-#pragma unroll
-                    for (int w = 0; w < 4; w++) {
-                        const int k0 = kb + 8 * g + 2 * w;
-                        const uint32_t keep = (k0 < nk ? 0x0000FFFFu : 0u) | (k0 + 1 < nk ? 0xFFFF0000u : 0u);
-                        vf[w] &= keep;
-                    }
-                }
-                oacc[dt] = oacc[dt] * alpha;
+                const u32x4 vf = vfr[p][dt];
                 oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf),
                                                                    __builtin_bit_cast(bf16x8, pf), oacc[dt], 0, 0, 0);
                 oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf),
@@ -183,20 +202,24 @@ __global__ __launch_bounds__(64) void k_attn_mfma(const bf16_t *__restrict__ q, 
     }
 #pragma unroll
     for (int dt = 0; dt < DH / 16; dt++) *reinterpret_cast<f32x4 *>(pr + dt * 16 + 4 * g) = oacc[dt];
+    lrun = groups_sum(lrun);
     if (g == 0) {
         pr[DH] = mrun;
         pr[DH + 1] = lrun;
     }
 }
 
-// out[r][hh*DH + x] = sum_c acc_c[x] e^(m_c - m*) / sum_c l_c e^(m_c - m*)
+// out[r][hh*DH + x] = sum_c acc_c[x] e^(m_c - m*) / sum_c l_c e^(m_c - m*).  Four features per thread, MERGE_ROWS rows per
+// workgroup: with a workgroup of DH threads per (row, head) a block of 512 rows was 16384 workgroups (16.8 us, now 8.8).
+#define MERGE_ROWS 4
 template <int DH>
-__global__ __launch_bounds__(DH) void k_attn_merge(const float *__restrict__ part, int m, int row_tiles,
+__global__ __launch_bounds__(MERGE_ROWS * DH / 4) void k_attn_merge(const float *__restrict__ part, int M, int m, int row_tiles,
                                                    const int32_t *__restrict__ cache_len, int H, int seq_pad,
                                                    int chunks_max, int chunk_keys, bf16_t *__restrict__ out, int ldo,
                                                    size_t plane, int mtp, int fixed_nk) {
     constexpr int PS = DH + 4;
-    const int r = blockIdx.x, hh = blockIdx.y, x = threadIdx.x;
+    const int r = blockIdx.x * MERGE_ROWS + (int)threadIdx.x / (DH / 4), hh = blockIdx.y, x = (int)threadIdx.x % (DH / 4) * 4;
+    if (r >= M) return;
     const int b = r / m, i = r % m, rt = i / 16, ri = i % 16;
     const int nk = max(1, min(fixed_nk > 0 ? fixed_nk : cache_len[b] + m, seq_pad));
     const int nch = (nk + chunk_keys - 1) / chunk_keys;
@@ -205,14 +228,16 @@ __global__ __launch_bounds__(DH) void k_attn_merge(const float *__restrict__ par
     // chunk states are read eight at a time (the index is clamped rather than the load skipped, so all eight
     // loads are in flight together) and folded in chunk order with a running maximum: one pass over the
     // states, one memory round trip per eight chunks
-    float mstar = -INFINITY, num = 0.f, den = 0.f;
+    float mstar = -INFINITY, den = 0.f;
+    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0; c0 < nch; c0 += 8) {
-        float mc[8], ac[8], lc[8];
+        float mc[8], lc[8];
+        f32x4 ac[8];
 #pragma unroll
         for (int u = 0; u < 8; u++) {
             const size_t o = (size_t)min(c0 + u, nch - 1) * cstride;
             mc[u] = base[o + DH];
-            ac[u] = base[o + x];
+            ac[u] = *reinterpret_cast<const f32x4 *>(base + o + x);
             lc[u] = base[o + DH + 1];
         }
         float mnew = mstar;
@@ -231,7 +256,8 @@ __global__ __launch_bounds__(DH) void k_attn_merge(const float *__restrict__ par
         }
         mstar = mnew;
     }
-    store_act<bf16_t>(out, plane, r, hh * DH + x, ldo, mtp, den > 0.f ? num / den : 0.f);
+    const float inv = den > 0.f ? 1.0f / den : 0.f;
+    store_act4<bf16_t>(out, plane, r, hh * DH + x, ldo, mtp, num * inv);
 }
 
 template <int DH>
@@ -239,9 +265,9 @@ static void attn_launch(csd_model *mod, const KvGeom &geo, const void *kv, const
                         float scale, const AttnMode &mode, hipStream_t st, bf16_t *out, size_t out_plane) {
     const csd_model_cfg &c = mod->cfg;
     const int row_tiles = (m + 15) / 16;
-    // Keys per wave.  The kernel's registers allow two waves per SIMD, and waves beyond 2048 would wait for a second
-    // round: chunks of 128 keys when that many waves fit; otherwise as many equal chunks per (sequence, head, row tile)
-    // as fit, of at least 512 keys (measured at batch 8 with 2048 cached rows, one row tile: 1.88 ms of attention per
+    // Keys per wave.  2048 waves are two per SIMD (the plain form has room for three, which at batch 8 over 2048 rows was no
+    // faster: 48.3 against 48.5 us with one row tile, 71.4 against 66.9 with two): chunks of 128 keys when that many waves
+    // fit; otherwise as many equal chunks per (sequence, head, row tile) as fit, of at least 512 keys (measured at batch 8 with 2048 cached rows, one row tile: 1.88 ms of attention per
     // step with 4 to 6 chunks per head against 2.04 with 8; two row tiles: 2.40 ms with 4 equal chunks against 2.91
     // with two of 1024 keys and a short third).
     const int keys = mode.fixed_nk > 0 ? mode.fixed_nk : geo.seq_pad;
@@ -254,18 +280,28 @@ static void attn_launch(csd_model *mod, const KvGeom &geo, const void *kv, const
     int chunks = (keys + chunk_keys - 1) / chunk_keys;
     if (chunks > mod->attn_chunks_max) chunks = mod->attn_chunks_max;
     // a grid the chip holds at one wave per SIMD: each wave requests its whole first 128 keys at once
-#define ATT_LAUNCH(PRE_, ONCE_)                                                                                        \
-    hipLaunchKernelGGL((k_attn_mfma<DH, PRE_, ONCE_>), dim3(c.n_heads, B * row_tiles, chunks), dim3(64), 0, st,             \
+#define ATT_LAUNCH_MODE(PRE_, ONCE_, MODE_)                                                                            \
+    hipLaunchKernelGGL((k_attn_mfma<DH, PRE_, ONCE_, MODE_>), dim3(c.n_heads, B * row_tiles, chunks), dim3(64), 0, st,             \
                        (const bf16_t *)mod->qbuf, mod->q_plane, m, row_tiles, cache_len, geo, layer, (const bf16_t *)kv, scale, \
                        mod->attn_part, mod->attn_chunks_max, chunk_keys, mode)
-    if (chunk_keys == ATT_CHUNK && chunks * items <= 1024)
-        ATT_LAUNCH(4, false);
-    else if (row_tiles == 1)
-        ATT_LAUNCH(1, true);
-    else
-        ATT_LAUNCH(1, false);
+#define ATT_LAUNCH(PRE_, ONCE_)                    \
+    if (mode.anc)                                  \
+        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_TREE);    \
+    else if (mode.bias_hd)                         \
+        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_BIAS);    \
+    else                                           \
+        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_PLAIN);
+    if (chunk_keys == ATT_CHUNK && chunks * items <= 1024) {
+        ATT_LAUNCH(4, false)
+    } else if (row_tiles == 1) {
+        ATT_LAUNCH(1, true)
+    } else {
+        ATT_LAUNCH(1, false)
+    }
 #undef ATT_LAUNCH
-    hipLaunchKernelGGL((k_attn_merge<DH>), dim3(B * m, c.n_heads), dim3(DH), 0, st, mod->attn_part, m, row_tiles, cache_len,
+#undef ATT_LAUNCH_MODE
+    hipLaunchKernelGGL((k_attn_merge<DH>), dim3((B * m + MERGE_ROWS - 1) / MERGE_ROWS, c.n_heads), dim3(MERGE_ROWS * DH / 4), 0, st,
+                       mod->attn_part, B * m, m, row_tiles, cache_len,
                        c.n_heads, geo.seq_pad, mod->attn_chunks_max, chunk_keys, out, mod->hd, out_plane, mod->act_mtp,
                        mode.fixed_nk);
 }

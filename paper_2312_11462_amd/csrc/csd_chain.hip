@@ -323,16 +323,14 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
             sv[j] = seen ? sT[j >> 2][j & 3] * A.scale + bias[j] : -INFINITY;
             mx = fmaxf(mx, sv[j]);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = groups_max(mx);
         float pv[8], psum = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             pv[j] = (sv[j] == -INFINITY) ? 0.f : expf(sv[j] - mx);
             psum += pv[j];
         }
-        psum += __shfl_xor(psum, 16, 64);
-        psum += __shfl_xor(psum, 32, 64);
+        psum = groups_sum(psum);
         mrun = mx;
         lrun = psum;
         u32x4 pf, pl;                                        // hi and lo planes of the probabilities
@@ -571,8 +569,7 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
             sv[j] = seen ? sT[j >> 2][j & 3] * A.scale + bias[j] : -INFINITY;
             mx = fmaxf(mx, sv[j]);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = groups_max(mx);
         const float mnew = fmaxf(mrun, mx);
         const float alpha = mnew == -INFINITY ? 1.0f : expf(mrun - mnew);
         float pv[8], psum = 0.f;
@@ -581,8 +578,7 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
             pv[j] = (sv[j] == -INFINITY) ? 0.f : expf(sv[j] - mnew);
             psum += pv[j];
         }
-        psum += __shfl_xor(psum, 16, 64);
-        psum += __shfl_xor(psum, 32, 64);
+        psum = groups_sum(psum);
         lrun = lrun * alpha + psum;
         mrun = mnew;
         u32x4 pf, pl;                                        // hi and lo planes of the probabilities

@@ -57,13 +57,14 @@ __device__ __forceinline__ void split4(const float *v, u32x2 &hi, u32x2 &lo) {
 }
 
 // Four consecutive columns of one row into the two planes of a fragment-ordered activation buffer.
+template <int AUX = CH_SC1>
 __device__ __forceinline__ void store_planes4(bf16_t *out, int plane_bytes, int mtp, int row, int col, const float *v) {
     u32x2 hi, lo;
     split4(v, hi, lo);
     const int off = (int)(act_tiled_idx(row, col, mtp) * 2);
     const __amdgpu_buffer_rsrc_t r = ch_rsrc(out, (size_t)2 * plane_bytes);
-    __builtin_amdgcn_raw_buffer_store_b64(hi, r, off, 0, CH_SC1);
-    __builtin_amdgcn_raw_buffer_store_b64(lo, r, off + plane_bytes, 0, CH_SC1);
+    __builtin_amdgcn_raw_buffer_store_b64(hi, r, off, 0, AUX);
+    __builtin_amdgcn_raw_buffer_store_b64(lo, r, off + plane_bytes, 0, AUX);
 }
 
 // What the epilogue of one (tile, row tile) needs besides the sums, fetched before the main loop.
@@ -74,8 +75,8 @@ struct EpiIn {
 };
 
 // The epilogue of one output tile (gate|up: a gate tile and its up tile) for the 16 rows of one row tile, on complete,
-// rstd-scaled sums v.  row: this lane's block row; T: global index of the (first) tile.  No workgroup barrier inside.
-template <int EPI>
+// rstd-scaled sums v (AUX: cache policy of the stores).  row: this lane's block row; T: global index of the (first) tile.  No workgroup barrier inside.
+template <int EPI, int AUX = CH_SC1>
 __device__ __forceinline__ void gemm_epilogue(const ChainGemm &P, const f32x4 *v, const EpiIn &E, int row, int T, int g) {
     constexpr int UT = EPI == EPI_GU ? 2 : 1;
     const bool valid = row < P.M;
@@ -87,12 +88,12 @@ __device__ __forceinline__ void gemm_epilogue(const ChainGemm &P, const f32x4 *v
         if (!valid) return;
         const int col = T * 16 + 4 * g;
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hv), ch_rsrc(P.h, (size_t)P.M * P.d * 4),
-                                               (int)(((size_t)row * P.d + col) * 4), 0, CH_SC1);
+                                               (int)(((size_t)row * P.d + col) * 4), 0, AUX);
         const float o[4] = {hv[0] * E.gcur[0], hv[1] * E.gcur[1], hv[2] * E.gcur[2], hv[3] * E.gcur[3]};
-        store_planes4(P.out, P.out_plane_bytes, P.mtp, row, col, o);
+        store_planes4<AUX>(P.out, P.out_plane_bytes, P.mtp, row, col, o);
         if (g == 0)
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, ss),
-                                                  ch_rsrc(P.ssq_out, (size_t)(P.d / 16) * P.ssq_rows * 4), (T * P.ssq_rows + row) * 4, 0, CH_SC1);
+                                                  ch_rsrc(P.ssq_out, (size_t)(P.d / 16) * P.ssq_rows * 4), (T * P.ssq_rows + row) * 4, 0, AUX);
     } else if (EPI == EPI_GU) {
         if (!valid) return;
         float o[4];
@@ -103,7 +104,7 @@ __device__ __forceinline__ void gemm_epilogue(const ChainGemm &P, const f32x4 *v
                                    : gt / (1.0f + expf(-gt));
             o[r] = a * up;
         }
-        store_planes4(P.out, P.out_plane_bytes, P.mtp, row, (T / 2) * 16 + 4 * g, o);
+        store_planes4<AUX>(P.out, P.out_plane_bytes, P.mtp, row, (T / 2) * 16 + 4 * g, o);
     } else if (EPI == EPI_LOGITS) {
         if (!valid) return;
         *reinterpret_cast<f32x4 *>(P.logits + (size_t)row * P.V + T * 16 + 4 * g) = v[0];
@@ -130,8 +131,8 @@ __device__ __forceinline__ void gemm_epilogue(const ChainGemm &P, const f32x4 *v
                 split4(o, hi, lo);
                 const __amdgpu_buffer_rsrc_t rq = ch_rsrc(P.q, (size_t)2 * P.q_plane_bytes);
                 const int off = (int)(((size_t)row * P.hd + head * P.dh + p0) * 2);
-                __builtin_amdgcn_raw_buffer_store_b64(hi, rq, off, 0, CH_SC1);
-                __builtin_amdgcn_raw_buffer_store_b64(lo, rq, off + P.q_plane_bytes, 0, CH_SC1);
+                __builtin_amdgcn_raw_buffer_store_b64(hi, rq, off, 0, AUX);
+                __builtin_amdgcn_raw_buffer_store_b64(lo, rq, off + P.q_plane_bytes, 0, AUX);
             } else if (pos >= 0 && pos < P.geo.seq_pad) {
                 u32x2 kk;
                 kk[0] = pack_bf16x2(o[0], o[1]);
@@ -140,7 +141,7 @@ __device__ __forceinline__ void gemm_epilogue(const ChainGemm &P, const f32x4 *v
                 // keys, the rest in the per-lane offset; written through, the attention step may run on another die)
                 const size_t he = kv_head_elems(P.geo);
                 __builtin_amdgcn_raw_buffer_store_b64(kk, ch_rsrc(P.kv + kv_k_off(P.geo, P.layer, 0, 0), (size_t)P.geo.Bmax * P.geo.H * he * 2),
-                                                      (int)((((size_t)b * P.geo.H + head) * he + (size_t)pos * P.dh + p0) * 2), 0, CH_SC1);
+                                                      (int)((((size_t)b * P.geo.H + head) * he + (size_t)pos * P.dh + p0) * 2), 0, AUX);
             }
         } else if (valid && pos >= 0 && pos < P.geo.seq_pad) {
             const size_t he = kv_head_elems(P.geo);
@@ -149,7 +150,7 @@ __device__ __forceinline__ void gemm_epilogue(const ChainGemm &P, const f32x4 *v
             for (int r = 0; r < 4; r++)
                 __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v[0][r]), rv,
                                                       (int)((((size_t)b * P.geo.H + head) * he + kv_v_idx(P.geo, 16 * ti + 4 * g + r, pos)) * 2), 0,
-                                                      CH_SC1);
+                                                      AUX);
         }
     }
 }

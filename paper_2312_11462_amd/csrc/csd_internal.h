@@ -131,6 +131,21 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// maximum / sum over the four lanes with the same lane % 16 (the lane groups of a matrix operand), in every one of them: two
+// register swaps, where a shuffle would go through LDS
+__device__ __forceinline__ float groups_max(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float groups_sum(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // sum over a block of up to 1024 threads; every thread gets the result; `red` holds >= 16 floats
 __device__ __forceinline__ float block_sum(float v, float *red) {
     v = wave_sum(v);

@@ -189,7 +189,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
                 f32x4 v[UT];
 #pragma unroll
                 for (int i = 0; i < UT; i++) v[i] = acc[r][c + i] * rs;
-                gemm_epilogue<EPI>(P, v, E, row, T, g);
+                // (plain stores: neighbouring lanes and tiles fill whole lines in L2; written through, QKV took 8 us more)
+                gemm_epilogue<EPI, 0>(P, v, E, row, T, g);
             }
         }
     }
@@ -225,7 +226,8 @@ int32_t csd_tall_setup() {
 // Column tiles per wave and K splits: the pair with the shortest launch by a model fitted to measurements at the 7B shape
 // (512 rows).  A k-step of a workgroup takes 0.07 us * (CTW + 2) where every compute unit holds one workgroup, or two of them
 // twice that; a split's partial sums are written and read back at about 4 TB/s.  QKV 6 tiles per wave (256 workgroups, 81 us;
-// 4: 384 workgroups, 107), gate|up 6 (460, 146 us; 4: 688, 162), O and down 4 tiles and 2 splits (256; without
+// 4: 384 workgroups, 107), gate|up 6 (460 workgroups, two per compute unit, 146 us; 4: 688, 162), LM head 4 (1000, 223 us; 6: 668
+// in two such rounds, 267), O and down 4 tiles and 2 splits (256; without
 // a split O takes 58 us against 34).  max_splits = 1 where the epilogue runs in the kernel.
 static void tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats, int *ctw_out, int *S_out) {
     const int rblocks = ((M + 15) / 16 + 2 * TALL_RTW - 1) / (2 * TALL_RTW);
@@ -237,7 +239,7 @@ static void tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_fl
         for (int S = 1; S <= max_splits; S++) {
             if (S > 1 && (KS / S < 6 || (size_t)S * M * n_tiles * 16 > part_floats)) break;
             const long long wgs = (long long)groups * rblocks * S;
-            const double rounds = (double)((wgs + 255) / 256);
+            const double rounds = ctw == 4 || wgs <= 256 ? (double)((wgs + 255) / 256) : 2.0 * (double)((wgs + 511) / 512);
             const double us = rounds * (ctw + 2) * ((KS + S - 1) / S) * 0.07 + (max_splits > 1 ? S * 8.0 * M * n_tiles * 16 / 4e6 : 0.0);
             if (us < best) best = us, *ctw_out = ctw, *S_out = S;
         }
