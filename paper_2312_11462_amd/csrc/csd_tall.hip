@@ -1,5 +1,5 @@
 // GEMM for blocks of more rows than csd_chain.hip and k_gemm_rs take (a new prompt in large blocks, the encoder rows of
-// an arch 1 prompt): tiles of up to 192 columns x 128 rows per workgroup, both operands through LDS.
+// an arch 1 prompt): tiles of up to 192 columns x 128 rows (96 where that wastes less) per workgroup, both operands through LDS.
 //
 // With hundreds of rows the matrix instructions bound a launch (two activation planes: 4 * M * N * K operations), so what
 // counts is how little has to move per matrix instruction.  Four waves share a tile as a 2 x 2 grid; a wave owns CTW column
@@ -198,15 +198,25 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
 
 // ------------------------------------------------------------------------------- host driver
 
-#define TALL_RTW 4            /* 128 rows per workgroup */
+// Row tiles per wave: 4 (128 rows per workgroup), or 3 (96) where that takes no more row blocks: as many workgroups, each
+// with three quarters of the matrix instructions and fewer fragments to bring in (145 to 192 rows, 257 to 288, encoder
+// rows up to 96).  Forward of eight layers of the 7B shape and the LM head: 192 rows 2163 -> 1894 us, 288 rows 3083 -> 2676; twelve layers of the
+// 160M shape: 192 rows 1012 -> 881, 288 rows 1039 -> 905; 193 and 289 rows, on four row tiles both times, unchanged.
+static int tall_rtw(int M) {
+    const int row_tiles = (M + 15) / 16;
+    return (row_tiles + 5) / 6 == (row_tiles + 7) / 8 ? 3 : 4;
+}
+static int tall_rblocks(int M) { return ((M + 15) / 16 + 2 * tall_rtw(M) - 1) / (2 * tall_rtw(M)); }
 
-template <int CTW, int NST>
-static constexpr int tall_lds() { return NST * (2 * CTW + 4 * TALL_RTW) * 1024; }
+template <int CTW, int RTW, int NST>
+static constexpr int tall_lds() { return NST * (2 * CTW + 4 * RTW) * 1024; }
 
 template <int CTW, int NST, int EPI>
 static hipError_t tall_allow_lds() {
-    return hipFuncSetAttribute((const void *)k_gemm_tall<CTW, TALL_RTW, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               tall_lds<CTW, NST>());
+    const hipError_t e = hipFuncSetAttribute((const void *)k_gemm_tall<CTW, 4, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             tall_lds<CTW, 4, NST>());
+    return e != hipSuccess ? e : hipFuncSetAttribute((const void *)k_gemm_tall<CTW, 3, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     tall_lds<CTW, 3, NST>());
 }
 
 int32_t csd_tall_setup() {
@@ -230,7 +240,7 @@ int32_t csd_tall_setup() {
 // in two such rounds, 267), O and down 4 tiles and 2 splits (256; without
 // a split O takes 58 us against 34).  max_splits = 1 where the epilogue runs in the kernel.
 static void tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats, int *ctw_out, int *S_out) {
-    const int rblocks = ((M + 15) / 16 + 2 * TALL_RTW - 1) / (2 * TALL_RTW);
+    const int rblocks = tall_rblocks(M);
     double best = 1e30;
     *ctw_out = 6;
     *S_out = 1;
@@ -250,19 +260,26 @@ template <int EPI>
 static int32_t tall_launch(TallArgs &A, int max_splits, size_t part_floats, hipStream_t st) {
     int ctw;
     tall_plan(A.n_tiles, A.g.KS, A.g.M, max_splits, part_floats, &ctw, &A.S);
-    A.rblocks = ((A.g.M + 15) / 16 + 2 * TALL_RTW - 1) / (2 * TALL_RTW);
+    A.rblocks = tall_rblocks(A.g.M);
     const int grid = (A.n_tiles + 2 * ctw - 1) / (2 * ctw) * A.rblocks * A.S;
-#define TALL_LAUNCH(CTW, NST) \
-    hipLaunchKernelGGL((k_gemm_tall<CTW, TALL_RTW, NST, EPI>), dim3(grid), dim3(256), (tall_lds<CTW, NST>()), st, A)
+#define TALL_LAUNCH_R(CTW, RTW, NST) \
+    hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, A)
+#define TALL_LAUNCH(CTW, NST)           \
+    if (tall_rtw(A.g.M) == 3)           \
+        TALL_LAUNCH_R(CTW, 3, NST);     \
+    else                                \
+        TALL_LAUNCH_R(CTW, 4, NST)
     // with more workgroups than compute units two of them share one (two stages each), which evens out the last round:
     // gate|up 146 us against 155 with three stages and one workgroup at a time; at 256 workgroups 117 against 81
-    if (ctw == 4)
+    if (ctw == 4) {
         TALL_LAUNCH(4, 4);
-    else if (grid > 256)
+    } else if (grid > 256) {
         TALL_LAUNCH(6, 2);
-    else
+    } else {
         TALL_LAUNCH(6, 3);
+    }
 #undef TALL_LAUNCH
+#undef TALL_LAUNCH_R
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }

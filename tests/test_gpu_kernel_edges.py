@@ -47,9 +47,9 @@ BF128 = I.ModelShape("edge_dh128", 0, "bf16", 2, 256, 2, 128, 480, 1040)
 
 
 @pytest.mark.parametrize("shape", [BF, BF128], ids=["dh64", "dh128"])
-@pytest.mark.parametrize("B,m", [(1, 145), (1, 256), (1, 257), (2, 100), (3, 173)])
+@pytest.mark.parametrize("B,m", [(1, 145), (1, 192), (1, 193), (1, 256), (1, 257), (1, 288), (1, 289), (2, 100), (3, 173)])
 def test_tall_blocks(P, shape, B, m):
-    """The GEMMs over many rows: one row more than the row-split form takes, whole and ragged 128-row blocks, rows of several
+    """The GEMMs over many rows: one row more than the row-split form takes, whole and ragged blocks of 96 and of 128 rows, rows of several
     sequences in one row tile, column tiles that do not fill a workgroup.  Tolerances: the project's (bf16)."""
     from gpu_util import make_pair, prefill_both, tol_ok
     gm, om = make_pair(shape, 17, B, 40 + m, m, std=0.05)
@@ -73,7 +73,7 @@ def test_tall_blocks(P, shape, B, m):
             assert ok, f"cache rows of sequence {b}: max abs err {err}"
 
 
-@pytest.mark.parametrize("B,enc_len", [(1, 1), (1, 31), (1, 130), (2, 300), (3, 171)])
+@pytest.mark.parametrize("B,enc_len", [(1, 1), (1, 31), (1, 96), (1, 97), (1, 130), (2, 300), (3, 171)])
 def test_cross_projection_rows(P, B, enc_len):
     """Encoder rows of several sequences in one pass: a single row, ragged row tiles and row blocks, sequences that cross the
     limit of 512 rows per pass."""
