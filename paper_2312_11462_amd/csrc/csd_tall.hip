@@ -1,5 +1,5 @@
 // GEMM for blocks of more rows than csd_chain.hip and k_gemm_rs take (a new prompt in large blocks, the encoder rows of
-// an arch 1 prompt): tiles of up to 192 columns x 128 rows (96 where that wastes less) per workgroup, both operands through LDS.
+// an arch 1 prompt): tiles of up to 192 columns x 128 rows per workgroup, both operands through LDS.
 //
 // With hundreds of rows the matrix instructions bound a launch (two activation planes: 4 * M * N * K operations), so what
 // counts is how little has to move per matrix instruction.  Four waves share a tile as a 2 x 2 grid; a wave owns CTW column
@@ -198,88 +198,87 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
 
 // ------------------------------------------------------------------------------- host driver
 
-// Row tiles per wave: 4 (128 rows per workgroup), or 3 (96) where that takes no more row blocks: as many workgroups, each
-// with three quarters of the matrix instructions and fewer fragments to bring in (145 to 192 rows, 257 to 288, encoder
-// rows up to 96).  Forward of eight layers of the 7B shape and the LM head: 192 rows 2163 -> 1894 us, 288 rows 3083 -> 2676; twelve layers of the
-// 160M shape: 192 rows 1012 -> 881, 288 rows 1039 -> 905; 193 and 289 rows, on four row tiles both times, unchanged.
-static int tall_rtw(int M) {
-    const int row_tiles = (M + 15) / 16;
-    return (row_tiles + 5) / 6 == (row_tiles + 7) / 8 ? 3 : 4;
-}
-static int tall_rblocks(int M) { return ((M + 15) / 16 + 2 * tall_rtw(M) - 1) / (2 * tall_rtw(M)); }
-
 template <int CTW, int RTW, int NST>
 static constexpr int tall_lds() { return NST * (2 * CTW + 4 * RTW) * 1024; }
 
-template <int CTW, int NST, int EPI>
+template <int CTW, int RTW, int NST, int EPI>
 static hipError_t tall_allow_lds() {
-    const hipError_t e = hipFuncSetAttribute((const void *)k_gemm_tall<CTW, 4, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             tall_lds<CTW, 4, NST>());
-    return e != hipSuccess ? e : hipFuncSetAttribute((const void *)k_gemm_tall<CTW, 3, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     tall_lds<CTW, 3, NST>());
+    return hipFuncSetAttribute((const void *)k_gemm_tall<CTW, RTW, NST, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               tall_lds<CTW, RTW, NST>());
 }
 
 int32_t csd_tall_setup() {
-#define TALL_ALLOW(EPI)                         \
-    CSD_HIP((tall_allow_lds<4, 4, EPI>()));     \
-    CSD_HIP((tall_allow_lds<6, 3, EPI>()));     \
-    CSD_HIP((tall_allow_lds<6, 2, EPI>()));
+#define TALL_ALLOW_R(RTW, EPI)                       \
+    CSD_HIP((tall_allow_lds<4, RTW, 4, EPI>()));     \
+    CSD_HIP((tall_allow_lds<6, RTW, 3, EPI>()));     \
+    CSD_HIP((tall_allow_lds<6, RTW, 2, EPI>()));
+#define TALL_ALLOW(EPI) TALL_ALLOW_R(2, EPI) TALL_ALLOW_R(3, EPI) TALL_ALLOW_R(4, EPI)
     TALL_ALLOW(EPI_PART)
     TALL_ALLOW(EPI_CROSS)
     TALL_ALLOW(EPI_QKV)
     TALL_ALLOW(EPI_GU)
     TALL_ALLOW(EPI_LOGITS)
 #undef TALL_ALLOW
+#undef TALL_ALLOW_R
     return CSD_OK;
 }
 
-// Column tiles per wave and K splits: the pair with the shortest launch by a model fitted to measurements at the 7B shape
-// (512 rows).  A k-step of a workgroup takes 0.07 us * (CTW + 2) where every compute unit holds one workgroup, or two of them
-// twice that; a split's partial sums are written and read back at about 4 TB/s.  QKV 6 tiles per wave (256 workgroups, 81 us;
-// 4: 384 workgroups, 107), gate|up 6 (460 workgroups, two per compute unit, 146 us; 4: 688, 162), LM head 4 (1000, 223 us; 6: 668
-// in two such rounds, 267), O and down 4 tiles and 2 splits (256; without
-// a split O takes 58 us against 34).  max_splits = 1 where the epilogue runs in the kernel.
-static void tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats, int *ctw_out, int *S_out) {
-    const int rblocks = tall_rblocks(M);
-    double best = 1e30;
-    *ctw_out = 6;
-    *S_out = 1;
-    for (int ctw = 6; ctw >= 4; ctw -= 2) {
-        const int groups = (n_tiles + 2 * ctw - 1) / (2 * ctw);
+// Column tiles per wave (6 or 4), row tiles per wave (4, 3 or 2: row blocks of 128, 96 or 64) and K splits: the triple with the
+// shortest launch by a model fitted to traces of the 7B and 160M shapes at 160 to 512 rows (60 launches in each of the six forms; the
+// form it picks is on average within 1 % of the fastest one).  A k-step of one workgroup per compute unit takes `one` us; with 6
+// column tiles and more workgroups than compute units two share one (two stages each) and 512 of them take `two`; 4 column tiles go in rounds of
+// 256.  Beside it the prologue and the epilogue, 0.5 us per tile of a wave (once per round where only one workgroup fits a compute unit,
+// else under the other's k-steps), and the splits' partial sums.
+// Narrow tiles fill the chip where a matrix is small or its row blocks few: 160M shape, 512 rows, QKV 29.8 us in 48 workgroups
+// of 6 x 4 tiles per wave, 14.1 in 144 of 4 x 2; 7B shape, 384 rows, QKV 92.3 us at 6 x 4 (192 workgroups), 77.2 at 6 x 3 (256); 512 rows, where 6 x 4
+// makes 256 workgroups, 98.5 against 127.6 at 6 x 3.  max_splits = 1 where the epilogue runs in the kernel.
+struct TallPlan {
+    int ctw, rtw, S, rblocks, grid;
+};
+static TallPlan tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats) {
+    static const struct {
+        int ctw, rtw;
+        double one, two;
+    } forms[6] = {{6, 4, 0.60, 1.09}, {6, 3, 0.49, 0.885}, {6, 2, 0.43, 0.85}, {4, 4, 0.45, 0}, {4, 3, 0.37, 0}, {4, 2, 0.29, 0}};
+    const int row_tiles = (M + 15) / 16;
+    TallPlan best{};
+    double best_us = 1e30;
+    for (const auto &f : forms) {
+        const int rblocks = (row_tiles + 2 * f.rtw - 1) / (2 * f.rtw), groups = (n_tiles + 2 * f.ctw - 1) / (2 * f.ctw);
         for (int S = 1; S <= max_splits; S++) {
             if (S > 1 && (KS / S < 6 || (size_t)S * M * n_tiles * 16 > part_floats)) break;
             const long long wgs = (long long)groups * rblocks * S;
-            const double rounds = ctw == 4 || wgs <= 256 ? (double)((wgs + 255) / 256) : 2.0 * (double)((wgs + 511) / 512);
-            const double us = rounds * (ctw + 2) * ((KS + S - 1) / S) * 0.07 + (max_splits > 1 ? S * 8.0 * M * n_tiles * 16 / 4e6 : 0.0);
-            if (us < best) best = us, *ctw_out = ctw, *S_out = S;
+            const bool pairs = f.ctw == 6 && wgs > 256;
+            const double rounds = (double)(pairs ? (wgs + 511) / 512 : (wgs + 255) / 256);
+            const double ends = 0.5 * f.ctw * f.rtw * (f.ctw == 4 && f.rtw == 4 ? rounds : 1.0);
+            const double us = rounds * ((KS + S - 1) / S) * (pairs ? f.two : f.one) + ends +
+                              (max_splits > 1 ? S * 4.0 * M * n_tiles * 16 / 4e6 : 0.0);
+            if (us < best_us) best_us = us, best = TallPlan{f.ctw, f.rtw, S, rblocks, (int)wgs};
         }
     }
+    return best;
 }
 
 template <int EPI>
 static int32_t tall_launch(TallArgs &A, int max_splits, size_t part_floats, hipStream_t st) {
-    int ctw;
-    tall_plan(A.n_tiles, A.g.KS, A.g.M, max_splits, part_floats, &ctw, &A.S);
-    A.rblocks = tall_rblocks(A.g.M);
-    const int grid = (A.n_tiles + 2 * ctw - 1) / (2 * ctw) * A.rblocks * A.S;
-#define TALL_LAUNCH_R(CTW, RTW, NST) \
-    hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, A)
-#define TALL_LAUNCH(CTW, NST)           \
-    if (tall_rtw(A.g.M) == 3)           \
-        TALL_LAUNCH_R(CTW, 3, NST);     \
-    else                                \
-        TALL_LAUNCH_R(CTW, 4, NST)
-    // with more workgroups than compute units two of them share one (two stages each), which evens out the last round:
-    // gate|up 146 us against 155 with three stages and one workgroup at a time; at 256 workgroups 117 against 81
-    if (ctw == 4) {
-        TALL_LAUNCH(4, 4);
-    } else if (grid > 256) {
-        TALL_LAUNCH(6, 2);
-    } else {
-        TALL_LAUNCH(6, 3);
+    const TallPlan p = tall_plan(A.n_tiles, A.g.KS, A.g.M, max_splits, part_floats);
+    A.S = p.S;
+    A.rblocks = p.rblocks;
+#define TALL_LAUNCH(CTW, RTW, NST) \
+    hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(p.grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, A)
+    // with 6 column tiles and more workgroups than compute units two of them share one (two stages each), which evens out the
+    // last round: gate|up at 512 rows 146 us against 155 with three stages and one workgroup at a time; at 256 workgroups 117 against 81
+#define TALL_LAUNCH_R(RTW)                                \
+    {                                                     \
+        if (p.ctw == 4) TALL_LAUNCH(4, RTW, 4);           \
+        else if (p.grid > 256) TALL_LAUNCH(6, RTW, 2);    \
+        else TALL_LAUNCH(6, RTW, 3);                      \
     }
-#undef TALL_LAUNCH
+    if (p.rtw == 4) TALL_LAUNCH_R(4)
+    else if (p.rtw == 3) TALL_LAUNCH_R(3)
+    else TALL_LAUNCH_R(2)
 #undef TALL_LAUNCH_R
+#undef TALL_LAUNCH
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }

@@ -73,6 +73,20 @@ def test_tall_blocks(P, shape, B, m):
             assert ok, f"cache rows of sequence {b}: max abs err {err}"
 
 
+@pytest.mark.parametrize("m", [192, 256, 384, 512])
+def test_tall_tile_forms(P, m):
+    """Matrices wide enough that the plan takes every width and height of tile, and two workgroups per compute unit (the
+    shapes above all go to the narrowest).  Tolerances: the project's (bf16)."""
+    from gpu_util import make_pair, tol_ok
+    shape = I.ModelShape("edge_forms", 0, "bf16", 1, 512, 16, 128, 6144, 32000)
+    gm, om = make_pair(shape, 19, 1, m + 3, m, std=0.05)
+    block = I.token_ids(m, shape.vocab, 19, 1).reshape(1, m).numpy().astype(np.int32)
+    cl = np.zeros(1, np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+
+
 @pytest.mark.parametrize("B,enc_len", [(1, 1), (1, 31), (1, 96), (1, 97), (1, 130), (2, 300), (3, 171)])
 def test_cross_projection_rows(P, B, enc_len):
     """Encoder rows of several sequences in one pass: a single row, ragged row tiles and row blocks, sequences that cross the
