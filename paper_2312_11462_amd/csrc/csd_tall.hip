@@ -19,6 +19,7 @@ enum { EPI_PART = 4, EPI_CROSS = 5 };       // besides the epilogues of csd_epil
 struct TallArgs {
     ChainGemm g;
     int n_tiles, S, rblocks;
+    int chain;                // k-steps (even) added up in the accumulators before these go into the sums kept beside them
     float *part;              // EPI_PART: partial sums [S][M][16 n_tiles]
     const float *rstd;        // [M] scale of the folded norm (EPI_QKV, EPI_GU, EPI_LOGITS)
     int enc_len, row0;        // EPI_CROSS: row r of the launch is encoder row (row0 + r) % enc_len of sequence (row0 + r) / enc_len
@@ -68,8 +69,21 @@ __device__ __forceinline__ void cross_epilogue(const TallArgs &A, const f32x4 &v
     }
 }
 
+// Sums over K in chains, as many as the row-split form has K splits for the same matrix: one chain through all of K rounds at the
+// size of the whole sum in every step (7B shape, two layers, 512 rows, against 64 bits with the K/V rows as stored: logits off by
+// 5.52e-6 in one chain, 5.42e-6 in chains and with the row-split form; encoder rows through 4096 features: 2.7e-4 of the K/V
+// elements rounded to the other side in one chain, 2.0e-4 with the split form, 1.5e-4 in chains).  At a chain's end the
+// accumulators go into a second set of sums and start from zero.  Where two workgroups with 6 x 4 tiles per wave share a compute
+// unit there are no registers for a second set (one workgroup per compute unit: gate|up at 512 rows 8 % slower; the sums in memory:
+// 15 %): the upper 16 bits of the sum are set aside, packed in pairs, two thirds in registers and the rest in LDS, and the
+// accumulators go on from what is left below them, which is exact and as good as zero.  Cost of either: 1 to 2 % of a call.
+template <int CTW, int RTW, int NST>
+static constexpr bool tall_sums() { return !(CTW == 6 && RTW == 4 && NST == 2); }
+#define TALL_LEADS 16         /* tiles of a wave whose upper halves stay in registers */
+
 template <int CTW, int RTW, int NST, int EPI>
-__global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
+__global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void k_gemm_tall(const TallArgs A) {
+    constexpr bool SUMS = tall_sums<CTW, RTW, NST>();
     extern __shared__ __align__(16) char tall_smem[];
     constexpr int WF = 2 * CTW, NF = WF + 4 * RTW;               // fragments of a stage: W tiles, then [plane][row tile]
     constexpr int PW = (NF + 3) / 4;                             // per wave: fragments w, w + 4, ... (the last one again past the end)
@@ -119,6 +133,23 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
         for (int c = 0; c < CTW; c++) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < NST; p++) load_stage(ks0 + p, p);
+    f32x4 sum[RTW][CTW];
+    u32x2 lead[TALL_LEADS];
+    u32x2 *lead_lds = reinterpret_cast<u32x2 *>(tall_smem + NST * NF * 1024) + threadIdx.x;
+    auto set_lead = [&](int i, u32x2 v) {
+        if (i < TALL_LEADS)
+            lead[i] = v;
+        else
+            lead_lds[(i - TALL_LEADS) * 256] = v;
+    };
+    auto get_lead = [&](int i) { return i < TALL_LEADS ? lead[i < TALL_LEADS ? i : 0] : lead_lds[(i - TALL_LEADS) * 256]; };
+#pragma unroll
+    for (int r = 0; r < RTW; r++)
+#pragma unroll
+        for (int c = 0; c < CTW; c++) {
+            sum[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (!SUMS) set_lead(r * CTW + c, u32x2{0u, 0u});
+        }
     const u32x4 *L = reinterpret_cast<const u32x4 *>(tall_smem) + lane;
     const int wo = wc * CTW * 64, ao = (WF + wr * RTW) * 64;     // this wave's W tiles and (hi) row tiles of a stage
     u32x4 fa[2][2][RTW], fw[2][CTW];                             // [k-step parity]
@@ -150,16 +181,61 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
         cur = nxt;                                                                                                    \
         nxt = nxt + 1 == NST ? 0 : nxt + 1;                                                                           \
     }
+    const int t = lane & 15, g = lane >> 4;
+    bool kept = false;                                           // uniform
     int k = ks0;
-    for (; k + 1 < ks1; k += 2) {
-        TALL_STEP(0, k)
-        TALL_STEP(1, k + 1)
+    for (;;) {
+        const int ke = min(k + A.chain, ks1);
+        for (; k + 1 < ke; k += 2) {
+            TALL_STEP(0, k)
+            TALL_STEP(1, k + 1)
+        }
+        if (k + 1 >= ks1) break;
+        asm volatile("");                                        // (a branch, not a selection between both outcomes)
+#pragma unroll
+        for (int r = 0; r < RTW; r++)
+#pragma unroll
+            for (int c = 0; c < CTW; c++) {
+                if constexpr (SUMS) {
+                    sum[r][c] += acc[r][c];
+                    acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+                } else {
+                    u32x2 ld = get_lead(r * CTW + c);
+#pragma unroll
+                    for (int i = 0; i < 4; i++) {            // (a sum that is not finite stays one in the upper half)
+                        const float old = __uint_as_float(i & 1 ? ld[i / 2] & 0xFFFF0000u : ld[i / 2] << 16);
+                        const uint32_t top = __float_as_uint(old + acc[r][c][i]) & 0xFFFF0000u;
+                        const float rest = acc[r][c][i] - (__uint_as_float(top) - old);
+                        acc[r][c][i] = __builtin_isfinite(rest) ? rest : 0.f;
+                        ld[i / 2] = i & 1 ? (ld[i / 2] & 0xFFFFu) | top : (ld[i / 2] & 0xFFFF0000u) | (top >> 16);
+                    }
+                    set_lead(r * CTW + c, ld);
+                }
+            }
+        kept = true;
     }
     if (k < ks1) TALL_STEP(0, k)
 #undef TALL_STEP
     wait_loads<0>();                                             // nothing may land in this LDS after the workgroup has ended
+    if (kept) {
+        asm volatile("");
+#pragma unroll
+        for (int r = 0; r < RTW; r++)
+#pragma unroll
+            for (int c = 0; c < CTW; c++) {
+                if constexpr (SUMS) {
+                    acc[r][c] += sum[r][c];
+                } else {
+                    const u32x2 ld = get_lead(r * CTW + c);
+#pragma unroll
+                    for (int h = 0; h < 2; h++) {
+                        acc[r][c][2 * h] += __uint_as_float(ld[h] << 16);
+                        acc[r][c][2 * h + 1] += __uint_as_float(ld[h] & 0xFFFF0000u);
+                    }
+                }
+            }
+    }
 
-    const int t = lane & 15, g = lane >> 4;
 #pragma unroll
     for (int r = 0; r < RTW; r++) {
         const int row = (rt0 + wr * RTW + r) * 16 + t;
@@ -199,7 +275,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tall(const TallArgs A) {
 // ------------------------------------------------------------------------------- host driver
 
 template <int CTW, int RTW, int NST>
-static constexpr int tall_lds() { return NST * (2 * CTW + 4 * RTW) * 1024; }
+static constexpr int tall_lds() {
+    return NST * (2 * CTW + 4 * RTW) * 1024 + (tall_sums<CTW, RTW, NST>() ? 0 : (CTW * RTW - TALL_LEADS) * 256 * 8);
+}
 
 template <int CTW, int RTW, int NST, int EPI>
 static hipError_t tall_allow_lds() {
@@ -233,7 +311,7 @@ int32_t csd_tall_setup() {
 // of 6 x 4 tiles per wave, 14.1 in 144 of 4 x 2; 7B shape, 384 rows, QKV 92.3 us at 6 x 4 (192 workgroups), 77.2 at 6 x 3 (256); 512 rows, where 6 x 4
 // makes 256 workgroups, 98.5 against 127.6 at 6 x 3.  max_splits = 1 where the epilogue runs in the kernel.
 struct TallPlan {
-    int ctw, rtw, S, rblocks, grid;
+    int ctw, rtw, S, rblocks, grid, chain;
 };
 static TallPlan tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats) {
     static const struct {
@@ -241,6 +319,9 @@ static TallPlan tall_plan(int n_tiles, int KS, int M, int max_splits, size_t par
         double one, two;
     } forms[6] = {{6, 4, 0.60, 1.09}, {6, 3, 0.49, 0.885}, {6, 2, 0.43, 0.85}, {4, 4, 0.45, 0}, {4, 3, 0.37, 0}, {4, 2, 0.29, 0}};
     const int row_tiles = (M + 15) / 16;
+    int ct = 0, chains = 1;                                      // as the row-split form over 128 rows, memory for its partial sums aside
+    (void)csd_rs_plan_host(n_tiles * 16, KS * 32, 128, (size_t)1 << 60, &ct, &chains);
+    const int chain = ((KS + chains - 1) / chains + 1) / 2 * 2;
     TallPlan best{};
     double best_us = 1e30;
     for (const auto &f : forms) {
@@ -253,17 +334,18 @@ static TallPlan tall_plan(int n_tiles, int KS, int M, int max_splits, size_t par
             const double ends = 0.5 * f.ctw * f.rtw * (f.ctw == 4 && f.rtw == 4 ? rounds : 1.0);
             const double us = rounds * ((KS + S - 1) / S) * (pairs ? f.two : f.one) + ends +
                               (max_splits > 1 ? S * 4.0 * M * n_tiles * 16 / 4e6 : 0.0);
-            if (us < best_us) best_us = us, best = TallPlan{f.ctw, f.rtw, S, rblocks, (int)wgs};
+            if (us < best_us) best_us = us, best = TallPlan{f.ctw, f.rtw, S, rblocks, (int)wgs, chain};
         }
     }
     return best;
 }
 
 template <int EPI>
-static int32_t tall_launch(TallArgs &A, int max_splits, size_t part_floats, hipStream_t st) {
-    const TallPlan p = tall_plan(A.n_tiles, A.g.KS, A.g.M, max_splits, part_floats);
+static int32_t tall_launch(const csd_model *mod, TallArgs &A, int max_splits, hipStream_t st) {
+    const TallPlan p = tall_plan(A.n_tiles, A.g.KS, A.g.M, max_splits, mod->part_floats);
     A.S = p.S;
     A.rblocks = p.rblocks;
+    A.chain = p.chain;
 #define TALL_LAUNCH(CTW, RTW, NST) \
     hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(p.grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, A)
     // with 6 column tiles and more workgroups than compute units two of them share one (two stages each), which evens out the
@@ -302,7 +384,7 @@ static TallArgs tall_args(const csd_model *mod, const GemmW &w, const bf16_t *a,
 int32_t csd_tall_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st) {
     TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
     A.part = mod->part;
-    const int32_t rc = tall_launch<EPI_PART>(A, w.S < 8 ? w.S : 8, mod->part_floats, st);
+    const int32_t rc = tall_launch<EPI_PART>(mod, A, w.S < 8 ? w.S : 8, st);
     *S_used = A.S;
     return rc;
 }
@@ -324,7 +406,7 @@ int32_t csd_tall_qkv(csd_model *mod, const GemmW &w, const bf16_t *a, size_t pla
     A.g.rope = rope;
     A.g.q = (bf16_t *)mod->qbuf;
     A.g.q_plane_bytes = (int)(mod->q_plane * 2);
-    return tall_launch<EPI_QKV>(A, 1, 0, st);
+    return tall_launch<EPI_QKV>(mod, A, 1, st);
 }
 
 int32_t csd_tall_gu(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, bf16_t *out, size_t out_plane, int gelu,
@@ -333,14 +415,14 @@ int32_t csd_tall_gu(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plan
     A.g.out = out;
     A.g.out_plane_bytes = (int)(out_plane * 2);
     A.g.gelu = gelu;
-    return tall_launch<EPI_GU>(A, 1, 0, st);
+    return tall_launch<EPI_GU>(mod, A, 1, st);
 }
 
 int32_t csd_tall_logits(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, float *logits, hipStream_t st) {
     TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
     A.g.logits = logits;
     A.g.V = w.N;
-    return tall_launch<EPI_LOGITS>(A, 1, 0, st);
+    return tall_launch<EPI_LOGITS>(mod, A, 1, st);
 }
 
 int32_t csd_tall_cross(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int mtp, int M, int row0, int layer,
@@ -351,5 +433,5 @@ int32_t csd_tall_cross(csd_model *mod, const GemmW &w, const bf16_t *a, size_t p
     A.g.layer = layer;
     A.g.geo = geo;
     A.g.kv = (bf16_t *)kv_cross;
-    return tall_launch<EPI_CROSS>(A, 1, 0, st);
+    return tall_launch<EPI_CROSS>(mod, A, 1, st);
 }
