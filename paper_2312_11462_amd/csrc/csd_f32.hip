@@ -230,7 +230,8 @@ int32_t csd_f32_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const i
         Q.q = (float *)mod->qbuf;
         Q.kv = (float *)kv;
         F32_STEP(CSD_PROF_GEMM, (f32_launch<float, FG_QKV, true>(Q, st)))
-        F32_STEP(CSD_PROF_ATTN, csd_attn_simple_f32(mod, geo, (const float *)kv, cache_len, B, m, l, scale, am, st))
+        // (brackets itself for the profile: brackets do not nest)
+        if ((rc = csd_attn_simple_f32(mod, geo, (const float *)kv, cache_len, B, m, l, scale, am, st)) != CSD_OK) return rc;
         F32_STEP(CSD_PROF_GEMM, (f32_launch<float, FG_RESID, false>(gemm(lw.o, act, nullptr, mod->h), st)))
         F32_STEP(CSD_PROF_GEMM, (f32_launch<float, FG_GU, true>(gemm(lw.gu, mod->h, lw.ffn_norm, act), st)))
         F32_STEP(CSD_PROF_GEMM, (f32_launch<float, FG_RESID, false>(gemm(lw.down, act, nullptr, mod->h), st)))

@@ -182,6 +182,18 @@ def test_fp32_forward(P, dims, B, m, t):
             assert tol_ok(got.cpu().numpy().astype(np.float64), want, 1e-4, 1e-4)[0]
 
 
+def test_profile_of_an_fp32_forward(P):
+    """Launches per kernel class of the fp32 forward: four GEMMs and one attention per layer, the LM head, the embedding."""
+    shape = I.ModelShape("edge_prof", 0, "fp32", 3, 64, 4, 16, 128, 80)
+    gm = P.Model(shape, I.make_weights(shape, 5, device="cuda", std=0.1), max_batch=1, max_seq=32, max_block=4)
+    gm.prof_enable(True)
+    for _ in range(2):
+        gm.verify_block(torch.ones((1, 3), dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    got = [gm.prof_read(c) for c in range(3)]
+    assert [n for _, n in got] == [2 * 13, 2 * 3, 2] and all(ms > 0 for ms, _ in got)
+
+
 def test_generic_attention_longest_sequence(P):
     """The longest sequence that a model on the generic attention accepts: 64 KB of scores and query."""
     from gpu_util import import_synthetic_kv, make_pair, tol_ok
