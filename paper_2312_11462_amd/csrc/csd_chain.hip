@@ -684,11 +684,16 @@ __global__ __launch_bounds__(256) void kc_embed(const int32_t *__restrict__ toke
 
 // ------------------------------------------------------------------------------- host driver
 
-// keys (padded cache rows) up to which one workgroup per (sequence, head) takes them: see kc_attn_one
-#define CA_ONE_KEYS_128 448          /* at most 32 * CA_ONE_NW: one turn */
+// keys (padded cache rows) up to which one workgroup per (sequence, head) takes them: see kc_attn_one.  A workgroup fills a
+// compute unit, so more than one per unit run in rounds, each of them with the whole latency, however few the keys: four layers
+// with heads of 128, 512 workgroups, a cache of 448 rows with 40 in use 108 us against 65 with the kernels of csd_attention.hip, 1024
+// workgroups 198 against 74; heads of 64, 512 workgroups, 40 of 832 rows 63 against 53, 2048 workgroups 218 against 69.  256
+// workgroups, 40 / 220 / 440 of 448 rows: 52 / 51 / 60 us against 61 / 74 / 95.
+#define CA_ONE_KEYS_128 384          /* at most 32 * CA_ONE_NW: one turn */
 #define CA_ONE_KEYS_64 832
-static bool attn_one_fits(const csd_model *mod, int keys_pad) {
-    return keys_pad <= (mod->cfg.head_dim == 128 ? CA_ONE_KEYS_128 : CA_ONE_KEYS_64);
+#define CA_ONE_GROUPS 256
+static bool attn_one_fits(const csd_model *mod, int B, int keys_pad) {
+    return mod->cfg.n_heads * B <= CA_ONE_GROUPS && keys_pad <= (mod->cfg.head_dim == 128 ? CA_ONE_KEYS_128 : CA_ONE_KEYS_64);
 }
 template <int DH, bool BIAS>
 static void attn_one_launch(const AttnArgs &A, int H, int B, hipStream_t st) {
@@ -698,14 +703,14 @@ static int32_t attn_launch_small(const csd_model *mod, const AttnArgs &A, int ke
     const int H = mod->cfg.n_heads;
     const dim3 grid(H, B, (keys_pad + CA_KEYS - 1) / CA_KEYS);       // chunk index slowest: see kc_attn
     if (mod->cfg.head_dim == 128) {
-        if (!attn_one_fits(mod, keys_pad))
+        if (!attn_one_fits(mod, B, keys_pad))
             hipLaunchKernelGGL((kc_attn<128>), grid, dim3(256), 0, st, A);
         else if (A.bias_hd)
             attn_one_launch<128, true>(A, H, B, st);
         else
             attn_one_launch<128, false>(A, H, B, st);
     } else {
-        if (!attn_one_fits(mod, keys_pad))
+        if (!attn_one_fits(mod, B, keys_pad))
             hipLaunchKernelGGL((kc_attn<64>), grid, dim3(256), 0, st, A);
         else if (A.bias_hd)
             attn_one_launch<64, true>(A, H, B, st);
@@ -908,7 +913,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
             // that bandwidth rather than latency binds) the one with longer key runs and a merge kernel
             auto attention = [&](const KvGeom &g_, const void *kv_, int keys_pad, const AttnMode &mode) -> int32_t {
                 const int chunks = (keys_pad + CA_KEYS - 1) / CA_KEYS;
-                if (m > 16 || (!attn_one_fits(mod, keys_pad) && ((long long)chunks * c.n_heads * B > 1024 || chunks > CA_MAX_CHUNKS)))
+                if (m > 16 || (!attn_one_fits(mod, B, keys_pad) && ((long long)chunks * c.n_heads * B > 1024 || chunks > CA_MAX_CHUNKS)))
                     return csd_attn_mfma_enqueue(mod, g_, kv_, cache_len, B, m, l, scale, mode, st, X2, mod->x_plane[1]);
                 ProfScope ps(mod, st, CSD_PROF_ATTN);
                 AttnArgs A = attn;
@@ -942,7 +947,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
                 if ((rc = chain_launch<EPI_QKV>(Pq, lw.qkv.N / 16, st)) != CSD_OK) return rc;
                 CSD_LAUNCH_CHECK();
             }
-            if (m > 16 || (!attn_one_fits(mod, mod->seq_pad) && (long long)chunks * c.n_heads * B > 1024)) {
+            if (m > 16 || (!attn_one_fits(mod, B, mod->seq_pad) && (long long)chunks * c.n_heads * B > 1024)) {
                 // many sequences or long caches: the attention is bound by bandwidth, not by latency, and the kernel
                 // with longer key runs per wave (and a merge kernel) moves the cache faster; it also takes the blocks of
                 // more than 16 rows per sequence

@@ -230,6 +230,27 @@ def test_small_block_attention(P, arch, dh, max_seq, B, m, t):
     assert ok, f"max abs err {err}"
 
 
+@pytest.mark.parametrize("arch,dh", [(0, 64), (0, 128), (1, 64)])
+@pytest.mark.parametrize("max_seq,B,m,t", [(128, 8, 4, 90), (128, 9, 3, 90), (128, 32, 1, 120), (384, 9, 3, 300), (384, 32, 1, 17), (448, 1, 5, 440)])
+def test_small_block_attention_of_many_heads(P, arch, dh, max_seq, B, m, t):
+    """Caches short enough for one workgroup per head, with as many (sequence, head) pairs as compute units and with more, where
+    the chunked kernels take over; and the first length past the limit for heads of 128."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_heads", arch, "bf16", 1, 64, 32, dh, 64, 512, rms_eps=1e-6 if arch else 1e-5, enc_len=70 if arch else 0)
+    gm, om = make_pair(shape, 43, B, max_seq, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, t, 43, B=B)
+    if arch:
+        enc = I.encoder_output(shape, B, 43)
+        gm.cross_kv_init(enc.cuda())
+        om.cross_kv_init(enc.numpy())
+    block = I.token_ids(B * m, shape.vocab, 43, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([max(0, t - 3 * b) for b in range(B)], np.int32)
+    assert gm.path(B, m) == 1
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+
+
 @pytest.mark.parametrize("V", [4, 512, 2048, 2052, 8192, 8196, 32768])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_review_of_all_rows_equals_softmax_then_accept(P, V, mode):
