@@ -1037,7 +1037,10 @@ static int32_t cross_init_typed(csd_model *mod, void *kv, const float *enc_out, 
     const KvGeom cgeo = cross_geom(mod);
     TC *kvc = (TC *)((char *)kv + csd_self_kv_bytes(mod));
     int32_t rc;
-    if constexpr (sizeof(TA) == 2) {
+    // One sequence of few rows streams the matrices: k_gemm_ws or k_gemm_rs and a kernel for the epilogue take 17 / 22 / 33 us per layer
+    // for 8 / 32 / 64 rows of 4096 features, the tall form, made for matrix instructions, 33 for any of them, and both take 36 at 100
+    // rows (768 features: 8 / 8 / 10 against 10 / 11 / 11).  Several sequences are one launch for the tall form and one each for the others.
+    if (sizeof(TA) == 2 && (B > 1 || E > CSD_CROSS_FEW || E > mod->m_max)) {
         // the rows of all sequences follow each other: as many per pass over the matrices as the row buffer holds, keys and
         // values written by the GEMM itself (in chunks of the 8 rows of a decoder block, 512 rows took 64 passes: 40 ms at the
         // T5-XXL shape)
@@ -1073,7 +1076,7 @@ static int32_t cross_init_typed(csd_model *mod, void *kv, const float *enc_out, 
             }
             for (int l = 0; l < c.n_layers; l++) {
                 const LayerW &lw = mod->layers[l];
-                if ((rc = run_gemm(mod, lw.ckv, mod->act, 0, rows, &S_g, st)) != CSD_OK) return rc;
+                if ((rc = run_gemm(mod, lw.ckv, mod->act, mod->act_plane, rows, &S_g, st)) != CSD_OK) return rc;
                 ProfScope ps(mod, st, CSD_PROF_OTHER);
                 hipLaunchKernelGGL((k_fix_cross_kv<TC>), dim3((hd + 255) / 256, rows), dim3(256), 0, st, mod->part, S_g, rows,
                                    cgeo, l, b, row0, kvc);

@@ -148,9 +148,20 @@ def test_tall_sums_that_overflow(P, V, m):
 def test_cross_projection_rows(P, B, enc_len):
     """Encoder rows of several sequences in one pass: a single row, ragged row tiles and row blocks, sequences that cross the
     limit of 512 rows per pass."""
+    _check_cross_projection(P, B, enc_len, 8)
+
+
+@pytest.mark.parametrize("B,enc_len,max_block", [(1, 16, 64), (1, 33, 64), (1, 64, 64), (1, 64, 63), (1, 65, 80), (2, 30, 64)])
+def test_cross_projection_of_few_rows(P, B, enc_len, max_block):
+    """One sequence whose rows fit a decoder block: the GEMMs that stream the matrices (a whole row tile, the first count of the
+    row-split form, the last one here); one row more than a block, than those rows, and a second sequence: the tall form."""
+    _check_cross_projection(P, B, enc_len, max_block)
+
+
+def _check_cross_projection(P, B, enc_len, max_block):
     from gpu_util import make_pair, tol_ok
     shape = I.ModelShape("edge_t5", 1, "bf16", 2, 256, 4, 64, 512, 1024, rms_eps=1e-6, enc_len=enc_len)
-    gm, om = make_pair(shape, 29, B, 32, 8, std=0.05)
+    gm, om = make_pair(shape, 29, B, max(32, max_block), max_block, std=0.05)
     enc = I.encoder_output(shape, B, 29)
     gm.cross_kv_init(enc.cuda())
     om.cross_kv_init(enc.numpy())
