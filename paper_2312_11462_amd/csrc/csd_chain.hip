@@ -805,7 +805,14 @@ static int32_t chain_launch(ChainGemm &P, int n_tiles, hipStream_t st) {
     return CSD_ESHAPE;
 }
 
+bool csd_planes_fit(const csd_model *mod) {
+    size_t most = mod->q_plane;
+    for (size_t p : mod->x_plane) most = p > most ? p : most;
+    return 2 * 2 * most < (size_t)1 << 31;
+}
+
 bool csd_chain_eligible(const csd_model *mod, int32_t B, int32_t m) {
+    if (!csd_planes_fit(mod)) return false;
     // (the cache appends address a layer's keys, or values, through one 32-bit offset)
     const size_t layer_kv = (size_t)mod->cfg.max_batch * mod->cfg.n_heads * mod->seq_pad * mod->cfg.head_dim * 2;
     if (B * m > 16 && 3 * mod->hd / 16 > 6 * 256) return false;

@@ -312,6 +312,8 @@ size_t csd_self_kv_bytes(const csd_model *mod);     // the self-attention part o
 // csd_chain.hip: forward for blocks of up to 32 rows, epilogues inside the GEMM kernels
 int32_t csd_chain_setup();
 
+// the GEMM epilogues address both planes of a buffer through one signed 32-bit offset (at 4096 rows: features below 131072)
+bool csd_planes_fit(const csd_model *mod);
 bool csd_chain_eligible(const csd_model *mod, int32_t B, int32_t m);
 int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int32_t B, int32_t m,
                           float *logits, hipStream_t st);

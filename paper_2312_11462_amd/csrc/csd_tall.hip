@@ -96,10 +96,13 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
     const int rb = wg % A.rblocks, s = (wg / A.rblocks) % A.S, grp = wg / (A.rblocks * A.S);
     const int ks0 = (int)((long long)P.KS * s / A.S), ks1 = (int)((long long)P.KS * (s + 1) / A.S);
     const int tile0 = grp * WF, rt0 = rb * 2 * RTW;
-    const __amdgpu_buffer_rsrc_t rw = ch_rsrc(P.Wp, (size_t)P.wbytes), ra = ch_rsrc(P.a, (size_t)2 * P.a_plane_bytes);
+    const __amdgpu_buffer_rsrc_t rw = ch_rsrc(P.Wp, (size_t)P.wbytes);
+    // (both planes of the input may take up to 4 GiB: no load here counts on an offset beyond 2 GiB being outside)
+    const __amdgpu_buffer_rsrc_t ra =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(P.a), 0, (int)(2u * (unsigned)P.a_plane_bytes), 0x00020000);
     // Tiles and row tiles past the end are read as the last one (their sums are not stored), k-steps past the slice likewise:
     // every address is inside the matrix, and every wave issues PW loads per stage, so the waits can count them.
-    int base[PW], step[PW];
+    unsigned base[PW], step[PW];
 #pragma unroll
     for (int i = 0; i < PW; i++) {
         const int f = min(i * 4 + w, NF - 1);
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
             step[i] = 1024;
         } else {
             const int a = f - WF;
-            base[i] = a / (2 * RTW) * P.a_plane_bytes + min(rt0 + a % (2 * RTW), P.mtp - 1) * 1024;
+            base[i] = a / (2 * RTW) * (unsigned)P.a_plane_bytes + min(rt0 + a % (2 * RTW), P.mtp - 1) * 1024;
             step[i] = P.mtp * 1024;
         }
     }
@@ -120,9 +123,9 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
             const int f = min(i * 4 + w, NF - 1);
             const lds_void d = (lds_void)(tall_smem + (buf * NF + f) * 1024);
             if (f < WF)
-                lds_load16<0>(rw, d, vw, base[i] + k * step[i]);
+                lds_load16<0>(rw, d, vw, (int)(base[i] + k * step[i]));
             else
-                lds_load16<0>(ra, d, va, base[i] + k * step[i]);
+                lds_load16<0>(ra, d, va, (int)(base[i] + k * step[i]));
         }
     };
     const int wc = w & 1, wr = w >> 1;
@@ -390,6 +393,7 @@ int32_t csd_tall_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t pl
 }
 
 bool csd_tall_fused(const csd_model *mod, int M) {
+    if (!csd_planes_fit(mod)) return false;
     // the cache appends of the epilogue address a layer's keys, or values, through one 32-bit offset
     const size_t layer_kv = (size_t)mod->cfg.max_batch * mod->cfg.n_heads * mod->seq_pad * mod->cfg.head_dim * 2;
     return mod->chain_on && M >= CSD_TALL_MIN_ROWS && layer_kv < (1ull << 31);

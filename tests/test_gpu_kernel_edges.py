@@ -87,6 +87,29 @@ def test_tall_tile_forms(P, m):
     assert ok, f"max abs err {err}"
 
 
+@pytest.mark.parametrize("m", [20, 145])
+def test_planes_of_more_than_two_gib(P, m):
+    """Room for 4096 rows of 196608 features: both planes of the feed-forward input take 3.2 GB.  The lower plane carries the bits
+    behind the first eight: without it the feed-forward sums are off by about 2^-9 of their size, with it by 2^-17, and a K or V
+    element rounded to the other side adds 1e-5 or so."""
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 120 GiB of device memory")
+    shape = I.ModelShape("edge_wide", 0, "bf16", 1, 32, 1, 64, 196608, 64)
+    from oracle import csd_oracle as O
+    w = I.make_weights(shape, 47, device="cuda", std=0.05)
+    gm = P.Model(shape, w, max_batch=8, max_seq=512, max_block=512)
+    om = O.Model(shape, [x.cpu() for x in w], max_batch=1, max_seq=512, max_block=m)
+    assert gm.path(1, m) == 0
+    block = I.token_ids(m, shape.vocab, 47, 1).reshape(1, m).numpy().astype(np.int32)
+    cl = np.zeros(1, np.int32)
+    got = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda()).cpu().numpy().astype(np.float64)
+    ref = om.verify_block(block, cl)
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print("m", m, "relative error", err)
+    gm.close()
+    assert err < 1e-4
+
+
 def _head_alone(P, K, V, rows, emb, lm):
     """Logits of a model of one layer that adds nothing to its input: the LM head over the embedding rows 0 .. rows - 1."""
     shape = I.ModelShape("edge_head", 0, "bf16", 1, K, 1, 64, 64, V)
