@@ -256,8 +256,8 @@ __global__ __launch_bounds__(MERGE_ROWS * DH / 4) void k_attn_merge(const float 
         }
         mstar = mnew;
     }
-    const float inv = den > 0.f ? 1.0f / den : 0.f;
-    store_act4<bf16_t>(out, plane, r, hh * DH + x, ldo, mtp, num * inv);
+    // (a division per feature: times the rounded reciprocal would round once more)
+    store_act4<bf16_t>(out, plane, r, hh * DH + x, ldo, mtp, den > 0.f ? num / den : f32x4{0.f, 0.f, 0.f, 0.f});
 }
 
 template <int DH>

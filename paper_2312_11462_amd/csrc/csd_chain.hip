@@ -639,8 +639,8 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
             o += L.o[i][dt][lane] * L.w[i][col];
             den += L.l[i][col] * L.w[i][col];
         }
-        const float inv = den > 0.f ? 1.0f / den : 0.f;
-        const float v[4] = {o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
+        if (den == 0.f) den = 1.f;                           // (no key seen: the sums are 0)
+        const float v[4] = {o[0] / den, o[1] / den, o[2] / den, o[3] / den};
         store_planes4(A.out, A.out_plane_bytes, A.mtp, b * m + col, hh * DH + dt * 16 + 4 * g, v);
     }
 }

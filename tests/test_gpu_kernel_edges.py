@@ -285,6 +285,35 @@ def test_small_block_attention_of_many_heads(P, arch, dh, max_seq, B, m, t):
     assert ok, f"max abs err {err}"
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("max_seq,m,t", [(192, 9, 150), (192, 40, 150), (704, 17, 640), (2048, 33, 1900), (512, 150, 300)])
+def test_attention_output_is_rounded_once(P, dh, max_seq, m, t):
+    """Rows of a zero embedding: every visible key has the score 0, so row i's output is the sum of the cached values over the
+    t + i + 1 keys it sees (the block's own values are 0).  The values are whole numbers, their sums exact, so what the output
+    projection (a unit matrix) adds to the zero residual is one correctly rounded quotient, in two bf16 planes, to the last bit."""
+    d = 64
+    shape = I.ModelShape("edge_quot", 0, "bf16", 1, d, d // dh if dh < d else 1, dh, 32, 32)
+    z = lambda r, c: torch.zeros((r, c), dtype=torch.bfloat16, device="cuda")
+    one = torch.ones(d, device="cuda")
+    wo = z(dh, d)
+    wo[:d] = torch.eye(d, device="cuda")
+    gm = P.Model(shape, [z(32, d), one, z(d, dh), z(d, dh), z(d, dh), wo, one, z(d, 32), z(d, 32), z(32, d), one, z(d, 32)],
+                 max_batch=1, max_seq=max_seq, max_block=m)
+    v = torch.randint(-60, 61, (t, dh), device="cuda").float()
+    v[:, :32] = torch.arange(1, 33, device="cuda").float()   # exact quotients among the results
+    gm.kv_write(0, 0, 0, torch.randn((t, dh), device="cuda"), v)
+    tr = torch.zeros((2, m, d), device="cuda")
+    gm.set_trace(tr)
+    gm.verify_block(torch.zeros((1, m), dtype=torch.int32, device="cuda"), torch.tensor([t], dtype=torch.int32, device="cuda"))
+    gm.set_trace(None)
+    q = (v.double().sum(0)[None, :d] / torch.arange(t + 1, t + m + 1, device="cuda")[:, None].double()).float()
+    hi = q.bfloat16().float()
+    want = hi + (q - hi).bfloat16().float()
+    gm.close()
+    print("differ", (tr[1] != want).sum().item(), "of", want.numel())
+    assert torch.equal(tr[1], want)
+
+
 @pytest.mark.parametrize("V", [4, 512, 2048, 2052, 8192, 8196, 32768])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_review_of_all_rows_equals_softmax_then_accept(P, V, mode):
