@@ -35,8 +35,10 @@ __device__ __forceinline__ u32x4 attn_load(const bf16_t *p) {
 // out (a 512-row block over an empty cache: half of the work), a tile that every row sees whole is not masked, and the output is
 // rescaled only where a maximum has moved.  512 rows of the 7B shape, mean over cached lengths 0 and 512: 48.5 -> 33.6 us.
 enum { ATT_PLAIN = 0, ATT_BIAS = 1, ATT_TREE = 2 };
-template <int DH, int PRE, bool ONCE, int MODE>
-__global__ __launch_bounds__(64, PRE == 1 && (MODE == ATT_PLAIN || DH == 64) ? 3 : 1) void k_attn_mfma(const bf16_t *__restrict__ q, size_t qplane, int m, int row_tiles,
+//
+// WPS: waves per SIMD that the registers leave room for at least (heads of 128: 168 of them for three, else 166 + 32): see attn_launch.
+template <int DH, int PRE, bool ONCE, int MODE, int WPS>
+__global__ __launch_bounds__(64, WPS) void k_attn_mfma(const bf16_t *__restrict__ q, size_t qplane, int m, int row_tiles,
                                                   const int32_t *__restrict__ cache_len, KvGeom geo, int layer,
                                                   const bf16_t *__restrict__ kv, float scale, float *__restrict__ part,
                                                   int chunks_max, int chunk_keys, AttnMode mode) {
@@ -279,24 +281,31 @@ static void attn_launch(csd_model *mod, const KvGeom &geo, const void *kv, const
     const int chunk_keys = n_c == n_max ? ATT_CHUNK : ((keys + n_c - 1) / n_c + 31) / 32 * 32;
     int chunks = (keys + chunk_keys - 1) / chunk_keys;
     if (chunks > mod->attn_chunks_max) chunks = mod->attn_chunks_max;
-    // a grid the chip holds at one wave per SIMD: each wave requests its whole first 128 keys at once
-#define ATT_LAUNCH_MODE(PRE_, ONCE_, MODE_)                                                                            \
-    hipLaunchKernelGGL((k_attn_mfma<DH, PRE_, ONCE_, MODE_>), dim3(c.n_heads, B * row_tiles, chunks), dim3(64), 0, st,             \
+    // WIDE, registers for two waves per SIMD only: more waves than SIMDs with every row read once are bound by bandwidth, and the
+    // loads of a wave that is not held to a third of the registers get more of it.  32 heads of 128, 32 sequences, four layers: full caches of 1024 rows
+    // 577 us with room for three, 560 with two, of 2048 rows 925 and 886 (64 heads of 64: 857 and 846).  Up to one wave per SIMD it is the other way round:
+    // 16 sequences over 20 rows 212 and 216, 8 over 1000 rows 268 and 272.
+    // PRE = 4 for a grid the chip holds at one wave per SIMD: each wave requests its whole first 128 keys at once
+#define ATT_LAUNCH_MODE(PRE_, ONCE_, MODE_, WIDE_)                                                                     \
+    hipLaunchKernelGGL((k_attn_mfma<DH, PRE_, ONCE_, MODE_, PRE_ == 1 && !WIDE_ && (MODE_ == ATT_PLAIN || DH == 64) ? 3 : 1>),  \
+                       dim3(c.n_heads, B * row_tiles, chunks), dim3(64), 0, st,                                            \
                        (const bf16_t *)mod->qbuf, mod->q_plane, m, row_tiles, cache_len, geo, layer, (const bf16_t *)kv, scale, \
                        mod->attn_part, mod->attn_chunks_max, chunk_keys, mode)
-#define ATT_LAUNCH(PRE_, ONCE_)                    \
-    if (mode.anc)                                  \
-        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_TREE);    \
-    else if (mode.bias_hd)                         \
-        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_BIAS);    \
-    else                                           \
-        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_PLAIN);
+#define ATT_LAUNCH(PRE_, ONCE_, WIDE_)                    \
+    if (mode.anc)                                         \
+        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_TREE, WIDE_);    \
+    else if (mode.bias_hd)                                \
+        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_BIAS, WIDE_);    \
+    else                                                  \
+        ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_PLAIN, WIDE_);
     if (chunk_keys == ATT_CHUNK && chunks * items <= 1024) {
-        ATT_LAUNCH(4, false)
+        ATT_LAUNCH(4, false, false)
+    } else if (row_tiles == 1 && chunks * items > 1024) {
+        ATT_LAUNCH(1, true, true)
     } else if (row_tiles == 1) {
-        ATT_LAUNCH(1, true)
+        ATT_LAUNCH(1, true, false)
     } else {
-        ATT_LAUNCH(1, false)
+        ATT_LAUNCH(1, false, false)
     }
 #undef ATT_LAUNCH
 #undef ATT_LAUNCH_MODE

@@ -314,6 +314,26 @@ def test_attention_output_is_rounded_once(P, dh, max_seq, m, t):
     assert torch.equal(tr[1], want)
 
 
+@pytest.mark.parametrize("arch,dh,tree", [(0, 64, False), (0, 128, False), (1, 64, False), (1, 128, False), (0, 64, True), (0, 128, True)])
+@pytest.mark.parametrize("B,H,m,t", [(20, 64, 1, 250), (13, 96, 2, 200)])
+def test_small_block_attention_of_more_waves_than_simds(P, arch, dh, tree, B, H, m, t):
+    """More (sequence, head) pairs than SIMDs, one row tile each: the form with registers for two waves per SIMD."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_waves", arch, "bf16", 1, 64, H, dh, 64, 512, rms_eps=1e-6 if arch else 1e-5, enc_len=70 if arch else 0)
+    gm, om = make_pair(shape, 73, B, 256, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, t, 73, B=B)
+    if arch:
+        enc = I.encoder_output(shape, B, 73)
+        gm.cross_kv_init(enc.cuda())
+        om.cross_kv_init(enc.numpy())
+    block = I.token_ids(B * m, shape.vocab, 73, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([t - 9 * b for b in range(B)], np.int32)
+    dev = [torch.from_numpy(x).cuda() for x in (block, np.tile(np.arange(-1, m - 1, dtype=np.int32), (B, 1)), cl)]
+    lg = gm.verify_tree(*dev) if tree else gm.verify_block(dev[0], dev[2])
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+
+
 @pytest.mark.parametrize("V", [4, 512, 2048, 2052, 8192, 8196, 32768])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_review_of_all_rows_equals_softmax_then_accept(P, V, mode):
