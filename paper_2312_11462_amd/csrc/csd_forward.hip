@@ -1037,10 +1037,14 @@ static int32_t cross_init_typed(csd_model *mod, void *kv, const float *enc_out, 
     const KvGeom cgeo = cross_geom(mod);
     TC *kvc = (TC *)((char *)kv + csd_self_kv_bytes(mod));
     int32_t rc;
-    // One sequence of few rows streams the matrices: k_gemm_ws or k_gemm_rs and a kernel for the epilogue take 17 / 22 / 33 us per layer
-    // for 8 / 32 / 64 rows of 4096 features, the tall form, made for matrix instructions, 33 for any of them, and both take 36 at 100
-    // rows (768 features: 8 / 8 / 10 against 10 / 11 / 11).  Several sequences are one launch for the tall form and one each for the others.
-    if (sizeof(TA) == 2 && (B > 1 || E > CSD_CROSS_FEW || E > mod->m_max)) {
+    // One sequence of few rows streams the matrices: k_gemm_ws or k_gemm_rs and a kernel for the epilogue take 17 / 22 / 33 / 35 us per
+    // layer for 8 / 32 / 64 / 96 rows of 4096 features, the tall form, made for matrix instructions, 33 to 36 for any of them.  The smaller
+    // the matrix, the fewer workgroups the tall form has and the later it overtakes: 1024 features, 65 / 128 / 129 rows 10.5 / 12.8 / 13.9 us
+    // against 13.4 for any, 2048 features, 65 / 104 / 112 / 120 rows 16.6 / 20.6 / 21.3 / 22.0 against 21.2 to 21.5, 4096, 88 / 104 rows
+    // 34.8 / 36.6 against 35.7.  Several sequences are one launch for the tall form and one each for the others.
+    const size_t matrix = (size_t)d * 2 * hd;
+    const int few = matrix <= (size_t)1 << 22 ? 128 : matrix <= (size_t)1 << 24 ? 112 : 96;
+    if (sizeof(TA) == 2 && (B > 1 || E > few || E > mod->m_max)) {
         // the rows of all sequences follow each other: as many per pass over the matrices as the row buffer holds, keys and
         // values written by the GEMM itself (in chunks of the 8 rows of a decoder block, 512 rows took 64 passes: 40 ms at the
         // T5-XXL shape)

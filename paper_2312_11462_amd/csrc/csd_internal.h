@@ -327,7 +327,6 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
 // csd_tall.hip: GEMMs over more rows than k_gemm_rs takes, partial sums or with the epilogue inside
 #define CSD_TALL_MIN_ROWS 145
 #define CSD_CROSS_ROWS 512       /* encoder rows that csd_cross_kv_init projects per pass over a layer's matrix */
-#define CSD_CROSS_FEW 64         /* ... up to which one sequence takes the GEMMs that stream the matrices */
 int32_t csd_tall_setup();
 bool csd_tall_fused(const csd_model *mod, int M);
 int32_t csd_tall_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st);

@@ -174,10 +174,10 @@ def test_cross_projection_rows(P, B, enc_len):
     _check_cross_projection(P, B, enc_len, 8)
 
 
-@pytest.mark.parametrize("B,enc_len,max_block", [(1, 16, 64), (1, 33, 64), (1, 64, 64), (1, 64, 63), (1, 65, 80), (2, 30, 64)])
+@pytest.mark.parametrize("B,enc_len,max_block", [(1, 16, 64), (1, 33, 64), (1, 64, 64), (1, 64, 63), (1, 128, 140), (1, 129, 140), (2, 30, 64)])
 def test_cross_projection_of_few_rows(P, B, enc_len, max_block):
     """One sequence whose rows fit a decoder block: the GEMMs that stream the matrices (a whole row tile, the first count of the
-    row-split form, the last one here); one row more than a block, than those rows, and a second sequence: the tall form."""
+    row-split form, the last one for a matrix of this size); one row more than a block, than those rows, and a second sequence: the tall form."""
     _check_cross_projection(P, B, enc_len, max_block)
 
 
