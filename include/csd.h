@@ -335,6 +335,12 @@ int32_t csd_debug_path(const csd_model *model, int32_t B, int32_t m);
  * CSD_EINVAL for other shapes or rows outside [1, 144]. */
 int32_t csd_debug_gemm_plan(int32_t N, int32_t K, int32_t rows, int32_t max_splits, int32_t *ct, int32_t *S);
 
+/* The same for the GEMM that serves blocks of more than 144 rows and encoder rows: a workgroup's tile is 2 x *ctw column tiles
+ * by 2 x *rtw row tiles of 16, *stages k-steps of its operands are in LDS, K is cut into *S splits (max_splits = 1: the
+ * epilogue runs in the kernel). */
+int32_t csd_debug_tall_plan(int32_t N, int32_t K, int32_t rows, int32_t max_splits, int32_t *ctw, int32_t *rtw, int32_t *stages,
+                            int32_t *S);
+
 /* Counter calibration for benchmarks: a plain streaming copy of `bytes` bytes (a multiple of 16; dst and
  * src are device pointers, 16-byte aligned, not overlapping), launched as kernel k_copy_calib, so that a
  * hardware counter's reading for exactly 2 x bytes of HBM traffic (one read, one write) can be taken

@@ -328,6 +328,8 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
 #define CSD_TALL_MIN_ROWS 145
 #define CSD_CROSS_ROWS 512       /* encoder rows that csd_cross_kv_init projects per pass over a layer's matrix */
 int32_t csd_tall_setup();
+int32_t csd_tall_plan_host(int32_t N, int32_t K, int32_t rows, int32_t max_splits, size_t part_floats, int32_t *ctw, int32_t *rtw,
+                           int32_t *stages, int32_t *S);
 bool csd_tall_fused(const csd_model *mod, int M);
 int32_t csd_tall_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st);
 int32_t csd_tall_qkv(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int m, int layer, const KvGeom &geo,

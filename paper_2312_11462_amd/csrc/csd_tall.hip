@@ -313,8 +313,11 @@ int32_t csd_tall_setup() {
 // Narrow tiles fill the chip where a matrix is small or its row blocks few: 160M shape, 512 rows, QKV 29.8 us in 48 workgroups
 // of 6 x 4 tiles per wave, 14.1 in 144 of 4 x 2; 7B shape, 384 rows, QKV 92.3 us at 6 x 4 (192 workgroups), 77.2 at 6 x 3 (256); 512 rows, where 6 x 4
 // makes 256 workgroups, 98.5 against 127.6 at 6 x 3.  max_splits = 1 where the epilogue runs in the kernel.
+// Stages: four of the narrow tiles; with 6 column tiles and more workgroups than compute units two of them share one (two stages
+// each), which evens out the last round: gate|up at 512 rows 146 us against 155 with three stages and one workgroup at a time; at 256
+// workgroups 117 against 81.
 struct TallPlan {
-    int ctw, rtw, S, rblocks, grid, chain;
+    int ctw, rtw, stages, S, rblocks, grid, chain;
 };
 static TallPlan tall_plan(int n_tiles, int KS, int M, int max_splits, size_t part_floats) {
     static const struct {
@@ -337,10 +340,19 @@ static TallPlan tall_plan(int n_tiles, int KS, int M, int max_splits, size_t par
             const double ends = 0.5 * f.ctw * f.rtw * (f.ctw == 4 && f.rtw == 4 ? rounds : 1.0);
             const double us = rounds * ((KS + S - 1) / S) * (pairs ? f.two : f.one) + ends +
                               (max_splits > 1 ? S * 4.0 * M * n_tiles * 16 / 4e6 : 0.0);
-            if (us < best_us) best_us = us, best = TallPlan{f.ctw, f.rtw, S, rblocks, (int)wgs, chain};
+            if (us < best_us) best_us = us, best = TallPlan{f.ctw, f.rtw, f.ctw == 4 ? 4 : pairs ? 2 : 3, S, rblocks, (int)wgs, chain};
         }
     }
     return best;
+}
+
+int32_t csd_tall_plan_host(int32_t N, int32_t K, int32_t rows, int32_t max_splits, size_t part_floats, int32_t *ctw, int32_t *rtw,
+                           int32_t *stages, int32_t *S) {
+    if (!ctw || !rtw || !stages || !S) return CSD_ENULL;
+    if (N <= 0 || K <= 0 || N % 16 || K % 32 || rows < 1 || max_splits < 1) return CSD_EINVAL;
+    const TallPlan p = tall_plan(N / 16, K / 32, rows, max_splits, part_floats);
+    *ctw = p.ctw, *rtw = p.rtw, *stages = p.stages, *S = p.S;
+    return CSD_OK;
 }
 
 template <int EPI>
@@ -351,12 +363,10 @@ static int32_t tall_launch(const csd_model *mod, TallArgs &A, int max_splits, hi
     A.chain = p.chain;
 #define TALL_LAUNCH(CTW, RTW, NST) \
     hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(p.grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, A)
-    // with 6 column tiles and more workgroups than compute units two of them share one (two stages each), which evens out the
-    // last round: gate|up at 512 rows 146 us against 155 with three stages and one workgroup at a time; at 256 workgroups 117 against 81
 #define TALL_LAUNCH_R(RTW)                                \
     {                                                     \
         if (p.ctw == 4) TALL_LAUNCH(4, RTW, 4);           \
-        else if (p.grid > 256) TALL_LAUNCH(6, RTW, 2);    \
+        else if (p.stages == 2) TALL_LAUNCH(6, RTW, 2);   \
         else TALL_LAUNCH(6, RTW, 3);                      \
     }
     if (p.rtw == 4) TALL_LAUNCH_R(4)

@@ -95,3 +95,27 @@ def test_gemm_plan_of_tall_blocks_fills_the_compute_units(L):
     assert L.csd_debug_gemm_plan(64, 64, 145, 4, C.byref(bad), C.byref(bad)) == -1
     assert L.csd_debug_gemm_plan(64, 64, 64, 4, None, C.byref(bad)) == -3
 
+
+def test_tall_gemm_plan_stays_in_bounds(L):
+    """Host logic only: forms that exist, K splits that the partial-sum buffer holds and that leave six k-steps each, and the
+    forms of the 7B- and 160M-shaped matrices at the block sizes that the profiles name."""
+    def plan(N, K, rows, ms=1):
+        v = [C.c_int32() for _ in range(4)]
+        assert L.csd_debug_tall_plan(N, K, rows, ms, *[C.byref(x) for x in v]) == 0
+        return tuple(x.value for x in v)
+    for N, K in [(12288, 4096), (4096, 11008), (22016, 4096), (32000, 4096), (2304, 768), (768, 3072), (1040, 256), (16, 32), (32, 64)]:
+        for rows in (1, 16, 65, 145, 192, 193, 289, 512, 1000, 4096):
+            for ms in (1, 2, 8):
+                ctw, rtw, stages, S = plan(N, K, rows, ms)
+                assert (ctw, stages) in ((4, 4), (6, 2), (6, 3)) and rtw in (2, 3, 4)
+                assert 1 <= S <= ms and (S == 1 or K // 32 // S >= 6)
+                wgs = -(-N // (32 * ctw)) * -(-rows // (32 * rtw)) * S
+                assert stages == (4 if ctw == 4 else 2 if wgs > 256 else 3)
+    assert plan(12288, 4096, 512) == (6, 4, 3, 1) and plan(12288, 4096, 384) == (6, 3, 3, 1)
+    assert plan(22016, 4096, 512) == (6, 4, 2, 1) and plan(32000, 4096, 512) == (6, 3, 2, 1)
+    assert plan(4096, 4096, 512, 8)[:3] == (4, 4, 4) and plan(2304, 768, 512) == (4, 2, 4, 1)
+    v = C.c_int32()
+    p = C.byref(v)
+    assert L.csd_debug_tall_plan(24, 64, 200, 1, p, p, p, p) == -1 and L.csd_debug_tall_plan(32, 48, 200, 1, p, p, p, p) == -1
+    assert L.csd_debug_tall_plan(32, 64, 0, 1, p, p, p, p) == -1 and L.csd_debug_tall_plan(32, 64, 200, 0, p, p, p, p) == -1
+    assert L.csd_debug_tall_plan(32, 64, 200, 1, None, p, p, p) == -3

@@ -1,4 +1,6 @@
 """Kernels at the edges of their tiles, tables and dispatch ranges, against the oracle or a plain fp32 reference."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -75,7 +77,7 @@ def test_tall_blocks(P, shape, B, m):
 
 @pytest.mark.parametrize("m", [192, 256, 384, 512])
 def test_tall_tile_forms(P, m):
-    """Matrices wide enough that the plan takes every width and height of tile, and two workgroups per compute unit (the
+    """Matrices wide enough that the plan takes wide tiles of several heights, and two workgroups per compute unit (the
     shapes above all go to the narrowest).  Tolerances: the project's (bf16)."""
     from gpu_util import make_pair, tol_ok
     shape = I.ModelShape("edge_forms", 0, "bf16", 1, 512, 16, 128, 6144, 32000)
@@ -85,6 +87,160 @@ def test_tall_tile_forms(P, m):
     lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
     ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
     assert ok, f"max abs err {err}"
+
+
+def _tall_plan(P, N, K, rows, split):
+    """(column tiles, row tiles, stages, K splits) of a GEMM over many rows; split: it writes partial sums, in as many splits as
+    the matrix has been packed for at most."""
+    S = 1
+    while split and N // 16 * S < 2048 and K // 32 // (2 * S) >= 8 and S < 8:
+        S *= 2
+    v = [C.c_int32() for _ in range(4)]
+    assert P.lib().csd_debug_tall_plan(N, K, rows, S, *[C.byref(x) for x in v]) == 0
+    return tuple(x.value for x in v)
+
+
+def _check_cache(gm, om, layers, b, n):
+    from gpu_util import tol_ok
+    for l in range(layers):
+        for got, want in zip(gm.kv_read(l, b, 0, n), om.kv_read(l, b, 0, n)):
+            ok, err = tol_ok(got.cpu().numpy().astype(np.float64), want, 2e-2, 1e-2)
+            assert ok, f"cache rows of sequence {b}, layer {l}: max abs err {err}"
+
+
+@pytest.mark.parametrize("dims,m,t,want", [
+    ((256, 2, 64, 512, 1024), 154, 37, {"qkv": (4, 2, 4), "gu": (4, 2, 4)}),
+    ((512, 32, 128, 6144, 16384), 146, 201, {"qkv": (4, 3, 4), "gu": (4, 3, 4), "lm": (4, 3, 4), "o": (4, 2, 4, 8)}),
+    ((512, 32, 128, 6144, 4096), 201, 64, {"qkv": (6, 2, 3), "gu": (6, 2, 3), "lm": (4, 2, 4)}),
+    ((768, 24, 128, 8192, 16384), 473, 15, {"qkv": (6, 3, 3), "gu": (6, 3, 2), "lm": (6, 3, 2), "down": (4, 3, 4, 8)}),
+    ((512, 2, 128, 6144, 32000), 325, 500, {"gu": (6, 3, 3), "lm": (6, 4, 2)}),
+    ((1024, 32, 128, 6144, 1024), 487, 33, {"qkv": (6, 4, 3), "gu": (6, 4, 3)}),
+    ((512, 4, 64, 11008, 1024), 451, 300, {"gu": (6, 4, 2)}),
+    ((768, 32, 128, 512, 1024), 527, 9, {"qkv": (6, 3, 2)}),
+    ((512, 64, 128, 512, 512), 385, 21, {"qkv": (6, 4, 2)}),
+    ((2048, 1, 64, 4096, 512), 516, 5, {"down": (4, 4, 4, 3)})], ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
+def test_tall_tile_form_of_every_epilogue(P, dims, m, t, want):
+    """Every pair of tile form and epilogue that matrices of ordinary shapes lead to, by the plan's own word: ragged row counts
+    over a cache that is not empty, logits and cache rows.  Tolerances: the project's (bf16)."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    d, H, dh, F, V = dims
+    hd = H * dh
+    plans = {"qkv": (3 * hd, d, m, False), "o": (d, hd, m, True), "gu": (2 * F, d, m, False), "down": (d, F, m, True), "lm": (V, d, m, False)}
+    for k, form in want.items():
+        assert _tall_plan(P, *plans[k])[:len(form)] == form, k
+    shape = I.ModelShape("edge_forms", 0, "bf16", 1, d, H, dh, F, V)
+    gm, om = make_pair(shape, 19, 1, t + m + 3, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, t, 19)
+    block = I.token_ids(m, shape.vocab, 19, 1).reshape(1, m).numpy().astype(np.int32)
+    cl = np.full(1, t, np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+    _check_cache(gm, om, 1, 0, t + m)
+
+
+@pytest.mark.parametrize("dims,B,m,want", [
+    ((256, 2, 64, 512, 1024), 2, 73, {(4, 2, 4)}),
+    ((512, 32, 128, 4096, 32128), 1, 321, {(4, 3, 4), (6, 3, 3), (6, 4, 2)}),
+    ((1024, 32, 128, 8192, 32128), 1, 208, {(4, 4, 4), (6, 2, 3), (6, 3, 2)}),
+    ((1024, 32, 128, 512, 1024), 1, 497, {(6, 4, 3)}),
+    ((256, 16, 64, 512, 1024), 1, 203, {(4, 2, 4)})], ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
+def test_tall_blocks_of_the_encoder_decoder(P, dims, B, m, want):
+    """arch 1 blocks of more than 144 rows: every GEMM writes partial sums, in every form; attention with the distance bias over
+    many row tiles and cached rows (the last shape on single key tiles per request)."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    d, H, dh, F, V = dims
+    hd, M = H * dh, B * m
+    assert want <= {_tall_plan(P, N, K, M, True)[:3] for N, K in ((3 * hd, d), (d, hd), (hd, d), (2 * F, d), (d, F), (V, d))}
+    t = 161
+    shape = I.ModelShape("edge_t5_tall", 1, "bf16", 1, d, H, dh, F, V, rms_eps=1e-6, enc_len=70)
+    gm, om = make_pair(shape, 53, B, 760, m, std=0.05)
+    enc = I.encoder_output(shape, B, 53)
+    gm.cross_kv_init(enc.cuda())
+    om.cross_kv_init(enc.numpy())
+    import_synthetic_kv(gm, om, shape, t, 53, B=B)
+    block = I.token_ids(M, V, 53, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([t - 30 * b for b in range(B)], np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+    for b in range(B):
+        _check_cache(gm, om, 1, b, int(cl[b]) + m)
+
+
+@pytest.mark.parametrize("d,H,dh,B,enc_len,form", [(512, 32, 128, 1, 257, (4, 3, 4)), (1024, 32, 128, 1, 385, (4, 4, 4)),
+                                                   (1024, 32, 128, 2, 251, (4, 4, 4))])
+def test_cross_projection_tile_forms(P, d, H, dh, B, enc_len, form):
+    """The encoder projection in the taller tiles, ragged; (4, 2, 4) is what test_cross_projection_rows takes."""
+    from gpu_util import make_pair, tol_ok
+    assert _tall_plan(P, 2 * H * dh, d, B * enc_len, False)[:3] == form
+    shape = I.ModelShape("edge_cross", 1, "bf16", 1, d, H, dh, 256, 512, rms_eps=1e-6, enc_len=enc_len)
+    gm, om = make_pair(shape, 59, B, 32, 8, std=0.05)
+    enc = I.encoder_output(shape, B, 59)
+    gm.cross_kv_init(enc.cuda())
+    om.cross_kv_init(enc.numpy())
+    block = I.token_ids(B * 5, shape.vocab, 59, 1).reshape(B, 5).numpy().astype(np.int32)
+    cl = np.zeros(B, np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+
+
+@pytest.mark.parametrize("H,dh,m,t,max_seq", [(12, 64, 200, 0, 1024), (12, 64, 331, 431, 1024), (16, 64, 512, 477, 1024), (12, 128, 200, 311, 1024),
+                                              (16, 128, 512, 389, 1024)])
+def test_attention_of_tall_blocks(P, H, dh, m, t, max_seq):
+    """So many row tiles that a wave requests one key tile at a time: row tiles that see few of the chunk's keys, several chunks,
+    an odd number of cached rows, one row in the last tile."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    assert H * ((m + 15) // 16) * (max_seq // 128) > 1024
+    shape = I.ModelShape("edge_tall_attn", 0, "bf16", 1, 256, H, dh, 128, 512)
+    gm, om = make_pair(shape, 61, 1, max_seq, m, std=0.05)
+    if t:
+        import_synthetic_kv(gm, om, shape, t, 61)
+    block = I.token_ids(m, shape.vocab, 61, 1).reshape(1, m).numpy().astype(np.int32)
+    cl = np.full(1, t, np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+
+
+@pytest.mark.parametrize("H,dh", [(12, 64), (8, 128)])
+@pytest.mark.parametrize("B,m", [(8, 40), (3, 64), (6, 25)])
+def test_tree_blocks_of_many_rows(P, H, dh, B, m):
+    """Tree blocks of several sequences, more than 144 rows in all: rotation by depth in the epilogue of the tall GEMM, ancestor masks of
+    several sequences in one launch, ragged cached lengths, logits and cache rows."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_tree", 0, "bf16", 1, 256, H, dh, 512, 1024)
+    gm, om = make_pair(shape, 67, B, 512, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, 333, 67, B=B)
+    r = np.random.RandomState(m)
+    parent = np.stack([np.asarray([-1] + [r.randint(max(0, i - 7), i) for i in range(1, m)]) for _ in range(B)]).astype(np.int32)
+    block = I.token_ids(B * m, shape.vocab, 67, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([333 - 41 * b for b in range(B)], np.int32)
+    lg = gm.verify_tree(torch.from_numpy(block).cuda(), torch.from_numpy(parent).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_tree(block, parent, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+    for b in (0, B - 1):
+        _check_cache(gm, om, 1, b, int(cl[b]) + m)
+
+
+@pytest.mark.parametrize("dh,path", [(64, "multikernel"), (128, "multikernel"), (32, "default")])
+@pytest.mark.parametrize("B,m", [(1, 150), (2, 130)])
+def test_tall_blocks_with_epilogue_kernels(P, monkeypatch, dh, path, B, m):
+    """More than 144 rows where the GEMMs write partial sums for epilogue kernels: the forward with one kernel per operation when
+    it is asked for, and models whose head size leaves the attention to the generic kernel."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    monkeypatch.setenv("CSD_PATH", path)
+    shape = I.ModelShape("edge_unfused", 0, "bf16", 2, 256, 256 // dh, dh, 512, 1024)
+    gm, om = make_pair(shape, 71, B, m + 60, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, 51, 71, B=B)
+    block = I.token_ids(B * m, shape.vocab, 71, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([51 - 20 * b for b in range(B)], np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+    for b in range(B):
+        _check_cache(gm, om, 2, b, int(cl[b]) + m)
 
 
 @pytest.mark.parametrize("m", [20, 145])
@@ -174,7 +330,7 @@ def test_cross_projection_rows(P, B, enc_len):
     _check_cross_projection(P, B, enc_len, 8)
 
 
-@pytest.mark.parametrize("B,enc_len,max_block", [(1, 16, 64), (1, 33, 64), (1, 64, 64), (1, 64, 63), (1, 128, 140), (1, 129, 140), (2, 30, 64)])
+@pytest.mark.parametrize("B,enc_len,max_block", [(1, 16, 64), (1, 33, 64), (1, 64, 64), (1, 64, 63), (1, 65, 80), (1, 128, 140), (1, 129, 140), (2, 30, 64)])
 def test_cross_projection_of_few_rows(P, B, enc_len, max_block):
     """One sequence whose rows fit a decoder block: the GEMMs that stream the matrices (a whole row tile, the first count of the
     row-split form, the last one for a matrix of this size); one row more than a block, than those rows, and a second sequence: the tall form."""
