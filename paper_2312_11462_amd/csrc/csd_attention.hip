@@ -8,9 +8,9 @@
 // group) becomes the B operand of the second directly, because the keys are assigned to A-rows
 // so that every lane ends up holding 8 consecutive keys; V is cached transposed so that the
 // matching A operand is one 16-byte load.  Chunks keep an online-softmax state (max, sum,
-// un-normalised output) that a small merge kernel combines.  The host doubles the keys per wave
-// (chunk_keys) while there are more than two waves per SIMD, which shrinks the partial states the merge
-// kernel has to read.  (A form that loads each key tile once for two row tiles of
+// un-normalised output) that a small merge kernel combines.  Where chunks of 128 keys would be more than two waves
+// per SIMD, the host cuts the keys into fewer, equal chunks (chunk_keys), which shrinks the partial states the
+// merge kernel has to read.  (A form that loads each key tile once for two row tiles of
 // the block was slower: its register need halves the waves in flight.)
 #include "csd_internal.h"
 

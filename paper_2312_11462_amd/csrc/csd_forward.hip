@@ -571,8 +571,7 @@ __global__ __launch_bounds__(256) void k_rows_to_act(const float *__restrict__ s
 }
 
 // Generic causal block attention: one workgroup per (block row, head).  Scores of the visible cache rows 0..pos go
-// through LDS; softmax in fp32 with max subtraction; o = sum_j p_j V_j with the keys dealt over 256 / dh groups of threads
-//.
+// through LDS; softmax in fp32 with max subtraction; o = sum_j p_j V_j with the keys dealt over 256 / dh groups of threads.
 #define AS_THREADS 256
 template <typename TA, typename TC>
 __global__ __launch_bounds__(AS_THREADS) void k_attn_simple(const TA *__restrict__ q, int m, const int32_t *__restrict__ cache_len,
@@ -768,9 +767,9 @@ static int32_t launch_gemm_rs(const csd_model *mod, const GemmW &w, const bf16_t
         case 8: return launch_gemm_rs_t<8, 2>(w, act, plane, mtp, part, M, S, groups, st);
         default: return launch_gemm_rs_t<6, 2>(w, act, plane, mtp, part, M, S, groups, st);
     }
-    if (MT <= 12) return ct == 8 ? launch_gemm_rs_t<8, 3>(w, act, plane, mtp, part, M, S, groups, st)
-                                : launch_gemm_rs_t<6, 3>(w, act, plane, mtp, part, M, S, groups, st);
-    return CSD_ESHAPE;
+    if (MT > 9) return CSD_ESHAPE;                           // taller blocks take csd_tall.hip
+    return ct == 8 ? launch_gemm_rs_t<8, 3>(w, act, plane, mtp, part, M, S, groups, st)
+                   : launch_gemm_rs_t<6, 3>(w, act, plane, mtp, part, M, S, groups, st);
 }
 
 // Once per process and device, at model creation (no runtime call besides launches happens later): allow

@@ -9,9 +9,10 @@
 // placed in operand order; NST stages of one k-step are in flight or in use.  A wave holds the fragments of the running
 // k-step in registers and reads the next one's between its matrix instructions; one workgroup barrier per k-step.
 // Row blocks of one column group go to one compute die, which then fetches those weights once.
-// 7B shape, 512 rows, against four launches of the row-split form over 128 rows each: QKV 122 -> 81 us (1.27 PFLOP/s, both
-// planes counted), gate|up 188 -> 146, down 111 -> 79, O 57 -> 34, LM head 254 -> 223; with the loads of the main loop
-// switched off 57-68 us for QKV, so it is bound by the operand traffic into LDS beside the matrix instructions.
+// 7B shape, 512 rows, against four launches of the row-split form over 128 rows each, every GEMM timed by itself: QKV 122 -> 81 us
+// (1.27 PFLOP/s, both planes counted), gate|up 188 -> 146, down 111 -> 79, O 57 -> 34, LM head 254 -> 223.  In traces of whole calls, where
+// the chip is under load throughout: QKV 95 (1.09 PFLOP/s), gate|up 147, O and down 58 on average, LM head 233.  With the loads of the main loop
+// switched off 57-68 us for QKV by itself, so it is bound by the operand traffic into LDS beside the matrix instructions.
 #include "csd_epilogue.h"
 
 enum { EPI_PART = 4, EPI_CROSS = 5 };       // besides the epilogues of csd_epilogue.h
@@ -312,7 +313,7 @@ int32_t csd_tall_setup() {
 // else under the other's k-steps), and the splits' partial sums.
 // Narrow tiles fill the chip where a matrix is small or its row blocks few: 160M shape, 512 rows, QKV 29.8 us in 48 workgroups
 // of 6 x 4 tiles per wave, 14.1 in 144 of 4 x 2; 7B shape, 384 rows, QKV 92.3 us at 6 x 4 (192 workgroups), 77.2 at 6 x 3 (256); 512 rows, where 6 x 4
-// makes 256 workgroups, 98.5 against 127.6 at 6 x 3.  max_splits = 1 where the epilogue runs in the kernel.
+// makes 256 workgroups, 98.5 against 127.6 at 6 x 3 (all in traces of whole calls, before the sums were kept in chains).  max_splits = 1 where the epilogue runs in the kernel.
 // Stages: four of the narrow tiles; with 6 column tiles and more workgroups than compute units two of them share one (two stages
 // each), which evens out the last round: gate|up at 512 rows 146 us against 155 with three stages and one workgroup at a time; at 256
 // workgroups 117 against 81.
