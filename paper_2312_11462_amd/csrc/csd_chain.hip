@@ -689,11 +689,18 @@ __global__ __launch_bounds__(256) void kc_embed(const int32_t *__restrict__ toke
 // with heads of 128, 512 workgroups, a cache of 448 rows with 40 in use 108 us against 65 with the kernels of csd_attention.hip, 1024
 // workgroups 198 against 74; heads of 64, 512 workgroups, 40 of 832 rows 63 against 53, 2048 workgroups 218 against 69.  256
 // workgroups, 40 / 220 / 440 of 448 rows: 52 / 51 / 60 us against 61 / 74 / 95.
-#define CA_ONE_KEYS_128 384          /* at most 32 * CA_ONE_NW: one turn */
+// Heads of 128: the few workgroups of one sequence lose to kc_attn's chunks on more compute units above 384 rows (32 workgroups, 440
+// keys 11.5 us against 10.7); from 64 on the four chunks of up to 448 rows would be as many workgroups as there are compute
+// units, and one turn of this form wins: steps of the 7B shape
+// with 384 rows in use of 448, 4 / 6 / 8 sequences 3416 / 3981 / 4227 us against 3501 / 4110 / 4439.
+#define CA_ONE_KEYS_128_FEW 384
+#define CA_ONE_KEYS_128 448          /* at most 32 * CA_ONE_NW: one turn */
 #define CA_ONE_KEYS_64 832
 #define CA_ONE_GROUPS 256
 static bool attn_one_fits(const csd_model *mod, int B, int keys_pad) {
-    return mod->cfg.n_heads * B <= CA_ONE_GROUPS && keys_pad <= (mod->cfg.head_dim == 128 ? CA_ONE_KEYS_128 : CA_ONE_KEYS_64);
+    const int groups = mod->cfg.n_heads * B;
+    const int most = mod->cfg.head_dim == 64 ? CA_ONE_KEYS_64 : groups < 64 ? CA_ONE_KEYS_128_FEW : CA_ONE_KEYS_128;
+    return groups <= CA_ONE_GROUPS && keys_pad <= most;
 }
 template <int DH, bool BIAS>
 static void attn_one_launch(const AttnArgs &A, int H, int B, hipStream_t st) {

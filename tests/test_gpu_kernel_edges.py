@@ -421,10 +421,11 @@ def test_small_block_attention(P, arch, dh, max_seq, B, m, t):
 
 
 @pytest.mark.parametrize("arch,dh", [(0, 64), (0, 128), (1, 64)])
-@pytest.mark.parametrize("max_seq,B,m,t", [(128, 8, 4, 90), (128, 9, 3, 90), (128, 32, 1, 120), (384, 9, 3, 300), (384, 32, 1, 17), (448, 1, 5, 440)])
+@pytest.mark.parametrize("max_seq,B,m,t", [(128, 8, 4, 90), (128, 9, 3, 90), (128, 32, 1, 120), (384, 9, 3, 300), (384, 32, 1, 17), (448, 1, 5, 440),
+                                           (448, 2, 5, 440), (448, 8, 1, 447), (512, 2, 3, 450)])
 def test_small_block_attention_of_many_heads(P, arch, dh, max_seq, B, m, t):
     """Caches short enough for one workgroup per head, with as many (sequence, head) pairs as compute units and with more, where
-    the chunked kernels take over; and the first length past the limit for heads of 128."""
+    the chunked kernels take over; and either side of the two limits for heads of 128, below and from 64 pairs on."""
     from gpu_util import import_synthetic_kv, make_pair, tol_ok
     shape = I.ModelShape("edge_heads", arch, "bf16", 1, 64, 32, dh, 64, 512, rms_eps=1e-6 if arch else 1e-5, enc_len=70 if arch else 0)
     gm, om = make_pair(shape, 43, B, max_seq, m, std=0.05)
