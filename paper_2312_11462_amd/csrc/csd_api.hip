@@ -133,7 +133,7 @@ static int32_t create_impl(csd_model *mod, const void *const *weights, hipStream
             if (n * esz >= ((size_t)1 << 31)) return CSD_ESHAPE;
     }
     if ((rc = csd_pack_weights(mod, weights, st)) != CSD_OK) return rc;
-    if (mod->mfma && ((rc = csd_gemm_setup()) != CSD_OK || (rc = csd_tall_setup()) != CSD_OK)) return rc;
+    if (mod->mfma && ((rc = csd_gemm_setup()) != CSD_OK || (rc = csd_rows_setup()) != CSD_OK || (rc = csd_tall_setup()) != CSD_OK)) return rc;
 
     const int m_pad = (mod->m_max + 15) / 16 * 16;
     int wmax = d > F ? d : F;

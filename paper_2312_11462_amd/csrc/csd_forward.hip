@@ -83,7 +83,6 @@ __global__ __launch_bounds__(512) void k_gemm_ws(const u32x4 *__restrict__ Wp, c
     const int ks0 = (int)((long long)KS * s / S), ks1 = (int)((long long)KS * (s + 1) / S);
     const int n_chunks = (ks1 - ks0 + U - 1) / U;
     const int t = lane & 15, g = lane >> 4;
-    const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
 
     if (w < 4) {
         // ------------------------------------------------------------ weight stream + matrix cores
@@ -210,145 +209,6 @@ __global__ __launch_bounds__(512) void k_gemm_ws(const u32x4 *__restrict__ Wp, c
         }
 #undef CSD_WS_LOAD_ACT
 #undef CSD_WS_PUT_ACT
-    }
-}
-
-// Blocks of 33 to 144 rows (3 to 9 row tiles), where the matrix cores and LDS bandwidth matter as much as HBM: the
-// rows are split over the 4 compute waves (RW row tiles each) and the weights are what is shared.  Waves
-// 4-7 stream the weight fragments of CT column tiles from HBM into LDS (two chunks ahead in registers, one
-// in LDS); a compute wave keeps its own rows' activation fragments in registers (fetched from L2 one chunk
-// of k-steps ahead, slot by slot as they are used up) and reads every weight fragment once from LDS for
-// 2 * RW matrix instructions: with two row tiles per wave the matrix cores get four instructions per
-// 16-byte LDS read, where the activation-sharing form above gets two (its LDS reads then take as long as
-// its matrix instructions), and nothing goes through LDS that only one wave needs.
-template <int CT, int RW, int U>
-__global__ __launch_bounds__(512) void k_gemm_rs(const u32x4 *__restrict__ Wp, const bf16_t *__restrict__ act, size_t plane,
-                                                 int mtp, float *__restrict__ part, int M, int K, int N, int S) {
-    extern __shared__ __align__(16) char wg_smem[];
-    constexpr int CH = U * CT * 64;                          // 16-byte weight fragments (per lane) of a chunk
-    constexpr int ST = CH / 256;                             // staging loads per staging thread and chunk
-    constexpr int PD = 3;                                    // LDS reads run this many column tiles ahead
-    static_assert(CH % 256 == 0 && U * CT > PD, "chunk shape");
-    u32x4 *lbuf = reinterpret_cast<u32x4 *>(wg_smem);        // [2][CH]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int s = blockIdx.x % S, grp = blockIdx.x / S;
-    const int KS = K / 32, n_tiles = N / 16;
-    const int ks0 = (int)((long long)KS * s / S), ks1 = (int)((long long)KS * (s + 1) / S);
-    const int n_chunks = (ks1 - ks0 + U - 1) / U;
-    const int t = lane & 15, g = lane >> 4;
-    const int tile0 = grp * CT;
-    const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
-
-    if (w < 4) {
-        // ------------------------------------------------------------ own rows x all column tiles
-        const __amdgpu_buffer_rsrc_t ra =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(act), 0, (int)(2 * plane * sizeof(bf16_t)), 0x00020000);
-        const int lo_off = (int)(plane * sizeof(bf16_t));
-        int voff[RW];                                        // rows past M: an offset beyond the buffer (loads give 0)
-#pragma unroll
-        for (int r = 0; r < RW; r++) {
-            const int row = (w * RW + r) * 16 + t;
-            voff[r] = row < M ? (4 * t + g) * 16 : (int)0x80000000;
-        }
-        const bool has_rows = w * RW * 16 < M;               // uniform
-        f32x4 acc[RW][CT];
-#pragma unroll
-        for (int r = 0; r < RW; r++)
-#pragma unroll
-            for (int ct = 0; ct < CT; ct++) acc[r][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-        u32x4 a[U][RW][2];
-
-#define CSD_RS_LOAD_A(UU, KS_AT)                                                                  \
-    {                                                                                             \
-        const int ksa_ = (KS_AT);                                                                 \
-        const bool in_ = ksa_ < ks1; /* uniform; past the slice: an offset beyond the buffer, no branch */ \
-        _Pragma("unroll") for (int r = 0; r < RW; r++) {                                          \
-            const int vo_ = in_ ? voff[r] : (int)0x80000000;                                      \
-            const int so_ = in_ ? (ksa_ * mtp + w * RW + r) * 1024 : 0; /* one stored fragment, see act_tiled_idx */ \
-            a[UU][r][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, vo_, so_, 0)); \
-            a[UU][r][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, vo_, in_ ? so_ + lo_off : 0, 0)); \
-        }                                                                                         \
-    }
-#define CSD_RS_MMA(BUF, KS_NEXT)                                                                  \
-    if (has_rows) {                                                                               \
-        const u32x4 *lb_ = lbuf + (BUF) * CH + lane;                                              \
-        u32x4 wf_[PD + 1];                                                                        \
-        _Pragma("unroll") for (int p = 0; p < PD; p++) wf_[p] = lb_[p * 64];                      \
-        _Pragma("unroll") for (int idx = 0; idx < U * CT; idx++) {                                \
-            if (idx + PD < U * CT) wf_[(idx + PD) % (PD + 1)] = lb_[(idx + PD) * 64];             \
-            const int u = idx / CT, ct = idx % CT;                                                \
-            _Pragma("unroll") for (int r = 0; r < RW; r++)                                        \
-                acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                             \
-                    __builtin_bit_cast(bf16x8, wf_[idx % (PD + 1)]), __builtin_bit_cast(bf16x8, a[u][r][0]), acc[r][ct], 0, 0, 0); \
-            _Pragma("unroll") for (int r = 0; r < RW; r++)                                        \
-                acc[r][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                             \
-                    __builtin_bit_cast(bf16x8, wf_[idx % (PD + 1)]), __builtin_bit_cast(bf16x8, a[u][r][1]), acc[r][ct], 0, 0, 0); \
-            if (ct == CT - 1) CSD_RS_LOAD_A(u, (KS_NEXT) + u) /* slot u is free: k-step U ahead */  \
-            if (RW != 3 || (idx & 3) == 3) __builtin_amdgcn_sched_barrier(0);                    \
-        }                                                                                         \
-    }
-
-        if (has_rows) {
-#pragma unroll
-            for (int u = 0; u < U; u++) CSD_RS_LOAD_A(u, ks0 + u)
-        }
-        lds_sync();                                          // weight chunk 0 is in LDS
-        for (int c = 0; c < n_chunks; c += 2) {
-            CSD_RS_MMA(0, ks0 + (c + 1) * U)
-            lds_sync();                                      // chunk c consumed, chunk c + 1 staged
-            if (c + 1 >= n_chunks) break;
-            CSD_RS_MMA(1, ks0 + (c + 2) * U)
-            lds_sync();
-        }
-#undef CSD_RS_LOAD_A
-#undef CSD_RS_MMA
-#pragma unroll
-        for (int r = 0; r < RW; r++) {
-            const int row = (w * RW + r) * 16 + t;
-            if (row < M) {
-#pragma unroll
-                for (int ct = 0; ct < CT; ct++)
-                    if (tile0 + ct < n_tiles) {
-                        float *o = part + ((size_t)s * M + row) * N + (size_t)(tile0 + ct) * 16 + 4 * g;
-                        *reinterpret_cast<f32x4 *>(o) = acc[r][ct];
-                    }
-            }
-        }
-    } else {
-        // ------------------------------------------------------------ weight staging
-        // fragment i * 256 + (tid - 256) of a chunk = (u, column tile, lane): u and the tile are the same
-        // for a whole wave and go into the scalar offset
-        const int sw = w - 4, stid = tid - 256;
-        const __amdgpu_buffer_rsrc_t rw =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wp), 0, (int)((size_t)K * N * sizeof(bf16_t)), 0x00020000);
-        const int voff = lane * 16;
-        u32x4 sa[ST], sb[ST];
-#define CSD_RS_LOAD_W(SF, KS_AT)                                                                  \
-    _Pragma("unroll") for (int i = 0; i < ST; i++) {                                              \
-        const int rest_ = i * 4 + sw, tile_ = tile0 + rest_ % CT, ksu_ = (KS_AT) + rest_ / CT;    \
-        const bool in_ = ksu_ < ks1 && tile_ < n_tiles; /* uniform; else an offset beyond the buffer */ \
-        SF[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(                  \
-            rw, in_ ? voff : (int)0x80000000, in_ ? (tile_ * KS + ksu_) * 1024 : 0, 2));          \
-    }
-#define CSD_RS_PUT_W(SF, BUF)                                                                     \
-    _Pragma("unroll") for (int i = 0; i < ST; i++) lbuf[(BUF) * CH + i * 256 + stid] = SF[i];
-
-        CSD_RS_LOAD_W(sa, ks0)
-        CSD_RS_LOAD_W(sb, ks0 + U)
-        CSD_RS_PUT_W(sa, 0)
-        lds_sync();
-        for (int c = 0; c < n_chunks; c += 2) {
-            CSD_RS_LOAD_W(sa, ks0 + (c + 2) * U)
-            CSD_RS_PUT_W(sb, 1)                              // chunk c + 1, fetched one round ago
-            lds_sync();
-            if (c + 1 >= n_chunks) break;
-            CSD_RS_LOAD_W(sb, ks0 + (c + 3) * U)
-            CSD_RS_PUT_W(sa, 0)
-            lds_sync();
-        }
-#undef CSD_RS_LOAD_W
-#undef CSD_RS_PUT_W
     }
 }
 
@@ -701,99 +561,20 @@ static int32_t launch_gemm_ws(const GemmW &w, const bf16_t *act, size_t plane, i
     switch ((M + 15) / 16) {
     case 1: return launch_gemm_ws_mt<1>(w, act, plane, mtp, part, M, S, groups, st);
     case 2: return launch_gemm_ws_mt<2>(w, act, plane, mtp, part, M, S, groups, st);
-    default: return CSD_ESHAPE;       // taller blocks take the row-split form
+    default: return CSD_ESHAPE;       // taller blocks take csd_rows.hip
     }
-}
-
-template <int CT, int RW>
-static int32_t launch_gemm_rs_t(const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M, int S,
-                                int groups, hipStream_t st) {
-    const size_t lds = (size_t)2 * WG_U_MAX * CT * 64 * 16;          // allowed at csd_gemm_setup
-    hipLaunchKernelGGL((k_gemm_rs<CT, RW, WG_U_MAX>), dim3(groups * S), dim3(512), lds, st, reinterpret_cast<const u32x4 *>(w.data),
-                       act, plane, mtp, part, M, w.K, w.N, S);
-    return CSD_OK;
-}
-
-// The row-split form.  Its launches are bound by the matrix instructions of the busiest compute wave, so what
-// matters is how many compute units have a workgroup: the column tiles per workgroup (CT) and the K splits (S, at most
-// 8: the partial sums are traffic too) are chosen per matrix so that the launch comes as close to one workgroup per
-// compute unit as the shape allows, the wider workgroup winning a tie (it reads the activation rows less often).
-// Measured per launch at 128 rows of the 7B shape, against 16 tiles and 128 workgroups for every matrix: QKV 40.6 ->
-// 33.1 us (12 tiles, 4 splits, 256 workgroups), O and down 30.6 -> 23.6 (8, 8, 256), gate|up 57.2 -> 49.1 (11, 2, 252).
-static int rs_splits(int groups, int KS, int M, int N, size_t part_floats) {
-    int S = 1;
-    while (groups * (S + 1) <= 256 && S < 8 && KS / (S + 1) >= 2 * WG_U_MAX && (size_t)(S + 1) * M * N <= part_floats) S++;
-    return S;
-}
-// rows: 33 to 144; the partial-sum buffer holds S x rows x N floats.
-static void rs_plan(int N, int K, int rows, size_t part_floats, int *ct_out, int *S_out) {
-    const int n_tiles = N / 16, KS = K / 32, MT = (rows + 15) / 16;
-    const int rw = MT <= 8 ? 2 : 3;          // row tiles per compute wave: waves past the block's rows only pass the barriers
-    static const int cts2[] = {16, 12, 11, 8, 6, 0}, cts3[] = {8, 6, 0};
-    const int *cts = rw == 2 ? cts2 : cts3;
-    int ct = cts[0], S = 1;
-    double best = -1.0;
-    for (int i = 0; cts[i]; i++) {
-        const int groups = (n_tiles + cts[i] - 1) / cts[i];
-        const int s = rs_splits(groups, KS, rows, N, part_floats);
-        const int wgs = groups * s;
-        const double fill = (double)wgs / (256.0 * ((wgs + 255) / 256));
-        if (fill > best) best = fill, ct = cts[i], S = s;
-    }
-    *ct_out = ct;
-    *S_out = S;
-}
-int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats, int32_t *ct, int32_t *S) {
-    if (!ct || !S) return CSD_ENULL;
-    if (N <= 0 || K <= 0 || N % 16 || K % 32 || rows < 1 || rows > 144) return CSD_EINVAL;
-    int c = 0, s = 0;
-    rs_plan(N, K, rows, part_floats, &c, &s);
-    *ct = c;
-    *S = s;
-    return CSD_OK;
-}
-static int32_t launch_gemm_rs(const csd_model *mod, const GemmW &w, const bf16_t *act, size_t plane, int mtp, float *part, int M,
-                              int *S_used, hipStream_t st) {
-    const int n_tiles = w.N / 16, MT = (M + 15) / 16;
-    const int rw = MT <= 8 ? 2 : 3;
-    int ct = 0, S = 0;
-    rs_plan(w.N, w.K, M, mod->part_floats, &ct, &S);
-    *S_used = S;
-    const int groups = (n_tiles + ct - 1) / ct;
-    if (rw == 2) switch (ct) {
-        case 16: return launch_gemm_rs_t<16, 2>(w, act, plane, mtp, part, M, S, groups, st);
-        case 12: return launch_gemm_rs_t<12, 2>(w, act, plane, mtp, part, M, S, groups, st);
-        case 11: return launch_gemm_rs_t<11, 2>(w, act, plane, mtp, part, M, S, groups, st);
-        case 8: return launch_gemm_rs_t<8, 2>(w, act, plane, mtp, part, M, S, groups, st);
-        default: return launch_gemm_rs_t<6, 2>(w, act, plane, mtp, part, M, S, groups, st);
-    }
-    if (MT > 9) return CSD_ESHAPE;                           // taller blocks take csd_tall.hip
-    return ct == 8 ? launch_gemm_rs_t<8, 3>(w, act, plane, mtp, part, M, S, groups, st)
-                   : launch_gemm_rs_t<6, 3>(w, act, plane, mtp, part, M, S, groups, st);
 }
 
 // Once per process and device, at model creation (no runtime call besides launches happens later): allow
-// every GEMM instantiation its dynamic LDS (up to 144 KB).
+// the GEMM its dynamic LDS.
 template <int MT>
 static hipError_t ws_allow_lds() {
     return hipFuncSetAttribute((const void *)k_gemm_ws<1, MT, WG_U_MAX>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                2 * WG_U_MAX * MT * 2 * 64 * 16);
 }
-template <int CT, int RW>
-static hipError_t rs_allow_lds() {
-    return hipFuncSetAttribute((const void *)k_gemm_rs<CT, RW, WG_U_MAX>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               2 * WG_U_MAX * CT * 64 * 16);
-}
 int32_t csd_gemm_setup() {
     CSD_HIP(ws_allow_lds<1>());
     CSD_HIP(ws_allow_lds<2>());
-    CSD_HIP((rs_allow_lds<16, 2>()));
-    CSD_HIP((rs_allow_lds<12, 2>()));
-    CSD_HIP((rs_allow_lds<11, 2>()));
-    CSD_HIP((rs_allow_lds<8, 2>()));
-    CSD_HIP((rs_allow_lds<6, 2>()));
-    CSD_HIP((rs_allow_lds<8, 3>()));
-    CSD_HIP((rs_allow_lds<6, 3>()));
     return CSD_OK;
 }
 
@@ -806,7 +587,7 @@ static int32_t run_gemm(csd_model *mod, const GemmW &w, const void *act, size_t 
         *S_used = 0;
         const bf16_t *a = (const bf16_t *)act;
         const int32_t rc = M >= CSD_TALL_MIN_ROWS ? csd_tall_part(mod, w, a, plane, M, S_used, st)
-                           : M >= mod->gemm_rs_min_rows ? launch_gemm_rs(mod, w, a, plane, mod->act_mtp, mod->part, M, S_used, st)
+                           : M >= mod->gemm_rs_min_rows ? csd_rows_part(mod, w, a, plane, M, S_used, st)
                                                         : launch_gemm_ws(w, a, plane, mod->act_mtp, mod->part, M, S_used, st);
         if (rc != CSD_OK) return rc;
     } else {
@@ -1036,7 +817,7 @@ static int32_t cross_init_typed(csd_model *mod, void *kv, const float *enc_out, 
     const KvGeom cgeo = cross_geom(mod);
     TC *kvc = (TC *)((char *)kv + csd_self_kv_bytes(mod));
     int32_t rc;
-    // One sequence of few rows streams the matrices: k_gemm_ws or k_gemm_rs and a kernel for the epilogue take 17 / 22 / 33 / 35 us per
+    // One sequence of few rows streams the matrices: k_gemm_ws or k_gemm_rs (csd_rows.hip) and a kernel for the epilogue take 17 / 22 / 33 / 35 us per
     // layer for 8 / 32 / 64 / 96 rows of 4096 features, the tall form, made for matrix instructions, 33 to 36 for any of them.  The smaller
     // the matrix, the fewer workgroups the tall form has and the later it overtakes: 1024 features, 65 / 128 / 129 rows 10.5 / 12.8 / 13.9 us
     // against 13.4 for any, 2048 features, 65 / 104 / 112 / 120 rows 16.6 / 20.6 / 21.3 / 22.0 against 21.2 to 21.5, 4096, 88 / 104 rows

@@ -306,7 +306,7 @@ int32_t csd_forward_enqueue(csd_model *mod, void *kv, const int32_t *tokens, con
                             int32_t B, int32_t m, float *logits, hipStream_t st);
 int32_t csd_pack_weights(csd_model *mod, const void *const *w, hipStream_t st);
 int32_t csd_gemm_setup();    // MFMA models, at creation: lets the GEMM kernels use their dynamic LDS
-// host only: column tiles per workgroup and K splits the row-split GEMM takes for an N x K matrix and a block of `rows` rows
+// csd_rows.hip, host only: column tiles per workgroup and K splits the row-split GEMM takes for an N x K matrix and a block of `rows` rows
 int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats, int32_t *ct, int32_t *S);
 size_t csd_self_kv_bytes(const csd_model *mod);     // the self-attention part of the cache (arch 1 appends the cross part)
 // csd_chain.hip: forward for blocks of up to 32 rows, epilogues inside the GEMM kernels
@@ -324,6 +324,9 @@ int32_t csd_attn_simple_f32(csd_model *mod, const KvGeom &geo, const float *kv, 
 int32_t csd_f32_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int32_t B, int32_t m,
                         float *logits, hipStream_t st);
 int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int M, hipStream_t st);
+// csd_rows.hip: the GEMM over 33 to 144 rows, partial sums
+int32_t csd_rows_setup();
+int32_t csd_rows_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st);
 // csd_tall.hip: GEMMs over more rows than k_gemm_rs takes, partial sums or with the epilogue inside
 #define CSD_TALL_MIN_ROWS 145
 #define CSD_CROSS_ROWS 512       /* encoder rows that csd_cross_kv_init projects per pass over a layer's matrix */

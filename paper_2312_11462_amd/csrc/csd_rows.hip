@@ -1,0 +1,209 @@
+// GEMM for blocks of 33 to 144 rows (3 to 9 row tiles of 16), where the matrix cores and the traffic of a compute unit matter as
+// much as HBM.
+//
+// The rows are split over the waves of a workgroup (RW row tiles each) and the weights are what is shared: CT column tiles come
+// into LDS by direct loads, a k-step per stage, every wave bringing its share and reading every fragment once for 2 * RW
+// matrix instructions; a wave's own activation fragments go straight to registers.  Both streams run NSET - 1 k-steps ahead
+// (loads return in order, so a wait for the activations of a k-step is one for all weights issued before them: the weights
+// cannot run further ahead than the activations).  One barrier per k-step, the loads of a k-step dealt between its matrix
+// instructions, so that a wave that waits for a place in the memory pipeline has instructions in the matrix pipe meanwhile.
+// K is split over workgroups (rs_plan), one chain of sums per split.
+//
+// Bound by what a compute unit moves (activations from L2: every workgroup reads all rows of its K slice) and, at 40 rows, by
+// the weight stream.  Against the form before it, whose four extra waves carried the weights to LDS through registers
+// and whose compute waves always owned two or three row tiles (33 to 48 rows kept two of four busy, 144 rows three), per launch of the 7B
+// shape in traces of whole steps: 40 rows QKV 24.8 -> 22.6 us, gate|up 37.7 -> 33.8, O and down together 34.0 -> 31.5; 136 rows QKV and
+// gate|up together 98.8 -> 94.4, O and down 53.9 -> 52.0.  The weights are read once, so they pass the caches by (non-temporal: 22.2
+// -> 20.5 us for QKV at 40 rows by itself).  Measured and not taken: 6 to 12 k-steps ahead (no faster), all of K in one workgroup
+// and the epilogue inside (40 rows, gate|up by itself 39 to 43 us against 33 and 5 for the epilogue kernel; 136 rows 68.8 against 58.0 and 7.8).
+#include "csd_tall.h"
+
+#define RS_SETS 4             /* k-steps of activations in registers; as many stages of weights, and one in use, in LDS */
+
+template <int CT>
+static constexpr int rs_lds() { return (RS_SETS + 1) * CT * 1024; }
+
+template <int CT, int RW, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
+    extern __shared__ __align__(16) char rs_smem[];
+    constexpr int PW = (CT + NW - 1) / NW;                       // weight loads per wave and k-step (the last tile again past the end)
+    constexpr int AL = 2 * RW, NA = RS_SETS - 1, NST = RS_SETS + 1;
+    constexpr int RA = 4;                                        // weight fragments read ahead
+    const ChainGemm &P = A.g;
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    // workgroups go to the eight compute dies round-robin: consecutive shares to the workgroups of one die
+    const int per_die = gridDim.x >> 3, rest = gridDim.x & 7, die = blockIdx.x & 7;
+    const int wg = die * per_die + (die < rest ? die : rest) + (blockIdx.x >> 3);
+    const int s = wg % A.S, grp = wg / A.S;
+    const int ks0 = (int)((long long)P.KS * s / A.S), ks1 = (int)((long long)P.KS * (s + 1) / A.S);
+    const int tile0 = grp * CT, rt0 = w * RW;
+    const __amdgpu_buffer_rsrc_t rw = ch_rsrc(P.Wp, (size_t)P.wbytes);
+    const __amdgpu_buffer_rsrc_t ra =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(P.a), 0, (int)(2u * (unsigned)P.a_plane_bytes), 0x00020000);
+    // Column tiles and row tiles past the end are read as the last one, k-steps past the slice likewise (their sums are not
+    // stored, or not made): every address is inside, and every wave issues the same loads, so the waits can count them.
+    int wbase[PW];
+#pragma unroll
+    for (int i = 0; i < PW; i++) wbase[i] = min(tile0 + min(i * NW + w, CT - 1), A.n_tiles - 1) * P.KS * 1024;
+    unsigned abase[RW];
+#pragma unroll
+    for (int r = 0; r < RW; r++) abase[r] = min(rt0 + r, (P.M - 1) >> 4) * 1024;
+    const int vw = lane * 16, va = (4 * (lane & 15) + (lane >> 4)) * 16;     // see act_tiled_idx
+    auto load_w = [&](int i, int k, int buf) {
+        lds_load16<2>(rw, (lds_void)(rs_smem + (buf * CT + min(i * NW + w, CT - 1)) * 1024), vw, wbase[i] + min(k, ks1 - 1) * 1024);
+    };
+    u32x4 fa[RS_SETS][RW][2];
+    auto load_a = [&](int i, int k, int set) {
+        const unsigned off = abase[i >> 1] + (unsigned)(min(k, ks1 - 1) * P.mtp) * 1024u + (i & 1 ? (unsigned)P.a_plane_bytes : 0u);
+        fa[set][i >> 1][i & 1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, va, (int)off, 0));
+    };
+    f32x4 acc[RW][CT];
+#pragma unroll
+    for (int r = 0; r < RW; r++)
+#pragma unroll
+        for (int c = 0; c < CT; c++) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // order of issue: W(0), then A(k), W(k + 1) for k = 0 .. NA - 1; in k-step k: A(k + NA), W(k + NA + 1)
+#pragma unroll
+    for (int i = 0; i < PW; i++) load_w(i, ks0, 0);
+#pragma unroll
+    for (int p = 0; p < NA; p++) {
+#pragma unroll
+        for (int i = 0; i < AL; i++) load_a(i, ks0 + p, p);
+#pragma unroll
+        for (int i = 0; i < PW; i++) load_w(i, ks0 + p + 1, p + 1);
+    }
+    const u32x4 *L = reinterpret_cast<const u32x4 *>(rs_smem) + lane;
+    u32x4 f[CT + RA];
+    wait_loads<NA * (PW + AL)>();
+    stage_barrier();
+#pragma unroll
+    for (int c = 0; c < RA; c++) f[c] = L[c * 64];
+    int cur = 0, last = NST - 1, k = ks0;                        // the stages of W(k) and of W(k - 1), the latter free for W(k + NA + 1)
+    auto step = [&](int set) {
+        wait_loads<(NA - 1) * (PW + AL)>();                      // W(k + 1), this wave's share
+        stage_barrier();
+        const u32x4 *Lc = L + cur * CT * 64;
+        const int nxt = cur + 1 == NST ? 0 : cur + 1;
+        const u32x4 *Ln = L + nxt * CT * 64;
+#pragma unroll
+        for (int c = 0; c < CT; c++) {
+            f[c + RA] = c + RA < CT ? Lc[(c + RA) * 64] : Ln[(c + RA - CT) * 64];
+#pragma unroll
+            for (int i = 0; i < AL + PW; i++)
+                if (i * CT / (AL + PW) == c) {
+                    if (i < AL)
+                        load_a(i, k + NA, (set + NA) % RS_SETS);
+                    else
+                        load_w(i - AL, k + NA + 1, last);
+                }
+#pragma unroll
+            for (int p = 0; p < 2; p++)
+#pragma unroll
+                for (int r = 0; r < RW; r++)
+                    acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[c]),
+                                                                        __builtin_bit_cast(bf16x8, fa[set][r][p]), acc[r][c], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int c = 0; c < RA; c++) f[c] = f[c + CT];
+        last = cur;
+        cur = nxt;
+        k++;
+    };
+    while (k + RS_SETS <= ks1) {
+#pragma unroll
+        for (int u = 0; u < RS_SETS; u++) step(u);
+    }
+#pragma unroll
+    for (int u = 0; u < RS_SETS - 1; u++)
+        if (k < ks1) step(u);                                    // uniform over the workgroup
+    wait_loads<0>();                                             // nothing may land in this LDS after the workgroup has ended
+
+    const int t = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < RW; r++) {
+        const int row = (rt0 + r) * 16 + t;
+        if (row < P.M) {
+#pragma unroll
+            for (int c = 0; c < CT; c++)
+                if (tile0 + c < A.n_tiles)
+                    *reinterpret_cast<f32x4 *>(A.part + (((size_t)s * P.M + row) * A.n_tiles + tile0 + c) * 16 + 4 * g) = acc[r][c];
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------- host driver
+
+// Waves and row tiles per wave for 3 to 9 row tiles: as many waves as fill without a tile that is all padding, nine as three of three.
+#define RS_FOR_ALL_ROWS(X) X(1, 3) X(1, 4) X(2, 3) X(2, 4) X(3, 3)
+#define RS_FOR_ALL_CT(X, RW, NW) X(16, RW, NW) X(12, RW, NW) X(11, RW, NW) X(8, RW, NW) X(6, RW, NW)
+
+template <int CT, int RW, int NW>
+static hipError_t rs_allow_lds() {
+    return hipFuncSetAttribute((const void *)k_gemm_rs<CT, RW, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, rs_lds<CT>());
+}
+
+int32_t csd_rows_setup() {
+#define RS_ALLOW(CT, RW, NW) CSD_HIP((rs_allow_lds<CT, RW, NW>()));
+#define RS_ALLOW_ALL(RW, NW) RS_FOR_ALL_CT(RS_ALLOW, RW, NW)
+    RS_FOR_ALL_ROWS(RS_ALLOW_ALL)
+#undef RS_ALLOW_ALL
+#undef RS_ALLOW
+    return CSD_OK;
+}
+
+// What matters is how many compute units have a workgroup: the column tiles per workgroup (CT) and the K splits (S, at most
+// 8: the partial sums are traffic too) are chosen per matrix so that the launch comes as close to one workgroup per
+// compute unit as the shape allows, the wider workgroup winning a tie (it reads the activation rows less often).
+// 7B shape, 40 rows, against half the tiles and half the splits, which leaves half of the partial sums: QKV 20.5 us against 21.3, O 9.7
+// against 12.3, down 19.9 against 27.4.  rows: 33 to 144; the partial-sum buffer holds S x rows x N floats.
+static void rs_plan(int N, int K, int rows, size_t part_floats, const int *cts, int *ct, int *S) {
+    const int n_tiles = N / 16, KS = K / 32;
+    double best = -1.0;
+    for (; *cts; cts++) {
+        const int groups = (n_tiles + *cts - 1) / *cts;
+        int s = 1;
+        while (groups * (s + 1) <= 256 && s < 8 && KS / (s + 1) >= 8 && (size_t)(s + 1) * rows * N <= part_floats) s++;
+        const int wgs = groups * s;
+        const double fill = (double)wgs / (256.0 * ((wgs + 255) / 256));
+        if (fill > best) best = fill, *ct = *cts, *S = s;
+    }
+}
+static const int rs_cts[] = {16, 12, 11, 8, 6, 0}, rs_cts_low[] = {8, 6, 0};
+
+int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats, int32_t *ct, int32_t *S) {
+    if (!ct || !S) return CSD_ENULL;
+    if (N <= 0 || K <= 0 || N % 16 || K % 32 || rows < 1 || rows > 144) return CSD_EINVAL;
+    rs_plan(N, K, rows, part_floats, rows <= 128 ? rs_cts : rs_cts_low, ct, S);
+    return CSD_OK;
+}
+
+template <int CT, int RW, int NW>
+static int32_t rs_launch_t(const TallArgs &A, hipStream_t st) {
+    const int grid = (A.n_tiles + CT - 1) / CT * A.S;
+    hipLaunchKernelGGL((k_gemm_rs<CT, RW, NW>), dim3(grid), dim3(NW * 64), rs_lds<CT>(), st, A);
+    CSD_LAUNCH_CHECK();
+    return CSD_OK;
+}
+
+static int32_t rs_launch(const TallArgs &A, int ct, hipStream_t st) {
+    const int mt = (A.g.M + 15) / 16;
+    if (mt > 9) return CSD_ESHAPE;                               // taller blocks take csd_tall.hip
+    const int rw = mt <= 4 ? 1 : mt <= 8 ? 2 : 3, nw = (mt + rw - 1) / rw < 4 ? 3 : 4;
+#define RS_LAUNCH(CT, RW, NW) if (ct == CT && rw == RW && nw == NW) return rs_launch_t<CT, RW, NW>(A, st);
+#define RS_LAUNCH_ALL(RW, NW) RS_FOR_ALL_CT(RS_LAUNCH, RW, NW)
+    RS_FOR_ALL_ROWS(RS_LAUNCH_ALL)
+#undef RS_LAUNCH_ALL
+#undef RS_LAUNCH
+    return CSD_ESHAPE;
+}
+
+int32_t csd_rows_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st) {
+    TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
+    int ct = 0;
+    rs_plan(w.N, w.K, M, mod->part_floats, rs_cts, &ct, &A.S);    // (nine row tiles: QKV 34 us in 12 tiles and 4 splits, 36.9 in 6 and 2)
+    A.part = mod->part;
+    *S_used = A.S;
+    return rs_launch(A, ct, st);
+}

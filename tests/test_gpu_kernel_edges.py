@@ -302,6 +302,22 @@ def test_tall_sums_are_no_further_from_64_bits_than_row_split_ones(P, K, V, m):
     assert tall < 1.03 * split
 
 
+@pytest.mark.parametrize("K,V", [(96, 528), (544, 12304), (4096, 4096)])
+@pytest.mark.parametrize("m", [33, 48, 49, 64, 65, 96, 97, 128, 129, 144])
+def test_row_split_sums(P, K, V, m):
+    """The GEMM over 33 to 144 rows in each of its forms (one to three row tiles on three or four waves, the first and last row count
+    of each), with K slices shorter than the stages in flight, slices that end inside a turn, and ragged column groups.  A sum of K
+    exact products in 32 bits is within K 2^-23 of the sum of their sizes, the scale of the row and the partial sums add a few units."""
+    g = torch.Generator(device="cuda").manual_seed(K + m)
+    emb = torch.empty((V, K), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    lm = torch.empty((K, V), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    x = emb[:m].double()
+    rstd = torch.rsqrt((x * x).mean(-1, keepdim=True) + 1e-5)
+    ref, size = (x @ lm.double()) * rstd, (x.abs() @ lm.double().abs()) * rstd
+    got = _head_alone(P, K, V, m, emb, lm).double()
+    assert ((got - ref).abs() <= (K + 16) * 2.0 ** -23 * size).all()
+
+
 @pytest.mark.parametrize("V,m", [(22016, 512), (4096, 512)])
 def test_tall_sums_that_overflow(P, V, m):
     """Infinite products, sums that leave the range within a part of K and only when parts are added, infinities of both signs: the
