@@ -83,6 +83,7 @@ __device__ __forceinline__ unsigned long long range_weight(const float *__restri
     unsigned long long sum = 0ull;
     int v = v0;
     if (vec) {
+#pragma unroll 1
         for (; v + 4 <= v1; v += 4) {
             const float4 pv = *reinterpret_cast<const float4 *>(prow + v);
             float w[4] = {pv.x, pv.y, pv.z, pv.w};
@@ -104,6 +105,7 @@ __device__ __forceinline__ unsigned long long range_weight(const float *__restri
             for (int i = 0; i < 4; i++) sum += fixed40(w[i]);
         }
     }
+#pragma unroll 1
     for (; v < v1; v++) sum += fixed40(weight_at(prow, qrow, x, lenience, residual, v));
     return sum;
 }
@@ -130,13 +132,96 @@ __device__ __forceinline__ unsigned long long block_exclusive_scan(unsigned long
     return before + incl - mine;
 }
 
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// The draw inside the wave that owns T: its values in token order are (group j, lane, position in the group), `run` the weight of
+// all tokens before it.  They go through LDS (`own`, a float4 per lane and group) so that the loop over groups needs no registers
+// for them: unrolled over registers it spilled in kernels of 1024 threads.  Writes the token to *out (one lane does).
+template <int NG>
+__device__ __forceinline__ void wave_draw(const float *val, float4 *own, unsigned long long T, unsigned long long run, int vbase, int V,
+                                          int *out) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < NG; j++) own[j * 64 + lane] = make_float4(val[4 * j], val[4 * j + 1], val[4 * j + 2], val[4 * j + 3]);
+#pragma unroll 1
+    for (int j = 0; j < NG; j++) {
+        const float4 t = own[j * 64 + lane];
+        unsigned long long upto[4];
+        upto[0] = fixed40_small(t.x);
+        upto[1] = upto[0] + fixed40_small(t.y);
+        upto[2] = upto[1] + fixed40_small(t.z);
+        upto[3] = upto[2] + fixed40_small(t.w);
+        const unsigned long long tot = wave_sum_u64(upto[3]);
+        if (T >= run + tot) {                                // (the same in every lane)
+            run += tot;
+            continue;
+        }
+        unsigned long long incl = upto[3];                   // these 256 tokens: the lanes in order
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long up = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += up;
+        }
+        const unsigned long long cum = run + incl - upto[3];
+        if (T >= cum && T < cum + upto[3]) {                 // exactly one lane: the first position whose running sum passes T
+            const int c = T < cum + upto[0] ? 0 : T < cum + upto[1] ? 1 : T < cum + upto[2] ? 2 : 3;
+            *out = min(V - 1, vbase + 256 * j + c);
+        }
+        break;
+    }
+}
+
+// A row of up to 32 * ACC_THREADS values in the registers of a workgroup: wave w holds 256 * ng consecutive tokens, lane l of it
+// the 4-token groups at 256 j + 4 l, so every load is a contiguous kilobyte per wave and all of them are in flight together.
+#define ACC_NG 8
+__device__ __forceinline__ void load_row(float (&val)[4 * ACC_NG], const float *__restrict__ row, int vbase, int ng, int V, float pad) {
+#pragma unroll
+    for (int j = 0; j < ACC_NG; j++) {
+        const int v = vbase + 256 * j;
+        float4 t = make_float4(pad, pad, pad, pad);
+        if (j < ng && v < V) t = *reinterpret_cast<const float4 *>(row + v);
+        val[4 * j] = t.x, val[4 * j + 1] = t.y, val[4 * j + 2] = t.z, val[4 * j + 3] = t.w;
+    }
+}
+__device__ __forceinline__ bool row_fits(const float *row, int V) {
+    return V % 4 == 0 && V <= 4 * ACC_NG * ACC_THREADS && (uintptr_t)row % 16 == 0;
+}
+__device__ int row_argmax(const float (&val)[4 * ACC_NG], int vbase, ArgMax *red) {
+    float bv = -INFINITY;
+    int bi = -1;
+#pragma unroll
+    for (int i = 0; i < 4 * ACC_NG; i++)                     // (the padding is NaN, which never wins; a row of -inf gives its first token)
+        if (val[i] > bv || (bi < 0 && val[i] == bv)) bv = val[i], bi = i;
+    ArgMax best = {bv, bi < 0 ? 0x7FFFFFFF : vbase + 256 * (bi >> 2) + (bi & 3)};
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        ArgMax other = {__shfl_xor(best.v, o, 64), __shfl_xor(best.i, o, 64)};
+        best = better(best, other);
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
+    __syncthreads();
+    ArgMax t = red[threadIdx.x & (ACC_THREADS / 64 - 1)];
+#pragma unroll
+    for (int o = ACC_THREADS / 128; o > 0; o >>= 1) {
+        ArgMax other = {__shfl_xor(t.v, o, 64), __shfl_xor(t.i, o, 64)};
+        t = better(t, other);
+    }
+    return t.i == 0x7FFFFFFF ? 0 : t.i;
+}
+
 // The review of one sequence by one workgroup (every thread calls it; the result is valid in every thread).
 // pb: reviewer rows [k+1][V]; qb: draft rows [k][V] or null; q_onehot: [k] flags or null; db: drafts [k];
 // ua: [k] uniforms of the acceptance tests; us: the uniform of the draw.
 struct AcceptShared {
     ArgMax red_am[ACC_THREADS / 64];
     unsigned long long wave_tot[ACC_THREADS / 64];
-    int s_n, s_tok;
+    int s_n, s_tok, s_large;
+    float4 own[ACC_NG * 64];
 };
 __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__restrict__ pb, const float *__restrict__ qb,
                                             const uint8_t *__restrict__ q_onehot, const int32_t *__restrict__ db,
@@ -144,8 +229,21 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
                                             int32_t mode, int &n_out, int &tok_out) {
     if (mode == CSD_MODE_GREEDY) {
         int n = 0, am = 0;
+        const bool fits = row_fits(pb, V);
+        const int ng = (V + 256 * (ACC_THREADS / 64) - 1) / (256 * (ACC_THREADS / 64));
+        int vbase = (threadIdx.x >> 6) * 256 * ng + 4 * (threadIdx.x & 63);
+        asm volatile("" : "+v"(vbase));                      // (in a loop over reviews the offsets made from it are not kept in registers)
+        float val[4 * ACC_NG], next[4 * ACC_NG];             // a row, and the one behind it, which is read while the first is compared
+        if (fits) load_row(next, pb, vbase, ng, V, NAN);
         for (; n <= k; n++) {
-            am = block_argmax(pb + (size_t)n * V, V, S.red_am);
+            if (fits) {
+#pragma unroll
+                for (int i = 0; i < 4 * ACC_NG; i++) val[i] = next[i];
+                if (n < k) load_row(next, pb + (size_t)(n + 1) * V, vbase, ng, V, NAN);
+                am = row_argmax(val, vbase, S.red_am);
+            } else {
+                am = block_argmax(pb + (size_t)n * V, V, S.red_am);
+            }
             if (n == k) break;
             const int x = db[n];
             bool ok = (x == am);
@@ -183,6 +281,7 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
         if (threadIdx.x == 0) {
             S.s_n = n;
             S.s_tok = -1;
+            S.s_large = 0;
         }
     }
     __syncthreads();
@@ -196,6 +295,61 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
     if (residual && qb && !(q_onehot && q_onehot[n])) qrow = qb + (size_t)n * V;
     const bool vec = ((uintptr_t)prow % 16 == 0) && (!qrow || (uintptr_t)qrow % 16 == 0);
 
+    // The weights in registers: the row is read once, all loads in flight together, and the draw looks at what the threads hold.
+    // The general way below takes what is rare: an all-zero residual, and weights above 256 (no distribution under any lenience; NaN),
+    // whose sums may wrap.
+    if (row_fits(prow, V) && vec) {
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = ACC_THREADS / 64;
+        const int ng = (V + 256 * nw - 1) / (256 * nw);
+        int vbase = w * 256 * ng + 4 * lane;
+        asm volatile("" : "+v"(vbase));
+        float val[4 * ACC_NG], qv[4 * ACC_NG];
+        load_row(val, prow, vbase, ng, V, 0.f);
+        if (qrow) load_row(qv, qrow, vbase, ng, V, 0.f);
+        unsigned long long mine = 0ull;
+        uint32_t sl = 0;
+        bool large = false;
+#pragma unroll
+        for (int j = 0; j < ACC_NG; j++) {
+            uint32_t sh = 0;
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const int i = 4 * j + c;
+                if (residual) {
+                    const float df = __fsub_rn(__fmul_rn(lenience, val[i]), qrow ? qv[i] : (vbase + 256 * j + c == x ? 1.0f : 0.0f));
+                    val[i] = df > 0.0f ? df : 0.0f;
+                }
+                large |= !(val[i] <= 256.0f);
+                uint32_t h, l;
+                fixed40_parts(val[i], h, l);
+                sh += h, sl += l;
+            }
+            mine += sh;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        mine = (mine << 20) + sl;
+        const unsigned long long wave_total = wave_sum_u64(mine);
+        if (large) S.s_large = 1;
+        if (lane == 0) S.wave_tot[w] = wave_total;
+        __syncthreads();
+        unsigned long long Z = 0ull, before = 0ull;
+        for (int i = 0; i < nw; i++) {
+            if (i == w) before = Z;
+            Z += S.wave_tot[i];
+        }
+        if (!S.s_large && (Z != 0ull || !residual)) {
+            if (Z != 0ull) {                                 // else not a distribution: the token stays -1
+                const unsigned long long u24 = fixed40(us) >> 16;
+                const unsigned long long hi = __umul64hi(u24, Z), lo = u24 * Z;
+                const unsigned long long T = (hi << 40) | (lo >> 24);
+                if (T >= before && T < before + wave_total) wave_draw<ACC_NG>(val, S.own, T, before, vbase, V, &S.s_tok);   // exactly one wave
+            }
+            __syncthreads();
+            n_out = n;
+            tok_out = S.s_tok;
+            return;
+        }
+    }
     // thread t owns tokens [v0, v1), a whole number of 4-token groups
     const int chunk = ((V + ACC_THREADS - 1) / ACC_THREADS + 3) / 4 * 4;
     const int v0 = min(V, (int)threadIdx.x * chunk), v1 = min(V, v0 + chunk);
@@ -214,6 +368,7 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
         if (T >= excl && T < excl + mine) {                  // exactly one thread owns T
             unsigned long long cum = excl;
             int tok = v1 - 1;
+#pragma unroll 1
             for (int v = v0; v < v1; v++) {
                 cum += fixed40(weight_at(prow, qrow, x, lenience, residual, v));
                 if (cum > T) { tok = v; break; }
@@ -341,11 +496,6 @@ int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int
 // bound by, padding included (V = 512: 16.8 us with 64 values, 6.5 with 4).
 #define RR_THREADS 512
 #define RR_PER_MAX 64
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 template <int RR_PER>
 __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
     const float *__restrict__ logits, float *__restrict__ probs, unsigned long long *__restrict__ recs,
@@ -358,6 +508,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
     __shared__ unsigned long long red64[RR_THREADS / 64];
     __shared__ ArgMax red_am[RR_THREADS / 64];
     __shared__ int s_tok;
+    __shared__ float4 s_own[NG * 64];                            // the values of the wave that draws
     __shared__ unsigned s_old;
     const int row = blockIdx.x, b = blockIdx.y;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -519,39 +670,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 const unsigned long long hi = __umul64hi(u24, Z), lo = u24 * Z;
                 const unsigned long long T = (hi << 40) | (lo >> 24);
                 if (T >= before && T < before + wave_total) {          // exactly one wave owns T
-                    unsigned long long run = before;
-                    bool found = false;
-#pragma unroll
-                    for (int j = 0; j < NG; j++) {
-                        if (found) continue;                 // (the same in every lane)
-                        unsigned long long gj = 0ull;
-#pragma unroll
-                        for (int c = 0; c < 4; c++) gj += fixed40_small(val[4 * j + c]);
-                        const unsigned long long tot = wave_sum_u64(gj);
-                        if (T >= run + tot) {
-                            run += tot;
-                            continue;
-                        }
-                        found = true;                        // these 256 tokens: the lanes in order
-                        unsigned long long incl = gj;
-#pragma unroll
-                        for (int o = 1; o < 64; o <<= 1) {
-                            const unsigned long long up = __shfl_up(incl, o, 64);
-                            if (lane >= o) incl += up;
-                        }
-                        unsigned long long cum = run + incl - gj;
-                        if (T >= cum && T < cum + gj) {      // exactly one lane
-                            int t = 3;
-#pragma unroll
-                            for (int c = 2; c >= 0; c--) {   // the first position whose running sum passes T
-                                unsigned long long upto = cum;
-#pragma unroll
-                                for (int cc = 0; cc <= c; cc++) upto += fixed40_small(val[4 * j + cc]);
-                                if (upto > T) t = c;
-                            }
-                            s_tok = min(V - 1, vbase + 256 * j + t);
-                        }
-                    }
+                    wave_draw<NG>(val, s_own, T, before, vbase, V, &s_tok);
                 }
             }
             __syncthreads();
@@ -653,10 +772,11 @@ extern "C" int32_t csd_accept(const float *p, const float *q, const uint8_t *q_o
 // draw from the row with the walk's next uniform, or its arg-max), and if a child of the row carries that token
 // keep the child and go on from it; otherwise the token is what the review emits.  One workgroup per sequence; a
 // walk step is the draw of a plain review with no drafts.  Rows only have children below them, so the walk ends.
+template <int mode>
 __global__ __launch_bounds__(ACC_THREADS) void k_tree_accept(
     const float *__restrict__ p, const int32_t *__restrict__ tokens, const int32_t *__restrict__ parent,
-    const float *__restrict__ u, int32_t m, int32_t V, int32_t mode, int32_t *__restrict__ n_accepted,
-    int32_t *__restrict__ path, int32_t *__restrict__ next_token) {
+    const float *__restrict__ u, int32_t m, int32_t V, int32_t *__restrict__ n_accepted, int32_t *__restrict__ path,
+    int32_t *__restrict__ next_token) {
     __shared__ AcceptShared S;
     __shared__ int s_child;
     const int b = blockIdx.x;
@@ -693,8 +813,8 @@ extern "C" int32_t csd_tree_accept(const float *p, const int32_t *tokens, const 
     if (mode == CSD_MODE_SAMPLE && !u) return CSD_ENULL;
     if (B < 0 || m < 1 || V < 1) return CSD_EINVAL;
     if (B == 0) return CSD_OK;
-    hipLaunchKernelGGL(k_tree_accept, dim3(B), dim3(ACC_THREADS), 0, (hipStream_t)stream, p, tokens, parent, u, m, V, mode,
-                       n_accepted, path, next_token);
+    hipLaunchKernelGGL(mode == CSD_MODE_SAMPLE ? k_tree_accept<CSD_MODE_SAMPLE> : k_tree_accept<CSD_MODE_GREEDY>, dim3(B),
+                       dim3(ACC_THREADS), 0, (hipStream_t)stream, p, tokens, parent, u, m, V, n_accepted, path, next_token);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
@@ -792,7 +912,13 @@ __global__ __launch_bounds__(ACC_THREADS) void k_review_commit(const ReviewArgs 
     if (A.out_q_tab && A.mode == CSD_MODE_SAMPLE) {
         float *dst = A.out_q_tab + ((size_t)b * A.out_stride + pf - A.out_base[b]) * V;
         const size_t total = (size_t)(n + 1) * V;
-        for (size_t i = threadIdx.x; i < total; i += blockDim.x) dst[i] = pb[i];
+        if (V % 4 == 0 && (uintptr_t)dst % 16 == 0 && (uintptr_t)pb % 16 == 0) {
+#pragma unroll 8
+            for (size_t i = 4 * (size_t)threadIdx.x; i < total; i += 4 * ACC_THREADS)
+                *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(pb + i);
+        } else {
+            for (size_t i = threadIdx.x; i < total; i += blockDim.x) dst[i] = pb[i];
+        }
     }
 }
 
