@@ -426,7 +426,9 @@ __device__ __forceinline__ float recip_of_total(unsigned long long total) {
 
 // one workgroup per row.  Each thread keeps its SM_PER elements in registers between the three steps (rows
 // longer than SM_THREADS * SM_PER take the generic loop).
-__global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, float *probs, int32_t V, float inv_t) {
+__global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, float *probs, int32_t V, float inv_t,
+                                                        const int32_t *__restrict__ live, int32_t m) {
+    if (live && (int)blockIdx.x % m >= live[blockIdx.x / m]) return;    // a row that is not needed
     __shared__ float red[SM_THREADS / 64];
     __shared__ unsigned long long red64[SM_THREADS / 64];
     const float *x = logits + (size_t)blockIdx.x * V;
@@ -471,9 +473,9 @@ __global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, flo
 }
 
 int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int32_t V, float temperature,
-                            hipStream_t st) {
+                            hipStream_t st, const int32_t *live, int32_t m) {
     if (rows <= 0) return CSD_OK;
-    hipLaunchKernelGGL(k_softmax, dim3((unsigned)rows), dim3(SM_THREADS), 0, st, logits, probs, V, 1.0f / temperature);
+    hipLaunchKernelGGL(k_softmax, dim3((unsigned)rows), dim3(SM_THREADS), 0, st, logits, probs, V, 1.0f / temperature, live, m);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
@@ -834,7 +836,7 @@ extern "C" int32_t csd_tree_accept(const float *p, const int32_t *tokens, const 
 __global__ void k_gather_block(const int32_t *__restrict__ ctx, int32_t ctx_stride, const int32_t *__restrict__ ctx_len,
                                const int32_t *__restrict__ cache_len, const int32_t *__restrict__ prefix_len, int32_t m_max,
                                const int32_t *__restrict__ q_base, int32_t q_stride, const int32_t *__restrict__ out_base,
-                               int32_t out_stride, int32_t *__restrict__ block, int32_t *__restrict__ status) {
+                               int32_t out_stride, int32_t *__restrict__ block, int32_t *__restrict__ status, int32_t *__restrict__ live) {
     const int b = blockIdx.x;
     const int n = ctx_len[b], cl = cache_len[b], pf = prefix_len[b];
     const int rows = n - cl;
@@ -845,7 +847,10 @@ __global__ void k_gather_block(const int32_t *__restrict__ ctx, int32_t ctx_stri
     else if (out_base && (pf - out_base[b] < 0 || n + 1 - out_base[b] > out_stride)) st = 2;
     for (int i = threadIdx.x; i < m_max; i += blockDim.x)
         block[(size_t)b * m_max + i] = (st == 0 && i < rows) ? ctx[(size_t)b * ctx_stride + cl + i] : 0;
-    if (threadIdx.x == 0) status[b] = st;
+    if (threadIdx.x == 0) {
+        status[b] = st;
+        live[b] = st == 0 ? rows : 0;
+    }
 }
 
 struct ReviewArgs {
@@ -943,14 +948,17 @@ extern "C" int32_t csd_review_ctx(csd_model *mod, void *kv, const csd_review *r,
     int32_t *block = mod->review_block;
     hipLaunchKernelGGL(k_gather_block, dim3(B), dim3(64), 0, st, r->ctx, r->ctx_stride, r->ctx_len, r->cache_len, r->prefix_len, m_max,
                        (r->q_tab || r->q_onehot_tab) ? r->q_base : nullptr, r->q_stride,
-                       (r->out_q_tab || r->out_onehot_tab) ? r->out_base : nullptr, r->out_stride, block, r->status);
+                       (r->out_q_tab || r->out_onehot_tab) ? r->out_base : nullptr, r->out_stride, block, r->status, mod->review_live);
     CSD_LAUNCH_CHECK();
     const float *rows = r->ext_rows;
     if (!rows) {
         int32_t rc;
         float *lg = mod->probs;                               // logits, then probabilities in place
-        if ((rc = csd_forward_enqueue(mod, kv, block, r->cache_len, B, m_max, lg, st)) != CSD_OK) return rc;
-        if (need_probs && (rc = csd_softmax_enqueue(lg, lg, (int64_t)B * m_max, V, temperature, st)) != CSD_OK) return rc;
+        mod->live = mod->review_live;
+        rc = csd_forward_enqueue(mod, kv, block, r->cache_len, B, m_max, lg, st);
+        mod->live = nullptr;
+        if (rc != CSD_OK) return rc;
+        if (need_probs && (rc = csd_softmax_enqueue(lg, lg, (int64_t)B * m_max, V, temperature, st, mod->review_live, m_max)) != CSD_OK) return rc;
         rows = lg;
     }
     ReviewArgs A;

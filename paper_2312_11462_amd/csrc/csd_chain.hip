@@ -205,12 +205,14 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
     }
 }
 
-template <int NT, int R, int EPI, int MT>
+// LIVE: a review of one sequence that the device may have skipped (a separate form: the look costs a plain step 0.7 %)
+template <int NT, int R, int EPI, int MT, bool LIVE>
 __global__ __launch_bounds__(CH_THREADS) void kc_gemm(const ChainGemm P) {
     extern __shared__ __align__(16) char ch_smem[];
     const GemmShare S = gemm_share<EPI>(P, blockIdx.x, gridDim.x, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
     u32x4 Wr[R][NT];
     gemm_prefetch<NT, R>(Wr, P, S);
+    if (LIVE && P.live[0] == 0) return;                      // (the first weights are on their way meanwhile)
     gemm_run<NT, R, EPI, MT>(Wr, P, S, ch_smem);
 }
 
@@ -238,6 +240,8 @@ struct AttnArgs {
     int fixed_nk;             // > 0 (arch 1 cross-attention): every row sees keys [0, fixed_nk), whatever cache_len says
     bf16_t *out;              // merged rows: the O projection's input planes, fragment order
     int out_plane_bytes, mtp;
+    const int32_t *live;      // as in ChainGemm: rows of a sequence past these are neither attended nor written (from then on they and their
+                              // K/V rows hold anything, and no other row looks at them)
 };
 template <int DH>
 struct AttnLds {
@@ -250,12 +254,13 @@ struct AttnLds {
 
 // One chunk of one (sequence, head) by a group of four waves (gtid = thread index in the group, 0 .. 255).
 // Holds five workgroup barriers whatever `have` says, so groups with and without an item stay in step.
-template <int DH>
+template <int DH, bool LIVE>
 __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, bool have, int c, int hh, int b, int gtid) {
     constexpr int PS = DH + 4;                               // floats per partial row: DH outputs, max, sum, pad
     constexpr int DT = DH / 16;
     const KvGeom &geo = A.geo;
-    const int m = A.m;
+    const int m = LIVE ? min(A.m, A.live[b]) : A.m, stride = A.m;
+    if (LIVE && m <= 0) return;                              // a skipped sequence: no workgroup of it arrives
     const int lane = gtid & 63, col = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(gtid >> 6);
     const int hd = geo.H * DH;
@@ -269,7 +274,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
     u32x4 qf[DH / 32][2], kf[2][DH / 32], vf[DT];
 #pragma unroll
     for (int s = 0; s < DH / 32; s++) {
-        const int qo = col < m ? (int)(((size_t)(b * m + col) * hd + hh * DH + s * 32 + 8 * g) * 2) : CH_OOB;
+        const int qo = col < m ? (int)(((size_t)(b * stride + col) * hd + hh * DH + s * 32 + 8 * g) * 2) : CH_OOB;
         qf[s][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rqb, qo, 0, 0));
         qf[s][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rqb, qo, A.q_plane * 2, 0));
     }
@@ -291,7 +296,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
     const int nch = (nk + CA_KEYS - 1) / CA_KEYS;
     const bool active = have && c < nch;                     // a chunk past the end is not counted
     const int qpos = t + col;                                // block row `col` sees cache rows 0 .. qpos
-    const unsigned long long anc_row = (A.anc && have && col < m) ? A.anc[b * m + col] : 0ull;
+    const unsigned long long anc_row = (A.anc && have && col < m) ? A.anc[b * stride + col] : 0ull;
     float bias[8];                                           // requested ahead of the scores they are added to
 #pragma unroll
     for (int j = 0; j < 8; j++) {
@@ -453,7 +458,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
                 const int r = r0 + rr * RG;
                 if (r >= m) break;
                 const bf16_t hi = f32_to_bf16(num[rr]);
-                const int off = (int)(act_tiled_idx(b * m + r, hh * DH + x, A.mtp) * 2);
+                const int off = (int)(act_tiled_idx(b * stride + r, hh * DH + x, A.mtp) * 2);
                 __builtin_amdgcn_raw_buffer_store_b16(hi, ro, off, 0, CH_SC1);
                 __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(num[rr] - bf16_to_f32(hi)), ro, off + A.out_plane_bytes, 0, CH_SC1);
             }
@@ -469,12 +474,12 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
 // transposed), the four softmax states are merged in LDS, and the workgroup writes one partial state per
 // chunk.  The last workgroup of a (sequence, head) to finish (an arrival counter) merges the chunks and
 // writes the rows as the O projection's input; the counter is back at zero when the kernel ends.
-template <int DH>
+template <int DH, bool LIVE>
 __global__ __launch_bounds__(256) void kc_attn(const AttnArgs A) {
     __shared__ __align__(16) AttnLds<DH> L;
     // Grid (head, sequence, chunk): the last chunk of a head holds little besides the block's own rows, and with the chunk
     // index slowest those short workgroups are dispatched after every long one has a compute unit of its own.
-    attn_item<DH>(A, L, true, blockIdx.z, blockIdx.x, blockIdx.y, threadIdx.x);
+    attn_item<DH, LIVE>(A, L, true, blockIdx.z, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
 // The same for caches short enough that one workgroup of sixteen waves reads all of a (sequence, head): a 32-key tile per
@@ -490,13 +495,15 @@ struct AttnOneLds {
     f32x4 o[NW][DH / 16][64];
     float m[NW][16], l[NW][16], w[NW][16];
 };
-template <int DH, int NW, bool BIAS>
+template <int DH, int NW, bool BIAS, bool LIVE>
 __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
     extern __shared__ __align__(16) char one_smem[];
     AttnOneLds<DH, NW> &L = *reinterpret_cast<AttnOneLds<DH, NW> *>(one_smem);
     constexpr int DT = DH / 16;
     const KvGeom &geo = A.geo;
-    const int m = A.m, hh = blockIdx.x, b = blockIdx.y;
+    const int hh = blockIdx.x, b = blockIdx.y;
+    const int m = LIVE ? min(A.m, A.live[b]) : A.m, stride = A.m;
+    if (LIVE && m <= 0) return;                              // a skipped sequence
     const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int hd = geo.H * DH;
@@ -527,7 +534,7 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
     u32x4 qf[DH / 32][2];
 #pragma unroll
     for (int s = 0; s < DH / 32; s++) {
-        const int qo = col < m ? (int)(((size_t)(b * m + col) * hd + hh * DH + s * 32 + 8 * g) * 2) : CH_OOB;
+        const int qo = col < m ? (int)(((size_t)(b * stride + col) * hd + hh * DH + s * 32 + 8 * g) * 2) : CH_OOB;
         qf[s][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rqb, qo, 0, 0));
         qf[s][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rqb, qo, A.q_plane * 2, 0));
     }
@@ -536,7 +543,7 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
     const int nk = max(0, min(causal ? t + m : A.fixed_nk, geo.seq_pad));   // cache rows in play for this block
     const int n_tiles = (nk + 31) / 32;
     const int qpos = t + col;                                // block row `col` sees cache rows 0 .. qpos
-    const unsigned long long anc_row = (A.anc && col < m) ? A.anc[b * m + col] : 0ull;
+    const unsigned long long anc_row = (A.anc && col < m) ? A.anc[b * stride + col] : 0ull;
     float mrun = -INFINITY, lrun = 0.f;
     f32x4 oacc[DT];
 #pragma unroll
@@ -641,7 +648,7 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const AttnArgs A) {
         }
         if (den == 0.f) den = 1.f;                           // (no key seen: the sums are 0)
         const float v[4] = {o[0] / den, o[1] / den, o[2] / den, o[3] / den};
-        store_planes4(A.out, A.out_plane_bytes, A.mtp, b * m + col, hh * DH + dt * 16 + 4 * g, v);
+        store_planes4(A.out, A.out_plane_bytes, A.mtp, b * stride + col, hh * DH + dt * 16 + 4 * g, v);
     }
 }
 
@@ -704,21 +711,22 @@ static bool attn_one_fits(const csd_model *mod, int B, int keys_pad) {
 }
 template <int DH, bool BIAS>
 static void attn_one_launch(const AttnArgs &A, int H, int B, hipStream_t st) {
-    hipLaunchKernelGGL((kc_attn_one<DH, CA_ONE_NW, BIAS>), dim3(H, B), dim3(CA_ONE_NW * 64), sizeof(AttnOneLds<DH, CA_ONE_NW>), st, A);
+    hipLaunchKernelGGL((A.live ? kc_attn_one<DH, CA_ONE_NW, BIAS, true> : kc_attn_one<DH, CA_ONE_NW, BIAS, false>), dim3(H, B), dim3(CA_ONE_NW * 64),
+                       sizeof(AttnOneLds<DH, CA_ONE_NW>), st, A);
 }
 static int32_t attn_launch_small(const csd_model *mod, const AttnArgs &A, int keys_pad, int B, hipStream_t st) {
     const int H = mod->cfg.n_heads;
     const dim3 grid(H, B, (keys_pad + CA_KEYS - 1) / CA_KEYS);       // chunk index slowest: see kc_attn
     if (mod->cfg.head_dim == 128) {
         if (!attn_one_fits(mod, B, keys_pad))
-            hipLaunchKernelGGL((kc_attn<128>), grid, dim3(256), 0, st, A);
+            hipLaunchKernelGGL((A.live ? kc_attn<128, true> : kc_attn<128, false>), grid, dim3(256), 0, st, A);
         else if (A.bias_hd)
             attn_one_launch<128, true>(A, H, B, st);
         else
             attn_one_launch<128, false>(A, H, B, st);
     } else {
         if (!attn_one_fits(mod, B, keys_pad))
-            hipLaunchKernelGGL((kc_attn<64>), grid, dim3(256), 0, st, A);
+            hipLaunchKernelGGL((A.live ? kc_attn<64, true> : kc_attn<64, false>), grid, dim3(256), 0, st, A);
         else if (A.bias_hd)
             attn_one_launch<64, true>(A, H, B, st);
         else
@@ -732,8 +740,12 @@ static int32_t attn_launch_small(const csd_model *mod, const AttnArgs &A, int ke
 
 template <int NT, int R, int EPI, int MT>
 static hipError_t chain_allow_lds() {
-    return hipFuncSetAttribute((const void *)kc_gemm<NT, R, EPI, MT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               CH_WAVES * NT * 64 * 16 + CH_WAVES * MT * 16 * 4);
+    const int lds = CH_WAVES * NT * 64 * 16 + CH_WAVES * MT * 16 * 4;
+    if constexpr (MT == 1) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kc_gemm<NT, R, EPI, MT, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    return hipFuncSetAttribute((const void *)kc_gemm<NT, R, EPI, MT, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
 #ifndef CH_R1
@@ -761,7 +773,9 @@ int32_t csd_chain_setup() {
     CH_FOR_GU_TALL(CH_ALLOW, 2)
 #undef CH_ALLOW
 #define CA_ALLOW(DH, BIAS)                                                                                                            \
-    CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+    CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                (int)sizeof(AttnOneLds<DH, CA_ONE_NW>)));                                                             \
+    CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS, true>, hipFuncAttributeMaxDynamicSharedMemorySize,      \
                                 (int)sizeof(AttnOneLds<DH, CA_ONE_NW>)));
     CA_ALLOW(128, false)
     CA_ALLOW(128, true)
@@ -775,8 +789,11 @@ template <int EPI, int MT>
 static int32_t chain_launch_mt(ChainGemm &P, int G, int per, hipStream_t st) {
 #define CH_LAUNCH(NT, R, E, MT_)                                                                                   \
     if (per <= NT) {                                                                                              \
-        hipLaunchKernelGGL((kc_gemm<NT, R, E, MT_>), dim3(G), dim3(CH_THREADS),                                    \
-                           CH_WAVES * NT * 64 * 16 + CH_WAVES * MT_ * 16 * 4, st, P);                              \
+        const int lds = CH_WAVES * NT * 64 * 16 + CH_WAVES * MT_ * 16 * 4;                                        \
+        if (MT_ == 1 && P.live && P.M == P.m)                                                                     \
+            hipLaunchKernelGGL((kc_gemm<NT, R, E, MT_, MT_ == 1>), dim3(G), dim3(CH_THREADS), lds, st, P);         \
+        else                                                                                                      \
+            hipLaunchKernelGGL((kc_gemm<NT, R, E, MT_, false>), dim3(G), dim3(CH_THREADS), lds, st, P);            \
         return CSD_OK;                                                                                            \
     }
     if constexpr (MT == 1) {
@@ -866,6 +883,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
     base.q = (bf16_t *)mod->qbuf;
     base.q_plane_bytes = (int)(mod->q_plane * 2);
     base.kv = (bf16_t *)kv;
+    base.live = mod->live;
     base.n_ssq = d / 16;
     base.ssq_rows = ssq_rows;
     auto gemm = [&](const GemmW &w, const bf16_t *a, int a_plane_bytes, const float *ssq_in) {
@@ -879,7 +897,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
         return P;
     };
     const AttnArgs attn{(const bf16_t *)mod->qbuf, (int)mod->q_plane, m, cache_len, geo, 0, (const bf16_t *)kv, scale, mod->attn_part,
-                        mod->attn_chunks_max, mod->attn_cnt, mod->tree_call ? mod->tree_anc : nullptr, nullptr, 0, X2, pb_hd, mtp};
+                        mod->attn_chunks_max, mod->attn_cnt, mod->tree_call ? mod->tree_anc : nullptr, nullptr, 0, X2, pb_hd, mtp, mod->live};
     int32_t rc;
     for (int l = 0; l < L; l++) {
         const LayerW &lw = mod->layers[l];

@@ -35,6 +35,7 @@ struct ChainGemm {
     int gelu;                 // EPI_GU: tanh-GELU instead of SiLU
     float *logits;            // EPI_LOGITS [M][V]
     int V;
+    const int32_t *live;      // per sequence of m rows the rows that are needed (csd_review_ctx), or null: all
 };
 
 // A buffer descriptor must sit in scalar registers.  Base addresses here are the same in every lane, but the

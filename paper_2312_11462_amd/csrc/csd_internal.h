@@ -272,6 +272,8 @@ struct csd_model {
     float *rel_bias_hd = nullptr;    // [H][128]: rel_bias[rel_bucket[n]][h]
     float *trace = nullptr;
     int32_t *review_block = nullptr;  // [max_batch][max_block] block tokens gathered by csd_review_ctx
+    int32_t *review_live = nullptr;   // [max_batch] rows of its block that csd_review_ctx needs, 0 for a skipped sequence
+    const int32_t *live = nullptr;    // the forward being enqueued: per sequence the rows that are needed, or null (all)
     // profiling
     bool prof = false;
     std::vector<hipEvent_t> ev;
@@ -343,8 +345,9 @@ int32_t csd_tall_logits(csd_model *mod, const GemmW &w, const bf16_t *a, size_t 
 int32_t csd_tall_cross(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int mtp, int M, int row0, int layer,
                        const KvGeom &geo, void *kv_cross, hipStream_t st);
 // csd_accept.hip
+// live: per sequence of m rows the rows that are needed, or null
 int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int32_t V, float temperature,
-                            hipStream_t st);
+                            hipStream_t st, const int32_t *live = nullptr, int32_t m = 1);
 bool csd_review_rows_fits(const float *logits, const float *probs, const float *q, int32_t V);
 int32_t csd_review_rows_enqueue(const float *logits, float *probs, unsigned long long *recs, unsigned *counters,
                                 float temperature, const float *q, const uint8_t *q_onehot, const int32_t *draft,

@@ -271,3 +271,43 @@ def test_resident_cascade_sampling_matches_the_oracle_driver_token_for_token(K, 
     want = _oracle_steps(olevels, otable, prompt, K, lenience, 0, n_steps, lambda d, kind, pos: float(u[d, kind, pos]))
     assert got == want
     assert len(got) - len(prompt) >= n_steps
+
+
+@pytest.mark.parametrize("B", [1, 2, 3])
+@pytest.mark.parametrize("H,dh,max_seq", [(4, 64, 192), (4, 64, 1088), (2, 128, 192), (2, 128, 1088)])
+def test_review_of_fewer_rows_than_the_call_has_room_for(H, dh, max_seq, B):
+    """csd_review_ctx with room for 16 rows reviews 6, 1 and 4 of them, after a call in which every sequence is skipped and together with a skipped
+    one: what the unused rows and the cache behind the used ones hold (NaN here) reaches nothing, and a plain review of
+    exactly those rows decides the same."""
+    import paper_2312_11462_amd as P
+    shape = I.ModelShape("live", 0, "bf16", 2, 256, H, dh, 512, 1024)
+    w = I.make_weights(shape, 5, device="cuda", std=0.05)
+    gm = P.Model(shape, w, max_batch=B, max_seq=max_seq, max_block=16)
+    ref = P.Model(shape, w, max_batch=B, max_seq=max_seq, max_block=16)
+    gm.kv.view(torch.uint8).fill_(0xFF)
+    t, i32 = 20, dict(dtype=torch.int32, device="cuda")
+    tok = torch.stack([I.token_ids(48, shape.vocab, 5, b) for b in range(B)]).to(torch.int32).cuda()
+    for m in (gm, ref):
+        for pos in (0, 10):
+            m.verify_block(tok[:, pos:pos + 10].contiguous(), torch.full((B,), pos, **i32))
+    cache, length = torch.full((B,), t, **i32), torch.full((B,), t, **i32)
+    ctx, skip = tok.clone(), torch.full((B,), -1, **i32)
+    status, n_acc, nxt = (torch.zeros(B, **i32) for _ in range(3))
+
+    def review(prefix):
+        gm.review_ctx(ctx, length, cache, prefix, 16, status, n_accepted=n_acc, next_token=nxt, mode=1)
+
+    for rows in (6, 1, 4):
+        start = cache.clone()
+        length.copy_(start + rows)
+        review(skip)
+        assert (status == 1).all() and torch.equal(length, start + rows) and torch.equal(cache, start)
+        block = torch.stack([ctx[b, int(start[b]):int(start[b]) + rows] for b in range(B)]).contiguous()
+        n_ref, nxt_ref = ref.verify_accept(block, start, None, None, mode=1)
+        for turn in range(B):                                # all but one sequence skipped, one after the other
+            review(torch.where(torch.arange(B, device="cuda") == turn, start + 1, skip))
+            assert int(status[turn]) == 0 and int(n_acc[turn]) == int(n_ref[turn]) and int(nxt[turn]) == int(nxt_ref[turn])
+            length[turn] = cache[turn] + 1
+        assert torch.equal(cache, start + 1 + n_ref)
+    gm.close()
+    ref.close()
