@@ -247,13 +247,13 @@ template <int DH>
 struct AttnLds {
     f32x4 o[4][DH / 16][64];
     float m[4][16], l[4][16];
-    float mc[CA_MAX_CHUNKS * 16], lc[CA_MAX_CHUNKS * 16], w[CA_MAX_CHUNKS * 16];   // chunk states and weights of the merge
+    float w[4][CA_MAX_CHUNKS * 16];                          // weights of the merge, every wave its own
     unsigned old;
     unsigned pad[3];
 };
 
 // One chunk of one (sequence, head) by a group of four waves (gtid = thread index in the group, 0 .. 255).
-// Holds five workgroup barriers whatever `have` says, so groups with and without an item stay in step.
+// Holds three workgroup barriers whatever `have` says, so groups with and without an item stay in step.
 template <int DH, bool LIVE>
 __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, bool have, int c, int hh, int b, int gtid) {
     constexpr int PS = DH + 4;                               // floats per partial row: DH outputs, max, sum, pad
@@ -404,7 +404,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
     const __amdgpu_buffer_rsrc_t rm = ch_rsrc(pbase, last ? (size_t)A.chunks_max * 16 * PS * 4 : 0);
     // out[r][x] = sum_c weight[c][r] * acc_c[r][x] with weight[c][r] = e^(m_c - m*) / sum_c l_c e^(m_c - m*).  A thread
     // takes feature x of every (256 / DH)-th row; the accumulators of four rows x sixteen chunks are requested
-    // together, and the first such batch before the states, so that the common case is one memory round trip.
+    // together, and the first such batch before the states, so that the common case is one memory round trip.  Every wave makes all
+    // the weights for itself, lane (c % 4, r): no barrier, and up to 16 chunks without a loop over them.
     const int x = gtid % DH;
     constexpr int RG = 256 / DH;
     const int r_first = gtid / DH;
@@ -415,33 +416,40 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
         ac[rr][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(                                  \
                                                   rm, (r_ < m && (C0) + u < nch) ? ((((C0) + u) * 16 + r_) * PS + x) * 4 : CH_OOB, 0, 0)); \
     }
+    float *wgt_c = L.w[wv];
     if (last) {
         CA_LOAD_ACC(r_first, 0)
-        const int r = gtid & 15;
-        for (int cc = gtid >> 4; cc < nch; cc += 16) {
-            const int o = (cc * 16 + r) * PS * 4;
-            L.mc[cc * 16 + r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, DH * 4, 0));
-            L.lc[cc * 16 + r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, (DH + 1) * 4, 0));
+        float mc[4], lc[4], mst = -INFINITY, den = 0.f;
+        auto states = [&](int c0) {                              // chunks c0 .. c0 + 15 of row `col`
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int cc = c0 + 4 * j + g, o = cc < nch ? (cc * 16 + col) * PS * 4 : CH_OOB;
+                mc[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, DH * 4, 0));
+                lc[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, (DH + 1) * 4, 0));
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (c0 + 4 * j + g >= nch) mc[j] = -INFINITY, lc[j] = 0.f;
+        };
+        for (int c0 = (nch - 1) / 16 * 16; c0 >= 0; c0 -= 16) {  // (the first sixteen last: their states stay in registers)
+            states(c0);
+#pragma unroll
+            for (int j = 0; j < 4; j++) mst = fmaxf(mst, mc[j]);
         }
-    }
-    __syncthreads();
-    if (last) {
-        const int r = gtid & 15;
-        float mst = -INFINITY;
-        for (int cc = 0; cc < nch; cc++) mst = fmaxf(mst, L.mc[cc * 16 + r]);
-        float den = 0.f;
-        for (int cc = 0; cc < nch; cc++) {
-            const float mc = L.mc[cc * 16 + r];
-            den += (mc == -INFINITY ? 0.f : expf(mc - mst)) * L.lc[cc * 16 + r];       // chunks in order
+        mst = groups_max(mst);
+        for (int c0 = 0; c0 < nch; c0 += 16) {
+            if (c0 != 0) states(c0);
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const float e = mc[j] == -INFINITY ? 0.f : expf(mc[j] - mst);
+                den += e * lc[j];
+                if (c0 + 4 * j + g < CA_MAX_CHUNKS) wgt_c[(c0 + 4 * j + g) * 16 + col] = e;
+            }
         }
+        den = groups_sum(den);
         const float inv = den > 0.f ? 1.0f / den : 0.f;
-        for (int cc = gtid >> 4; cc < nch; cc += 16) {
-            const float mc = L.mc[cc * 16 + r];
-            L.w[cc * 16 + r] = (mc == -INFINITY ? 0.f : expf(mc - mst)) * inv;
-        }
-    }
-    __syncthreads();
-    if (last) {
+        for (int cc = g; cc < nch; cc += 4) wgt_c[cc * 16 + col] *= inv;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // read by the other lanes
         const __amdgpu_buffer_rsrc_t ro = ch_rsrc(A.out, (size_t)2 * A.out_plane_bytes);
         for (int r0 = r_first; r0 < m; r0 += 4 * RG) {
             float num[4] = {0.f, 0.f, 0.f, 0.f};
@@ -451,7 +459,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
                 for (int rr = 0; rr < 4; rr++)
 #pragma unroll
                     for (int u = 0; u < 16; u++)
-                        if (r0 + rr * RG < m && c0 + u < nch) num[rr] += ac[rr][u] * L.w[(c0 + u) * 16 + r0 + rr * RG];
+                        if (r0 + rr * RG < m && c0 + u < nch) num[rr] += ac[rr][u] * wgt_c[(c0 + u) * 16 + r0 + rr * RG];
             }
 #pragma unroll
             for (int rr = 0; rr < 4; rr++) {
