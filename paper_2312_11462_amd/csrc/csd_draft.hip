@@ -21,23 +21,16 @@ __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v
     return t;
 }
 
-// Each thread scores candidate match ends e = tid, tid+256, ... <= len-2 by comparing
+// The tokens of a sequence go to LDS: every thread compares positions backwards, a chain of dependent reads that cost a trip to L2
+// each where they went to memory (4000 tokens 6.7 us with 256 threads, 5.3 in LDS with 1024).  Longer sequences are read where they are.
+#define DRAFT_LDS 8192
+// As many tokens per thread are requested before the length is known (the row has ctx_stride of them).
+#define DRAFT_EARLY 4
+
+// Each thread scores candidate match ends e = tid, tid + threads, ... <= len - 2 by comparing
 // backwards against the suffix; the key (match length, ~e) makes the block maximum the
 // longest match and, among equals, the left-most end.
-__global__ __launch_bounds__(DRAFT_THREADS) void k_bigram_draft(
-    const int32_t *__restrict__ ctx, const int32_t *__restrict__ ctx_len, int32_t ctx_stride,
-    const int32_t *__restrict__ next_table, int32_t vocab, int32_t k, int32_t max_match,
-    int32_t *__restrict__ out_tokens, int32_t *__restrict__ out_match_len) {
-    __shared__ unsigned long long red[DRAFT_THREADS / 64];
-    const int b = blockIdx.x;
-    const int32_t *s = ctx + (size_t)b * ctx_stride;
-    int len = ctx_len[b];
-    int32_t *out = out_tokens + (size_t)b * k;
-    if (len < 1 || len > ctx_stride) {   // device-side guard: no valid context
-        for (int j = threadIdx.x; j < k; j += blockDim.x) out[j] = -1;
-        if (out_match_len && threadIdx.x == 0) out_match_len[b] = 0;
-        return;
-    }
+__device__ __forceinline__ unsigned long long match_key(const int32_t *s, int len, int32_t max_match) {
     unsigned long long best = 0ull;
     for (int e = threadIdx.x; e <= len - 2; e += blockDim.x) {
         int r = 0;
@@ -47,7 +40,52 @@ __global__ __launch_bounds__(DRAFT_THREADS) void k_bigram_draft(
             best = key > best ? key : best;
         }
     }
-    best = block_max_u64(best, red);
+    return best;
+}
+struct DraftShared {
+    int32_t s[DRAFT_LDS];
+    unsigned long long red[1024 / 64];
+};
+// The longest match of the suffix of s[0 .. len); every thread gets the key (0: none).  early[i] = s[i * threads + tid] where that is inside the row.
+__device__ __forceinline__ unsigned long long draft_match(DraftShared &S, const int32_t *s, const int (&early)[DRAFT_EARLY], int len,
+                                                          int32_t max_match) {
+    unsigned long long best;
+    if (len <= DRAFT_LDS) {                                  // uniform
+#pragma unroll
+        for (int i = 0; i < DRAFT_EARLY; i++) {
+            const int x = i * blockDim.x + threadIdx.x;
+            if (x < len) S.s[x] = early[i];
+        }
+        for (int x = DRAFT_EARLY * blockDim.x + threadIdx.x; x < len; x += blockDim.x) S.s[x] = s[x];
+        __syncthreads();
+        best = match_key(S.s, len, max_match);
+    } else {
+        best = match_key(s, len, max_match);
+    }
+    return block_max_u64(best, S.red);
+}
+__device__ __forceinline__ void draft_early(int (&early)[DRAFT_EARLY], const int32_t *s, int32_t stride) {
+#pragma unroll
+    for (int i = 0; i < DRAFT_EARLY; i++) early[i] = s[min(i * (int)blockDim.x + (int)threadIdx.x, stride - 1)];
+}
+
+__global__ __launch_bounds__(1024) void k_bigram_draft(
+    const int32_t *__restrict__ ctx, const int32_t *__restrict__ ctx_len, int32_t ctx_stride,
+    const int32_t *__restrict__ next_table, int32_t vocab, int32_t k, int32_t max_match,
+    int32_t *__restrict__ out_tokens, int32_t *__restrict__ out_match_len) {
+    __shared__ DraftShared S;
+    const int b = blockIdx.x;
+    const int32_t *s = ctx + (size_t)b * ctx_stride;
+    int early[DRAFT_EARLY];
+    draft_early(early, s, ctx_stride);
+    int len = ctx_len[b];
+    int32_t *out = out_tokens + (size_t)b * k;
+    if (len < 1 || len > ctx_stride) {   // device-side guard: no valid context
+        for (int j = threadIdx.x; j < k; j += blockDim.x) out[j] = -1;
+        if (out_match_len && threadIdx.x == 0) out_match_len[b] = 0;
+        return;
+    }
+    const unsigned long long best = draft_match(S, s, early, len, max_match);
     const int mlen = (int)(best >> 32);
     if (out_match_len && threadIdx.x == 0) out_match_len[b] = mlen;
     if (mlen == 0) {
@@ -67,27 +105,20 @@ __global__ __launch_bounds__(DRAFT_THREADS) void k_bigram_draft(
 
 // k_bigram_draft that appends its drafts to the context itself (device-resident cascade control): sequences whose
 // drafts in flight already number `need` or more (counted from start_len) are left alone.
-__global__ __launch_bounds__(DRAFT_THREADS) void k_bigram_draft_append(
-    int32_t *__restrict__ ctx, int32_t ctx_stride, int32_t *__restrict__ ctx_len, const int32_t *__restrict__ next_table,
+__global__ __launch_bounds__(1024) void k_bigram_draft_append(
+    int32_t *ctx, int32_t ctx_stride, int32_t *__restrict__ ctx_len, const int32_t *__restrict__ next_table,
     int32_t vocab, int32_t k, int32_t max_match, const int32_t *__restrict__ gate, uint8_t *__restrict__ q_onehot_tab,
     const int32_t *__restrict__ q_base, int32_t q_stride) {
-    __shared__ unsigned long long red[DRAFT_THREADS / 64];
+    __shared__ DraftShared S;
     const int b = blockIdx.x;
     int32_t *s = ctx + (size_t)b * ctx_stride;
+    int early[DRAFT_EARLY];
+    draft_early(early, s, ctx_stride);
     const int len = ctx_len[b];
     bool active = len >= 1 && len + k < ctx_stride && (!gate || gate[b] >= 0);
     if (active && q_onehot_tab && (len - q_base[b] < 0 || len + k - q_base[b] > q_stride)) active = false;
     if (!active) return;                                     // uniform over the workgroup
-    unsigned long long best = 0ull;
-    for (int e = threadIdx.x; e <= len - 2; e += blockDim.x) {
-        int r = 0;
-        while (r <= e && (max_match <= 0 || r < max_match) && s[e - r] == s[len - 1 - r]) r++;
-        if (r > 0) {
-            unsigned long long key = ((unsigned long long)(uint32_t)r << 32) | (uint32_t)(0xFFFFFFFFu - (uint32_t)e);
-            best = key > best ? key : best;
-        }
-    }
-    best = block_max_u64(best, red);                         // (its barriers: every thread has read the context by now)
+    const unsigned long long best = draft_match(S, s, early, len, max_match);   // (its barriers: every thread has read the context by now)
     const int mlen = (int)(best >> 32);
     int32_t *out = s + len;
     if (mlen == 0) {
@@ -107,6 +138,8 @@ __global__ __launch_bounds__(DRAFT_THREADS) void k_bigram_draft_append(
         for (int j = threadIdx.x; j < k; j += blockDim.x) q_onehot_tab[(size_t)b * q_stride + len + j - q_base[b]] = 1;
     if (threadIdx.x == 0) ctx_len[b] = len + k;
 }
+// threads of a workgroup for rows of `stride` tokens: a token each up to 1024
+static int draft_threads(int stride) { return stride <= 256 ? 256 : stride <= 512 ? 512 : 1024; }
 
 // gate[b] = ctx_len[b] when sequence b still needs tokens in the loop that started at loop_start[b] (fewer than `need`
 // exist) and the enclosing step is itself active (parent_gate null or >= 0); else -1.  A step gated with this value
@@ -170,15 +203,19 @@ __global__ __launch_bounds__(DRAFT_THREADS) void k_maxgram_enc(
 // Bigram fit, one workgroup, everything in LDS.  A hash table over positions gives every pair (s[i], s[i+1]) one
 // representative position, where its occurrences are counted and the last one is noted: key = count << 13 | last
 // position.  A second pass of the same table over the first tokens gives the pair with the largest key per token, which
-// is the fitted successor.  Linear probing over 1.5 slots per position, so a probe always finds its key or a free slot.
-// Latency of a few dependent LDS operations per position bounds it, eight positions per thread at most.  Comparing every
-// pair with every other one (the form before) took 4.32 ms for 4000 tokens; this takes 14 us (4.33 ms
-// and 20.8 us with the draft that follows).
+// is the fitted successor.  Linear probing over at least 1.5 slots per position, so a probe always finds its key or a free slot;
+// three where they fit, since a wave waits for its longest probe: 4000 tokens 15.6 us with 1.5, 9.4 with three.
+// Latency of a few dependent LDS operations per position bounds it, eight positions per thread at most (all probes of a
+// thread in flight together, turn by turn: 30 us, the turns cost more than the latency they hide).
 #define FIT_MAX 8192
 #define FIT_EMPTY (-1)
+#define FIT_SLOTS ((uint32_t)FIT_MAX * 3 / 2)
 struct FitShared {
     int32_t s[FIT_MAX];
-    int32_t slot[FIT_MAX * 3 / 2];      // representative position, or FIT_EMPTY
+    union {                             // representative position, or FIT_EMPTY
+        int32_t slot[FIT_SLOTS];
+        int4 slot4[FIT_SLOTS / 4];
+    };
     uint32_t key[FIT_MAX];              // of the pair whose representative is this position
     uint32_t best[FIT_MAX];             // largest key among the pairs whose first token has this representative
 };
@@ -203,12 +240,12 @@ __global__ __launch_bounds__(FIT_THREADS) void k_bigram_fit(const int32_t *__res
                                                             int32_t *__restrict__ next_table) {
     __shared__ FitShared S;
     constexpr int PER = FIT_MAX / FIT_THREADS;
-    const uint32_t n_slots = (uint32_t)n + (uint32_t)n / 2;
+    const uint32_t n_slots = min(3u * (uint32_t)n + 1u, FIT_SLOTS);
     for (int i = threadIdx.x; i < n; i += FIT_THREADS) {
         S.s[i] = s[i];
         S.key[i] = S.best[i] = 0u;
     }
-    for (uint32_t i = threadIdx.x; i < n_slots; i += FIT_THREADS) S.slot[i] = FIT_EMPTY;
+    for (uint32_t i = threadIdx.x; i < FIT_SLOTS / 4; i += FIT_THREADS) S.slot4[i] = make_int4(FIT_EMPTY, FIT_EMPTY, FIT_EMPTY, FIT_EMPTY);
     __syncthreads();
     int rep[PER];                                            // of this thread's positions; -1: not a pair of known tokens
 #pragma unroll
@@ -225,7 +262,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_bigram_fit(const int32_t *__res
     for (int p = 0; p < PER; p++)
         if (rep[p] >= 0)                                     // (the count no longer changes; only the position below it does)
             atomicMax(&S.key[rep[p]], (S.key[rep[p]] & ~(uint32_t)(FIT_MAX - 1)) | (uint32_t)(p * FIT_THREADS + (int)threadIdx.x));
-    for (uint32_t i = threadIdx.x; i < n_slots; i += FIT_THREADS) S.slot[i] = FIT_EMPTY;
+    for (uint32_t i = threadIdx.x; i < FIT_SLOTS / 4; i += FIT_THREADS) S.slot4[i] = make_int4(FIT_EMPTY, FIT_EMPTY, FIT_EMPTY, FIT_EMPTY);
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < PER; p++) {
@@ -262,7 +299,7 @@ extern "C" int32_t csd_bigram_draft(const int32_t *ctx, const int32_t *ctx_len, 
     if (B < 0 || k < 0 || vocab < 1 || ctx_stride < 1) return CSD_EINVAL;
     if (k > 0 && !out_tokens) return CSD_ENULL;
     if (B == 0 || (k == 0 && !out_match_len)) return CSD_OK;   // k == 0 still reports match lengths
-    hipLaunchKernelGGL(k_bigram_draft, dim3(B), dim3(DRAFT_THREADS), 0, (hipStream_t)stream, ctx, ctx_len, ctx_stride,
+    hipLaunchKernelGGL(k_bigram_draft, dim3(B), dim3(draft_threads(ctx_stride)), 0, (hipStream_t)stream, ctx, ctx_len, ctx_stride,
                        next_table, vocab, k, max_match, out_tokens, out_match_len);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
@@ -291,7 +328,7 @@ extern "C" int32_t csd_bigram_draft_append(int32_t *ctx, int32_t ctx_stride, int
     if (B < 0 || k < 0 || vocab < 1 || ctx_stride < 1) return CSD_EINVAL;
     if (q_onehot_tab && (!q_base || q_stride < 1)) return CSD_EINVAL;
     if (B == 0) return CSD_OK;
-    hipLaunchKernelGGL(k_bigram_draft_append, dim3(B), dim3(DRAFT_THREADS), 0, (hipStream_t)stream, ctx, ctx_stride, ctx_len,
+    hipLaunchKernelGGL(k_bigram_draft_append, dim3(B), dim3(draft_threads(ctx_stride)), 0, (hipStream_t)stream, ctx, ctx_stride, ctx_len,
                        next_table, vocab, k, max_match, gate, q_onehot_tab, q_base, q_stride);
     CSD_LAUNCH_CHECK();
     return CSD_OK;

@@ -48,6 +48,23 @@ BF = I.ModelShape("edge_dh64", 0, "bf16", 2, 256, 4, 64, 512, 1024)
 BF128 = I.ModelShape("edge_dh128", 0, "bf16", 2, 256, 2, 128, 480, 1040)
 
 
+@pytest.mark.parametrize("n,room", [(1, 0), (2, 254), (256, 0), (256, 1), (511, 1), (513, 0), (1024, 300), (4096, 1), (4097, 0), (8192, 5), (8193, 0), (9000, 60)])
+@pytest.mark.parametrize("max_match", [0, 3])
+def test_draft_of_long_and_short_sequences(P, n, room, max_match):
+    """Either side of every thread count, of the tokens that are requested before the length is known, and of what LDS holds."""
+    from oracle import csd_oracle as O
+    vocab, k = 50, 9
+    rng = np.random.default_rng(n + room)
+    ctx = rng.integers(0, vocab, (2, n + room)).astype(np.int32)
+    ctx[1, :n] = np.arange(n) % 49                           # a long period; and a suffix that is nowhere else
+    ctx[1, n - 1] = 49
+    table = rng.integers(0, vocab, vocab).astype(np.int32)
+    got, length = P.bigram_draft(torch.from_numpy(ctx).cuda(), torch.full((2,), n, dtype=torch.int32, device="cuda"), torch.from_numpy(table).cuda(), k,
+                                 max_match=max_match)
+    want, want_len = O.bigram_draft(ctx, [n, n], table, k, max_match=max_match)
+    assert np.array_equal(got.cpu().numpy(), want) and np.array_equal(length.cpu().numpy(), want_len)
+
+
 @pytest.mark.parametrize("shape", [BF, BF128], ids=["dh64", "dh128"])
 @pytest.mark.parametrize("B,m", [(1, 145), (1, 192), (1, 193), (1, 256), (1, 257), (1, 288), (1, 289), (2, 100), (3, 173)])
 def test_tall_blocks(P, shape, B, m):
