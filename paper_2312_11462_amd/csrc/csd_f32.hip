@@ -158,6 +158,252 @@ __global__ __launch_bounds__(256) void k_f32_embed(const int32_t *__restrict__ t
     }
 }
 
+// ------------------------------------------------------------------------------- small models: a layer per launch
+//
+// Where every matrix is at most 1024 columns wide and 32 K values large, a launch is latency and little else (3 to 6 us for 64 x 64
+// products), so one workgroup of 1024 threads takes a block row through everything between two appends to the cache: attention of the
+// row over all heads, O, gate|up, down, and the QKV projection of the next layer (the LM head after the last).  What bounds it is the
+// chain of LDS steps and barriers, and the instruction fetches of code that runs once: with every loop unrolled and integer divisions
+// (25 KB) a layer took 20.8 us, in 11 KB 12.6.  The weights of a product are requested one product ahead, a thread holding up to 32 values of
+// one column.  Tiny shape (64 features, 4 heads, 256 hidden, 512 tokens, 2 layers), verify step with 5 rows: 66 us in five launches per
+// layer, 40 in one.
+#define FR_THREADS 1024
+#define FR_X (FR_THREADS + 64)        /* an input row, zero past its end up to a multiple of the slices */
+struct RowProduct {
+    const float *W;                   // row-major [K][N]
+    int K, N, S, kper;                // S = FR_THREADS / N slices of kper = ceil(K / S) values
+};
+// x / n for 0 <= x < 2048, 1 <= n <= 1024: the quotient is at least 1 / 2048 away from the next whole number, the product within 2^-22 of it
+__device__ __forceinline__ int small_div(int x, int n) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)n)); }
+struct F32Row {
+    RowProduct o, gu, down, next;     // this layer's O, gate|up, down; the next product (QKV, or the LM head)
+    const float *ffn_gain, *next_gain;
+    int d, hd, F, m, layer, keys_pad; // layer: of the attention; QKV appends to layer + 1
+    int head_threads, pv_slices;      // FR_THREADS / n_heads, FR_THREADS / hd
+    float eps, scale, theta;
+    float *h, *q;                     // [M][d], [M][hd]
+    float *kv;
+    const int32_t *cache_len;
+    KvGeom geo;
+    float2 *rope;                     // [M][dh / 2]
+    const int32_t *tokens, *depth;    // FIRST
+    const float *embed;
+    int V;
+    const unsigned long long *anc;
+    float *logits;                    // LAST
+};
+
+// A row times a K x N matrix (N <= FR_THREADS): thread (slice s of K, column c).  At most PER values of the column per thread.
+template <int PER>
+struct RowSlice {
+    float w[PER];
+    int k0, c, s;
+    __device__ __forceinline__ void load(const RowProduct &Q) {
+        const int N = Q.N, K = Q.K, S = Q.S;
+        s = small_div(threadIdx.x, N);
+        c = threadIdx.x - s * N;
+        k0 = s * Q.kper;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(Q.W), 0, K * N * 4, 0x00020000);
+        // (rows past the slice are not used, rows past the matrix are outside the buffer and read as 0, and so is all of a thread
+        // without a slice: no load is under a branch)
+        int off = s < S ? (k0 * N + c) * 4 : (int)0x80000000;
+#pragma unroll
+        for (int j = 0; j < PER; j++) {
+            w[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+            off += N * 4;
+        }
+    }
+    // partial sums to red[s][c], in four chains
+    __device__ __forceinline__ void apply(const RowProduct &Q, const float *x, float *red) const {
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        const float *xs = x + (s < Q.S ? k0 : 0);
+#pragma unroll
+        for (int j = 0; j < PER; j++)
+            if (j < Q.kper) a[j & 3] = fmaf(xs[j], w[j], a[j & 3]);      // (uniform)
+        if (s < Q.S) red[s * Q.N + c] = (a[0] + a[1]) + (a[2] + a[3]);
+    }
+    static __device__ __forceinline__ float sum(const RowProduct &Q, const float *red, int col) {
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        int i = 0;
+#pragma unroll 1
+        for (; i + 4 <= Q.S; i += 4)
+#pragma unroll
+            for (int u = 0; u < 4; u++) a[u] += red[(i + u) * Q.N + col];
+#pragma unroll 1
+        for (; i < Q.S; i++) a[i & 1] += red[i * Q.N + col];
+        return (a[0] + a[1]) + (a[2] + a[3]);
+    }
+};
+
+// PO, PN: most values per thread of the O projection and of the next product
+template <bool FIRST, bool LAST, int PO, int PN>
+__global__ __launch_bounds__(FR_THREADS) void k_f32_row(const F32Row P) {
+    extern __shared__ float fr_smem[];
+    __shared__ float x[FR_X], red[FR_THREADS], hs[FR_THREADS], y[FR_THREADS], wave_red[2 * (FR_THREADS / 64)];
+    float *sc = fr_smem;                                         // scores [H][keys_pad]
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = blockIdx.x;
+    const int d = P.d, hd = P.hd, dh = P.geo.dh, H = P.geo.H, half = dh / 2;
+    const int b = r / P.m, i = r % P.m;
+    auto put_x = [&](int K, float v) {                           // x[0 .. K) = v of thread k, zeros behind
+        if (tid < K) x[tid] = v;
+        if (tid < 64) x[K + tid] = 0.f;
+    };
+    // 1 / rms of the row whose entries the threads below d hold
+    auto row_rstd = [&](float v) {
+        float ss = wave_sum(tid < d ? v * v : 0.f);
+        if (lane == 0) wave_red[wv] = ss;
+        __syncthreads();
+        ss = 0.f;
+#pragma unroll 1
+        for (int u = 0; u < (d + 63) / 64; u++) ss += wave_red[u];
+        return rsqrtf(ss / (float)d + P.eps);
+    };
+    const int t0 = P.cache_len[b];
+    RowSlice<PN> wn;
+    float hv = 0.f;                                              // this thread's entry of the residual stream
+    if constexpr (FIRST) {
+        wn.load(P.next);
+        const int tok = P.tokens[r];
+        if (tid < d) hv = tok >= 0 && tok < P.V ? P.embed[(size_t)tok * d + tid] : 0.f;
+        // the position of a row: where it sits in a plain block, how far it is from row 0 in a tree block
+        const int pos = t0 + (P.depth ? P.depth[r] : i);
+        if (tid < half) {
+            const double ang = (double)pos * pow((double)P.theta, -2.0 * (double)tid / (double)dh);
+            P.rope[(size_t)r * half + tid] = float2{(float)cos(ang), (float)sin(ang)};
+        }
+    } else {
+        RowSlice<PO> wo;
+        RowSlice<32> wg;
+        wo.load(P.o);
+        wg.load(P.gu);
+        // ---- attention of the row, all heads (the keys of a head as k_attn_simple takes them)
+        if (tid < hd) y[tid] = P.q[(size_t)r * hd + tid];
+        if (tid < d) hv = P.h[(size_t)r * d + tid];
+        const int qpos = t0 + i, nk = max(1, min(qpos + 1, P.geo.seq_pad));
+        const unsigned long long anc_row = P.anc ? P.anc[r] : 0ull;
+        const float *kc = P.kv + kv_k_off(P.geo, P.layer, b, 0), *vc = P.kv + kv_v_off(P.geo, P.layer, b, 0);
+        const size_t he = kv_head_elems(P.geo);
+        __syncthreads();
+        const int G = P.head_threads, hq = small_div(tid, G);
+        if (hq < H) {
+            const float *kh = kc + hq * he, *qr = y + hq * dh;
+#pragma unroll 1
+            for (int j = tid - hq * G; j < nk; j += G) {
+                const float *kr = kh + (size_t)j * dh;
+                float s = 0.f;
+                if (dh % 16 == 0) {
+#pragma unroll 1
+                    for (int e = 0; e < dh; e += 16) {
+                        f32x4 kk[4];
+#pragma unroll
+                        for (int u = 0; u < 4; u++) kk[u] = *reinterpret_cast<const f32x4 *>(kr + e + 4 * u);
+#pragma unroll
+                        for (int u = 0; u < 16; u++) s = fmaf(qr[e + u], kk[u / 4][u % 4], s);
+                    }
+                } else {
+#pragma unroll 1
+                    for (int e = 0; e < dh; e++) s = fmaf(qr[e], kr[e], s);
+                }
+                s *= P.scale;
+                if (P.anc && !tree_sees(anc_row, j, t0)) s = -INFINITY;   // a row of the block that is not above this one
+                sc[hq * P.keys_pad + j] = s;
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int hh = wv; hh < H; hh += FR_THREADS / 64) {       // a wave per head
+            float *row = sc + hh * P.keys_pad;
+            float mx = -INFINITY, z = 0.f;
+#pragma unroll 1
+            for (int j = lane; j < nk; j += 64) mx = fmaxf(mx, row[j]);
+            mx = wave_max(mx);
+#pragma unroll 1
+            for (int j = lane; j < nk; j += 64) {
+                const float e = expf(row[j] - mx);
+                row[j] = e;
+                z += e;
+            }
+            z = wave_sum(z);
+            if (lane == 0) hs[hh] = 1.0f / z;
+        }
+        __syncthreads();
+        {
+            const int S = P.pv_slices, c = small_div(tid, S), s = tid - c * S;  // slices of the keys next to each other: V is contiguous in them
+            float o = 0.f;
+            if (c < hd) {
+                const int hh = small_div(c, dh), e = c - hh * dh;
+                const float *row = sc + hh * P.keys_pad, *vr = vc + hh * he;
+#pragma unroll 4
+                for (int j = s; j < nk; j += S) o = fmaf(row[j], vr[kv_v_idx(P.geo, e, j)], o);
+                red[s * hd + c] = o;
+            }
+            __syncthreads();
+            o = 0.f;
+            if (tid < hd) {
+#pragma unroll 4
+                for (int u = 0; u < S; u++) o += red[u * hd + tid];
+                o *= hs[small_div(tid, dh)];
+            }
+            put_x(hd, o);
+            __syncthreads();
+        }
+        // ---- O, residual
+        RowSlice<16> wd;
+        wo.apply(P.o, x, red);
+        wd.load(P.down);
+        __syncthreads();
+        if (tid < d) hv += wo.sum(P.o, red, tid);
+        float rstd = row_rstd(hv);                               // (its barrier: red and x have been read)
+        put_x(d, tid < d ? hv * P.ffn_gain[tid] : 0.f);
+        __syncthreads();
+        // ---- gate|up, activation
+        wg.apply(P.gu, x, red);
+        wn.load(P.next);
+        __syncthreads();
+        float f = 0.f;
+        if (tid < P.F) {
+            const float gt = wg.sum(P.gu, red, tid) * rstd, up = wg.sum(P.gu, red, P.F + tid) * rstd;
+            f = gt / (1.0f + expf(-gt)) * up;
+        }
+        put_x(P.F, f);
+        __syncthreads();
+        // ---- down, residual
+        wd.apply(P.down, x, red);
+        __syncthreads();
+        if (tid < d) hv += wd.sum(P.down, red, tid);
+    }
+    if (tid < d) P.h[(size_t)r * d + tid] = hv;
+    const float rstd = row_rstd(hv);
+    put_x(d, tid < d ? hv * P.next_gain[tid] : 0.f);
+    __syncthreads();
+    wn.apply(P.next, x, red);
+    __syncthreads();
+    float v = 0.f;
+    if (tid < P.next.N) v = wn.sum(P.next, red, tid) * rstd;
+    if constexpr (LAST) {
+        if (tid < P.next.N) P.logits[(size_t)r * P.next.N + tid] = v;
+    } else {
+        y[tid] = v;
+        __syncthreads();
+        if (tid >= P.next.N) return;
+        const int region = small_div(tid, hd), c = tid - region * hd, hh = small_div(c, dh), e = c - hh * dh;
+        if (region < 2) {
+            const float2 cs = P.rope[(size_t)r * half + (e < half ? e : e - half)];   // (FIRST: written by this workgroup before its barriers)
+            const float other = y[e < half ? tid + half : tid - half];
+            v = e < half ? v * cs.x - other * cs.y : other * cs.y + v * cs.x;
+        }
+        const int pos = t0 + i, layer = FIRST ? 0 : P.layer + 1;
+        if (region == 0)
+            P.q[(size_t)r * hd + c] = v;
+        else if (pos >= 0 && pos < P.geo.seq_pad) {
+            if (region == 1)
+                P.kv[kv_k_off(P.geo, layer, b, hh) + (size_t)pos * dh + e] = v;
+            else
+                P.kv[kv_v_off(P.geo, layer, b, hh) + kv_v_idx(P.geo, e, pos)] = v;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------- host driver
 
 template <typename TW, int EPI, bool NORM>
@@ -190,10 +436,79 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
     return mod->cfg.dtype == CSD_DTYPE_BF16 ? f32_launch<bf16_t, FG_PART, false>(P, st) : f32_launch<float, FG_PART, false>(P, st);
 }
 
+// Whether the launch of a layer per row takes the model and the call: every product's columns over the threads, at most PER values
+// of a column in each, at most one workgroup per compute unit; the scores of a row in LDS.  Not while csd_prof_read asks for the time of each
+// class of kernels, which one launch cannot tell apart.
+static bool row_product_fits(int K, int N, int per) { return N >= 16 && N <= FR_THREADS && (K + FR_THREADS / N - 1) / (FR_THREADS / N) <= per; }
+static bool f32_rows_fit(const csd_model *mod, int M) {
+    const csd_model_cfg &c = mod->cfg;
+    const int d = c.d_model, hd = mod->hd, F = c.d_ffn;
+    return !mod->prof && M <= 256 && (long long)c.n_heads * mod->seq_pad <= 11000 && row_product_fits(hd, d, 8) && row_product_fits(d, 2 * F, 32) &&
+           row_product_fits(F, d, 16) && row_product_fits(d, 3 * hd, 32) && row_product_fits(d, c.vocab, 32);
+}
+static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int M, int m, float *logits,
+                                hipStream_t st) {
+    const csd_model_cfg &c = mod->cfg;
+    const int d = c.d_model, L = c.n_layers;
+    F32Row P{};
+    auto product = [](const GemmW &w) {
+        const int S = FR_THREADS / w.N;
+        return RowProduct{(const float *)w.data, w.K, w.N, S, (w.K + S - 1) / S};
+    };
+    P.head_threads = FR_THREADS / c.n_heads;
+    P.pv_slices = FR_THREADS / mod->hd;
+    P.d = d;
+    P.hd = mod->hd;
+    P.F = c.d_ffn;
+    P.m = m;
+    P.keys_pad = mod->seq_pad;
+    P.eps = c.rms_eps;
+    P.scale = 1.0f / sqrtf((float)c.head_dim);
+    P.theta = c.rope_theta;
+    P.h = mod->h;
+    P.q = (float *)mod->qbuf;
+    P.kv = (float *)kv;
+    P.cache_len = cache_len;
+    P.geo = KvGeom{c.max_batch, c.n_heads, c.head_dim, mod->seq_pad, L, mod->kperm ? 1 : 0};
+    P.rope = mod->rope;
+    P.tokens = tokens;
+    P.embed = (const float *)mod->embed;
+    P.V = c.vocab;
+    P.logits = logits;
+    if (mod->tree_call) P.depth = mod->tree_depth, P.anc = mod->tree_anc;
+    const size_t lds = sizeof(float) * (size_t)c.n_heads * mod->seq_pad;
+    const bool few = row_product_fits(mod->hd, d, 4) && row_product_fits(d, 3 * mod->hd, 16);
+    for (int l = -1; l < L; l++) {                               // layer l, and the QKV projection of the next one
+        ProfScope ps(mod, st, CSD_PROF_GEMM);
+        const GemmW &next = l + 1 < L ? mod->layers[l + 1].qkv : mod->lm;
+        P.next = product(next);
+        P.next_gain = l + 1 < L ? mod->layers[l + 1].attn_norm : mod->final_norm;
+        P.layer = l;
+        if (l >= 0) {
+            const LayerW &lw = mod->layers[l];
+            P.o = product(lw.o);
+            P.gu = product(lw.gu);
+            P.down = product(lw.down);
+            P.ffn_gain = lw.ffn_norm;
+        }
+        if (l < 0)
+            hipLaunchKernelGGL((few ? k_f32_row<true, false, 4, 16> : k_f32_row<true, false, 8, 32>), dim3(M), dim3(FR_THREADS), 0, st, P);
+        else if (l + 1 < L)
+            hipLaunchKernelGGL((few ? k_f32_row<false, false, 4, 16> : k_f32_row<false, false, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P);
+        else
+            hipLaunchKernelGGL((few ? k_f32_row<false, true, 4, 32> : k_f32_row<false, true, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P);
+        CSD_LAUNCH_CHECK();
+        if (mod->trace)
+            CSD_HIP(hipMemcpyAsync(mod->trace + (size_t)(l + 1) * M * d, mod->h, sizeof(float) * (size_t)M * d, hipMemcpyDeviceToDevice, st));
+    }
+    return CSD_OK;
+}
+
 int32_t csd_f32_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int32_t B, int32_t m,
                         float *logits, hipStream_t st) {
     const csd_model_cfg &c = mod->cfg;
     const int M = B * m, d = c.d_model, L = c.n_layers;
+    if (f32_rows_fit(mod, M)) return f32_rows_enqueue(mod, kv, tokens, cache_len, M, m, logits, st);
     const KvGeom geo{c.max_batch, c.n_heads, c.head_dim, mod->seq_pad, L, mod->kperm ? 1 : 0};
     float *act = (float *)mod->act;
     const float scale = 1.0f / sqrtf((float)c.head_dim);
