@@ -87,7 +87,9 @@ def _ptr(t, dtype=None):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream.  Its handle alone: torch.cuda.current_stream() makes an object around it, 2.8 us a call
+    against 0.2, which the smallest calls (10 us of kernels) waited for."""
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 class Model:
