@@ -18,6 +18,8 @@
 // and the epilogue inside (40 rows, gate|up by itself 39 to 43 us against 33 and 5 for the epilogue kernel; 136 rows 68.8 against 58.0 and 7.8).
 #include "csd_tall.h"
 
+#include <type_traits>
+
 #define RS_SETS 4             /* k-steps of activations in registers; as many stages of weights, and one in use, in LDS */
 
 template <int CT>
@@ -80,8 +82,11 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
 #pragma unroll
     for (int c = 0; c < RA; c++) f[c] = L[c * 64];
     int cur = 0, last = NST - 1, k = ks0;                        // the stages of W(k) and of W(k - 1), the latter free for W(k + NA + 1)
-    auto step = [&](int set) {
-        wait_loads<(NA - 1) * (PW + AL)>();                      // W(k + 1), this wave's share
+    // END: how many k-steps behind the last one that issued loads (0: this one issues its own).  The last k-steps of a slice issue none: the
+    // activations would not be used, and the compiler takes such loads out, but not those to LDS; the waits have to count what is issued.
+    auto step = [&](int set, auto END) {
+        constexpr int E = decltype(END)::value;
+        wait_loads<(E ? NA - E : NA - 1) * (PW + AL)>();         // W(k + 1), this wave's share
         stage_barrier();
         const u32x4 *Lc = L + cur * CT * 64;
         const int nxt = cur + 1 == NST ? 0 : cur + 1;
@@ -91,7 +96,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
             f[c + RA] = c + RA < CT ? Lc[(c + RA) * 64] : Ln[(c + RA - CT) * 64];
 #pragma unroll
             for (int i = 0; i < AL + PW; i++)
-                if (i * CT / (AL + PW) == c) {
+                if (E == 0 && i * CT / (AL + PW) == c) {
                     if (i < AL)
                         load_a(i, k + NA, (set + NA) % RS_SETS);
                     else
@@ -113,11 +118,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
     };
     while (k + RS_SETS <= ks1) {
 #pragma unroll
-        for (int u = 0; u < RS_SETS; u++) step(u);
+        for (int u = 0; u < RS_SETS; u++) step(u, std::integral_constant<int, 0>{});
     }
-#pragma unroll
-    for (int u = 0; u < RS_SETS - 1; u++)
-        if (k < ks1) step(u);                                    // uniform over the workgroup
+    static_assert(RS_SETS == 4, "a k-step of each remainder");
+    if (k < ks1) step(0, std::integral_constant<int, 1>{});      // uniform over the workgroup
+    if (k < ks1) step(1, std::integral_constant<int, 2>{});
+    if (k < ks1) step(2, std::integral_constant<int, 3>{});
     wait_loads<0>();                                             // nothing may land in this LDS after the workgroup has ended
 
     const int t = lane & 15, g = lane >> 4;
