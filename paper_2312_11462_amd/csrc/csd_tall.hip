@@ -9,10 +9,15 @@
 // placed in operand order; NST stages of one k-step are in flight or in use.  A wave holds the fragments of the running
 // k-step in registers and reads the next one's between its matrix instructions; one workgroup barrier per k-step.
 // Row blocks of one column group go to one compute die, which then fetches those weights once.
-// 7B shape, 512 rows, against four launches of the row-split form over 128 rows each, every GEMM timed by itself: QKV 122 -> 81 us
-// (1.27 PFLOP/s, both planes counted), gate|up 188 -> 146, down 111 -> 79, O 57 -> 34, LM head 254 -> 223.  In traces of whole calls, where
-// the chip is under load throughout: QKV 95 (1.09 PFLOP/s), gate|up 147, O and down 58 on average, LM head 233.  With the loads of the main loop
-// switched off 57-68 us for QKV by itself, so it is bound by the operand traffic into LDS beside the matrix instructions.
+// A wave issues in order, and with one or two waves per SIMD whatever is issued in a bunch leaves the matrix pipe empty: operand reads and
+// loads go between the matrix instructions one at a time (in a bunch per column tile: a prompt of 1000 rows of the 7B shape 27.8 ms against 26.7; QKV at 512
+// rows in traces of whole calls 98 us against 90, O and down together 116 against 105).
+// 7B shape, 512 rows, against four launches of the row-split form over 128 rows each, every GEMM timed by itself before that: QKV 122 -> 81 us,
+// gate|up 188 -> 146, down 111 -> 79, O 57 -> 34, LM head 254 -> 223.
+// What bounds QKV now, by the counters: of 196000 cycles a SIMD's matrix pipe is busy for 98000, waves wait 30000 for barriers and loads,
+// 28000 are launch and teardown; the rest is prologue, epilogue, and what does not fit between the matrix instructions.  Loads further ahead (four and five
+// stages: 94.6 and 96.1 us against 94.9) and the 32x32x16 instruction (10 % slower in a loop of nothing else on random operands: 1.8 against 2.0
+// PFLOP/s) gain nothing.
 #include "csd_tall.h"
 
 // EPI_CROSS: keys | values of the encoder rows into the cross-attention part of the cache
@@ -51,7 +56,9 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
     constexpr bool SUMS = tall_sums<CTW, RTW, NST>();
     extern __shared__ __align__(16) char tall_smem[];
     constexpr int WF = 2 * CTW, NF = WF + 4 * RTW;               // fragments of a stage: W tiles, then [plane][row tile]
-    constexpr int PW = (NF + 3) / 4;                             // per wave: fragments w, w + 4, ... (the last one again past the end)
+    static_assert(WF % 4 == 0 && NF % 4 == 0, "every wave brings as many of either kind");
+    constexpr int PW = NF / 4;                                   // per wave: fragments w, w + 4, ...
+    constexpr int STB = NF * 1024;                               // bytes of a stage
     const ChainGemm &P = A.g;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -67,31 +74,24 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(P.a), 0, (int)(2u * (unsigned)P.a_plane_bytes), 0x00020000);
     // Tiles and row tiles past the end are read as the last one (their sums are not stored), k-steps past the slice likewise:
     // every address is inside the matrix, and every wave issues PW loads per stage, so the waits can count them.
-    unsigned base[PW], step[PW];
+    unsigned base[PW];
 #pragma unroll
     for (int i = 0; i < PW; i++) {
-        const int f = min(i * 4 + w, NF - 1);
-        if (f < WF) {
-            base[i] = min(tile0 + f, A.n_tiles - 1) * P.KS * 1024;
-            step[i] = 1024;
-        } else {
-            const int a = f - WF;
-            base[i] = a / (2 * RTW) * (unsigned)P.a_plane_bytes + min(rt0 + a % (2 * RTW), P.mtp - 1) * 1024;
-            step[i] = P.mtp * 1024;
-        }
+        const int f = i * 4 + w, a = f - WF;
+        base[i] = i < WF / 4 ? min(tile0 + f, A.n_tiles - 1) * P.KS * 1024
+                             : a / (2 * RTW) * (unsigned)P.a_plane_bytes + min(rt0 + a % (2 * RTW), P.mtp - 1) * 1024;
     }
-    const int vw = lane * 16, va = (4 * (lane & 15) + (lane >> 4)) * 16;     // see act_tiled_idx
-    auto load_stage = [&](int ks, int buf) {
+    // Activations: a fragment is 16 rows of 64 bytes.  Four lanes fetch a row's (lanes 64 bytes apart get 33 bytes per cycle into a compute unit,
+    // neighbours 55), in an order that spreads the 16 bytes of a lane group's rows over all banks when they are read as operands.
+    const int vw = lane * 16, va = (lane ^ (lane >> 4)) * 16;
+    // load i of this wave for k-step ks, whose stage begins at byte `stage` (its place for this wave: + w KB)
+    auto load_part = [&](int i, int ks, int stage) {
         const int k = min(ks, ks1 - 1);
-#pragma unroll
-        for (int i = 0; i < PW; i++) {
-            const int f = min(i * 4 + w, NF - 1);
-            const lds_void d = (lds_void)(tall_smem + (buf * NF + f) * 1024);
-            if (f < WF)
-                lds_load16<0>(rw, d, vw, (int)(base[i] + k * step[i]));
-            else
-                lds_load16<0>(ra, d, va, (int)(base[i] + k * step[i]));
-        }
+        const lds_void d = (lds_void)(tall_smem + stage + w * 1024 + i * 4096);
+        if (i < WF / 4)
+            lds_load16<0>(rw, d, vw, (int)(base[i] + k * 1024));
+        else
+            lds_load16<0>(ra, d, va, (int)(base[i] + k * P.mtp * 1024));
     };
     const int wc = w & 1, wr = w >> 1;
     f32x4 acc[RTW][CTW];
@@ -100,7 +100,9 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
 #pragma unroll
         for (int c = 0; c < CTW; c++) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int p = 0; p < NST; p++) load_stage(ks0 + p, p);
+    for (int p = 0; p < NST; p++)
+#pragma unroll
+        for (int i = 0; i < PW; i++) load_part(i, ks0 + p, p * STB);
     f32x4 sum[RTW][CTW];
     u32x2 lead[TALL_LEADS];
     u32x2 *lead_lds = reinterpret_cast<u32x2 *>(tall_smem + NST * NF * 1024) + threadIdx.x;
@@ -118,36 +120,43 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
             sum[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
             if (!SUMS) set_lead(r * CTW + c, u32x2{0u, 0u});
         }
-    const u32x4 *L = reinterpret_cast<const u32x4 *>(tall_smem) + lane;
-    const int wo = wc * CTW * 64, ao = (WF + wr * RTW) * 64;     // this wave's W tiles and (hi) row tiles of a stage
-    u32x4 fa[2][2][RTW], fw[2][CTW];                             // [k-step parity]
+    // this wave's operands of a stage: W tiles, (hi) row tiles
+    const char *Lw = tall_smem + wc * CTW * 1024 + lane * 16;
+    const char *La = tall_smem + (WF + wr * RTW) * 1024 + ((lane & 15) * 4 + ((lane >> 4) ^ ((lane >> 2) & 3))) * 16;
+    u32x4 fa[2][2 * RTW], fw[2][CTW];                            // [k-step parity]
+    // operand i of a k-step: W tile i, then hi and lo row tiles
+    auto read_part = [&](int i, int set, int stage) {
+        if (i < CTW)
+            fw[set][i] = *reinterpret_cast<const u32x4 *>(Lw + stage + i * 1024);
+        else
+            fa[set][i - CTW] = *reinterpret_cast<const u32x4 *>(La + stage + ((i - CTW) / RTW * 2 * RTW + (i - CTW) % RTW) * 1024);
+    };
     wait_loads<(NST - 1) * PW>();
     stage_barrier();
 #pragma unroll
-    for (int p = 0; p < 2; p++)
-#pragma unroll
-        for (int r = 0; r < RTW; r++) fa[0][p][r] = L[ao + (p * 2 * RTW + r) * 64];
-#pragma unroll
-    for (int c = 0; c < CTW; c++) fw[0][c] = L[wo + c * 64];
-    int cur = 0, nxt = 1;
-    // k-step K with its fragments in set PAR: the stage behind it has arrived, its own stage is free for k-step K + NST
+    for (int i = 0; i < CTW + 2 * RTW; i++) read_part(i, 0, 0);
+    int cur = 0, nxt = STB;
+    // k-step K with its fragments in set PAR: the stage behind it has arrived, its own stage is free for k-step K + NST.  A wave issues
+    // in order, and a matrix instruction takes as long as four others: what else there is to issue (two operand reads, then a load with its two
+    // address sums) goes between them one by one.
 #define TALL_STEP(PAR, K)                                                                                             \
     {                                                                                                                 \
         wait_loads<(NST - 2) * PW>();                                                                                 \
         stage_barrier();                                                                                              \
-        load_stage((K) + NST, cur);                                                                                   \
-        const u32x4 *Ln = L + nxt * NF * 64;                                                                          \
-        _Pragma("unroll") for (int c = 0; c < CTW; c++) {                                                             \
-            fw[1 - (PAR)][c] = Ln[wo + c * 64];                                                                       \
-            _Pragma("unroll") for (int a = 0; a < 2 * RTW; a++) if (a * CTW / (2 * RTW) == c)                         \
-                fa[1 - (PAR)][a / RTW][a % RTW] = Ln[ao + (a / RTW * 2 * RTW + a % RTW) * 64];                        \
-            _Pragma("unroll") for (int p = 0; p < 2; p++) _Pragma("unroll") for (int r = 0; r < RTW; r++)             \
-                acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[PAR][c]),           \
-                                                                    __builtin_bit_cast(bf16x8, fa[PAR][p][r]), acc[r][c], 0, 0, 0); \
+        _Pragma("unroll") for (int n = 0; n < 2 * CTW * RTW; n++) {                                                   \
+            const int c = n / (2 * RTW), a = n % (2 * RTW), r = a % RTW;                                              \
+            acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[PAR][c]),               \
+                                                                __builtin_bit_cast(bf16x8, fa[PAR][a]), acc[r][c], 0, 0, 0); \
+            _Pragma("unroll") for (int j = 0; j < 3 * PW; j++) if (j * (2 * CTW * RTW - 4) / (3 * PW) == n) {         \
+                if (j % 3 < 2)                                                                                        \
+                    read_part(j / 3 * 2 + j % 3, 1 - (PAR), nxt);                                                     \
+                else                                                                                                  \
+                    load_part(j / 3, (K) + NST, cur);                                                                 \
+            }                                                                                                         \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
         }                                                                                                             \
         cur = nxt;                                                                                                    \
-        nxt = nxt + 1 == NST ? 0 : nxt + 1;                                                                           \
+        nxt = nxt + STB == NST * STB ? 0 : nxt + STB;                                                                 \
     }
     const int t = lane & 15, g = lane >> 4;
     bool kept = false;                                           // uniform
