@@ -138,7 +138,8 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
     int cur = 0, nxt = STB;
     // k-step K with its fragments in set PAR: the stage behind it has arrived, its own stage is free for k-step K + NST.  A wave issues
     // in order, and a matrix instruction takes as long as four others: what else there is to issue (two operand reads, then a load with its two
-    // address sums) goes between them one by one.
+    // address sums) goes between them one by one.  With two stages the loads come first, since all they have to arrive in is the rest of the k-step (512
+    // rows, gate|up 161 -> 156 us, LM head 257 -> 238; all of them in front of the first matrix instruction: 166 and 245).
 #define TALL_STEP(PAR, K)                                                                                             \
     {                                                                                                                 \
         wait_loads<(NST - 2) * PW>();                                                                                 \
@@ -148,10 +149,10 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
             acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[PAR][c]),               \
                                                                 __builtin_bit_cast(bf16x8, fa[PAR][a]), acc[r][c], 0, 0, 0); \
             _Pragma("unroll") for (int j = 0; j < 3 * PW; j++) if (j * (2 * CTW * RTW - 4) / (3 * PW) == n) {         \
-                if (j % 3 < 2)                                                                                        \
-                    read_part(j / 3 * 2 + j % 3, 1 - (PAR), nxt);                                                     \
+                if (NST == 2 ? j < PW : j % 3 == 2)                                                                   \
+                    load_part(NST == 2 ? j : j / 3, (K) + NST, cur);                                                  \
                 else                                                                                                  \
-                    load_part(j / 3, (K) + NST, cur);                                                                 \
+                    read_part(NST == 2 ? j - PW : j / 3 * 2 + j % 3, 1 - (PAR), nxt);                                 \
             }                                                                                                         \
             __builtin_amdgcn_sched_barrier(0);                                                                        \
         }                                                                                                             \
