@@ -405,6 +405,59 @@ def test_fp32_forward(P, dims, B, m, t):
             assert tol_ok(got.cpu().numpy().astype(np.float64), want, 1e-4, 1e-4)[0]
 
 
+@pytest.mark.parametrize("dims,B,m,t,max_seq", [
+    ((128, 4, 12, 40, 200), 2, 5, 31, 64), ((40, 1, 130, 9, 129), 1, 3, 70, 128), ((32, 2, 10, 512, 1024), 3, 4, 9, 32), ((16, 1, 6, 8, 16), 1, 2, 0, 8),
+    ((32, 2, 16, 24, 50), 4, 64, 10, 80), ((32, 2, 16, 24, 50), 4, 65, 10, 80), ((32, 4, 8, 24, 50), 1, 3, 2600, 2688), ((32, 4, 8, 24, 50), 1, 3, 2750, 2816)],
+    ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
+def test_small_fp32_models(P, dims, B, m, t, max_seq):
+    """The forward of a workgroup per block row at the edges of what it takes: most values per thread in each product, 1024 and 16 columns, heads
+    whose keys are not read 16 values at a time, 256 rows and more, the most scores in LDS and more."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    d, H, dh, F, V = dims
+    shape = I.ModelShape("edge_small", 0, "fp32", 2, d, H, dh, F, V)
+    gm, om = make_pair(shape, 33, B, max_seq, m, std=0.1)
+    if t:
+        import_synthetic_kv(gm, om, shape, t, 33, B=B)
+    block = I.token_ids(B * m, V, 33, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([max(0, t - 3 * b) for b in range(B)], np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 1e-4, 1e-4)
+    assert ok, f"max abs err {err}"
+    for b in range(B):
+        for got, want in zip(gm.kv_read(1, b, 0, int(cl[b]) + m), om.kv_read(1, b, 0, int(cl[b]) + m)):
+            assert tol_ok(got.cpu().numpy().astype(np.float64), want, 1e-4, 1e-4)[0]
+
+
+@pytest.mark.parametrize("V", [32764, 32766, 32768, 32772])
+@pytest.mark.parametrize("kind", ["plain", "zero_residual", "large", "empty"])
+def test_accept_at_the_longest_row_in_registers(P, V, kind):
+    """Either side of the vocabulary that a workgroup holds in registers, and what it hands on to the general way: a residual without weight,
+    weights above 256, a row of zeros.  Whole numbers, decided by exact sums."""
+    from oracle import csd_oracle as O
+    B, k = 3, 2
+    g = torch.Generator().manual_seed(V)
+    p = torch.softmax(2.0 * torch.randn((B, k + 1, V), generator=g), -1)
+    q = torch.softmax(2.0 * torch.randn((B, k, V), generator=g), -1)
+    draft = torch.stack([torch.tensor([0, V - 1]), torch.tensor([V // 2, 3]), torch.tensor([V - 1, 255])]).int()
+    if kind == "zero_residual":
+        q = 2.0 * p[:, :k]                                   # (every draft is rejected: the uniforms are 0.5 and more)
+    elif kind == "large":
+        p = p * 3e4
+        p[0, :, V - 1] = 300.0
+    elif kind == "empty":
+        p[1:] = 0.0
+    u_acc, u_s = torch.rand((B, k), generator=g) * 0.5 + 0.5, torch.rand(B, generator=g)
+    for dense in (q, None):
+        if dense is None and kind == "large":
+            continue
+        n, tok = P.accept(p.cuda(), None if dense is None else dense.cuda(), draft.cuda(), u_acc.cuda(), u_s.cuda(), 1.0, 0)
+        s = 1 if kind == "empty" else B                      # (the oracle refuses a row of zeros; here its token is -1)
+        wn, wt = O.accept(p[:s].numpy(), None if dense is None else dense[:s].numpy(), draft[:s].numpy(), u_acc[:s].numpy(), u_s[:s].numpy(), 1.0, 0)
+        n, tok = n.cpu().numpy(), tok.cpu().numpy()
+        assert np.array_equal(n[:s], wn) and np.array_equal(tok[:s], wt), (kind, dense is None)
+        assert (n[s:] == 0).all() and (tok[s:] == -1).all()
+
+
 def test_profile_of_an_fp32_forward(P):
     """Launches per kernel class of the fp32 forward: four GEMMs and one attention per layer, the LM head, the embedding."""
     shape = I.ModelShape("edge_prof", 0, "fp32", 3, 64, 4, 16, 128, 80)
@@ -426,6 +479,21 @@ def test_generic_attention_longest_sequence(P):
     block, cl = np.asarray([[5, 9]], np.int32), np.asarray([16300], np.int32)
     lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
     ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 1e-4, 1e-4)
+    assert ok, f"max abs err {err}"
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("max_seq,m,t", [(2048, 3, 2040), (2112, 16, 2060), (4224, 5, 4200)])
+def test_small_block_attention_over_many_chunks(P, dh, max_seq, m, t):
+    """16 chunks and more: the merge takes the chunk states of a head 16 at a time."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_chunks", 0, "bf16", 1, 256, 2, dh, 256, 512)
+    gm, om = make_pair(shape, 43, 1, max_seq, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, t, 43)
+    block = I.token_ids(m, shape.vocab, 43, 1).reshape(1, m).numpy().astype(np.int32)
+    cl = np.full(1, t, np.int32)
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
     assert ok, f"max abs err {err}"
 
 
