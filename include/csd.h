@@ -332,7 +332,6 @@ int32_t csd_debug_path(const csd_model *model, int32_t B, int32_t m);
  * N x K weight matrix (N a multiple of 16, K of 32) and a block of `rows` rows when the partial-sum buffer holds
  * max_splits planes of rows x N floats: *ct = 16-column tiles per workgroup, *S = K splits.  The plan comes as close
  * to one workgroup per compute unit (256) as ceil(N / 16 / ct) * S allows, S <= 8, the wider workgroup on a tie.
- * Above 128 rows the answer is the plan with at most 8 tiles; launches over 129 to 144 rows choose among all widths.
  * CSD_EINVAL for other shapes or rows outside [1, 144]. */
 int32_t csd_debug_gemm_plan(int32_t N, int32_t K, int32_t rows, int32_t max_splits, int32_t *ct, int32_t *S);
 

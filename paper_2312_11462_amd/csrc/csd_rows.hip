@@ -164,24 +164,24 @@ int32_t csd_rows_setup() {
 // compute unit as the shape allows, the wider workgroup winning a tie (it reads the activation rows less often).
 // 7B shape, 40 rows, against half the tiles and half the splits, which leaves half of the partial sums: QKV 20.5 us against 21.3, O 9.7
 // against 12.3, down 19.9 against 27.4.  rows: 33 to 144; the partial-sum buffer holds S x rows x N floats.
-static void rs_plan(int N, int K, int rows, size_t part_floats, const int *cts, int *ct, int *S) {
+// Nine row tiles take the same widths (QKV at 136 rows 34 us in 12 tiles and 4 splits, 36.9 in 6 and 2).
+static void rs_plan(int N, int K, int rows, size_t part_floats, int *ct, int *S) {
     const int n_tiles = N / 16, KS = K / 32;
     double best = -1.0;
-    for (; *cts; cts++) {
-        const int groups = (n_tiles + *cts - 1) / *cts;
+    for (const int w : {16, 12, 11, 8, 6}) {
+        const int groups = (n_tiles + w - 1) / w;
         int s = 1;
         while (groups * (s + 1) <= 256 && s < 8 && KS / (s + 1) >= 8 && (size_t)(s + 1) * rows * N <= part_floats) s++;
         const int wgs = groups * s;
         const double fill = (double)wgs / (256.0 * ((wgs + 255) / 256));
-        if (fill > best) best = fill, *ct = *cts, *S = s;
+        if (fill > best) best = fill, *ct = w, *S = s;
     }
 }
-static const int rs_cts[] = {16, 12, 11, 8, 6, 0}, rs_cts_low[] = {8, 6, 0};
 
 int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats, int32_t *ct, int32_t *S) {
     if (!ct || !S) return CSD_ENULL;
     if (N <= 0 || K <= 0 || N % 16 || K % 32 || rows < 1 || rows > 144) return CSD_EINVAL;
-    rs_plan(N, K, rows, part_floats, rows <= 128 ? rs_cts : rs_cts_low, ct, S);
+    rs_plan(N, K, rows, part_floats, ct, S);
     return CSD_OK;
 }
 
@@ -208,7 +208,7 @@ static int32_t rs_launch(const TallArgs &A, int ct, hipStream_t st) {
 int32_t csd_rows_part(csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int M, int *S_used, hipStream_t st) {
     TallArgs A = tall_args(mod, w, a, plane, mod->act_mtp, M);
     int ct = 0;
-    rs_plan(w.N, w.K, M, mod->part_floats, rs_cts, &ct, &A.S);    // (nine row tiles: QKV 34 us in 12 tiles and 4 splits, 36.9 in 6 and 2)
+    rs_plan(w.N, w.K, M, mod->part_floats, &ct, &A.S);
     A.part = mod->part;
     *S_used = A.S;
     return rs_launch(A, ct, st);
