@@ -436,15 +436,27 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
     return mod->cfg.dtype == CSD_DTYPE_BF16 ? f32_launch<bf16_t, FG_PART, false>(P, st) : f32_launch<float, FG_PART, false>(P, st);
 }
 
-// Whether the launch of a layer per row takes the model and the call: every product's columns over the threads, at most PER values
-// of a column in each, at most one workgroup per compute unit; the scores of a row in LDS.  Not while csd_prof_read asks for the time of each
+// Whether the launch of a layer per row takes the model and the call: every product's columns over the threads, at most 32 values
+// of a column in each, at most one workgroup per compute unit, the scores of a row in LDS.  Not while csd_prof_read asks for the time of each
 // class of kernels, which one launch cannot tell apart.
+// And only where it is the faster form when the cache is full.  One compute unit does the attention of a row over all heads, where k_attn_simple has a
+// workgroup per head: its keys and values take longer than what four launches a layer cost once heads x features x keys is large, and sooner where a
+// head's keys are not read 16 values at a time.  Forward of two layers of 32 features in us, this form / five launches per layer, one row of a
+// block, full cache: 4 heads of 16, 500 / 2000 / 2600 keys 37 / 48, 73 / 76, 88 / 88; 8 of 16, 120 / 250 / 376 keys 33 / 41, 42 / 43, 51 / 47; 3 of 64,
+// 120 / 376 keys 41 / 49, 71 / 67; 8 of 8, 184 / 376 keys 38 / 40, 51 / 43; 3 of 30, 120 / 376 keys 37 / 45, 63 / 54; 1 of 128, 2600 / 10500 keys
+// 248 / 441, 926 / 1648; 16 of 16 with 5 rows, 56 / 120 keys 42 / 46, 57 / 47.  More rows gain more (256 rows, 4 of 16, 500 / 2600 keys 43 / 82, 98 / 215).
 static bool row_product_fits(int K, int N, int per) { return N >= 16 && N <= FR_THREADS && (K + FR_THREADS / N - 1) / (FR_THREADS / N) <= per; }
+static bool row_attention_fits(int H, int dh, int keys) {
+    const long long hd = (long long)H * dh;
+    if ((long long)H * keys > 10240) return false;
+    if (dh % 16 == 0) return H == 1 || hd <= 64 || hd * keys <= 24576;
+    return hd * keys <= 12288;
+}
 static bool f32_rows_fit(const csd_model *mod, int M) {
     const csd_model_cfg &c = mod->cfg;
     const int d = c.d_model, hd = mod->hd, F = c.d_ffn;
-    return !mod->prof && M <= 256 && (long long)c.n_heads * mod->seq_pad <= 11000 && row_product_fits(hd, d, 8) && row_product_fits(d, 2 * F, 32) &&
-           row_product_fits(F, d, 16) && row_product_fits(d, 3 * hd, 32) && row_product_fits(d, c.vocab, 32);
+    return !mod->prof && M <= 256 && row_attention_fits(c.n_heads, c.head_dim, mod->seq_pad) && row_product_fits(hd, d, 8) &&
+           row_product_fits(d, 2 * F, 32) && row_product_fits(F, d, 16) && row_product_fits(d, 3 * hd, 32) && row_product_fits(d, c.vocab, 32);
 }
 static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const int32_t *cache_len, int M, int m, float *logits,
                                 hipStream_t st) {

@@ -407,11 +407,13 @@ def test_fp32_forward(P, dims, B, m, t):
 
 @pytest.mark.parametrize("dims,B,m,t,max_seq", [
     ((128, 4, 12, 40, 200), 2, 5, 31, 64), ((40, 1, 130, 9, 129), 1, 3, 70, 128), ((32, 2, 10, 512, 1024), 3, 4, 9, 32), ((16, 1, 6, 8, 16), 1, 2, 0, 8),
-    ((32, 2, 16, 24, 50), 4, 64, 10, 80), ((32, 2, 16, 24, 50), 4, 65, 10, 80), ((32, 4, 8, 24, 50), 1, 3, 2600, 2688), ((32, 4, 8, 24, 50), 1, 3, 2750, 2816)],
+    ((32, 2, 16, 24, 50), 4, 64, 10, 80), ((32, 2, 16, 24, 50), 4, 65, 10, 80), ((32, 4, 8, 24, 50), 1, 3, 2600, 2688), ((32, 4, 8, 24, 50), 1, 3, 2750, 2816),
+    ((40, 1, 130, 9, 129), 1, 3, 50, 64), ((32, 4, 16, 24, 50), 1, 3, 2550, 2560), ((32, 1, 16, 24, 50), 1, 3, 10230, 10240), ((16, 16, 16, 24, 50), 1, 3, 50, 64),
+    ((32, 8, 16, 24, 50), 2, 9, 180, 192), ((32, 3, 30, 24, 50), 2, 9, 110, 128)],
     ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
 def test_small_fp32_models(P, dims, B, m, t, max_seq):
     """The forward of a workgroup per block row at the edges of what it takes: most values per thread in each product, 1024 and 16 columns, heads
-    whose keys are not read 16 values at a time, 256 rows and more, the most scores in LDS and more."""
+    whose keys are not read 16 values at a time, 256 rows and more, the most scores in LDS, the most features times keys of either kind of head, and more."""
     from gpu_util import import_synthetic_kv, make_pair, tol_ok
     d, H, dh, F, V = dims
     shape = I.ModelShape("edge_small", 0, "fp32", 2, d, H, dh, F, V)
@@ -456,6 +458,24 @@ def test_accept_at_the_longest_row_in_registers(P, V, kind):
         n, tok = n.cpu().numpy(), tok.cpu().numpy()
         assert np.array_equal(n[:s], wn) and np.array_equal(tok[:s], wt), (kind, dense is None)
         assert (n[s:] == 0).all() and (tok[s:] == -1).all()
+
+
+@pytest.mark.parametrize("H,dh,max_seq,row_form", [
+    (4, 16, 2560, True), (4, 16, 2561, False), (1, 64, 10240, True), (1, 64, 10241, False), (2, 32, 1024, True), (8, 16, 192, True), (8, 16, 193, False),
+    (3, 32, 256, True), (3, 32, 257, False), (3, 64, 128, True), (3, 64, 129, False), (16, 16, 64, True), (16, 16, 65, False), (2, 10, 576, True),
+    (2, 10, 577, False), (3, 30, 128, True), (3, 30, 129, False), (8, 8, 192, True), (8, 8, 193, False), (1, 300, 64, False)])
+def test_small_fp32_models_with_long_caches(P, H, dh, max_seq, row_form):
+    """The forward of a workgroup per block row is taken where it is the faster one with a full cache: heads x features x keys bounded, the bound half as
+    large for heads whose keys are not read 16 values at a time.  While the profile is on, the other form runs: where that is the form in
+    any case, the logits are the same bit for bit."""
+    shape = I.ModelShape("edge_rule", 0, "fp32", 2, 24, H, dh, 40, 300)
+    gm = P.Model(shape, I.make_weights(shape, 9, device="cuda", std=0.3), max_batch=1, max_seq=max_seq, max_block=8)
+    block, cl = I.token_ids(8, 300, 9, 1).reshape(1, 8).to(torch.int32).cuda(), torch.zeros(1, dtype=torch.int32, device="cuda")
+    plain = gm.verify_block(block, cl)
+    gm.prof_enable(True)
+    other = gm.verify_block(block, cl)
+    assert torch.equal(plain, other) == (not row_form)
+    assert ((plain - other).abs() <= 1e-4 + 1e-4 * plain.abs()).all()
 
 
 def test_profile_of_an_fp32_forward(P):
