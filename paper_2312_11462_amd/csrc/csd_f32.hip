@@ -448,7 +448,7 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
 static bool row_product_fits(int K, int N, int per) { return N >= 16 && N <= FR_THREADS && (K + FR_THREADS / N - 1) / (FR_THREADS / N) <= per; }
 static bool row_attention_fits(int H, int dh, int keys) {
     const long long hd = (long long)H * dh;
-    if ((long long)H * keys > 10240) return false;
+    if ((long long)H * keys > 11000) return false;
     if (dh % 16 == 0) return H == 1 || hd <= 64 || hd * keys <= 24576;
     return hd * keys <= 12288;
 }

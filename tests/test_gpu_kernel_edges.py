@@ -408,7 +408,7 @@ def test_fp32_forward(P, dims, B, m, t):
 @pytest.mark.parametrize("dims,B,m,t,max_seq", [
     ((128, 4, 12, 40, 200), 2, 5, 31, 64), ((40, 1, 130, 9, 129), 1, 3, 70, 128), ((32, 2, 10, 512, 1024), 3, 4, 9, 32), ((16, 1, 6, 8, 16), 1, 2, 0, 8),
     ((32, 2, 16, 24, 50), 4, 64, 10, 80), ((32, 2, 16, 24, 50), 4, 65, 10, 80), ((32, 4, 8, 24, 50), 1, 3, 2600, 2688), ((32, 4, 8, 24, 50), 1, 3, 2750, 2816),
-    ((40, 1, 130, 9, 129), 1, 3, 50, 64), ((32, 4, 16, 24, 50), 1, 3, 2550, 2560), ((32, 1, 16, 24, 50), 1, 3, 10230, 10240), ((16, 16, 16, 24, 50), 1, 3, 50, 64),
+    ((40, 1, 130, 9, 129), 1, 3, 50, 64), ((32, 4, 16, 24, 50), 1, 3, 2680, 2688), ((32, 1, 16, 24, 50), 1, 3, 10930, 10944), ((16, 16, 16, 24, 50), 1, 3, 50, 64),
     ((32, 8, 16, 24, 50), 2, 9, 180, 192), ((32, 3, 30, 24, 50), 2, 9, 110, 128)],
     ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
 def test_small_fp32_models(P, dims, B, m, t, max_seq):
@@ -461,7 +461,7 @@ def test_accept_at_the_longest_row_in_registers(P, V, kind):
 
 
 @pytest.mark.parametrize("H,dh,max_seq,row_form", [
-    (4, 16, 2560, True), (4, 16, 2561, False), (1, 64, 10240, True), (1, 64, 10241, False), (2, 32, 1024, True), (8, 16, 192, True), (8, 16, 193, False),
+    (4, 16, 2688, True), (4, 16, 2689, False), (1, 64, 10944, True), (1, 64, 10945, False), (2, 32, 1024, True), (8, 16, 192, True), (8, 16, 193, False),
     (3, 32, 256, True), (3, 32, 257, False), (3, 64, 128, True), (3, 64, 129, False), (16, 16, 64, True), (16, 16, 65, False), (2, 10, 576, True),
     (2, 10, 577, False), (3, 30, 128, True), (3, 30, 129, False), (8, 8, 192, True), (8, 8, 193, False), (1, 300, 64, False)])
 def test_small_fp32_models_with_long_caches(P, H, dh, max_seq, row_form):
