@@ -311,3 +311,62 @@ def test_review_of_fewer_rows_than_the_call_has_room_for(H, dh, max_seq, B):
         assert torch.equal(cache, start + 1 + n_ref)
     gm.close()
     ref.close()
+
+
+@pytest.mark.parametrize("mode,lenience", [(0, 1.0), (0, 2.0), (1, 1.0), (1, 2.0)])
+@pytest.mark.parametrize("B", [1, 2])
+@pytest.mark.parametrize("arch,H,dh,max_seq", [(0, 4, 64, 192), (0, 2, 128, 1088), (1, 4, 64, 192), (1, 4, 64, 1088), (1, 2, 128, 192), (1, 2, 128, 1088)])
+def test_review_after_nan_everywhere(arch, H, dh, max_seq, B, mode, lenience):
+    """csd_review_ctx with room for 16 rows after a call that left NaN in every buffer of the model and in the cache behind the kept rows: reviews of
+    fewer rows, after a call in which every sequence is skipped and beside a skipped one, decide as a plain review of exactly those rows does, and the
+    rows they hand on are its probabilities.  Both architectures, self- and cross-attention in either form for short blocks."""
+    import paper_2312_11462_amd as P
+    shape = I.ModelShape("live", arch, "bf16", 2, 256, H, dh, 512, 1024, rms_eps=1e-6 if arch else 1e-5, enc_len=90 if arch else 0)
+    w = I.make_weights(shape, 5, device="cuda", std=0.05)
+    gm = P.Model(shape, w, max_batch=B, max_seq=max_seq, max_block=16)
+    ref = P.Model(shape, w, max_batch=B, max_seq=max_seq, max_block=16)
+    t, i32, V = 20, dict(dtype=torch.int32, device="cuda"), shape.vocab
+    tok = torch.stack([I.token_ids(48, V, 5, b) for b in range(B)]).to(torch.int32).cuda()
+    gm.kv.view(torch.uint8).fill_(0xFF)
+    probs = torch.empty((B, 16, V), device="cuda")
+    gm.verify_accept(tok[:, :16].contiguous(), torch.full((B,), 100, **i32), None, None, mode=1)
+    gm.verify_block(tok[:, :16].contiguous(), torch.full((B,), 100, **i32), logits=probs, probs=probs)
+    assert probs.isnan().all()
+    gm.kv.view(torch.uint8).fill_(0xFF)
+    for m in (gm, ref):
+        if arch:
+            m.cross_kv_init(I.encoder_output(shape, B, 5).cuda())
+        for pos in (0, 10):
+            m.verify_block(tok[:, pos:pos + 10].contiguous(), torch.full((B,), pos, **i32))
+    cache, length = torch.full((B,), t, **i32), torch.full((B,), t, **i32)
+    ctx, skip = tok.clone(), torch.full((B,), -1, **i32)
+    status, n_acc, nxt = (torch.zeros(B, **i32) for _ in range(3))
+    u_acc, u_samp = I.uniforms(B * 48, 5, 1).reshape(B, 48).cuda(), I.uniforms(B * 48, 5, 2).reshape(B, 48).cuda()
+    u_acc[:, ::2] = 0.0                                      # (kept whatever their probability)
+    out_q, base = torch.full((B, 48, V), float("nan"), device="cuda"), torch.zeros(B, **i32)
+
+    def review(prefix):
+        gm.review_ctx(ctx, length, cache, prefix, 16, status, u_acc_tab=u_acc, u_samp_tab=u_samp, out_q_tab=out_q, out_base=base, n_accepted=n_acc,
+                      next_token=nxt, mode=mode, lenience=lenience)
+
+    for rows in (6, 1, 4):
+        start = cache.clone()
+        length.copy_(start + rows)
+        review(skip)
+        assert (status == 1).all() and torch.equal(length, start + rows) and torch.equal(cache, start)
+        at = start.long()[:, None] + 1 + torch.arange(rows, device="cuda")
+        block = torch.gather(ctx, 1, at - 1).contiguous()
+        p_ref = torch.empty((B, rows, V), device="cuda")
+        n_ref, nxt_ref = ref.verify_accept(block, start, torch.gather(u_acc, 1, at[:, :-1]).contiguous(), torch.gather(u_samp, 1, at[:, :1])[:, 0].contiguous(),
+                                           mode=mode, lenience=lenience, probs=p_ref)
+        for turn in range(B):                                # all but one sequence skipped, one after the other
+            review(torch.where(torch.arange(B, device="cuda") == turn, start + 1, skip))
+            n = int(n_ref[turn])
+            assert int(status[turn]) == 0 and int(n_acc[turn]) == n and int(nxt[turn]) == int(nxt_ref[turn])
+            if mode == 0:
+                first = int(start[turn]) + 1
+                assert torch.allclose(out_q[turn, first:first + n + 1], p_ref[turn, :n + 1], rtol=2e-2, atol=1e-6)
+            length[turn] = cache[turn] + 1
+        assert torch.equal(cache, start + 1 + n_ref)
+    gm.close()
+    ref.close()
