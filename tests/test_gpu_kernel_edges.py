@@ -302,7 +302,8 @@ def test_tall_sums_are_no_further_from_64_bits_than_row_split_ones(P, K, V, m):
     22016 columns at 512 rows) against 64 bits, beside the same rows on the row-split form.  The embedding rows are bf16, so the
     planes hold them exactly and what is left is the rounding of the sums, 2 to 5 units of 2^-24 of their size here; the scale of a
     row (one rounded number) is taken out.  Two draws of a row set differ by 1 % at most; one chain through all of K is 40 % to
-    190 % above the row-split form."""
+    190 % above the row-split form.  That form by itself: a chain of K / 32 steps, whose sums grow as the square root, each rounded by 0.29 to 0.58 units
+    of its size, ends within 0.58 sqrt(K / 64) of the last one's size, and the splits leave shorter ones; a sum that misses one step of K / 32 is off by 10^5 units."""
     g = torch.Generator(device="cuda").manual_seed(K + V)
     emb = torch.empty((V, K), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
     lm = torch.empty((K, V), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
@@ -316,15 +317,24 @@ def test_tall_sums_are_no_further_from_64_bits_than_row_split_ones(P, K, V, m):
 
     split, tall = error(128), error(m)
     print(K, V, m, "row-split", split, "tall", tall)
+    assert split < 1 + 0.58 * (K / 64) ** 0.5
     assert tall < 1.03 * split
 
 
-@pytest.mark.parametrize("K,V", [(96, 528), (544, 12304), (4096, 4096)])
+def _rows_plan(P, N, K, rows):
+    v = [C.c_int32(), C.c_int32()]
+    assert P.lib().csd_debug_gemm_plan(N, K, rows, 8, *[C.byref(x) for x in v]) == 0
+    return tuple(x.value for x in v)
+
+
+@pytest.mark.parametrize("K,V,plan", [(96, 528, (6, 1)), (544, 12304, (8, 2)), (4096, 4096, (8, 8)), (4096, 22016, (11, 2)), (4096, 12288, (12, 4)),
+                                      (768, 32000, (16, 2))])
 @pytest.mark.parametrize("m", [33, 48, 49, 64, 65, 96, 97, 128, 129, 144])
-def test_row_split_sums(P, K, V, m):
-    """The GEMM over 33 to 144 rows in each of its forms (one to three row tiles on three or four waves, the first and last row count
-    of each), with K slices shorter than the stages in flight, slices that end inside a turn, and ragged column groups.  A sum of K
+def test_row_split_sums(P, K, V, plan, m):
+    """The GEMM over 33 to 144 rows in each of its forms: the five widths, one to three row tiles on three or four waves with the first and last
+    row count of each, K slices shorter than the stages in flight, slices that end inside a turn, and ragged column groups.  A sum of K
     exact products in 32 bits is within K 2^-23 of the sum of their sizes, the scale of the row and the partial sums add a few units."""
+    assert _rows_plan(P, V, K, m) == plan
     g = torch.Generator(device="cuda").manual_seed(K + m)
     emb = torch.empty((V, K), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
     lm = torch.empty((K, V), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
@@ -387,13 +397,16 @@ def _check_cross_projection(P, B, enc_len, max_block):
 @pytest.mark.parametrize("dims", [(48, 3, 16, 100, 301), (64, 4, 16, 256, 512), (33, 3, 2, 65, 70), (40, 1, 130, 7, 129), (300, 5, 64, 90, 65)],
                          ids=lambda d: "-".join(map(str, d)))
 @pytest.mark.parametrize("B,m,t", [(1, 1, 1), (2, 4, 30), (1, 9, 400), (3, 17, 63)])
-def test_fp32_forward(P, dims, B, m, t):
+@pytest.mark.parametrize("form", ["by_rule", "five_launches"])
+def test_fp32_forward(P, dims, B, m, t, form):
     """The fp32 GEMMs (K slices shorter than a turn, ragged column groups and rotary pairs, rows across workgroups) and the
-    generic attention (heads narrower and wider than the groups of its threads, few and many keys)."""
+    generic attention (heads narrower and wider than the groups of its threads, few and many keys).  They run for every model while the
+    profile is on; by the rule, some of these models take the form of a workgroup per block row."""
     from gpu_util import import_synthetic_kv, make_pair, tol_ok
     d, H, dh, F, V = dims
     shape = I.ModelShape("edge_fp32", 0, "fp32", 2, d, H, dh, F, V)
     gm, om = make_pair(shape, 31, B, t + m + 3, m, std=0.1)
+    gm.prof_enable(form == "five_launches")
     import_synthetic_kv(gm, om, shape, t, 31, B=B)
     block = I.token_ids(B * m, V, 31, 1).reshape(B, m).numpy().astype(np.int32)
     cl = np.asarray([max(0, t - 5 * b) for b in range(B)], np.int32)
@@ -458,6 +471,34 @@ def test_accept_at_the_longest_row_in_registers(P, V, kind):
         n, tok = n.cpu().numpy(), tok.cpu().numpy()
         assert np.array_equal(n[:s], wn) and np.array_equal(tok[:s], wt), (kind, dense is None)
         assert (n[s:] == 0).all() and (tok[s:] == -1).all()
+
+
+@pytest.mark.parametrize("V", [1, 3, 4, 254, 256, 260, 4096, 8196, 32764, 32766, 32768, 32772])
+def test_arg_max_of_rows_with_nan_and_without_finite_values(P, V):
+    """The greedy rule's own token, in registers and in the general way: NaN never wins, the lowest index among equals does, a row of -inf gives its first
+    token that is not NaN, a row of NaN the first token."""
+    g = torch.Generator().manual_seed(V)
+    rows = torch.randn((9, V), generator=g)
+    rows[1] = float("nan")
+    rows[2] = float("-inf")
+    rows[3] = float("-inf")
+    rows[3, :V // 2] = float("nan")
+    rows[4, torch.randperm(V, generator=g)[:V // 2]] = float("nan")
+    rows[5, [V // 3, V - 1]] = float("inf")
+    rows[6, V // 2:] = rows[6].max() + 1.0
+    rows[7, :V - 1] = float("nan")
+    rows[8] = float("nan")
+    rows[8, V // 2] = float("-inf")
+    most = torch.where(rows.isnan(), torch.tensor(float("-inf")), rows).max(1, keepdim=True).values
+    want = (rows == most).numpy().argmax(1).tolist()         # (NaN equals nothing; numpy gives the first)
+    # two reviewer rows per sequence: a draft that is not the arg-max, so the first row decides; then drafts that are, so the second does
+    p = torch.stack([rows, rows.roll(1, 0)], 1).contiguous().cuda()
+    u, us = torch.zeros((9, 1), device="cuda"), torch.zeros(9, device="cuda")
+    miss = torch.full((9, 1), V, dtype=torch.int32, device="cuda")
+    n, tok = P.accept(p, None, miss, u, us, 1.0, 1)
+    assert n.tolist() == [0] * 9 and tok.tolist() == want
+    n, tok = P.accept(p, None, torch.tensor(want, dtype=torch.int32, device="cuda")[:, None].contiguous(), u, us, 1.0, 1)
+    assert n.tolist() == [1] * 9 and tok.tolist() == want[-1:] + want[:-1]
 
 
 @pytest.mark.parametrize("H,dh,max_seq,row_form", [

@@ -62,8 +62,11 @@ def _check_tree(gm, om, tokens, parent, cl, rtol, atol, what):
     return err
 
 
-def test_fp32_generic_kernels_two_sequences_ragged():
+@pytest.mark.parametrize("form", ["by_rule", "five_launches"])
+def test_fp32_generic_kernels_two_sequences_ragged(form):
+    """By the rule a model as small as this takes the form of a workgroup per block row; while the profile is on, the kernels of larger models."""
     gm, om = make_pair(FP, 5, 2, 96, 16, std=0.1)
+    gm.prof_enable(form == "five_launches")
     toks = I.token_ids(2 * 40, FP.vocab, 5, 1).reshape(2, 40)
     prefill_both(gm, om, toks[:, :20], 10)
     rng = np.random.default_rng(2)
