@@ -22,15 +22,26 @@
 
 #define RS_SETS 4             /* k-steps of activations in registers; as many stages of weights, and one in use, in LDS */
 
-template <int CT>
-static constexpr int rs_lds() { return (RS_SETS + 1) * CT * 1024; }
+// A stage's weight tiles, with four waves also places for what the padding loads write.
+template <int CT, int NW>
+static constexpr int rs_tiles() { return NW == 4 ? (CT + 3) / 4 * 4 : CT; }
+template <int CT, int NW>
+static constexpr int rs_lds() { return (RS_SETS + 1) * rs_tiles<CT, NW>() * 1024; }
 
 template <int CT, int RW, int NW>
 __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
     extern __shared__ __align__(16) char rs_smem[];
-    constexpr int PW = (CT + NW - 1) / NW;                       // weight loads per wave and k-step (the last tile again past the end)
+    constexpr int PW = (CT + NW - 1) / NW;                       // weight loads per wave and k-step
     constexpr int AL = 2 * RW, NA = RS_SETS - 1, NST = RS_SETS + 1;
     constexpr int RA = 4;                                        // weight fragments read ahead
+    // Every wave issues the same loads in every k-step but the last few, so the waits can count them, and some of them bring nothing that is used:
+    // k-steps past the slice (a turn of k-steps that ends with it requests three or four), and the waves' last tiles where CT is no multiple of the
+    // waves.  With four waves those are out of the buffer, where a load reads no memory; re-reading the slice's last k-step, or the last tile into its own place, cost
+    // 2 to 3 % of a call (7B shape, eight layers and the LM head, 128 rows 1485 -> 1438 us, 64 rows 1124 -> 1103; twelve layers of the 160M shape 809 -> 784 and
+    // 627 -> 614).  With three waves the selects cost as much as that or more (72 rows 1226 against 1232, 160M shape, 136 rows 824 against 835; 40 rows
+    // 1010 against 1002), and everything past an end is read as the last one.
+    constexpr bool SKIP = NW == 4;
+    constexpr int TILES = rs_tiles<CT, NW>();
     const ChainGemm &P = A.g;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -43,8 +54,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
     const __amdgpu_buffer_rsrc_t rw = ch_rsrc(P.Wp, (size_t)P.wbytes);
     const __amdgpu_buffer_rsrc_t ra =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(P.a), 0, (int)(2u * (unsigned)P.a_plane_bytes), 0x00020000);
-    // Column tiles and row tiles past the end are read as the last one, k-steps past the slice likewise (their sums are not
-    // stored, or not made): every address is inside, and every wave issues the same loads, so the waits can count them.
+    // Column tiles and row tiles past the end are read as the last one (their sums are not stored): every address is inside the matrix,
+    // or outside the buffer.
     int wbase[PW];
 #pragma unroll
     for (int i = 0; i < PW; i++) wbase[i] = min(tile0 + min(i * NW + w, CT - 1), A.n_tiles - 1) * P.KS * 1024;
@@ -53,12 +64,16 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
     for (int r = 0; r < RW; r++) abase[r] = min(rt0 + r, (P.M - 1) >> 4) * 1024;
     const int vw = lane * 16, va = (4 * (lane & 15) + (lane >> 4)) * 16;     // see act_tiled_idx
     auto load_w = [&](int i, int k, int buf) {
-        lds_load16<2>(rw, (lds_void)(rs_smem + (buf * CT + min(i * NW + w, CT - 1)) * 1024), vw, wbase[i] + min(k, ks1 - 1) * 1024);
+        const int t = i * NW + w;
+        const bool none = SKIP && (t >= CT || k >= ks1);         // (uniform)
+        lds_load16<2>(rw, (lds_void)(rs_smem + (buf * TILES + (SKIP ? t : min(t, CT - 1))) * 1024), none ? CH_OOB : vw,
+                      none ? 0 : wbase[i] + min(k, ks1 - 1) * 1024);
     };
     u32x4 fa[RS_SETS][RW][2];
     auto load_a = [&](int i, int k, int set) {
-        const unsigned off = abase[i >> 1] + (unsigned)(min(k, ks1 - 1) * P.mtp) * 1024u + (i & 1 ? (unsigned)P.a_plane_bytes : 0u);
-        fa[set][i >> 1][i & 1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, va, (int)off, 0));
+        const bool none = SKIP && k >= ks1;                      // (uniform; in planes of more than 2 GiB together it is read at 2 GiB)
+        const unsigned off = none ? 0u : abase[i >> 1] + (unsigned)(min(k, ks1 - 1) * P.mtp) * 1024u + (i & 1 ? (unsigned)P.a_plane_bytes : 0u);
+        fa[set][i >> 1][i & 1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, none ? CH_OOB : va, (int)off, 0));
     };
     f32x4 acc[RW][CT];
 #pragma unroll
@@ -88,9 +103,9 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
         constexpr int E = decltype(END)::value;
         wait_loads<(E ? NA - E : NA - 1) * (PW + AL)>();         // W(k + 1), this wave's share
         stage_barrier();
-        const u32x4 *Lc = L + cur * CT * 64;
+        const u32x4 *Lc = L + cur * TILES * 64;
         const int nxt = cur + 1 == NST ? 0 : cur + 1;
-        const u32x4 *Ln = L + nxt * CT * 64;
+        const u32x4 *Ln = L + nxt * TILES * 64;
 #pragma unroll
         for (int c = 0; c < CT; c++) {
             f[c + RA] = c + RA < CT ? Lc[(c + RA) * 64] : Ln[(c + RA - CT) * 64];
@@ -141,13 +156,14 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
 
 // ------------------------------------------------------------------------------- host driver
 
-// Waves and row tiles per wave for 3 to 9 row tiles: as many waves as fill without a tile that is all padding, nine as three of three.
+// Waves and row tiles per wave for 3 to 9 row tiles: three or four waves of one, two or three.  5 and 7 row tiles (65 to 80, 97 to 112 rows) are
+// 3 and 4 waves of two, the last one's second tile all padding.
 #define RS_FOR_ALL_ROWS(X) X(1, 3) X(1, 4) X(2, 3) X(2, 4) X(3, 3)
 #define RS_FOR_ALL_CT(X, RW, NW) X(16, RW, NW) X(12, RW, NW) X(11, RW, NW) X(8, RW, NW) X(6, RW, NW)
 
 template <int CT, int RW, int NW>
 static hipError_t rs_allow_lds() {
-    return hipFuncSetAttribute((const void *)k_gemm_rs<CT, RW, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, rs_lds<CT>());
+    return hipFuncSetAttribute((const void *)k_gemm_rs<CT, RW, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (rs_lds<CT, NW>()));
 }
 
 int32_t csd_rows_setup() {
@@ -188,7 +204,7 @@ int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats,
 template <int CT, int RW, int NW>
 static int32_t rs_launch_t(const TallArgs &A, hipStream_t st) {
     const int grid = (A.n_tiles + CT - 1) / CT * A.S;
-    hipLaunchKernelGGL((k_gemm_rs<CT, RW, NW>), dim3(grid), dim3(NW * 64), rs_lds<CT>(), st, A);
+    hipLaunchKernelGGL((k_gemm_rs<CT, RW, NW>), dim3(grid), dim3(NW * 64), (rs_lds<CT, NW>()), st, A);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
