@@ -86,10 +86,14 @@ def _ptr(t, dtype=None):
     return C.c_void_p(t.data_ptr())
 
 
+# (not a public name: a build of torch without it takes the public way)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream():
     """The current device's current stream.  Its handle alone: torch.cuda.current_stream() makes an object around it, 2.8 us a call
     against 0.2, which the smallest calls (10 us of kernels) waited for."""
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return C.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 class Model:

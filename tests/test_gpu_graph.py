@@ -70,3 +70,13 @@ def test_captured_step_replays_to_the_eager_result(static):
         gm.verify_block(toks[None, 8:16].contiguous().cuda(), torch.tensor([8], dtype=torch.int32).cuda())
     torch.cuda.synchronize()
     assert not torch.equal(want0[0], lg)       # the last replay saw other inputs than the first eager run
+
+
+def test_calls_go_to_the_current_stream():
+    """The stream that the binding hands on is torch's current one of the current device, by whichever way it asks for it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2312_11462_amd import binding
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            assert (binding._stream().value or 0) == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
