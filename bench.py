@@ -257,6 +257,7 @@ def main():
     # the dominant kernel: the weight-streaming GEMM.  One launch streams one matrix; the per-launch figures are
     # the step's weights over the step's GEMM launches.
     kernel = ("kc_gemm (GEMMs that own whole output tiles and hold their epilogues)" if path == 1 else
+              "k_f32_gemm (the form that the profile times; small models otherwise run k_f32_row)" if shape.dtype == "fp32" else
               ("k_gemm_rs" if B * m > 32 else "k_gemm_ws") + " (split-K GEMMs with epilogue kernels)") + \
              ": all weight-streaming GEMM launches of a step"
     launch_bytes = ab["weights"]

@@ -252,7 +252,9 @@ typedef struct csd_review {
 /*
  * One review.  Block of sequence b = ctx[b][cache_len[b] .. ctx_len[b]) (at most m_max rows, else status 2): rows the
  * reviewer has not cached yet, ending with the drafts ctx[b][prefix_len[b] .. ctx_len[b]).  The forward runs over
- * m_max rows per sequence (zero tokens as padding; their cache rows lie beyond the kept length), then accept /
+ * m_max rows per sequence (zero tokens as padding, of which nothing is defined: neither what is computed for them nor
+ * what their cache rows, which lie beyond the kept length, then hold; the same goes for all rows of a skipped
+ * sequence), then accept /
  * resample as csd_accept does, with k = ctx_len - prefix_len drafts per sequence, draft distributions and uniforms
  * taken by position, then the commit: ctx[prefix + n] = the reviewer's token, ctx_len = prefix + n + 1, cache_len =
  * prefix + n, lower levels' cache lengths = min(theirs, prefix + n), the reviewer's rows of the n + 1 emitted tokens
@@ -361,7 +363,10 @@ int32_t csd_debug_mfma(int64_t iters, uint32_t *sink, void *stream);
  * it launches with a pair of HIP events on the caller's stream (this perturbs the step, so
  * throughput is timed with the hook off).  After the caller has synchronised the stream,
  * csd_prof_read adds up the bracketed milliseconds and launch counts per kernel class since
- * the last reset: class 0 = weight-streaming GEMMs, 1 = attention, 2 = everything else. */
+ * the last reset: class 0 = weight-streaming GEMMs, 1 = attention, 2 = everything else.
+ * Small fp32 models otherwise run one launch per layer, which is all classes at once; while enabled they run the
+ * kernels of larger fp32 models instead (five launches per layer): the times say how a step divides between the
+ * classes, not how long it takes with the hook off, and the logits may differ in rounding. */
 int32_t csd_prof_enable(csd_model *model, int32_t on);
 int32_t csd_prof_read(csd_model *model, int32_t kernel_class, double *ms, int64_t *launches, int32_t reset);
 

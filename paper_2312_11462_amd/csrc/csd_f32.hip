@@ -6,7 +6,8 @@
 // the tiny shape, K = 64 and 256); here K is split over the eight waves of a workgroup, a wave requests eight rows of its
 // slice at once, the eight partial sums meet in LDS, and whatever follows a GEMM (rotary embedding and cache append, residual
 // sum, gated activation, the scale of the folded norm) runs on them in the same kernel, which computes the norm of its input
-// rows along the way: five launches per layer of 3 to 6 us.  Tiny shape, verify step: 363 -> 67 us.
+// rows along the way: five launches per layer of 3 to 6 us.  Tiny shape, verify step, before the small models got a form of their own
+// (below; the tiny shape runs here only while the profile is on): 363 -> 67 us.
 #include <cmath>
 
 #include "csd_internal.h"
@@ -166,7 +167,8 @@ __global__ __launch_bounds__(256) void k_f32_embed(const int32_t *__restrict__ t
 // chain of LDS steps and barriers, and the instruction fetches of code that runs once: with every loop unrolled and integer divisions
 // (25 KB) a layer took 20.8 us, in 11 KB 12.6.  The weights of a product are requested one product ahead, a thread holding up to 32 values of
 // one column.  Tiny shape (64 features, 4 heads, 256 hidden, 512 tokens, 2 layers), verify step with 5 rows: 66 us in five launches per
-// layer, 40 in one.
+// layer, 40 in one.  With up to twice the values per thread (the second set of instances), the forward alone, 5 rows over 32 cached: 128 features, 4 heads
+// of 16, 128 hidden, 256 tokens 49 us in five launches per layer, 31 in one; 96, 4 of 16, 160, 340: 50 and 31 (tiny shape: 46 and 30).
 #define FR_THREADS 1024
 #define FR_X (FR_THREADS + 64)        /* an input row, zero past its end up to a multiple of the slices */
 struct RowProduct {
@@ -437,8 +439,8 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
 }
 
 // Whether the launch of a layer per row takes the model and the call: every product's columns over the threads, at most 32 values
-// of a column in each, at most one workgroup per compute unit, the scores of a row in LDS.  Not while csd_prof_read asks for the time of each
-// class of kernels, which one launch cannot tell apart.
+// of a column in each, at most one workgroup per compute unit, the scores of a row in LDS.  Not while the profile is on (see csd_prof_enable):
+// one launch is GEMM, attention and the rest at once, and its classes cannot be told apart.
 // And only where it is the faster form when the cache is full.  One compute unit does the attention of a row over all heads, where k_attn_simple has a
 // workgroup per head: its keys and values take longer than what four launches a layer cost once heads x features x keys is large, and sooner where a
 // head's keys are not read 16 values at a time.  Forward of two layers of 32 features in us, this form / five launches per layer, one row of a
@@ -491,7 +493,6 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
     const size_t lds = sizeof(float) * (size_t)c.n_heads * mod->seq_pad;
     const bool few = row_product_fits(mod->hd, d, 4) && row_product_fits(d, 3 * mod->hd, 16);
     for (int l = -1; l < L; l++) {                               // layer l, and the QKV projection of the next one
-        ProfScope ps(mod, st, CSD_PROF_GEMM);
         const GemmW &next = l + 1 < L ? mod->layers[l + 1].qkv : mod->lm;
         P.next = product(next);
         P.next_gain = l + 1 < L ? mod->layers[l + 1].attn_norm : mod->final_norm;
