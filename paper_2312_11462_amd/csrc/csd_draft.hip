@@ -5,34 +5,36 @@
 #define DRAFT_THREADS 256
 #define FIT_THREADS 1024
 
-// Max over the block of a 64-bit key; every thread gets the result.
-__device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v, unsigned long long *red) {
+// Max over the first `waves` waves of the workgroup of a 64-bit key; every thread of them gets the result.
+__device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v, unsigned long long *red, int waves) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         unsigned long long other = __shfl_xor(v, o, 64);
         v = other > v ? other : v;
     }
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     unsigned long long t = red[0];
-    for (int i = 1; i < nw; i++) t = red[i] > t ? red[i] : t;
+    for (int i = 1; i < waves; i++) t = red[i] > t ? red[i] : t;
     return t;
 }
 
-// The tokens of a sequence go to LDS: every thread compares positions backwards, a chain of dependent reads that cost a trip to L2
-// each where they went to memory (4000 tokens 6.7 us with 256 threads, 5.3 in LDS with 1024).  Longer sequences are read where they are.
+// Rows with room for more than DRAFT_FEW tokens take workgroups of 1024 threads, which bring a sequence of up to DRAFT_LDS tokens to LDS: every
+// thread compares positions backwards, a chain of dependent reads that cost a trip to L2 each where they go to memory (4000 tokens 6.2 us with
+// 256 threads that read memory, 5.0 in LDS with 1024; 8000 tokens 10.1 and 6.1).  Longer sequences are read where they are (20000 tokens, 256 and 1024
+// threads 21.4 and 9.7).  Up to DRAFT_FEW tokens 256 threads that read memory are the faster form (500 tokens 2.6 us against 4.2, 2040 4.0 against
+// 4.4), and in a row with room for more the other waves leave at once (2.9 and 4.1).
+#define DRAFT_LONG_THREADS 1024
+#define DRAFT_FEW 2048
 #define DRAFT_LDS 8192
-// As many tokens per thread are requested before the length is known (the row has ctx_stride of them).
-#define DRAFT_EARLY 4
 
 // Each thread scores candidate match ends e = tid, tid + threads, ... <= len - 2 by comparing
 // backwards against the suffix; the key (match length, ~e) makes the block maximum the
 // longest match and, among equals, the left-most end.
-__device__ __forceinline__ unsigned long long match_key(const int32_t *s, int len, int32_t max_match) {
+__device__ __forceinline__ unsigned long long match_key(const int32_t *s, int len, int32_t max_match, int threads) {
     unsigned long long best = 0ull;
-    for (int e = threadIdx.x; e <= len - 2; e += blockDim.x) {
+    for (int e = threadIdx.x; e <= len - 2; e += threads) {
         int r = 0;
         while (r <= e && (max_match <= 0 || r < max_match) && s[e - r] == s[len - 1 - r]) r++;
         if (r > 0) {
@@ -42,50 +44,42 @@ __device__ __forceinline__ unsigned long long match_key(const int32_t *s, int le
     }
     return best;
 }
-struct DraftShared {
-    int32_t s[DRAFT_LDS];
-    unsigned long long red[1024 / 64];
-};
-// The longest match of the suffix of s[0 .. len); every thread gets the key (0: none).  early[i] = s[i * threads + tid] where that is inside the row.
-__device__ __forceinline__ unsigned long long draft_match(DraftShared &S, const int32_t *s, const int (&early)[DRAFT_EARLY], int len,
-                                                          int32_t max_match) {
+// How many threads of a workgroup of T work on a sequence of `len` tokens: the others leave.
+template <int T>
+__device__ __forceinline__ int draft_threads(int len) { return T > DRAFT_THREADS && len <= DRAFT_FEW ? DRAFT_THREADS : T; }
+// The longest match of the suffix of s[0 .. len); every one of the first `threads` threads (no others are left) gets the key (0: none).
+template <int T>
+__device__ __forceinline__ unsigned long long draft_match(const int32_t *s, int len, int32_t max_match, int threads) {
+    __shared__ unsigned long long red[T / 64];
     unsigned long long best;
-    if (len <= DRAFT_LDS) {                                  // uniform
-#pragma unroll
-        for (int i = 0; i < DRAFT_EARLY; i++) {
-            const int x = i * blockDim.x + threadIdx.x;
-            if (x < len) S.s[x] = early[i];
-        }
-        for (int x = DRAFT_EARLY * blockDim.x + threadIdx.x; x < len; x += blockDim.x) S.s[x] = s[x];
+    if (T > DRAFT_THREADS && len > DRAFT_FEW && len <= DRAFT_LDS) {      // uniform
+        __shared__ int32_t row[T > DRAFT_THREADS ? DRAFT_LDS : 1];
+        for (int x = threadIdx.x; x < len; x += T) row[x] = s[x];
         __syncthreads();
-        best = match_key(S.s, len, max_match);
+        best = match_key(row, len, max_match, T);
     } else {
-        best = match_key(s, len, max_match);
+        best = match_key(s, len, max_match, threads);
     }
-    return block_max_u64(best, S.red);
-}
-__device__ __forceinline__ void draft_early(int (&early)[DRAFT_EARLY], const int32_t *s, int32_t stride) {
-#pragma unroll
-    for (int i = 0; i < DRAFT_EARLY; i++) early[i] = s[min(i * (int)blockDim.x + (int)threadIdx.x, stride - 1)];
+    return block_max_u64(best, red, threads / 64);
 }
 
-__global__ __launch_bounds__(1024) void k_bigram_draft(
+template <int T>
+__global__ __launch_bounds__(T) void k_bigram_draft(
     const int32_t *__restrict__ ctx, const int32_t *__restrict__ ctx_len, int32_t ctx_stride,
     const int32_t *__restrict__ next_table, int32_t vocab, int32_t k, int32_t max_match,
     int32_t *__restrict__ out_tokens, int32_t *__restrict__ out_match_len) {
-    __shared__ DraftShared S;
     const int b = blockIdx.x;
     const int32_t *s = ctx + (size_t)b * ctx_stride;
-    int early[DRAFT_EARLY];
-    draft_early(early, s, ctx_stride);
     int len = ctx_len[b];
     int32_t *out = out_tokens + (size_t)b * k;
     if (len < 1 || len > ctx_stride) {   // device-side guard: no valid context
-        for (int j = threadIdx.x; j < k; j += blockDim.x) out[j] = -1;
+        for (int j = threadIdx.x; j < k; j += T) out[j] = -1;
         if (out_match_len && threadIdx.x == 0) out_match_len[b] = 0;
         return;
     }
-    const unsigned long long best = draft_match(S, s, early, len, max_match);
+    const int threads = draft_threads<T>(len);
+    if ((int)threadIdx.x >= threads) return;
+    const unsigned long long best = draft_match<T>(s, len, max_match, threads);
     const int mlen = (int)(best >> 32);
     if (out_match_len && threadIdx.x == 0) out_match_len[b] = mlen;
     if (mlen == 0) {
@@ -100,25 +94,25 @@ __global__ __launch_bounds__(1024) void k_bigram_draft(
     }
     const int e = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));
     const int period = len - (e + 1);   // >= 1: the sequence extended by its own draft repeats with this period
-    for (int j = threadIdx.x; j < k; j += blockDim.x) out[j] = s[e + 1 + (j % period)];
+    for (int j = threadIdx.x; j < k; j += threads) out[j] = s[e + 1 + (j % period)];
 }
 
 // k_bigram_draft that appends its drafts to the context itself (device-resident cascade control): sequences whose
 // drafts in flight already number `need` or more (counted from start_len) are left alone.
-__global__ __launch_bounds__(1024) void k_bigram_draft_append(
+template <int T>
+__global__ __launch_bounds__(T) void k_bigram_draft_append(
     int32_t *ctx, int32_t ctx_stride, int32_t *__restrict__ ctx_len, const int32_t *__restrict__ next_table,
     int32_t vocab, int32_t k, int32_t max_match, const int32_t *__restrict__ gate, uint8_t *__restrict__ q_onehot_tab,
     const int32_t *__restrict__ q_base, int32_t q_stride) {
-    __shared__ DraftShared S;
     const int b = blockIdx.x;
     int32_t *s = ctx + (size_t)b * ctx_stride;
-    int early[DRAFT_EARLY];
-    draft_early(early, s, ctx_stride);
     const int len = ctx_len[b];
     bool active = len >= 1 && len + k < ctx_stride && (!gate || gate[b] >= 0);
     if (active && q_onehot_tab && (len - q_base[b] < 0 || len + k - q_base[b] > q_stride)) active = false;
     if (!active) return;                                     // uniform over the workgroup
-    const unsigned long long best = draft_match(S, s, early, len, max_match);   // (its barriers: every thread has read the context by now)
+    const int threads = draft_threads<T>(len);
+    if ((int)threadIdx.x >= threads) return;
+    const unsigned long long best = draft_match<T>(s, len, max_match, threads);   // (its barriers: every thread has read the context by now)
     const int mlen = (int)(best >> 32);
     int32_t *out = s + len;
     if (mlen == 0) {
@@ -132,14 +126,12 @@ __global__ __launch_bounds__(1024) void k_bigram_draft_append(
     } else {
         const int e = (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull));
         const int period = len - (e + 1);                    // sources s[e + 1 ..  len - 1] lie before the drafts
-        for (int j = threadIdx.x; j < k; j += blockDim.x) out[j] = s[e + 1 + (j % period)];
+        for (int j = threadIdx.x; j < k; j += threads) out[j] = s[e + 1 + (j % period)];
     }
     if (q_onehot_tab)
-        for (int j = threadIdx.x; j < k; j += blockDim.x) q_onehot_tab[(size_t)b * q_stride + len + j - q_base[b]] = 1;
+        for (int j = threadIdx.x; j < k; j += threads) q_onehot_tab[(size_t)b * q_stride + len + j - q_base[b]] = 1;
     if (threadIdx.x == 0) ctx_len[b] = len + k;
 }
-// threads of a workgroup for rows of `stride` tokens: a token each up to 1024
-static int draft_threads(int stride) { return stride <= 256 ? 256 : stride <= 512 ? 512 : 1024; }
 
 // gate[b] = ctx_len[b] when sequence b still needs tokens in the loop that started at loop_start[b] (fewer than `need`
 // exist) and the enclosing step is itself active (parent_gate null or >= 0); else -1.  A step gated with this value
@@ -184,7 +176,7 @@ __global__ __launch_bounds__(DRAFT_THREADS) void k_maxgram_enc(
             best = key > best ? key : best;
         }
     }
-    best = block_max_u64(best, red);
+    best = block_max_u64(best, red, DRAFT_THREADS / 64);
     const int mlen = (int)(best >> 32);
     const int e = mlen ? (int)(0xFFFFFFFFu - (uint32_t)(best & 0xFFFFFFFFull)) : hl - 1;
     const int n_copied = mlen ? min(k, hl - 1 - e) : 0;
@@ -245,7 +237,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_bigram_fit(const int32_t *__res
         S.s[i] = s[i];
         S.key[i] = S.best[i] = 0u;
     }
-    for (uint32_t i = threadIdx.x; i < FIT_SLOTS / 4; i += FIT_THREADS) S.slot4[i] = make_int4(FIT_EMPTY, FIT_EMPTY, FIT_EMPTY, FIT_EMPTY);
+    for (uint32_t i = threadIdx.x; i < (n_slots + 3) / 4; i += FIT_THREADS) S.slot4[i] = make_int4(FIT_EMPTY, FIT_EMPTY, FIT_EMPTY, FIT_EMPTY);
     __syncthreads();
     int rep[PER];                                            // of this thread's positions; -1: not a pair of known tokens
 #pragma unroll
@@ -262,7 +254,7 @@ __global__ __launch_bounds__(FIT_THREADS) void k_bigram_fit(const int32_t *__res
     for (int p = 0; p < PER; p++)
         if (rep[p] >= 0)                                     // (the count no longer changes; only the position below it does)
             atomicMax(&S.key[rep[p]], (S.key[rep[p]] & ~(uint32_t)(FIT_MAX - 1)) | (uint32_t)(p * FIT_THREADS + (int)threadIdx.x));
-    for (uint32_t i = threadIdx.x; i < FIT_SLOTS / 4; i += FIT_THREADS) S.slot4[i] = make_int4(FIT_EMPTY, FIT_EMPTY, FIT_EMPTY, FIT_EMPTY);
+    for (uint32_t i = threadIdx.x; i < (n_slots + 3) / 4; i += FIT_THREADS) S.slot4[i] = make_int4(FIT_EMPTY, FIT_EMPTY, FIT_EMPTY, FIT_EMPTY);
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < PER; p++) {
@@ -299,8 +291,9 @@ extern "C" int32_t csd_bigram_draft(const int32_t *ctx, const int32_t *ctx_len, 
     if (B < 0 || k < 0 || vocab < 1 || ctx_stride < 1) return CSD_EINVAL;
     if (k > 0 && !out_tokens) return CSD_ENULL;
     if (B == 0 || (k == 0 && !out_match_len)) return CSD_OK;   // k == 0 still reports match lengths
-    hipLaunchKernelGGL(k_bigram_draft, dim3(B), dim3(draft_threads(ctx_stride)), 0, (hipStream_t)stream, ctx, ctx_len, ctx_stride,
-                       next_table, vocab, k, max_match, out_tokens, out_match_len);
+    const bool few = ctx_stride <= DRAFT_FEW;
+    hipLaunchKernelGGL((few ? k_bigram_draft<DRAFT_THREADS> : k_bigram_draft<DRAFT_LONG_THREADS>), dim3(B), dim3(few ? DRAFT_THREADS : DRAFT_LONG_THREADS), 0,
+                       (hipStream_t)stream, ctx, ctx_len, ctx_stride, next_table, vocab, k, max_match, out_tokens, out_match_len);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
@@ -328,8 +321,10 @@ extern "C" int32_t csd_bigram_draft_append(int32_t *ctx, int32_t ctx_stride, int
     if (B < 0 || k < 0 || vocab < 1 || ctx_stride < 1) return CSD_EINVAL;
     if (q_onehot_tab && (!q_base || q_stride < 1)) return CSD_EINVAL;
     if (B == 0) return CSD_OK;
-    hipLaunchKernelGGL(k_bigram_draft_append, dim3(B), dim3(draft_threads(ctx_stride)), 0, (hipStream_t)stream, ctx, ctx_stride, ctx_len,
-                       next_table, vocab, k, max_match, gate, q_onehot_tab, q_base, q_stride);
+    const bool few = ctx_stride <= DRAFT_FEW;
+    hipLaunchKernelGGL((few ? k_bigram_draft_append<DRAFT_THREADS> : k_bigram_draft_append<DRAFT_LONG_THREADS>), dim3(B),
+                       dim3(few ? DRAFT_THREADS : DRAFT_LONG_THREADS), 0, (hipStream_t)stream, ctx, ctx_stride, ctx_len, next_table, vocab, k, max_match,
+                       gate, q_onehot_tab, q_base, q_stride);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }

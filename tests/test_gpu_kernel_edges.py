@@ -48,10 +48,12 @@ BF = I.ModelShape("edge_dh64", 0, "bf16", 2, 256, 4, 64, 512, 1024)
 BF128 = I.ModelShape("edge_dh128", 0, "bf16", 2, 256, 2, 128, 480, 1040)
 
 
-@pytest.mark.parametrize("n,room", [(1, 0), (2, 254), (256, 0), (256, 1), (511, 1), (513, 0), (1024, 300), (4096, 1), (4097, 0), (8192, 5), (8193, 0), (9000, 60)])
+@pytest.mark.parametrize("n,room", [(1, 0), (2, 254), (256, 0), (256, 1), (511, 1), (513, 0), (1024, 300), (4096, 1), (4097, 0), (8192, 5), (8193, 0), (9000, 60), (1, 3000), (200, 1848),
+                                    (200, 1849), (2048, 0), (2048, 1), (2049, 0)])
 @pytest.mark.parametrize("max_match", [0, 3])
 def test_draft_of_long_and_short_sequences(P, n, room, max_match):
-    """Either side of every thread count, of the tokens that are requested before the length is known, and of what LDS holds."""
+    """Either side of what one workgroup size or the other takes, in tokens and in room for them, and of what LDS holds; drafts given and drafts
+    appended to the sequences (a sequence without room for them is left alone)."""
     from oracle import csd_oracle as O
     vocab, k = 50, 9
     rng = np.random.default_rng(n + room)
@@ -63,6 +65,11 @@ def test_draft_of_long_and_short_sequences(P, n, room, max_match):
                                  max_match=max_match)
     want, want_len = O.bigram_draft(ctx, [n, n], table, k, max_match=max_match)
     assert np.array_equal(got.cpu().numpy(), want) and np.array_equal(length.cpu().numpy(), want_len)
+    dev, dev_len = torch.from_numpy(ctx).cuda(), torch.full((2,), n, dtype=torch.int32, device="cuda")
+    P.bigram_draft_append(dev, dev_len, torch.from_numpy(table).cuda(), k, max_match=max_match)
+    if n + k < ctx.shape[1]:
+        ctx[:, n:n + k] = want
+    assert np.array_equal(dev.cpu().numpy(), ctx) and (dev_len == (n + k if n + k < ctx.shape[1] else n)).all()
 
 
 @pytest.mark.parametrize("shape", [BF, BF128], ids=["dh64", "dh128"])
@@ -443,10 +450,10 @@ def test_small_fp32_models(P, dims, B, m, t, max_seq):
             assert tol_ok(got.cpu().numpy().astype(np.float64), want, 1e-4, 1e-4)[0]
 
 
-@pytest.mark.parametrize("V", [32764, 32766, 32768, 32772])
+@pytest.mark.parametrize("V", [18428, 18432, 18436, 32764, 32766, 32768, 32772])
 @pytest.mark.parametrize("kind", ["plain", "zero_residual", "large", "empty"])
 def test_accept_at_the_longest_row_in_registers(P, V, kind):
-    """Either side of the vocabulary that a workgroup holds in registers, and what it hands on to the general way: a residual without weight,
+    """Either side of the vocabularies that a workgroup holds in registers, and what it hands on to the general way: a residual without weight,
     weights above 256, a row of zeros.  Whole numbers, decided by exact sums."""
     from oracle import csd_oracle as O
     B, k = 3, 2
@@ -473,7 +480,7 @@ def test_accept_at_the_longest_row_in_registers(P, V, kind):
         assert (n[s:] == 0).all() and (tok[s:] == -1).all()
 
 
-@pytest.mark.parametrize("V", [1, 3, 4, 254, 256, 260, 4096, 8196, 32764, 32766, 32768, 32772])
+@pytest.mark.parametrize("V", [1, 3, 4, 254, 256, 260, 4096, 12284, 12288, 12292, 32764, 32766, 32768, 32772])
 def test_arg_max_of_rows_with_nan_and_without_finite_values(P, V):
     """The greedy rule's own token, in registers and in the general way: NaN never wins, the lowest index among equals does, a row of -inf gives its first
     token that is not NaN, a row of NaN the first token."""
