@@ -187,8 +187,11 @@ __device__ __forceinline__ void load_row(float (&val)[4 * ACC_NG], const float *
         val[4 * j] = t.x, val[4 * j + 1] = t.y, val[4 * j + 2] = t.z, val[4 * j + 3] = t.w;
     }
 }
-__device__ __forceinline__ bool row_fits(const float *row, int V) {
-    return V % 4 == 0 && V <= 4 * ACC_NG * ACC_THREADS && (uintptr_t)row % 16 == 0;
+// Whether a launch reviews rows in registers.  Short rows are quicker in the general way, since the padding is worked on too.  Eight sequences, four
+// drafts, general / registers in us: greedy, all drafts kept, 8192 tokens 20.2 / 21.1, 12288 23.6 / 21.1, 32000 40.4 / 22.0; sampling 4096 tokens 5.4 / 7.9,
+// 16384 9.0 / 9.2, 18432 10.7 / 9.2, 32000 16.1 / 10.7.
+static bool rows_fit(const float *p, const float *q, int V, int mode) {
+    return V % 4 == 0 && V >= (mode == CSD_MODE_GREEDY ? 12288 : 18432) && V <= 4 * ACC_NG * ACC_THREADS && (uintptr_t)p % 16 == 0 && (uintptr_t)q % 16 == 0;
 }
 __device__ int row_argmax(const float (&val)[4 * ACC_NG], int vbase, ArgMax *red) {
     float bv = -INFINITY;
@@ -216,27 +219,29 @@ __device__ int row_argmax(const float (&val)[4 * ACC_NG], int vbase, ArgMax *red
 
 // The review of one sequence by one workgroup (every thread calls it; the result is valid in every thread).
 // pb: reviewer rows [k+1][V]; qb: draft rows [k][V] or null; q_onehot: [k] flags or null; db: drafts [k];
-// ua: [k] uniforms of the acceptance tests; us: the uniform of the draw.
+// ua: [k] uniforms of the acceptance tests; us: the uniform of the draw.  REGS: rows in registers (rows_fit).
 struct AcceptShared {
     ArgMax red_am[ACC_THREADS / 64];
     unsigned long long wave_tot[ACC_THREADS / 64];
     int s_n, s_tok, s_large;
     float4 own[ACC_NG * 64];
 };
+template <bool REGS>
 __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__restrict__ pb, const float *__restrict__ qb,
                                             const uint8_t *__restrict__ q_onehot, const int32_t *__restrict__ db,
                                             const float *__restrict__ ua, float us, int32_t k, int32_t V, float lenience,
                                             int32_t mode, int &n_out, int &tok_out) {
     if (mode == CSD_MODE_GREEDY) {
         int n = 0, am = 0;
-        const bool fits = row_fits(pb, V);
         const int ng = (V + 256 * (ACC_THREADS / 64) - 1) / (256 * (ACC_THREADS / 64));
         int vbase = (threadIdx.x >> 6) * 256 * ng + 4 * (threadIdx.x & 63);
-        asm volatile("" : "+v"(vbase));                      // (in a loop over reviews the offsets made from it are not kept in registers)
         float val[4 * ACC_NG], next[4 * ACC_NG];             // a row, and the one behind it, which is read while the first is compared
-        if (fits) load_row(next, pb, vbase, ng, V, NAN);
+        if constexpr (REGS) {
+            asm volatile("" : "+v"(vbase));                  // (in a loop over reviews the offsets made from it are not kept in registers)
+            load_row(next, pb, vbase, ng, V, NAN);
+        }
         for (; n <= k; n++) {
-            if (fits) {
+            if constexpr (REGS) {
 #pragma unroll
                 for (int i = 0; i < 4 * ACC_NG; i++) val[i] = next[i];
                 if (n < k) load_row(next, pb + (size_t)(n + 1) * V, vbase, ng, V, NAN);
@@ -298,7 +303,7 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
     // The weights in registers: the row is read once, all loads in flight together, and the draw looks at what the threads hold.
     // The general way below takes what is rare: an all-zero residual, and weights above 256 (no distribution under any lenience; NaN),
     // whose sums may wrap.
-    if (row_fits(prow, V) && vec) {
+    if constexpr (REGS) {
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = ACC_THREADS / 64;
         const int ng = (V + 256 * nw - 1) / (256 * nw);
         int vbase = w * 256 * ng + 4 * lane;
@@ -381,6 +386,7 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
     tok_out = S.s_tok;
 }
 
+template <bool REGS>
 __global__ __launch_bounds__(ACC_THREADS) void k_accept(
     const float *__restrict__ p, const float *__restrict__ q, const uint8_t *__restrict__ q_onehot,
     const int32_t *__restrict__ draft, int32_t draft_stride, const float *__restrict__ u_acc,
@@ -389,7 +395,7 @@ __global__ __launch_bounds__(ACC_THREADS) void k_accept(
     __shared__ AcceptShared S;
     const int b = blockIdx.x;
     int n, tok;
-    accept_core(S, p + (size_t)b * (k + 1) * V, q ? q + (size_t)b * k * V : nullptr, q_onehot, draft + (size_t)b * draft_stride,
+    accept_core<REGS>(S, p + (size_t)b * (k + 1) * V, q ? q + (size_t)b * k * V : nullptr, q_onehot, draft + (size_t)b * draft_stride,
                 u_acc ? u_acc + (size_t)b * k : nullptr, mode == CSD_MODE_SAMPLE ? u_samp[b] : 0.f, k, V, lenience, mode, n, tok);
     if (threadIdx.x == 0) {
         n_accepted[b] = n;
@@ -748,7 +754,7 @@ int32_t csd_accept_enqueue(const float *p, const float *q, const uint8_t *q_oneh
                            int32_t V, float lenience, int32_t mode, int32_t *n_accepted, int32_t *next_token,
                            hipStream_t st) {
     if (B <= 0) return CSD_OK;
-    hipLaunchKernelGGL(k_accept, dim3(B), dim3(ACC_THREADS), 0, st, p, q, q_onehot, draft, draft_stride, u_acc, u_samp,
+    hipLaunchKernelGGL((rows_fit(p, q, V, mode) ? k_accept<true> : k_accept<false>), dim3(B), dim3(ACC_THREADS), 0, st, p, q, q_onehot, draft, draft_stride, u_acc, u_samp,
                        k, V, lenience, mode, n_accepted, next_token);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
@@ -774,7 +780,7 @@ extern "C" int32_t csd_accept(const float *p, const float *q, const uint8_t *q_o
 // draw from the row with the walk's next uniform, or its arg-max), and if a child of the row carries that token
 // keep the child and go on from it; otherwise the token is what the review emits.  One workgroup per sequence; a
 // walk step is the draw of a plain review with no drafts.  Rows only have children below them, so the walk ends.
-template <int mode>
+template <int mode, bool REGS>
 __global__ __launch_bounds__(ACC_THREADS) void k_tree_accept(
     const float *__restrict__ p, const int32_t *__restrict__ tokens, const int32_t *__restrict__ parent,
     const float *__restrict__ u, int32_t m, int32_t V, int32_t *__restrict__ n_accepted, int32_t *__restrict__ path,
@@ -786,7 +792,7 @@ __global__ __launch_bounds__(ACC_THREADS) void k_tree_accept(
     int node = 0, n = 0, tok = -1;
     for (int step = 0; step < m; step++) {
         int unused;
-        accept_core(S, p + ((size_t)b * m + node) * V, nullptr, nullptr, nullptr, nullptr,
+        accept_core<REGS>(S, p + ((size_t)b * m + node) * V, nullptr, nullptr, nullptr, nullptr,
                     mode == CSD_MODE_SAMPLE ? u[(size_t)b * m + n] : 0.f, 0, V, 1.0f, mode, unused, tok);
         if (threadIdx.x == 0) s_child = 0x7FFFFFFF;
         __syncthreads();
@@ -815,8 +821,10 @@ extern "C" int32_t csd_tree_accept(const float *p, const int32_t *tokens, const 
     if (mode == CSD_MODE_SAMPLE && !u) return CSD_ENULL;
     if (B < 0 || m < 1 || V < 1) return CSD_EINVAL;
     if (B == 0) return CSD_OK;
-    hipLaunchKernelGGL(mode == CSD_MODE_SAMPLE ? k_tree_accept<CSD_MODE_SAMPLE> : k_tree_accept<CSD_MODE_GREEDY>, dim3(B),
-                       dim3(ACC_THREADS), 0, (hipStream_t)stream, p, tokens, parent, u, m, V, n_accepted, path, next_token);
+    const bool regs = rows_fit(p, nullptr, V, mode);
+    auto *kernel = mode == CSD_MODE_SAMPLE ? (regs ? k_tree_accept<CSD_MODE_SAMPLE, true> : k_tree_accept<CSD_MODE_SAMPLE, false>)
+                                           : (regs ? k_tree_accept<CSD_MODE_GREEDY, true> : k_tree_accept<CSD_MODE_GREEDY, false>);
+    hipLaunchKernelGGL(kernel, dim3(B), dim3(ACC_THREADS), 0, (hipStream_t)stream, p, tokens, parent, u, m, V, n_accepted, path, next_token);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
@@ -880,6 +888,7 @@ struct ReviewArgs {
 // accept / resample over the drafts in flight, then the commit: the reviewer's own token after the kept drafts, the
 // sequence length, this reviewer's cache length, the lower levels' cache lengths (clamped to what is still on the
 // path), and the rows the level above will review the emitted tokens against
+template <bool REGS>
 __global__ __launch_bounds__(ACC_THREADS) void k_review_commit(const ReviewArgs A) {
     __shared__ AcceptShared S;
     const int b = blockIdx.x;
@@ -900,7 +909,7 @@ __global__ __launch_bounds__(ACC_THREADS) void k_review_commit(const ReviewArgs 
     const float *ua = A.u_acc_tab ? A.u_acc_tab + (size_t)b * A.ctx_stride + pf : nullptr;
     const float us = (A.mode == CSD_MODE_SAMPLE && A.u_samp_tab) ? A.u_samp_tab[(size_t)b * A.ctx_stride + pf] : 0.f;
     int n, tok;
-    accept_core(S, pb, qb, oh, seq + pf, ua, us, k, V, A.lenience, A.mode, n, tok);
+    accept_core<REGS>(S, pb, qb, oh, seq + pf, ua, us, k, V, A.lenience, A.mode, n, tok);
     __syncthreads();                                         // every thread has read the lengths it needs
     if (threadIdx.x == 0) {
         seq[pf + n] = tok;
@@ -987,7 +996,7 @@ extern "C" int32_t csd_review_ctx(csd_model *mod, void *kv, const csd_review *r,
     A.V = V;
     A.lenience = lenience;
     A.mode = mode;
-    hipLaunchKernelGGL(k_review_commit, dim3(B), dim3(ACC_THREADS), 0, st, A);
+    hipLaunchKernelGGL((rows_fit(rows, r->q_tab, V, mode) ? k_review_commit<true> : k_review_commit<false>), dim3(B), dim3(ACC_THREADS), 0, st, A);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
