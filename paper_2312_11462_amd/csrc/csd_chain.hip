@@ -926,7 +926,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
         Pd.ssq_out = ssq1;
         if (t5) {
             // QKV -> self-attention (bias by relative position) -> O (+h) -> cross-q -> cross-attention over the projected
-            // encoder rows -> cross-O (+h) -> gate|up (tanh-GELU) -> down (+h): eight launches and two attention pairs
+            // encoder rows -> cross-O (+h) -> gate|up (tanh-GELU) -> down (+h): eight launches, two of them attention
             AttnMode self_mode, cross_mode;
             self_mode.rel_bias = mod->rel_bias;
             self_mode.bucket = mod->rel_bucket;

@@ -10,8 +10,8 @@
 // k-step in registers and reads the next one's between its matrix instructions; one workgroup barrier per k-step.
 // Row blocks of one column group go to one compute die, which then fetches those weights once.
 // A wave issues in order, and with one or two waves per SIMD whatever is issued in a bunch leaves the matrix pipe empty: operand reads and
-// loads go between the matrix instructions one at a time (in a bunch per column tile: a prompt of 1000 rows of the 7B shape 27.8 ms against 26.7; QKV at 512
-// rows in traces of whole calls 98 us against 90, O and down together 116 against 105).
+// loads go between the matrix instructions one at a time (in a bunch per column tile: a prompt of 1000 rows of the 7B shape 27.6 ms against 26.5; in traces of
+// whole calls, blocks of 512 and 488 rows, QKV 94.6 us against 89.8, O and down together 115 against 108, LM head 233 against 229, gate|up 147 against 149).
 // 7B shape, 512 rows, against four launches of the row-split form over 128 rows each, every GEMM timed by itself before that: QKV 122 -> 81 us,
 // gate|up 188 -> 146, down 111 -> 79, O 57 -> 34, LM head 254 -> 223.
 // What bounds QKV now, by the counters: of 196000 cycles a SIMD's matrix pipe is busy for 98000, waves wait 30000 for barriers and loads,
@@ -280,17 +280,19 @@ int32_t csd_tall_setup() {
 }
 
 // Column tiles per wave (6 or 4), row tiles per wave (4, 3 or 2: row blocks of 128, 96 or 64) and K splits: the triple with the
-// shortest launch by a model fitted to traces of the 7B and 160M shapes at 160 to 512 rows (60 launches in each of the six forms; the
-// form it picks is on average within 1 % of the fastest one).  A k-step of one workgroup per compute unit takes `one` us; with 6
+// shortest launch by a model whose constants were fitted to traces of the 7B and 160M shapes at 160 to 512 rows with operand reads and loads in
+// bunches.  Traces of the present loop, the same shapes in all six forms with two and three stages: the form it picks for QKV, gate|up and the LM head is on average 0.6 % slower
+// than the fastest one, 1.5 % at most at the 7B shape (LM head, 384 rows 160.6 us against 158.3) and 6 % at the 160M shape (LM head, 512 rows 54.0 against 50.8,
+// three stages instead of two).  A k-step of one workgroup per compute unit takes `one` us; with 6
 // column tiles and more workgroups than compute units two share one (two stages each) and 512 of them take `two`; 4 column tiles go in rounds of
 // 256.  Beside it the prologue and the epilogue, 0.5 us per tile of a wave (once per round where only one workgroup fits a compute unit,
 // else under the other's k-steps), and the splits' partial sums.
-// Narrow tiles fill the chip where a matrix is small or its row blocks few: 160M shape, 512 rows, QKV 29.8 us in 48 workgroups
-// of 6 x 4 tiles per wave, 14.1 in 144 of 4 x 2; 7B shape, 384 rows, QKV 92.3 us at 6 x 4 (192 workgroups), 77.2 at 6 x 3 (256); 512 rows, where 6 x 4
-// makes 256 workgroups, 98.5 against 127.6 at 6 x 3 (all in traces of whole calls, before the sums were kept in chains).  max_splits = 1 where the epilogue runs in the kernel.
+// Narrow tiles fill the chip where a matrix is small or its row blocks few (all figures of the present loop in traces of whole calls): 160M shape, 512 rows, QKV 29.4 us in 48
+// workgroups of 6 x 4 tiles per wave, 13.5 in 144 of 4 x 2; 7B shape, 384 rows, QKV 87.4 us at 6 x 4 (192 workgroups), 77.7 at 6 x 3 (256); 512 rows, where 6 x 4
+// makes 256 workgroups, 91.9 against 117.9 at 6 x 3.  max_splits = 1 where the epilogue runs in the kernel.
 // Stages: four of the narrow tiles; with 6 column tiles and more workgroups than compute units two of them share one (two stages
-// each), which evens out the last round: gate|up at 512 rows 146 us against 155 with three stages and one workgroup at a time; at 256
-// workgroups 117 against 81.
+// each), which evens out the last round: gate|up at 512 rows 151 us against 165 with three stages and one workgroup at a time; at 256
+// workgroups (QKV) 124 against 92.
 struct TallPlan {
     int ctw, rtw, stages, S, rblocks, grid, chain;
 };
