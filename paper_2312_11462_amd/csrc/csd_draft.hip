@@ -21,10 +21,10 @@ __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v
 }
 
 // Rows with room for more than DRAFT_FEW tokens take workgroups of 1024 threads, which bring a sequence of up to DRAFT_LDS tokens to LDS: every
-// thread compares positions backwards, a chain of dependent reads that cost a trip to L2 each where they go to memory (4000 tokens 6.2 us with
-// 256 threads that read memory, 5.0 in LDS with 1024; 8000 tokens 10.1 and 6.1).  Longer sequences are read where they are (20000 tokens, 256 and 1024
-// threads 21.4 and 9.7).  Up to DRAFT_FEW tokens 256 threads that read memory are the faster form (500 tokens 2.6 us against 4.2, 2040 4.0 against
-// 4.4), and in a row with room for more the other waves leave at once (2.9 and 4.1).
+// thread compares positions backwards, a chain of dependent reads that cost a trip to L2 each where they go to memory (4000 tokens 6.1 us with
+// 256 threads that read memory, 4.8 in LDS with 1024; 8000 tokens 10.0 and 5.9).  Longer sequences are read where they are (20000 tokens, 256 and 1024
+// threads 21.3 and 9.6).  Up to DRAFT_FEW tokens 256 threads that read memory are the faster form (500 tokens 2.7 us against 4.2, 2040 3.7 against
+// 4.4), and in a row with room for more the other waves leave at once (500 tokens 2.9 and 4.1).
 #define DRAFT_LONG_THREADS 1024
 #define DRAFT_FEW 2048
 #define DRAFT_LDS 8192
@@ -47,18 +47,33 @@ __device__ __forceinline__ unsigned long long match_key(const int32_t *s, int le
 // How many threads of a workgroup of T work on a sequence of `len` tokens: the others leave.
 template <int T>
 __device__ __forceinline__ int draft_threads(int len) { return T > DRAFT_THREADS && len <= DRAFT_FEW ? DRAFT_THREADS : T; }
+// The first tokens of a row, requested before the length is known: a pass over a row that no cache holds waits for memory once, not twice.
+template <int T>
+struct DraftEarly {
+    static constexpr int N = T > DRAFT_THREADS ? 4 : DRAFT_FEW / T;
+    int32_t v[N];
+    __device__ __forceinline__ void request(const int32_t *s, int32_t stride) {
+#pragma unroll
+        for (int i = 0; i < N; i++) v[i] = s[min(i * T + (int)threadIdx.x, stride - 1)];
+    }
+};
 // The longest match of the suffix of s[0 .. len); every one of the first `threads` threads (no others are left) gets the key (0: none).
 template <int T>
-__device__ __forceinline__ unsigned long long draft_match(const int32_t *s, int len, int32_t max_match, int threads) {
+__device__ __forceinline__ unsigned long long draft_match(const int32_t *s, const DraftEarly<T> &early, int len, int32_t max_match, int threads) {
     __shared__ unsigned long long red[T / 64];
     unsigned long long best;
     if (T > DRAFT_THREADS && len > DRAFT_FEW && len <= DRAFT_LDS) {      // uniform
         __shared__ int32_t row[T > DRAFT_THREADS ? DRAFT_LDS : 1];
-        for (int x = threadIdx.x; x < len; x += T) row[x] = s[x];
+#pragma unroll
+        for (int i = 0; i < early.N; i++)
+            if (i * T + (int)threadIdx.x < len) row[i * T + threadIdx.x] = early.v[i];
+        for (int x = early.N * T + threadIdx.x; x < len; x += T) row[x] = s[x];
         __syncthreads();
         best = match_key(row, len, max_match, T);
     } else {
         best = match_key(s, len, max_match, threads);
+#pragma unroll
+        for (int i = 0; i < early.N; i++) asm volatile("" : : "v"(early.v[i]));          // (read for the caches)
     }
     return block_max_u64(best, red, threads / 64);
 }
@@ -70,6 +85,8 @@ __global__ __launch_bounds__(T) void k_bigram_draft(
     int32_t *__restrict__ out_tokens, int32_t *__restrict__ out_match_len) {
     const int b = blockIdx.x;
     const int32_t *s = ctx + (size_t)b * ctx_stride;
+    DraftEarly<T> early;
+    early.request(s, ctx_stride);
     int len = ctx_len[b];
     int32_t *out = out_tokens + (size_t)b * k;
     if (len < 1 || len > ctx_stride) {   // device-side guard: no valid context
@@ -79,7 +96,7 @@ __global__ __launch_bounds__(T) void k_bigram_draft(
     }
     const int threads = draft_threads<T>(len);
     if ((int)threadIdx.x >= threads) return;
-    const unsigned long long best = draft_match<T>(s, len, max_match, threads);
+    const unsigned long long best = draft_match<T>(s, early, len, max_match, threads);
     const int mlen = (int)(best >> 32);
     if (out_match_len && threadIdx.x == 0) out_match_len[b] = mlen;
     if (mlen == 0) {
@@ -106,13 +123,15 @@ __global__ __launch_bounds__(T) void k_bigram_draft_append(
     const int32_t *__restrict__ q_base, int32_t q_stride) {
     const int b = blockIdx.x;
     int32_t *s = ctx + (size_t)b * ctx_stride;
+    DraftEarly<T> early;
+    early.request(s, ctx_stride);
     const int len = ctx_len[b];
     bool active = len >= 1 && len + k < ctx_stride && (!gate || gate[b] >= 0);
     if (active && q_onehot_tab && (len - q_base[b] < 0 || len + k - q_base[b] > q_stride)) active = false;
     if (!active) return;                                     // uniform over the workgroup
     const int threads = draft_threads<T>(len);
     if ((int)threadIdx.x >= threads) return;
-    const unsigned long long best = draft_match<T>(s, len, max_match, threads);   // (its barriers: every thread has read the context by now)
+    const unsigned long long best = draft_match<T>(s, early, len, max_match, threads);   // (its barriers: every thread has read the context by now)
     const int mlen = (int)(best >> 32);
     int32_t *out = s + len;
     if (mlen == 0) {
