@@ -50,16 +50,19 @@ __device__ __forceinline__ void gemm_load_w(u32x4 (&W)[NT], const ChainGemm &P, 
                                                                               tv ? ((S.t0 + j) * P.KS + ks) * 1024 : 0, 2));
     }
 }
-template <int MT>
-__device__ __forceinline__ void gemm_load_a(u32x4 (&A)[MT][2], const ChainGemm &P, const GemmShare &S, __amdgpu_buffer_rsrc_t ra, int ks,
+// Activation fragments of MT row tiles: the hi and the lo plane of each, or, with HALF, of a last tile of at most eight rows one fragment
+// for both: hi in its columns 0 to 7, lo in 8 to 15 (their sums meet after the reduction).  A launch over few rows is bound by the loads a
+// compute unit can issue (some 25 cycles per KB, whatever arrives) as much as by HBM, and a k-step of one tile is then two loads and one
+// matrix instruction instead of three and two: steps of the 7B shape with 6 rows 3130 -> 3090 us, of the T5 shape with 5 rows 2786 -> 2735.
+template <int MT, bool HALF>
+__device__ __forceinline__ void gemm_load_a(u32x4 (&A)[2 * MT - HALF], const ChainGemm &P, const GemmShare &S, __amdgpu_buffer_rsrc_t ra, int ks,
                                             const int (&voff_a)[MT]) {
     const bool in = ks < S.ks1;   // uniform
 #pragma unroll
-    for (int mt = 0; mt < MT; mt++) {
-        A[mt][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, in ? voff_a[mt] : CH_OOB,
-                                                                                  in ? (ks * P.mtp + mt) * 1024 : 0, 0));
-        A[mt][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                 ra, in ? voff_a[mt] : CH_OOB, in ? P.a_plane_bytes + (ks * P.mtp + mt) * 1024 : 0, 0));
+    for (int f = 0; f < 2 * MT - HALF; f++) {
+        const int mt = f / 2;
+        A[f] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             ra, in ? voff_a[mt] : CH_OOB, in ? (f & 1 ? P.a_plane_bytes : 0) + (ks * P.mtp + mt) * 1024 : 0, 0));
     }
 }
 
@@ -76,7 +79,7 @@ __device__ __forceinline__ void gemm_prefetch(u32x4 (&Wr)[R][NT], const ChainGem
 // The GEMM of one workgroup after gemm_prefetch: the wave's k-steps through the rings for MT row tiles of 16 rows, the
 // eight partial tiles added in LDS in wave order (one row tile at a time), the epilogue.  LDS: red [8 waves][NT][64 lanes]
 // 16-byte words, then [8 waves][16 MT rows] floats.  Every wave of the workgroup must call it (it holds workgroup barriers).
-template <int NT, int R, int EPI, int MT>
+template <int NT, int R, int EPI, int MT, bool HALF>
 __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P, const GemmShare &S, char *smem) {
     f32x4 *red = reinterpret_cast<f32x4 *>(smem);
     float *rs_part = reinterpret_cast<float *>(smem + (size_t)CH_WAVES * NT * 64 * 16);
@@ -89,6 +92,7 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
     int voff_a[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; mt++) voff_a[mt] = mt * 16 + t < P.M ? (4 * t + g) * 16 : CH_OOB;
+    if (HALF) voff_a[MT - 1] = (MT - 1) * 16 + (t & 7) < P.M ? (4 * (t & 7) + g) * 16 + (t < 8 ? 0 : P.a_plane_bytes) : CH_OOB;
 
     // partial sums of squares of the rows behind the folded norm: wave w, lane group g take every 32nd tile.
     // Eight independent loads per row tile and turn (a dependent chain of them would hold up the rings behind it).
@@ -113,14 +117,14 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
                 for (int n = 0; n < 8; n++) ssq[mt] += sv[mt][n];
         }
     }
-    u32x4 Ar[R][MT][2];
+    u32x4 Ar[R][2 * MT - HALF];
     f32x4 acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; mt++)
 #pragma unroll
         for (int j = 0; j < NT; j++) acc[mt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < R; r++) gemm_load_a<MT>(Ar[r], P, S, ra, ks0 + r, voff_a);
+    for (int r = 0; r < R; r++) gemm_load_a<MT, HALF>(Ar[r], P, S, ra, ks0 + r, voff_a);
 
     // epilogue inputs that do not depend on the sums: fetched now, used after the reduction
     EpiIn E[MT];
@@ -160,18 +164,13 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
 #pragma unroll
         for (int r = 0; r < R; r++) {
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++) {
+            for (int f = 0; f < 2 * MT - HALF; f++)
 #pragma unroll
                 for (int j = 0; j < NT; j++)
-                    acc[mt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wr[r][j]),
-                                                                         __builtin_bit_cast(bf16x8, Ar[r][mt][0]), acc[mt][j], 0, 0, 0);
-#pragma unroll
-                for (int j = 0; j < NT; j++)
-                    acc[mt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wr[r][j]),
-                                                                         __builtin_bit_cast(bf16x8, Ar[r][mt][1]), acc[mt][j], 0, 0, 0);
-            }
+                    acc[f / 2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wr[r][j]),
+                                                                            __builtin_bit_cast(bf16x8, Ar[r][f]), acc[f / 2][j], 0, 0, 0);
             gemm_load_w<NT>(Wr[r], P, S, rw, ks + r + R, lane);
-            gemm_load_a<MT>(Ar[r], P, S, ra, ks + r + R, voff_a);
+            gemm_load_a<MT, HALF>(Ar[r], P, S, ra, ks + r + R, voff_a);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -198,6 +197,10 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
                 v[x] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int i = 0; i < CH_WAVES; i++) v[x] += red[(i * NT + w * UT + x) * 64 + lane];
+                if (HALF && mt == MT - 1) {                    // row t: column t (hi) + column t + 8 (lo)
+#pragma unroll
+                    for (int i = 0; i < 4; i++) v[x][i] += across_half_row(v[x][i]);
+                }
                 v[x] *= rstd;
             }
             gemm_epilogue<EPI>(P, v, E[mt], mt * 16 + t, t0 + w * UT, g);
@@ -206,14 +209,14 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
 }
 
 // LIVE: a review of one sequence that the device may have skipped (a separate form: the look costs a plain step 0.7 %)
-template <int NT, int R, int EPI, int MT, bool LIVE>
+template <int NT, int R, int EPI, int MT, bool HALF, bool LIVE>
 __global__ __launch_bounds__(CH_THREADS) void kc_gemm(const ChainGemm P) {
     extern __shared__ __align__(16) char ch_smem[];
     const GemmShare S = gemm_share<EPI>(P, blockIdx.x, gridDim.x, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
     u32x4 Wr[R][NT];
     gemm_prefetch<NT, R>(Wr, P, S);
     if (LIVE && P.live[0] == 0) return;                      // (the first weights are on their way meanwhile)
-    gemm_run<NT, R, EPI, MT>(Wr, P, S, ch_smem);
+    gemm_run<NT, R, EPI, MT, HALF>(Wr, P, S, ch_smem);
 }
 
 // Causal attention of a block of up to 16 rows over the cached prefix, one launch per layer.  A workgroup
@@ -749,11 +752,14 @@ static int32_t attn_launch_small(const csd_model *mod, const AttnArgs &A, int ke
 template <int NT, int R, int EPI, int MT>
 static hipError_t chain_allow_lds() {
     const int lds = CH_WAVES * NT * 64 * 16 + CH_WAVES * MT * 16 * 4;
+    auto allow = [&](const void *f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+    hipError_t e = allow((const void *)kc_gemm<NT, R, EPI, MT, false, false>);
+    if (e == hipSuccess) e = allow((const void *)kc_gemm<NT, R, EPI, MT, true, false>);
     if constexpr (MT == 1) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kc_gemm<NT, R, EPI, MT, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
+        if (e == hipSuccess) e = allow((const void *)kc_gemm<NT, R, EPI, MT, false, true>);
+        if (e == hipSuccess) e = allow((const void *)kc_gemm<NT, R, EPI, MT, true, true>);
     }
-    return hipFuncSetAttribute((const void *)kc_gemm<NT, R, EPI, MT, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    return e;
 }
 
 #ifndef CH_R1
@@ -798,10 +804,10 @@ static int32_t chain_launch_mt(ChainGemm &P, int G, int per, hipStream_t st) {
 #define CH_LAUNCH(NT, R, E, MT_)                                                                                   \
     if (per <= NT) {                                                                                              \
         const int lds = CH_WAVES * NT * 64 * 16 + CH_WAVES * MT_ * 16 * 4;                                        \
-        if (MT_ == 1 && P.live && P.M == P.m)                                                                     \
-            hipLaunchKernelGGL((kc_gemm<NT, R, E, MT_, MT_ == 1>), dim3(G), dim3(CH_THREADS), lds, st, P);         \
-        else                                                                                                      \
-            hipLaunchKernelGGL((kc_gemm<NT, R, E, MT_, false>), dim3(G), dim3(CH_THREADS), lds, st, P);            \
+        const bool half = (P.M - 1) % 16 < 8, live = MT_ == 1 && P.live && P.M == P.m;                            \
+        hipLaunchKernelGGL((half ? live ? kc_gemm<NT, R, E, MT_, true, MT_ == 1> : kc_gemm<NT, R, E, MT_, true, false>     \
+                                 : live ? kc_gemm<NT, R, E, MT_, false, MT_ == 1> : kc_gemm<NT, R, E, MT_, false, false>), \
+                           dim3(G), dim3(CH_THREADS), lds, st, P);                                                \
         return CSD_OK;                                                                                            \
     }
     if constexpr (MT == 1) {

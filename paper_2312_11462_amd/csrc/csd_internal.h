@@ -146,6 +146,11 @@ __device__ __forceinline__ float groups_sum(float v) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// the value of the lane eight further (modulo 16) among the sixteen with the same lane / 16
+__device__ __forceinline__ float across_half_row(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
+}
+
 // sum over a block of up to 1024 threads; every thread gets the result; `red` holds >= 16 floats
 __device__ __forceinline__ float block_sum(float v, float *red) {
     v = wave_sum(v);

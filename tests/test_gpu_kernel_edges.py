@@ -290,12 +290,12 @@ def test_planes_of_more_than_two_gib(P, m):
     assert err < 1e-4
 
 
-def _head_alone(P, K, V, rows, emb, lm):
+def _head_alone(P, K, V, rows, emb, lm, gain=None):
     """Logits of a model of one layer that adds nothing to its input: the LM head over the embedding rows 0 .. rows - 1."""
     shape = I.ModelShape("edge_head", 0, "bf16", 1, K, 1, 64, 64, V)
     z = lambda r, c: torch.zeros((r, c), dtype=torch.bfloat16, device="cuda")
     one = torch.ones(K, device="cuda")
-    gm = P.Model(shape, [emb, one, z(K, 64), z(K, 64), z(K, 64), z(64, K), one, z(K, 64), z(K, 64), z(64, K), one, lm],
+    gm = P.Model(shape, [emb, one, z(K, 64), z(K, 64), z(K, 64), z(64, K), one, z(K, 64), z(K, 64), z(64, K), one if gain is None else gain, lm],
                  max_batch=1, max_seq=rows, max_block=rows)
     out = gm.verify_block(torch.arange(rows, dtype=torch.int32, device="cuda")[None], torch.zeros(1, dtype=torch.int32, device="cuda"))[0]
     gm.close()
@@ -350,6 +350,48 @@ def test_row_split_sums(P, K, V, plan, m):
     ref, size = (x @ lm.double()) * rstd, (x.abs() @ lm.double().abs()) * rstd
     got = _head_alone(P, K, V, m, emb, lm).double()
     assert ((got - ref).abs() <= (K + 16) * 2.0 ** -23 * size).all()
+
+
+@pytest.mark.parametrize("K,V", [(64, 528), (768, 4112), (4096, 8208)])
+@pytest.mark.parametrize("m", [1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32])
+def test_few_row_sums(P, K, V, m):
+    """The GEMM over up to 32 rows at either side of half a row tile, where one fragment holds both planes of the last rows, with inputs
+    that need the lo plane (rows times a gain of 24 bits).  The planes hold an input to 2^-17 of its size; a sum of K products of either
+    plane in 32 bits is within K 2^-23 of the sum of their sizes."""
+    g = torch.Generator(device="cuda").manual_seed(K + m)
+    emb = torch.empty((V, K), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    lm = torch.empty((K, V), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    gain = torch.rand(K, generator=g, device="cuda") + 0.5
+    x = emb[:m].double()
+    rstd = torch.rsqrt((x * x).mean(-1, keepdim=True) + 1e-5)
+    x = x * gain.double()
+    ref, size = (x @ lm.double()) * rstd, (x.abs() @ lm.double().abs()) * rstd
+    got = _head_alone(P, K, V, m, emb, lm, gain).double()
+    assert ((got - ref).abs() <= ((K + 16) * 2.0 ** -23 + 2.0 ** -17) * size).all()
+
+
+@pytest.mark.parametrize("arch,dh", [(0, 64), (1, 64), (0, 128)])
+@pytest.mark.parametrize("B,m", [(1, 8), (1, 9), (4, 2), (3, 8), (5, 5)])
+def test_blocks_of_half_row_tiles(P, arch, dh, B, m):
+    """Every epilogue over 8, 9, 24 and 25 rows, of one sequence and of several, on the forward with its epilogues inside the GEMMs."""
+    from gpu_util import import_synthetic_kv, make_pair, tol_ok
+    shape = I.ModelShape("edge_half", arch, "bf16", 2, 192, 3, dh, 320, 512, rms_eps=1e-6 if arch else 1e-5, enc_len=20 if arch else 0)
+    gm, om = make_pair(shape, 47, B, 96, m, std=0.05)
+    import_synthetic_kv(gm, om, shape, 40, 47, B=B)
+    if arch:
+        enc = I.encoder_output(shape, B, 47)
+        gm.cross_kv_init(enc.cuda())
+        om.cross_kv_init(enc.numpy())
+    block = I.token_ids(B * m, shape.vocab, 47, 1).reshape(B, m).numpy().astype(np.int32)
+    cl = np.asarray([40 - 3 * b for b in range(B)], np.int32)
+    assert gm.path(B, m) == 1
+    lg = gm.verify_block(torch.from_numpy(block).cuda(), torch.from_numpy(cl).cuda())
+    ok, err = tol_ok(lg.cpu().numpy().astype(np.float64), om.verify_block(block, cl), 2e-2, 1e-2)
+    assert ok, f"max abs err {err}"
+    for b in range(B):
+        for got, want in zip(gm.kv_read(1, b, 0, int(cl[b]) + m), om.kv_read(1, b, 0, int(cl[b]) + m)):
+            ok, err = tol_ok(got.cpu().numpy().astype(np.float64), want, 2e-2, 1e-2)
+            assert ok, f"cache rows of sequence {b}: max abs err {err}"
 
 
 @pytest.mark.parametrize("V,m", [(22016, 512), (4096, 512)])
