@@ -21,6 +21,8 @@ def build(verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 and link the C-ABI shared library."""
     cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # plain kernel arguments in scalar registers when a wave starts (as many dwords as there is room for)
+           "-mllvm", "-amdgpu-kernarg-preload-count=16",
            "-Wall", "-Wno-unused-function", "-Rpass-analysis=kernel-resource-usage",
            "-o", LIB] + os.environ.get("CSD_HIPCC_FLAGS", "").split() + [os.path.join(CSRC, s) for s in SOURCES]
     res = subprocess.run(cmd, capture_output=True, text=True)
