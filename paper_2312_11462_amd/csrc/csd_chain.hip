@@ -16,8 +16,9 @@
 // the producer of h writes h * g and one sum of squares per (row, 16-feature tile), the consumer's
 // epilogue scales its output rows by 1 / sqrt(sum / d + eps).
 #include <cmath>
+#include <type_traits>
 
-#include "csd_epilogue.h"
+#include "csd_warm.h"
 
 #define CH_WAVES 8
 #define CH_THREADS (CH_WAVES * 64)
@@ -210,9 +211,10 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
 
 // LIVE: a review of one sequence that the device may have skipped (a separate form: the look costs a plain step 0.7 %)
 //
-// What the first loads need comes as plain arguments ahead of the structure: the build asks for them to be in registers when a
-// wave starts (14 dwords of them fit), where the structure is a cold read of memory in front of everything else, once per launch.  kc_gemm and the
-// attention together, per step: 160M shape 417 -> 396 us, 7B shape 3090 -> 2963, T5 shape 2735 -> 2649 (64, 162 and 196 launches).
+// What the first loads need comes as plain arguments ahead of the structure: the build asks for 14 dwords of them to be in registers when a
+// wave starts (build.py), where the structure is a cold read of memory in front of everything else.  The kernels of the small-block forward
+// begin with it 64 to 196 times in a row per step: with kc_gemm's alone 160M shape 400 -> 378 us per step, 7B shape 3061 -> 2986, T5 shape 2640 -> 2562;
+// with the attention's too 374, 2963 and 2562.
 template <int NT, int R, int EPI, int MT, bool HALF, bool LIVE>
 __global__ __launch_bounds__(CH_THREADS) void kc_gemm(const u32x4 *Wp, int KS, int n_units, int wbytes, int G, const bf16_t *a, int a_plane_bytes,
                                                       int mtp, int M, const int32_t *live, const ChainGemm rest) {
@@ -251,6 +253,7 @@ struct AttnArgs {
     float scale;
     float *part;              // chunk states [B][H][chunks_max][16 rows][DH + 4]
     int chunks_max;
+    int chunk_slots;          // chunks the grid holds (workgroups past them read ahead, see csd_warm.h)
     unsigned *counters;       // arrivals per (sequence, head): zero between launches
     const unsigned long long *anc;   // tree block: per block row the rows it sees (see AttnMode), or null
     const float *bias_hd;     // arch 1 self-attention: [H][128] bias by distance query - key (127: that or more), or null
@@ -263,7 +266,7 @@ struct AttnArgs {
 // The arguments that the first loads need come ahead of the structure, in registers when a wave starts (see kc_gemm).
 template <int DH>
 __device__ __forceinline__ AttnArgs attn_args(const bf16_t *k, const bf16_t *v, const bf16_t *q, const int32_t *cache_len, const int32_t *live,
-                                              int q_plane, int H, int seq_pad, int rows, const AttnArgs &rest) {
+                                              int q_plane, int H, int seq_pad, int rows_slots, const AttnArgs &rest) {
     AttnArgs A = rest;
     A.k = k;
     A.v = v;
@@ -274,10 +277,11 @@ __device__ __forceinline__ AttnArgs attn_args(const bf16_t *k, const bf16_t *v, 
     A.geo.H = H;
     A.geo.seq_pad = seq_pad;
     A.geo.dh = DH;
-    A.m = rows;
+    A.m = rows_slots & 31;                                   // (up to 16 rows)
+    A.chunk_slots = rows_slots >> 5;
     return A;
 }
-#define CA_ARGS(A) (A).k, (A).v, (A).q, (A).cache_len, (A).live, (A).q_plane, (A).geo.H, (A).geo.seq_pad, (A).m, A
+#define CA_ARGS(A) (A).k, (A).v, (A).q, (A).cache_len, (A).live, (A).q_plane, (A).geo.H, (A).geo.seq_pad, (A).m | (A).chunk_slots << 5, A
 template <int DH>
 struct AttnLds {
     f32x4 o[4][DH / 16][64];
@@ -517,11 +521,17 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
 // transposed), the four softmax states are merged in LDS, and the workgroup writes one partial state per
 // chunk.  The last workgroup of a (sequence, head) to finish (an arrival counter) merges the chunks and
 // writes the rows as the O projection's input; the counter is back at zero when the kernel ends.
-template <int DH, bool LIVE>
+template <int DH, bool LIVE, class WARM>
 __global__ __launch_bounds__(256) void kc_attn(const bf16_t *k, const bf16_t *v, const bf16_t *q, const int32_t *cache_len, const int32_t *live, int q_plane,
-                                               int H, int seq_pad, int rows, const AttnArgs rest) {
+                                               int H, int seq_pad, int rows_slots, const AttnArgs rest, const WARM Wm) {
     __shared__ __align__(16) AttnLds<DH> L;
-    const AttnArgs A = attn_args<DH>(k, v, q, cache_len, live, q_plane, H, seq_pad, rows, rest);
+    const AttnArgs A = attn_args<DH>(k, v, q, cache_len, live, q_plane, H, seq_pad, rows_slots, rest);
+    if constexpr (!std::is_same<WARM, NoWarm>::value)
+        if (__builtin_expect((int)blockIdx.z >= A.chunk_slots, 0)) {
+            const int per_z = gridDim.x * gridDim.y, e = (blockIdx.z - A.chunk_slots) * per_z + blockIdx.y * gridDim.x + blockIdx.x;
+            if (!(LIVE && A.live[blockIdx.y] <= 0)) l2_warm(Wm, e, A.chunk_slots * per_z + e, &L);
+            return;
+        }
     // Grid (head, sequence, chunk): the last chunk of a head holds little besides the block's own rows, and with the chunk
     // index slowest those short workgroups are dispatched after every long one has a compute unit of its own.
     attn_item<DH, LIVE>(A, L, true, blockIdx.z, blockIdx.x, blockIdx.y, threadIdx.x);
@@ -540,11 +550,17 @@ struct AttnOneLds {
     f32x4 o[NW][DH / 16][64];
     float m[NW][16], l[NW][16], w[NW][16];
 };
-template <int DH, int NW, bool BIAS, bool LIVE>
+template <int DH, int NW, bool BIAS, bool LIVE, class WARM>
 __global__ __launch_bounds__(NW * 64) void kc_attn_one(const bf16_t *k, const bf16_t *v, const bf16_t *q, const int32_t *cache_len, const int32_t *live, int q_plane,
-                                                       int H, int seq_pad, int rows, const AttnArgs rest) {
+                                                       int H, int seq_pad, int rows_slots, const AttnArgs rest, const WARM Wm) {
     extern __shared__ __align__(16) char one_smem[];
-    const AttnArgs A = attn_args<DH>(k, v, q, cache_len, live, q_plane, H, seq_pad, rows, rest);
+    const AttnArgs A = attn_args<DH>(k, v, q, cache_len, live, q_plane, H, seq_pad, rows_slots, rest);
+    if constexpr (!std::is_same<WARM, NoWarm>::value)
+        if (__builtin_expect(blockIdx.z > 0, 0)) {
+            const int per_z = gridDim.x * gridDim.y, e = (blockIdx.z - 1) * per_z + blockIdx.y * gridDim.x + blockIdx.x;
+            if (!(LIVE && A.live[blockIdx.y] <= 0)) l2_warm(Wm, e, per_z + e, one_smem);
+            return;
+        }
     AttnOneLds<DH, NW> &L = *reinterpret_cast<AttnOneLds<DH, NW> *>(one_smem);
     constexpr int DT = DH / 16;
     const KvGeom &geo = A.geo;
@@ -756,31 +772,76 @@ static bool attn_one_fits(const csd_model *mod, int B, int keys_pad) {
     const int most = mod->cfg.head_dim == 64 ? CA_ONE_KEYS_64 : groups < 64 ? CA_ONE_KEYS_128_FEW : CA_ONE_KEYS_128;
     return groups <= CA_ONE_GROUPS && keys_pad <= most;
 }
-template <int DH, bool BIAS>
-static void attn_one_launch(const AttnArgs &A, int H, int B, hipStream_t st) {
-    hipLaunchKernelGGL((A.live ? kc_attn_one<DH, CA_ONE_NW, BIAS, true> : kc_attn_one<DH, CA_ONE_NW, BIAS, false>), dim3(H, B),
-                       dim3(CA_ONE_NW * 64), sizeof(AttnOneLds<DH, CA_ONE_NW>), st, CA_ARGS(A));
+template <int DH, bool BIAS, class WARM>
+static void attn_one_launch(const AttnArgs &A, const WARM &Wm, const dim3 &grid, hipStream_t st) {
+    hipLaunchKernelGGL((A.live ? kc_attn_one<DH, CA_ONE_NW, BIAS, true, WARM> : kc_attn_one<DH, CA_ONE_NW, BIAS, false, WARM>), grid,
+                       dim3(CA_ONE_NW * 64), sizeof(AttnOneLds<DH, CA_ONE_NW>), st, CA_ARGS(A), Wm);
+}
+template <int DH, class WARM>
+static void attn_launch_dh(const AttnArgs &A, const WARM &Wm, bool one, const dim3 &grid, hipStream_t st) {
+    if (!one)
+        hipLaunchKernelGGL((A.live ? kc_attn<DH, true, WARM> : kc_attn<DH, false, WARM>), grid, dim3(256), 0, st, CA_ARGS(A), Wm);
+    else if (A.bias_hd)
+        attn_one_launch<DH, true>(A, Wm, grid, st);
+    else
+        attn_one_launch<DH, false>(A, Wm, grid, st);
 }
 
-static int32_t attn_launch_small(const csd_model *mod, const AttnArgs &A, int keys_pad, int B, hipStream_t st) {
+// a workgroup per compute unit, or as many more as keep a workgroup's tiles to eight
+static int chain_groups(int n_units, int ut) {
+    int G = n_units < 256 ? n_units : 256;
+    if ((n_units + G - 1) / G * ut > 8) G = (n_units * ut + 7) / 8;
+    return G;
+}
+
+// What the workgroups added to an attention launch read (csd_warm.h), us per step without them and with them:
+// - all the matrices behind it up to the next layer, where these are 20 MB at most (160M shape, 15.3 MB: 512 cached rows 396 -> 375, 14 of the MB 377, 8 of
+//   them 389; 100 rows 327 -> 307; chunks of 1024 rows 421 -> 402; with the next layer's QKV too, before arguments came in registers, 398 -> 425);
+// - else, beside one workgroup per head, as much of the first (and so on) as 30 MB, from 256 cache rows on (T5 shape, 33.6 MB: 14 MB 2612, 24 MB 2570,
+//   30 MB 2551, none 2649; 7B shape, 300 rows 2991 -> 2969), 14 MB with fewer, where the attention is shorter (7B shape, 100 rows 2772 -> 2784, with
+//   30 MB 2836; T5 shape, 20 rows and 40 encoder rows 2529 -> 2493, with 30 MB 2525);
+// - beside the chunks of large models nothing: their own loads keep the memory busy (7B shape, 1024 rows 2963 against 2960 with 14 MB, 2967 with
+//   16; two sequences of 700 rows 3198 against 3257).
+// 96 workgroups of 16 waves, 128 of 4: 184 and 224 are no faster, half as many are (T5 shape, 30 MB 2805 us), and no more than fit on the chip with the launch's own.
+#define WARM_LAYER (20u << 20)
+#define WARM_MOST (30u << 20)
+#define WARM_SHORT (14u << 20)
+#define WARM_LONG_KEYS 256
+static int warm_plan(L2Warm &Wm, const GemmW *const *mats, int n, bool one, int keys_pad, int per_z, int used) {
+    Wm = L2Warm{};
+    size_t left = 0;
+    for (int i = 0; i < n; i++) left += (size_t)mats[i]->K * mats[i]->N * 2;
+    if (left > WARM_LAYER) left = !one ? 0 : keys_pad >= WARM_LONG_KEYS ? WARM_MOST : WARM_SHORT;
+    const int want = one ? 96 : 128, room = (one ? 256 : 512) - used;
+    int z = (want + per_z - 1) / per_z;
+    if (z * per_z > room) z = room > 0 ? room / per_z : 0;
+    if (!left || z * per_z < 8) return 0;
+    for (int i = 0; i < n && i < L2_WARM_MATS; i++) {
+        const GemmW &w = *mats[i];
+        const int ut = i == 1 ? 2 : 1;                       // O, gate|up, down
+        L2Warm::Mat m{w.data, (int)((size_t)w.K * w.N * 2), w.K / 32, w.N / 16 / ut, ut, 0};
+        const size_t step = (size_t)w.N / 16 * 8 * 1024;     // one k-step of every wave
+        const size_t most = (size_t)(m.KS + 7) / 8, fit = left / step;
+        m.keep = chain_groups(m.units, ut) % 8 ? 0 : (int)(fit < most ? fit : most);
+        left -= m.keep * step < left ? m.keep * step : left;
+        Wm.mat[i] = m;
+    }
+    Wm.groups = z * per_z / 8 * 8;
+    return z;
+}
+
+// mats: the matrices of the GEMMs behind this launch (the output projection, then gate|up and down where they come next)
+static int32_t attn_launch_small(const csd_model *mod, AttnArgs A, const GemmW *const *mats, int n_mats, int keys_pad, int B, hipStream_t st) {
     const int H = mod->cfg.n_heads;
     const bool one = attn_one_fits(mod, B, keys_pad);
-    const dim3 grid(H, B, (keys_pad + CA_KEYS - 1) / CA_KEYS);       // chunk index slowest: see kc_attn
-    if (mod->cfg.head_dim == 128) {
-        if (!one)
-            hipLaunchKernelGGL((A.live ? kc_attn<128, true> : kc_attn<128, false>), grid, dim3(256), 0, st, CA_ARGS(A));
-        else if (A.bias_hd)
-            attn_one_launch<128, true>(A, H, B, st);
-        else
-            attn_one_launch<128, false>(A, H, B, st);
-    } else {
-        if (!one)
-            hipLaunchKernelGGL((A.live ? kc_attn<64, true> : kc_attn<64, false>), grid, dim3(256), 0, st, CA_ARGS(A));
-        else if (A.bias_hd)
-            attn_one_launch<64, true>(A, H, B, st);
-        else
-            attn_one_launch<64, false>(A, H, B, st);
-    }
+    A.chunk_slots = (keys_pad + CA_KEYS - 1) / CA_KEYS;
+    L2Warm Wm;
+    const int wz = warm_plan(Wm, mats, n_mats, one, keys_pad, H * B, H * B * (one ? 1 : A.chunk_slots));
+    const dim3 grid(H, B, (one ? 1 : A.chunk_slots) + wz);           // chunk index slowest: see kc_attn
+    if (mod->cfg.head_dim == 128)
+        wz ? attn_launch_dh<128>(A, Wm, one, grid, st) : attn_launch_dh<128>(A, NoWarm{}, one, grid, st);
+    else
+        wz ? attn_launch_dh<64>(A, Wm, one, grid, st) : attn_launch_dh<64>(A, NoWarm{}, one, grid, st);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }
@@ -824,16 +885,17 @@ int32_t csd_chain_setup() {
     CH_FOR_ALL_NT_TALL(CH_ALLOW, EPI_LOGITS, 2)
     CH_FOR_GU_TALL(CH_ALLOW, 2)
 #undef CH_ALLOW
-#define CA_ALLOW(DH, BIAS)                                                                                                            \
-    CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                (int)sizeof(AttnOneLds<DH, CA_ONE_NW>)));                                                             \
-    CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS, true>, hipFuncAttributeMaxDynamicSharedMemorySize,      \
+#define CA_ALLOW_ONE(DH, BIAS, LIVE, WARM)                                                                                         \
+    CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS, LIVE, WARM>, hipFuncAttributeMaxDynamicSharedMemorySize, \
                                 (int)sizeof(AttnOneLds<DH, CA_ONE_NW>)));
+#define CA_ALLOW(DH, BIAS) \
+    CA_ALLOW_ONE(DH, BIAS, false, NoWarm) CA_ALLOW_ONE(DH, BIAS, true, NoWarm) CA_ALLOW_ONE(DH, BIAS, false, L2Warm) CA_ALLOW_ONE(DH, BIAS, true, L2Warm)
     CA_ALLOW(128, false)
     CA_ALLOW(128, true)
     CA_ALLOW(64, false)
     CA_ALLOW(64, true)
 #undef CA_ALLOW
+#undef CA_ALLOW_ONE
     return CSD_OK;
 }
 
@@ -871,9 +933,7 @@ template <int EPI>
 static int32_t chain_launch(ChainGemm &P, int n_tiles, hipStream_t st) {
     constexpr int UT = EPI == EPI_GU ? 2 : 1;
     P.n_units = n_tiles / UT;
-    // a workgroup per compute unit, or as many more as keep a workgroup's tiles to eight
-    int G = P.n_units < 256 ? P.n_units : 256;
-    if ((P.n_units + G - 1) / G * UT > 8) G = (P.n_units * UT + 7) / 8;
+    const int G = chain_groups(P.n_units, UT);
     const int per = (P.n_units + G - 1) / G * UT;            // most tiles of a workgroup
     const int mt = (P.M + 15) / 16;
     if (mt == 1) return chain_launch_mt<EPI, 1>(P, G, per, st);
@@ -1014,7 +1074,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
     }
             // either attention: the kernel whose last chunk merges, or (more than 16 rows per sequence, or so many chunks
             // that bandwidth rather than latency binds) the one with longer key runs and a merge kernel
-            auto attention = [&](const KvGeom &g_, const void *kv_, int keys_pad, const AttnMode &mode) -> int32_t {
+            auto attention = [&](const KvGeom &g_, const void *kv_, int keys_pad, const AttnMode &mode, const GemmW *const *mats, int n_mats) -> int32_t {
                 const int chunks = (keys_pad + CA_KEYS - 1) / CA_KEYS;
                 if (m > 16 || (!attn_one_fits(mod, B, keys_pad) && ((long long)chunks * c.n_heads * B > 1024 || chunks > CA_MAX_CHUNKS)))
                     return csd_attn_mfma_enqueue(mod, g_, kv_, cache_len, B, m, l, scale, mode, st, X2, mod->x_plane[1]);
@@ -1022,13 +1082,14 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
                 AttnArgs A = attn_of(g_, kv_, l);
                 A.bias_hd = mode.bias_hd;
                 A.fixed_nk = mode.fixed_nk;
-                return attn_launch_small(mod, A, keys_pad, B, st);
+                return attn_launch_small(mod, A, mats, n_mats, keys_pad, B, st);
             };
+            const GemmW *const after_self[] = {&lw.o}, *const after_cross[] = {&lw.co, &lw.gu, &lw.down};
             CH_STEP(EPI_QKV, Pq, lw.qkv)
-            if ((rc = attention(geo, kv, mod->seq_pad, self_mode)) != CSD_OK) return rc;
+            if ((rc = attention(geo, kv, mod->seq_pad, self_mode, after_self, 1)) != CSD_OK) return rc;
             CH_STEP(EPI_RESID, Po, lw.o)
             CH_STEP(EPI_QKV, Pcq, lw.cq)
-            if ((rc = attention(cgeo, kv_cross, mod->enc_pad, cross_mode)) != CSD_OK) return rc;
+            if ((rc = attention(cgeo, kv_cross, mod->enc_pad, cross_mode, after_cross, 3)) != CSD_OK) return rc;
             CH_STEP(EPI_RESID, Pco, lw.co)
             CH_STEP(EPI_GU, Pg, lw.gu)
             CH_STEP(EPI_RESID, Pd, lw.down)
@@ -1056,7 +1117,8 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
                     return rc;
             } else {
                 ProfScope ps(mod, st, CSD_PROF_ATTN);
-                if ((rc = attn_launch_small(mod, A, mod->seq_pad, B, st)) != CSD_OK) return rc;
+                const GemmW *const mats[] = {&lw.o, &lw.gu, &lw.down};
+                if ((rc = attn_launch_small(mod, A, mats, 3, mod->seq_pad, B, st)) != CSD_OK) return rc;
             }
             {
                 ProfScope ps(mod, st, CSD_PROF_GEMM);

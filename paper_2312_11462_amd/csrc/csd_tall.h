@@ -24,6 +24,12 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, lds_void d,
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, d, 16, voff, soff, 0, AUX);
 #endif
 }
+// 4 bytes per lane likewise
+__device__ __forceinline__ void lds_load4(__amdgpu_buffer_rsrc_t r, lds_void d, int voff, int soff) {
+#ifdef __HIP_DEVICE_COMPILE__
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, d, 4, voff, soff, 0, 0);
+#endif
+}
 // At most V vector memory operations still outstanding, and no LDS read.
 template <int V>
 __device__ __forceinline__ void wait_loads() {
