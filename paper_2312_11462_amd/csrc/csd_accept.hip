@@ -57,7 +57,7 @@ __device__ __forceinline__ ArgMax better(ArgMax a, ArgMax b) {     // larger val
 
 __device__ int block_argmax(const float *__restrict__ row, int V, ArgMax *red) {
     ArgMax best = {-INFINITY, 0x7FFFFFFF};
-    for (int v = threadIdx.x; v < V; v += blockDim.x) {
+    for (int v = threadIdx.x; v < V; v += ACC_THREADS) {
         const float x = row[v];
         // NaN never wins; the first finite-or-inf value does
         if (x > best.v || (x == best.v && v < best.i)) best = {x, v};
@@ -67,7 +67,8 @@ __device__ int block_argmax(const float *__restrict__ row, int V, ArgMax *red) {
         ArgMax other = {__shfl_xor(best.v, o, 64), __shfl_xor(best.i, o, 64)};
         best = better(best, other);
     }
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    constexpr int nw = ACC_THREADS / 64;
+    const int w = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = best;
     __syncthreads();
@@ -113,7 +114,8 @@ __device__ __forceinline__ unsigned long long range_weight(const float *__restri
 // Exclusive prefix of one 64-bit value per thread over the block, in thread order, and the block total.
 __device__ __forceinline__ unsigned long long block_exclusive_scan(unsigned long long mine, unsigned long long *wave_tot,
                                                                    unsigned long long &total) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    constexpr int nw = ACC_THREADS / 64;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     unsigned long long incl = mine;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -412,15 +414,17 @@ __global__ __launch_bounds__(ACC_THREADS) void k_accept(
 #define SM_THREADS 1024
 #define SM_PER 32
 
+template <int T>
 __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long *red) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    const int w = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = v;
     __syncthreads();
     unsigned long long t = 0ull;
-    for (int i = 0; i < nw; i++) t += red[i];
+#pragma unroll
+    for (int i = 0; i < T / 64; i++) t += red[i];
     return t;
 }
 __device__ __forceinline__ float scaled_logit(float x, float inv_t) { return x * inv_t; }
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, flo
             val[i] = v < V ? scaled_logit(x[v], inv_t) : -INFINITY;
             mx = fmaxf(mx, val[i]);
         }
-        mx = block_max(mx, red);
+        mx = block_max<SM_THREADS>(mx, red);
         uint32_t sh = 0, sl = 0;                    // at most 32 terms of at most 2^20 each
 #pragma unroll
         for (int i = 0; i < SM_PER; i++) {
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, flo
             fixed40_parts(val[i], h, l);
             sh += h, sl += l;
         }
-        const float r = recip_of_total(block_sum_u64((unsigned long long)sh * (1u << 20) + sl, red64));
+        const float r = recip_of_total(block_sum_u64<SM_THREADS>((unsigned long long)sh * (1u << 20) + sl, red64));
 #pragma unroll
         for (int i = 0; i < SM_PER; i++) {
             const int v = i * SM_THREADS + (int)threadIdx.x;
@@ -466,16 +470,16 @@ __global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, flo
         return;
     }
     float mx = -INFINITY;
-    for (int v = threadIdx.x; v < V; v += blockDim.x) mx = fmaxf(mx, scaled_logit(x[v], inv_t));
-    mx = block_max(mx, red);
+    for (int v = threadIdx.x; v < V; v += SM_THREADS) mx = fmaxf(mx, scaled_logit(x[v], inv_t));
+    mx = block_max<SM_THREADS>(mx, red);
     unsigned long long s = 0ull;
-    for (int v = threadIdx.x; v < V; v += blockDim.x) {
+    for (int v = threadIdx.x; v < V; v += SM_THREADS) {
         const float e = exp_term(scaled_logit(x[v], inv_t), mx);
         y[v] = e;
         s += fixed40_small(e);
     }
-    const float r = recip_of_total(block_sum_u64(s, red64));
-    for (int v = threadIdx.x; v < V; v += blockDim.x) y[v] *= r;
+    const float r = recip_of_total(block_sum_u64<SM_THREADS>(s, red64));
+    for (int v = threadIdx.x; v < V; v += SM_THREADS) y[v] *= r;
 }
 
 int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int32_t V, float temperature,
@@ -560,7 +564,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             val[i] = scaled_logit(val[i], inv_t);
             mx = fmaxf(mx, val[i]);
         }
-        mx = block_max(mx, red);
+        mx = block_max<RR_THREADS>(mx, red);
         uint32_t sh = 0, sl = 0;                                 // at most 64 terms of at most 2^20 each
 #pragma unroll
         for (int i = 0; i < RR_PER; i++) {
@@ -569,7 +573,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             fixed40_parts(val[i], h, l);
             sh += h, sl += l;
         }
-        r = recip_of_total(block_sum_u64((unsigned long long)sh * (1u << 20) + sl, red64));
+        r = recip_of_total(block_sum_u64<RR_THREADS>((unsigned long long)sh * (1u << 20) + sl, red64));
 #pragma unroll
         for (int i = 0; i < RR_PER; i++) val[i] = val[i] * r;
         px = exp_term(scaled_logit(x_logit, inv_t), mx) * r;

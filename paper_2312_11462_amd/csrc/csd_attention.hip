@@ -38,22 +38,21 @@ enum { ATT_PLAIN = 0, ATT_BIAS = 1, ATT_TREE = 2 };
 //
 // WPS: waves per SIMD that the registers leave room for at least (heads of 128: 168 of them for three, else 166 + 32): see attn_launch.
 template <int DH, int PRE, bool ONCE, int MODE, int WPS>
-__global__ __launch_bounds__(64, WPS) void k_attn_mfma(const bf16_t *__restrict__ q, size_t qplane, int m, int row_tiles,
-                                                  const int32_t *__restrict__ cache_len, KvGeom geo, int layer,
-                                                  const bf16_t *__restrict__ kv, float scale, float *__restrict__ part,
-                                                  int chunks_max, int chunk_keys, AttnMode mode) {
+__global__ __launch_bounds__(64, WPS) void k_attn_mfma(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v, const bf16_t *__restrict__ q, const int32_t *__restrict__ cache_len,
+                                                  unsigned qplane, int m, int row_tiles, int H, int seq_pad, int chunk_keys, float scale,
+                                                  float *__restrict__ part, int chunks_max, AttnMode mode) {
     constexpr int PS = DH + 4;   // floats per partial row: DH outputs, running max, running sum, pad
     // the chunk index is the slowest grid dimension: the last chunk of every (sequence, head) holds the block's own few
     // rows and little else, and with those short waves dispatched last the long ones land one per SIMD, four per
     // compute unit (dispatched every fifth, they left one SIMD of most compute units with two long waves and one with none)
     const int hh = blockIdx.x, b = blockIdx.y / row_tiles, rt = blockIdx.y % row_tiles, c = blockIdx.z;
     const int lane = threadIdx.x, col = lane & 15, g = lane >> 4;
-    const int hd = geo.H * DH;
+    const int hd = H * DH;
     const bool causal = mode.fixed_nk <= 0;
     const int t = causal ? cache_len[b] : 0;
-    const int nk_all = max(0, min(causal ? t + m : mode.fixed_nk, geo.seq_pad));   // cache rows in play for this block
+    const int nk_all = max(0, min(causal ? t + m : mode.fixed_nk, seq_pad));   // cache rows in play for this block
     const int nk = causal && MODE != ATT_TREE ? min(nk_all, t + rt * 16 + 16) : nk_all;   // ... for this row tile
-    float *po = part + ((((size_t)b * geo.H + hh) * chunks_max + c) * row_tiles + rt) * 16 * PS;
+    float *po = part + ((((size_t)b * H + hh) * chunks_max + c) * row_tiles + rt) * 16 * PS;
     float *pr = po + (size_t)col * PS;
     const int key0 = c * chunk_keys;
     if (key0 >= nk) {                                        // chunk past the end: neutral element
@@ -76,8 +75,10 @@ __global__ __launch_bounds__(64, WPS) void k_attn_mfma(const bf16_t *__restrict_
             qf[s][1] = *reinterpret_cast<const u32x4 *>(qp + qplane);
         }
     }
-    const bf16_t *kc = kv + kv_k_off(geo, layer, b, hh);
-    const bf16_t *vc = kv + kv_v_off(geo, layer, b, hh);
+    const bf16_t *kc = k + ((size_t)b * H + hh) * seq_pad * DH;
+    const bf16_t *vc = v + ((size_t)b * H + hh) * seq_pad * DH;
+    KvGeom geo{};
+    geo.dh = DH;                                             // (what kv_v_idx looks at)
 
     f32x4 oacc[DH / 16];
 #pragma unroll
@@ -289,8 +290,8 @@ static void attn_launch(csd_model *mod, const KvGeom &geo, const void *kv, const
 #define ATT_LAUNCH_MODE(PRE_, ONCE_, MODE_, WIDE_)                                                                     \
     hipLaunchKernelGGL((k_attn_mfma<DH, PRE_, ONCE_, MODE_, PRE_ == 1 && !WIDE_ && (MODE_ == ATT_PLAIN || DH == 64) ? 3 : 1>),  \
                        dim3(c.n_heads, B * row_tiles, chunks), dim3(64), 0, st,                                            \
-                       (const bf16_t *)mod->qbuf, mod->q_plane, m, row_tiles, cache_len, geo, layer, (const bf16_t *)kv, scale, \
-                       mod->attn_part, mod->attn_chunks_max, chunk_keys, mode)
+                       (const bf16_t *)kv + kv_k_off(geo, layer, 0, 0), (const bf16_t *)kv + kv_v_off(geo, layer, 0, 0), (const bf16_t *)mod->qbuf, \
+                       cache_len, (unsigned)mod->q_plane, m, row_tiles, geo.H, geo.seq_pad, chunk_keys, scale, mod->attn_part, mod->attn_chunks_max, mode)
 #define ATT_LAUNCH(PRE_, ONCE_, WIDE_)                    \
     if (mode.anc)                                         \
         ATT_LAUNCH_MODE(PRE_, ONCE_, ATT_TREE, WIDE_);    \

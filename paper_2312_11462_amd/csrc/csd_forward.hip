@@ -227,15 +227,31 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int32_t *__restrict__ 
     const int tok = tokens[r];
     const bool ok = tok >= 0 && tok < V;
     float ss = 0.f;
-    for (int x = threadIdx.x; x < d; x += blockDim.x) {
+    for (int x = threadIdx.x; x < d; x += 256) {
         const float v = ok ? to_f32<TW>(E[(size_t)tok * d + x]) : 0.f;
         h[(size_t)r * d + x] = v;
         ss += v * v;
     }
-    ss = block_sum(ss, red);
+    ss = block_sum<256>(ss, red);
     if (threadIdx.x == 0) rstd[r] = rsqrtf(ss / (float)d + eps);
-    for (int x = threadIdx.x; x < d; x += blockDim.x)
+    for (int x = threadIdx.x; x < d; x += 256)
         store_act<TA>(a, plane, r, x, lda, mtp, h[(size_t)r * d + x] * g[x]);
+}
+
+// v += sum over S planes, in order, P of them requested together (past the last plane the last one again, not added): workgroups on other
+// dies have just written them, and one after the other each is a trip past the L2 (residual sums of eight planes, 33 / 40 / 136
+// rows 5.7 -> 5.2, 5.6 -> 5.3, 7.0 -> 6.7 us; the other epilogue kernels, which have many more waves in flight, gain nothing, and with a
+// workgroup and more per compute unit the registers cost what the loads gain: 512 rows 7.7 -> 8.3).
+template <int P>
+__device__ __forceinline__ void add_planes(f32x4 &v, const float *__restrict__ p, size_t stride, int S) {
+    for (int s0 = 0; s0 < S; s0 += P) {
+        f32x4 pv[P];
+#pragma unroll
+        for (int u = 0; u < P; u++) pv[u] = *reinterpret_cast<const f32x4 *>(p + (size_t)min(s0 + u, S - 1) * stride);
+#pragma unroll
+        for (int u = 0; u < P; u++)
+            if (s0 + u < S) v += pv[u];
+    }
 }
 
 // h[r] += sum_s part[s][r];  a[r] = h[r] * g, rstd[r] as above.  One workgroup of 1024 threads per row, four
@@ -243,7 +259,7 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int32_t *__restrict__ 
 // between the sum of squares and the scaling for rows of up to RN_THREADS * 4 * RN_PASSES features.
 #define RN_THREADS 1024
 #define RN_PASSES 2
-template <typename TA>
+template <typename TA, bool FEW>
 __global__ __launch_bounds__(RN_THREADS) void k_residual_norm(const float *__restrict__ part, int S, int M, int d,
                                                               const float *__restrict__ g, float eps, float *__restrict__ h,
                                                               TA *__restrict__ a, int lda, size_t plane, int mtp,
@@ -260,13 +276,19 @@ __global__ __launch_bounds__(RN_THREADS) void k_residual_norm(const float *__res
             if (x < d) {
                 gain[p] = *reinterpret_cast<const f32x4 *>(g + x);
                 f32x4 v = *reinterpret_cast<const f32x4 *>(h + (size_t)r * d + x);
-                for (int s = 0; s < S; s++) v += *reinterpret_cast<const f32x4 *>(part + ((size_t)s * M + r) * d + x);
+                const float *p0 = part + (size_t)r * d + x;
+                if (!FEW || S < 2)
+                    for (int s = 0; s < S; s++) v += *reinterpret_cast<const f32x4 *>(p0 + (size_t)s * M * d);
+                else if (S > 4)
+                    add_planes<8>(v, p0, (size_t)M * d, S);
+                else
+                    add_planes<4>(v, p0, (size_t)M * d, S);
                 *reinterpret_cast<f32x4 *>(h + (size_t)r * d + x) = v;
                 keep[p] = v;
                 ss += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
             }
         }
-        ss = block_sum(ss, red);
+        ss = block_sum<RN_THREADS>(ss, red);
         if (threadIdx.x == 0) rstd[r] = rsqrtf(ss / (float)d + eps);
 #pragma unroll
         for (int p = 0; p < RN_PASSES; p++) {
@@ -277,16 +299,16 @@ __global__ __launch_bounds__(RN_THREADS) void k_residual_norm(const float *__res
         }
         return;
     }
-    for (int x = threadIdx.x; x < d; x += blockDim.x) {
+    for (int x = threadIdx.x; x < d; x += RN_THREADS) {
         float v = 0.f;
         for (int s = 0; s < S; s++) v += part[((size_t)s * M + r) * d + x];
         v += h[(size_t)r * d + x];
         h[(size_t)r * d + x] = v;
         ss += v * v;
     }
-    ss = block_sum(ss, red);
+    ss = block_sum<RN_THREADS>(ss, red);
     if (threadIdx.x == 0) rstd[r] = rsqrtf(ss / (float)d + eps);
-    for (int x = threadIdx.x; x < d; x += blockDim.x)
+    for (int x = threadIdx.x; x < d; x += RN_THREADS)
         store_act<TA>(a, plane, r, x, lda, mtp, h[(size_t)r * d + x] * g[x]);
 }
 
@@ -303,7 +325,7 @@ __global__ void k_rope_table(const int32_t *__restrict__ cache_len, int m, int d
     const int r = blockIdx.x, half = dh / 2;
     // the position of a row: where it sits in a plain block, how far it is from row 0 in a tree block
     const int pos = cache_len[r / m] + (depth ? depth[r] : r % m);
-    for (int x = threadIdx.x; x < half; x += blockDim.x) {
+    for (int x = threadIdx.x; x < half; x += 64) {
         const double ang = (double)pos * pow((double)theta, -2.0 * (double)x / (double)dh);
         tab[(size_t)r * half + x] = float2{(float)cos(ang), (float)sin(ang)};
     }
@@ -325,7 +347,7 @@ __global__ __launch_bounds__(64) void k_fix_qkv(const float *__restrict__ part, 
     const bool pos_ok = pos >= 0 && pos < geo.seq_pad;
     TC *kc = kv + kv_k_off(geo, layer, b, hh);
     TC *vc = kv + kv_v_off(geo, layer, b, hh);
-    for (int x = threadIdx.x; x < half; x += blockDim.x) {
+    for (int x = threadIdx.x; x < half; x += 64) {
         float q0 = 0.f, q1 = 0.f, k0 = 0.f, k1 = 0.f, v0 = 0.f, v1 = 0.f;
         const int p0 = rope_perm(x, dh, geo.kperm), p1 = rope_perm(x + half, dh, geo.kperm);
         for (int s = 0; s < S; s++) {
@@ -362,7 +384,7 @@ __global__ __launch_bounds__(256) void k_fix_gu(const float *__restrict__ part, 
                                                 TA *__restrict__ f, int ldf, size_t plane, int mtp, int gelu,
                                                 const float *__restrict__ rstd) {
     const int r = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= F) return;
     const int gc = interleaved ? (j / 16) * 32 + (j % 16) : j;
     const int uc = interleaved ? gc + 16 : F + j;
@@ -382,7 +404,7 @@ __global__ __launch_bounds__(256) void k_fix_gu(const float *__restrict__ part, 
 __global__ __launch_bounds__(256) void k_fix_logits(const float *__restrict__ part, int S, int M, int V,
                                                     float *__restrict__ logits, const float *__restrict__ rstd) {
     const int r = blockIdx.y;
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    const int v = blockIdx.x * 256 + threadIdx.x;
     if (v >= V) return;
     float acc = 0.f;
     for (int s = 0; s < S; s++) acc += part[((size_t)s * M + r) * V + v];
@@ -394,7 +416,7 @@ template <typename TA>
 __global__ __launch_bounds__(256) void k_fix_plain(const float *__restrict__ part, int S, int M, int N, TA *__restrict__ out,
                                                    int ldo, size_t plane, const float *__restrict__ rstd) {
     const int r = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= N) return;
     float acc = 0.f;
     for (int s = 0; s < S; s++) acc += part[((size_t)s * M + r) * N + j];
@@ -407,7 +429,7 @@ template <typename TC>
 __global__ __launch_bounds__(256) void k_fix_cross_kv(const float *__restrict__ part, int S, int M, KvGeom geo, int layer,
                                                       int b, int row0, TC *__restrict__ kvc) {
     const int r = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * 256 + threadIdx.x;
     const int hd = geo.H * geo.dh;
     if (j >= hd) return;
     float k = 0.f, v = 0.f;
@@ -466,14 +488,14 @@ __global__ __launch_bounds__(AS_THREADS) void k_attn_simple(const TA *__restrict
         sc[j] = s;
         mx = fmaxf(mx, s);
     }
-    mx = block_max(mx, red);
+    mx = block_max<AS_THREADS>(mx, red);
     float z = 0.f;
     for (int j = threadIdx.x; j < nk; j += AS_THREADS) {
         const float e = expf(sc[j] - mx);
         sc[j] = e;
         z += e;
     }
-    z = block_sum(z, red);                                   // (its barriers also show every thread the weights)
+    z = block_sum<AS_THREADS>(z, red);                                   // (its barriers also show every thread the weights)
     const float rz = 1.0f / z;
     const int groups = dh < AS_THREADS ? AS_THREADS / dh : 1;
     const int g = dh < AS_THREADS ? (int)threadIdx.x / dh : 0;           // threads past the last whole group: no keys
@@ -660,7 +682,7 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
         if ((rc = run_gemm(mod, lw.o, x[1], xp[1], M, &S_g, st)) != CSD_OK) return rc;
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
-            hipLaunchKernelGGL((k_residual_norm<TA>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, lw.ffn_norm,
+            hipLaunchKernelGGL((M < CSD_TALL_MIN_ROWS ? k_residual_norm<TA, true> : k_residual_norm<TA, false>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, lw.ffn_norm,
                                c.rms_eps, mod->h, x[2], d, xp[2], mod->act_mtp, mod->rstd);
             CSD_LAUNCH_CHECK();
         }
@@ -678,7 +700,7 @@ static int32_t forward_typed(csd_model *mod, void *kv, const int32_t *tokens, co
         {
             ProfScope ps(mod, st, CSD_PROF_OTHER);
             const float *g = (l + 1 < L) ? mod->layers[l + 1].attn_norm : mod->final_norm;
-            hipLaunchKernelGGL((k_residual_norm<TA>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, g,
+            hipLaunchKernelGGL((M < CSD_TALL_MIN_ROWS ? k_residual_norm<TA, true> : k_residual_norm<TA, false>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, g,
                                c.rms_eps, mod->h, x[0], d, xp[0], mod->act_mtp, mod->rstd);
             CSD_LAUNCH_CHECK();
         }
@@ -753,7 +775,7 @@ static int32_t forward_t5(csd_model *mod, void *kv, const int32_t *tokens, const
     int S_g = 1;            // K splits the last GEMM wrote partial sums for
     auto resid_norm = [&](const GemmW &, const float *gain) -> int32_t {
         ProfScope ps(mod, st, CSD_PROF_OTHER);
-        hipLaunchKernelGGL((k_residual_norm<TA>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, gain, c.rms_eps, mod->h, act,
+        hipLaunchKernelGGL((M < CSD_TALL_MIN_ROWS ? k_residual_norm<TA, true> : k_residual_norm<TA, false>), dim3(M), dim3(RN_THREADS), 0, st, mod->part, S_g, M, d, gain, c.rms_eps, mod->h, act,
                            d, mod->act_plane, mod->act_mtp, mod->rstd);
         CSD_LAUNCH_CHECK();
         return CSD_OK;

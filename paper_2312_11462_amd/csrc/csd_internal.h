@@ -151,24 +151,31 @@ __device__ __forceinline__ float across_half_row(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
 }
 
-// sum over a block of up to 1024 threads; every thread gets the result; `red` holds >= 16 floats
+// sum over a block of T (up to 1024) threads; every thread gets the result; `red` holds >= 16 floats (the number of threads is
+// not read from the launch: that is one of the arguments behind the plain ones, a cold read of memory)
+template <int T>
 __device__ __forceinline__ float block_sum(float v, float *red) {
     v = wave_sum(v);
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    constexpr int nw = T / 64;
+    const int w = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = v;
     __syncthreads();
     float t = 0.f;
+#pragma unroll
     for (int i = 0; i < nw; i++) t += red[i];
     return t;
 }
+template <int T>
 __device__ __forceinline__ float block_max(float v, float *red) {
     v = wave_max(v);
-    const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+    constexpr int nw = T / 64;
+    const int w = threadIdx.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[w] = v;
     __syncthreads();
     float t = red[0];
+#pragma unroll
     for (int i = 1; i < nw; i++) t = fmaxf(t, red[i]);
     return t;
 }

@@ -29,7 +29,8 @@ template <int CT, int NW>
 static constexpr int rs_lds() { return (RS_SETS + 1) * rs_tiles<CT, NW>() * 1024; }
 
 template <int CT, int RW, int NW>
-__global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
+__global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(TALL_PARAMS) {
+    TALL_UNPACK(A)
     extern __shared__ __align__(16) char rs_smem[];
     constexpr int PW = (CT + NW - 1) / NW;                       // weight loads per wave and k-step
     constexpr int AL = 2 * RW, NA = RS_SETS - 1, NST = RS_SETS + 1;
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(const TallArgs A) {
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // workgroups go to the eight compute dies round-robin: consecutive shares to the workgroups of one die
-    const int per_die = gridDim.x >> 3, rest = gridDim.x & 7, die = blockIdx.x & 7;
+    const int grid = (A.n_tiles + CT - 1) / CT * A.S, per_die = grid >> 3, rest = grid & 7, die = blockIdx.x & 7;
     const int wg = die * per_die + (die < rest ? die : rest) + (blockIdx.x >> 3);
     const int s = wg % A.S, grp = wg / A.S;
     const int ks0 = (int)((long long)P.KS * s / A.S), ks1 = (int)((long long)P.KS * (s + 1) / A.S);
@@ -204,7 +205,7 @@ int32_t csd_rs_plan_host(int32_t N, int32_t K, int32_t rows, size_t part_floats,
 template <int CT, int RW, int NW>
 static int32_t rs_launch_t(const TallArgs &A, hipStream_t st) {
     const int grid = (A.n_tiles + CT - 1) / CT * A.S;
-    hipLaunchKernelGGL((k_gemm_rs<CT, RW, NW>), dim3(grid), dim3(NW * 64), (rs_lds<CT, NW>()), st, A);
+    hipLaunchKernelGGL((k_gemm_rs<CT, RW, NW>), dim3(grid), dim3(NW * 64), (rs_lds<CT, NW>()), st, TALL_ARGS(A));
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }

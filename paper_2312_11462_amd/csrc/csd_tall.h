@@ -46,6 +46,22 @@ __device__ __forceinline__ void stage_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The arguments that the first loads need come ahead of the structure, in registers when a wave starts (see kc_gemm).
+#define TALL_PARAMS const u32x4 *Wp, const bf16_t *a, int KS, int n_tiles, int S, int wbytes, int a_plane_bytes, int mtp, int M, int rblocks, const TallArgs args
+#define TALL_ARGS(A) (A).g.Wp, (A).g.a, (A).g.KS, (A).n_tiles, (A).S, (A).g.wbytes, (A).g.a_plane_bytes, (A).g.mtp, (A).g.M, (A).rblocks, A
+#define TALL_UNPACK(A)                     \
+    TallArgs A = args;                     \
+    A.g.Wp = Wp;                           \
+    A.g.a = a;                             \
+    A.g.KS = KS;                           \
+    A.n_tiles = n_tiles;                   \
+    A.S = S;                               \
+    A.g.wbytes = wbytes;                   \
+    A.g.a_plane_bytes = a_plane_bytes;     \
+    A.g.mtp = mtp;                         \
+    A.g.M = M;                             \
+    A.rblocks = rblocks;
+
 static inline TallArgs tall_args(const csd_model *mod, const GemmW &w, const bf16_t *a, size_t plane, int mtp, int M) {
     TallArgs A{};
     A.g.Wp = (const u32x4 *)w.data;

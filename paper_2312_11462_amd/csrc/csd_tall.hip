@@ -52,7 +52,8 @@ static constexpr bool tall_sums() { return !(CTW == 6 && RTW == 4 && NST == 2); 
 #define TALL_LEADS 16         /* tiles of a wave whose upper halves stay in registers */
 
 template <int CTW, int RTW, int NST, int EPI>
-__global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void k_gemm_tall(const TallArgs A) {
+__global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void k_gemm_tall(TALL_PARAMS) {
+    TALL_UNPACK(A)
     constexpr bool SUMS = tall_sums<CTW, RTW, NST>();
     extern __shared__ __align__(16) char tall_smem[];
     constexpr int WF = 2 * CTW, NF = WF + 4 * RTW;               // fragments of a stage: W tiles, then [plane][row tile]
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(256, CTW == 6 && RTW == 4 && NST == 3 ? 1 : 2) void
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // workgroups go to the eight compute dies round-robin: consecutive tiles to the workgroups of one die
-    const int per_die = gridDim.x >> 3, rest = gridDim.x & 7, die = blockIdx.x & 7;
+    const int grid = (A.n_tiles + WF - 1) / WF * A.rblocks * A.S, per_die = grid >> 3, rest = grid & 7, die = blockIdx.x & 7;
     const int wg = die * per_die + (die < rest ? die : rest) + (blockIdx.x >> 3);
     const int rb = wg % A.rblocks, s = (wg / A.rblocks) % A.S, grp = wg / (A.rblocks * A.S);
     const int ks0 = (int)((long long)P.KS * s / A.S), ks1 = (int)((long long)P.KS * (s + 1) / A.S);
@@ -339,7 +340,7 @@ static int32_t tall_launch(const csd_model *mod, TallArgs &A, int max_splits, hi
     A.rblocks = p.rblocks;
     A.chain = p.chain;
 #define TALL_LAUNCH(CTW, RTW, NST) \
-    hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(p.grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, A)
+    hipLaunchKernelGGL((k_gemm_tall<CTW, RTW, NST, EPI>), dim3(p.grid), dim3(256), (tall_lds<CTW, RTW, NST>()), st, TALL_ARGS(A))
 #define TALL_LAUNCH_R(RTW)                                \
     {                                                     \
         if (p.ctw == 4) TALL_LAUNCH(4, RTW, 4);           \
