@@ -140,17 +140,30 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
+// Most of a row carries no weight at all: what is below 2^-40 after the scaling by the lenience is 0 in 40-bit fixed point, and a
+// confident reviewer leaves nearly every token there.  The work on a thread's values is what the review kernels are bound by, so a group of 256
+// tokens (four per lane) is looked at first, and left out where all of it is that small.
+// Rows with nearly all of their weight on one token, 32000 tokens: eight sequences of k_accept 10.0 -> 8.3 us, nine rows of k_review_rows (160M step)
+// 5 us less; rows whose every group matters 9.7 -> 10.0.
+// (As bits, NaN and whatever is negative are above every small weight: the cheapest look that leaves them in.)
+__device__ __forceinline__ bool group_matters(const float *v) {
+    const uint32_t m = max(max(__float_as_uint(v[0]), __float_as_uint(v[1])), max(__float_as_uint(v[2]), __float_as_uint(v[3])));
+    return __any(m > __float_as_uint(0x1p-41f));
+}
+
 // The draw inside the wave that owns T: its values in token order are (group j, lane, position in the group), `run` the weight of
 // all tokens before it.  They go through LDS (`own`, a float4 per lane and group) so that the loop over groups needs no registers
 // for them: unrolled over registers it spilled in kernels of 1024 threads.  Writes the token to *out (one lane does).
+// live: the groups that hold any weight (bit j).
 template <int NG>
 __device__ __forceinline__ void wave_draw(const float *val, float4 *own, unsigned long long T, unsigned long long run, int vbase, int V,
-                                          int *out) {
+                                          uint32_t live, int *out) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int j = 0; j < NG; j++) own[j * 64 + lane] = make_float4(val[4 * j], val[4 * j + 1], val[4 * j + 2], val[4 * j + 3]);
 #pragma unroll 1
     for (int j = 0; j < NG; j++) {
+        if (!(live >> j & 1)) continue;                      // (uniform)
         const float4 t = own[j * 64 + lane];
         unsigned long long upto[4];
         upto[0] = fixed40_small(t.x);
@@ -314,18 +327,24 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
         load_row(val, prow, vbase, ng, V, 0.f);
         if (qrow) load_row(qv, qrow, vbase, ng, V, 0.f);
         unsigned long long mine = 0ull;
-        uint32_t sl = 0;
+        uint32_t sl = 0, live = 0;
         bool large = false;
 #pragma unroll
         for (int j = 0; j < ACC_NG; j++) {
+            if (residual) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    const int i = 4 * j + c;
+                    const float df = __fsub_rn(__fmul_rn(lenience, val[i]), qrow ? qv[i] : (vbase + 256 * j + c == x ? 1.0f : 0.0f));
+                    val[i] = df > 0.0f ? df : 0.0f;
+                }
+            }
+            if (!group_matters(val + 4 * j)) continue;
+            live |= 1u << j;
             uint32_t sh = 0;
 #pragma unroll
             for (int c = 0; c < 4; c++) {
                 const int i = 4 * j + c;
-                if (residual) {
-                    const float df = __fsub_rn(__fmul_rn(lenience, val[i]), qrow ? qv[i] : (vbase + 256 * j + c == x ? 1.0f : 0.0f));
-                    val[i] = df > 0.0f ? df : 0.0f;
-                }
                 large |= !(val[i] <= 256.0f);
                 uint32_t h, l;
                 fixed40_parts(val[i], h, l);
@@ -349,7 +368,7 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
                 const unsigned long long u24 = fixed40(us) >> 16;
                 const unsigned long long hi = __umul64hi(u24, Z), lo = u24 * Z;
                 const unsigned long long T = (hi << 40) | (lo >> 24);
-                if (T >= before && T < before + wave_total) wave_draw<ACC_NG>(val, S.own, T, before, vbase, V, &S.s_tok);   // exactly one wave
+                if (T >= before && T < before + wave_total) wave_draw<ACC_NG>(val, S.own, T, before, vbase, V, live, &S.s_tok);   // exactly one wave
             }
             __syncthreads();
             n_out = n;
@@ -390,9 +409,8 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
 
 template <bool REGS>
 __global__ __launch_bounds__(ACC_THREADS) void k_accept(
-    const float *__restrict__ p, const float *__restrict__ q, const uint8_t *__restrict__ q_onehot,
-    const int32_t *__restrict__ draft, int32_t draft_stride, const float *__restrict__ u_acc,
-    const float *__restrict__ u_samp, int32_t k, int32_t V, float lenience, int32_t mode,
+    const float *__restrict__ p, const int32_t *__restrict__ draft, const float *__restrict__ u_acc, const float *__restrict__ u_samp,
+    const float *__restrict__ q, int32_t k, int32_t V, int32_t draft_stride, int32_t mode, float lenience, const uint8_t *__restrict__ q_onehot,
     int32_t *__restrict__ n_accepted, int32_t *__restrict__ next_token) {
     __shared__ AcceptShared S;
     const int b = blockIdx.x;
@@ -510,11 +528,10 @@ int32_t csd_softmax_enqueue(const float *logits, float *probs, int64_t rows, int
 #define RR_PER_MAX 64
 template <int RR_PER>
 __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
-    const float *__restrict__ logits, float *__restrict__ probs, unsigned long long *__restrict__ recs,
-    unsigned *__restrict__ counters, float inv_t, const float *__restrict__ q, const uint8_t *__restrict__ q_onehot,
-    const int32_t *__restrict__ draft, int32_t draft_stride, const float *__restrict__ u_acc,
-    const float *__restrict__ u_samp, int32_t k, int32_t V, float lenience, int32_t mode, int32_t raw,
-    int32_t *__restrict__ n_accepted, int32_t *__restrict__ next_token) {
+    const float *__restrict__ logits, const int32_t *__restrict__ draft, const float *__restrict__ u_acc,
+    const float *__restrict__ u_samp, int32_t k, int32_t V, int32_t draft_stride, int32_t mode, float inv_t, float lenience,
+    const float *__restrict__ q, const uint8_t *__restrict__ q_onehot, float *__restrict__ probs, unsigned long long *__restrict__ recs,
+    unsigned *__restrict__ counters, int32_t raw, int32_t *__restrict__ n_accepted, int32_t *__restrict__ next_token) {
     constexpr int NG = RR_PER / 4;                               // 4-token groups per thread
     __shared__ float red[RR_THREADS / 64];
     __shared__ unsigned long long red64[RR_THREADS / 64];
@@ -558,6 +575,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             if (val[i] > best.v) best = {val[i], vbase + 256 * (i >> 2) + (i & 3)};
     }
     float px = x_logit, mx = -INFINITY, r = 1.0f;
+    uint32_t live = 0;                                           // bit j: group j of this wave (uniform over it)
     if (!raw || probs) {
 #pragma unroll
         for (int i = 0; i < RR_PER; i++) {
@@ -566,12 +584,26 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
         }
         mx = block_max<RR_THREADS>(mx, red);
         uint32_t sh = 0, sl = 0;                                 // at most 64 terms of at most 2^20 each
+        // e^-28 < 2^-40: groups that far below the maximum have no part in the sum nor, scaled by the lenience, in a draw, and their
+        // probabilities are only needed where the caller wants them all
+        const float cut = mx - 28.0f - logf(lenience);
 #pragma unroll
-        for (int i = 0; i < RR_PER; i++) {
-            val[i] = exp_term(val[i], mx);
-            uint32_t h, l;
-            fixed40_parts(val[i], h, l);
-            sh += h, sl += l;
+        for (int j = 0; j < NG; j++) {
+            // (NaN is no maximum: it carries no weight either)
+            if (!__any(fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3])) > cut) && !probs) {
+#pragma unroll
+                for (int c = 0; c < 4; c++) val[4 * j + c] = 0.f;
+                continue;
+            }
+            live |= 1u << j;
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const int i = 4 * j + c;
+                val[i] = exp_term(val[i], mx);
+                uint32_t h, l;
+                fixed40_parts(val[i], h, l);
+                sh += h, sl += l;
+            }
         }
         r = recip_of_total(block_sum_u64<RR_THREADS>((unsigned long long)sh * (1u << 20) + sl, red64));
 #pragma unroll
@@ -620,6 +652,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             if (residual) {                                  // the weights take the probabilities' place
 #pragma unroll
                 for (int j = 0; j < NG; j++) {
+                    if (!qrow && !(live >> j & 1)) continue;     // nothing is above 0 - q
                     float qv[4] = {0.f, 0.f, 0.f, 0.f};
                     const int v = vbase + 256 * j;
                     if (qrow) {
@@ -636,6 +669,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                         const float df = __fsub_rn(__fmul_rn(lenience, val[4 * j + c]), qv[c]);
                         val[4 * j + c] = df > 0.0f ? df : 0.0f;
                     }
+                    if (qrow) live = group_matters(val + 4 * j) ? live | 1u << j : live & ~(1u << j);
                 }
             }
             unsigned long long Z = 0ull, before = 0ull, wave_total = 0ull;
@@ -647,6 +681,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
 #pragma unroll
                 for (int j = 0; j < NG; j++) {
                     uint32_t sh = 0;
+                    if (!(live >> j & 1)) continue;
 #pragma unroll
                     for (int c = 0; c < 4; c++) {
                         uint32_t h, l;
@@ -667,6 +702,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 }
                 if (Z != 0ull || !residual) break;
                 residual = false;                            // all-zero residual: draw from the reviewer's row, rebuilt
+                live = NG < 32 ? (1u << NG) - 1 : ~0u;
 #pragma unroll
                 for (int j = 0; j < NG; j++) {
                     const int v = vbase + 256 * j;
@@ -682,7 +718,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 const unsigned long long hi = __umul64hi(u24, Z), lo = u24 * Z;
                 const unsigned long long T = (hi << 40) | (lo >> 24);
                 if (T >= before && T < before + wave_total) {          // exactly one wave owns T
-                    wave_draw<NG>(val, s_own, T, before, vbase, V, &s_tok);
+                    wave_draw<NG>(val, s_own, T, before, vbase, V, live, &s_tok);
                 }
             }
             __syncthreads();
@@ -739,9 +775,9 @@ int32_t csd_review_rows_enqueue(const float *logits, float *probs, unsigned long
     if (!csd_review_rows_fits(logits, probs, q, V)) return CSD_ESHAPE;
     const int32_t raw = mode == CSD_MODE_GREEDY && !(lenience > 1.0f);
 #define RR_LAUNCH(PER)                                                                                                     \
-    hipLaunchKernelGGL((k_review_rows<PER>), dim3(k + 1, B), dim3(RR_THREADS), 0, st, logits, probs, recs, counters,        \
-                       1.0f / (temperature > 0.f ? temperature : 1.0f), q, q_onehot, draft, draft_stride, u_acc, u_samp, k, \
-                       V, lenience, mode, raw, n_accepted, next_token)
+    hipLaunchKernelGGL((k_review_rows<PER>), dim3(k + 1, B), dim3(RR_THREADS), 0, st, logits, draft, u_acc, u_samp, k, V,   \
+                       draft_stride, mode, 1.0f / (temperature > 0.f ? temperature : 1.0f), lenience, q, q_onehot, probs, recs, counters, raw, \
+                       n_accepted, next_token)
     if (V <= RR_THREADS * 4)
         RR_LAUNCH(4);
     else if (V <= RR_THREADS * 16)
@@ -758,8 +794,8 @@ int32_t csd_accept_enqueue(const float *p, const float *q, const uint8_t *q_oneh
                            int32_t V, float lenience, int32_t mode, int32_t *n_accepted, int32_t *next_token,
                            hipStream_t st) {
     if (B <= 0) return CSD_OK;
-    hipLaunchKernelGGL((rows_fit(p, q, V, mode) ? k_accept<true> : k_accept<false>), dim3(B), dim3(ACC_THREADS), 0, st, p, q, q_onehot, draft, draft_stride, u_acc, u_samp,
-                       k, V, lenience, mode, n_accepted, next_token);
+    hipLaunchKernelGGL((rows_fit(p, q, V, mode) ? k_accept<true> : k_accept<false>), dim3(B), dim3(ACC_THREADS), 0, st, p, draft, u_acc, u_samp, q, k, V,
+                       draft_stride, mode, lenience, q_onehot, n_accepted, next_token);
     CSD_LAUNCH_CHECK();
     return CSD_OK;
 }

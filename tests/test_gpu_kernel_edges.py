@@ -522,6 +522,34 @@ def test_accept_at_the_longest_row_in_registers(P, V, kind):
         assert (n[s:] == 0).all() and (tok[s:] == -1).all()
 
 
+@pytest.mark.parametrize("V", [18432, 32000, 32768])
+@pytest.mark.parametrize("lenience", [1.0, 4.0, 256.0])
+def test_accept_of_rows_with_little_weight(P, V, lenience):
+    """Rows whose groups of 256 tokens are left out where they are below 2^-40: weight at the edges of groups, values on either side of the
+    line before and after the lenience, rejected drafts with and without draft distributions.  Whole numbers, decided by exact sums."""
+    from oracle import csd_oracle as O
+    B, k = 4, 2
+    g = torch.Generator().manual_seed(V)
+    small = torch.tensor([0.0, 2.0 ** -41, 2.0 ** -40 / 256, 2.0 ** -40 * (1 - 2.0 ** -24), 2.0 ** -40, 2.0 ** -39])
+    p = small[torch.randint(0, 6, (B, k + 1, V), generator=g)]
+    p[1, :, 2048:] = 2.0 ** -41                              # whole groups below the line; and above it
+    p[2, :, 2048:] = 2.0 ** -38
+    p[3] = 0.0
+    for b in range(B):
+        for i, v in enumerate([0, 255, 256, 1023, 2047, 2048, V // 2, V - 257, V - 1]):
+            p[b, :, v] = 0.1 + 0.01 * i
+    q = torch.where(torch.rand((B, k, V), generator=g) < 0.5, torch.zeros(()), p[:, :k] * 0.5)
+    draft = torch.tensor([[255, V - 1], [7, 256], [V - 1, 0], [2048, 9]]).int()
+    for b in range(B):
+        for i in range(k):
+            q[b, i, draft[b, i]] = 300.0                     # rejected at any lenience
+    u_acc, u_s = torch.rand((B, k), generator=g) * 0.25 + 0.75, torch.rand(B, generator=g)
+    for dense in (q, None):
+        n, tok = P.accept(p.cuda(), None if dense is None else dense.cuda(), draft.cuda(), u_acc.cuda(), u_s.cuda(), lenience, 0)
+        wn, wt = O.accept(p.numpy(), None if dense is None else dense.numpy(), draft.numpy(), u_acc.numpy(), u_s.numpy(), lenience, 0)
+        assert np.array_equal(n.cpu().numpy(), wn) and np.array_equal(tok.cpu().numpy(), wt)
+
+
 @pytest.mark.parametrize("V", [1, 3, 4, 254, 256, 260, 4096, 12284, 12288, 12292, 32764, 32766, 32768, 32772])
 def test_arg_max_of_rows_with_nan_and_without_finite_values(P, V):
     """The greedy rule's own token, in registers and in the general way: NaN never wins, the lowest index among equals does, a row of -inf gives its first
@@ -720,3 +748,24 @@ def test_review_of_all_rows_equals_softmax_then_accept(P, V, mode):
         n2, x2 = P.accept(lg if mode else p, q, block[:, 1:].contiguous(), ua, us, mode=mode)
         assert torch.equal(n, n2) and torch.equal(x, x2)
         assert torch.equal(probs, p)
+
+
+@pytest.mark.parametrize("V", [512, 8192, 32000])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("std", [0.3, 2.0, 6.0])
+def test_review_of_confident_rows_equals_softmax_then_accept(P, V, mode, std):
+    """Rows of which some groups, most or nearly all are too far below the maximum to carry weight, without probabilities asked for: the fused review,
+    which leaves such groups out, decides as the two kernels, bit for bit, at any lenience."""
+    shape = I.ModelShape("edge_review", 0, "fp32", 1, 16, 1, 16, 16, V)
+    gm = P.Model(shape, I.make_weights(shape, 43, device="cuda", std=std), max_batch=2, max_seq=16, max_block=6)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    cl = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for lenience in (1.0, 3.0, 256.0):
+        for dense in (False, True):
+            block = torch.randint(0, V, (2, 6), generator=g, device="cuda", dtype=torch.int32)
+            q = torch.softmax(6.0 * torch.randn((2, 5, V), generator=g, device="cuda"), -1) if dense else None
+            ua, us = torch.rand((2, 5), generator=g, device="cuda"), torch.rand(2, generator=g, device="cuda")
+            n, x = gm.verify_accept(block, cl, ua, us, q=q, mode=mode, lenience=lenience)
+            lg, p = gm.verify_block(block, cl, want_probs=True)
+            n2, x2 = P.accept(lg if mode and lenience == 1.0 else p, q, block[:, 1:].contiguous(), ua, us, lenience=lenience, mode=mode)
+            assert torch.equal(n, n2) and torch.equal(x, x2)
