@@ -180,16 +180,14 @@ __device__ __forceinline__ int small_div(int x, int n) { return (int)(((float)x 
 struct F32Row {
     RowProduct o, gu, down, next;     // this layer's O, gate|up, down; the next product (QKV, or the LM head)
     const float *ffn_gain, *next_gain;
-    int d, hd, F, m, layer, keys_pad; // layer: of the attention; QKV appends to layer + 1
+    int layer, keys_pad;              // layer: of the attention; QKV appends to layer + 1
     int head_threads, pv_slices;      // FR_THREADS / n_heads, FR_THREADS / hd
     float eps, scale, theta;
     float *h, *q;                     // [M][d], [M][hd]
     float *kv;
-    const int32_t *cache_len;
     KvGeom geo;
     float2 *rope;                     // [M][dh / 2]
-    const int32_t *tokens, *depth;    // FIRST
-    const float *embed;
+    const int32_t *depth;             // FIRST
     int V;
     const unsigned long long *anc;
     float *logits;                    // LAST
@@ -239,13 +237,20 @@ struct RowSlice {
 
 // PO, PN: most values per thread of the O projection and of the next product
 template <bool FIRST, bool LAST, int PO, int PN>
-__global__ __launch_bounds__(FR_THREADS) void k_f32_row(const F32Row P) {
+// What the first loads need comes ahead of the structure, in registers when a wave starts (see kc_gemm in csd_chain.hip): w0, w1 the O and
+// gate|up matrices, or (FIRST) w0 the QKV matrix, q the tokens and h the embedding.
+__global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const float *w1, const float *q0, const float *h0, const int32_t *cache_len,
+                                                        int d, int hd, int F, int m, const F32Row P) {
     extern __shared__ float fr_smem[];
     __shared__ float x[FR_X], red[FR_THREADS], hs[FR_THREADS], y[FR_THREADS], wave_red[2 * (FR_THREADS / 64)];
     float *sc = fr_smem;                                         // scores [H][keys_pad]
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = blockIdx.x;
-    const int d = P.d, hd = P.hd, dh = P.geo.dh, H = P.geo.H, half = dh / 2;
-    const int b = r / P.m, i = r % P.m;
+    const int dh = P.geo.dh, H = P.geo.H, half = dh / 2;
+    const int b = r / m, i = r % m;
+    auto product = [](const float *W, int K, int N) {            // as the host makes them (K + S <= 1024 + 64)
+        const int S = small_div(FR_THREADS, N);
+        return RowProduct{W, K, N, S, small_div(K + S - 1, S)};
+    };
     auto put_x = [&](int K, float v) {                           // x[0 .. K) = v of thread k, zeros behind
         if (tid < K) x[tid] = v;
         if (tid < 64) x[K + tid] = 0.f;
@@ -260,13 +265,13 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const F32Row P) {
         for (int u = 0; u < (d + 63) / 64; u++) ss += wave_red[u];
         return rsqrtf(ss / (float)d + P.eps);
     };
-    const int t0 = P.cache_len[b];
+    const int t0 = cache_len[b];
     RowSlice<PN> wn;
     float hv = 0.f;                                              // this thread's entry of the residual stream
     if constexpr (FIRST) {
-        wn.load(P.next);
-        const int tok = P.tokens[r];
-        if (tid < d) hv = tok >= 0 && tok < P.V ? P.embed[(size_t)tok * d + tid] : 0.f;
+        wn.load(product(w0, d, 3 * hd));
+        const int tok = reinterpret_cast<const int32_t *>(q0)[r];
+        if (tid < d) hv = tok >= 0 && tok < P.V ? h0[(size_t)tok * d + tid] : 0.f;
         // the position of a row: where it sits in a plain block, how far it is from row 0 in a tree block
         const int pos = t0 + (P.depth ? P.depth[r] : i);
         if (tid < half) {
@@ -276,29 +281,48 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const F32Row P) {
     } else {
         RowSlice<PO> wo;
         RowSlice<32> wg;
-        wo.load(P.o);
-        wg.load(P.gu);
+        wo.load(product(w0, hd, d));
+        wg.load(product(w1, d, 2 * F));
         // ---- attention of the row, all heads (the keys of a head as k_attn_simple takes them)
-        if (tid < hd) y[tid] = P.q[(size_t)r * hd + tid];
-        if (tid < d) hv = P.h[(size_t)r * d + tid];
+        if (tid < hd) y[tid] = q0[(size_t)r * hd + tid];
+        if (tid < d) hv = h0[(size_t)r * d + tid];
         const int qpos = t0 + i, nk = max(1, min(qpos + 1, P.geo.seq_pad));
         const unsigned long long anc_row = P.anc ? P.anc[r] : 0ull;
         const float *kc = P.kv + kv_k_off(P.geo, P.layer, b, 0), *vc = P.kv + kv_v_off(P.geo, P.layer, b, 0);
         const size_t he = kv_head_elems(P.geo);
+        // the first key of the thread (16 values of it) and its first values, requested before anything is waited for: one trip past the
+        // caches instead of three in a row (rows up to the padded cache exist; those past the last key are not used)
+        const int G = P.head_threads, hq = small_div(tid, G), j0 = tid - hq * G;
+        f32x4 kfirst[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) kfirst[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (dh % 16 == 0 && hq < H && j0 < P.geo.seq_pad) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) kfirst[u] = *reinterpret_cast<const f32x4 *>(kc + hq * he + (size_t)j0 * dh + 4 * u);
+        }
+        const int S = P.pv_slices, pc = small_div(tid, S), ps = tid - pc * S;  // slices of the keys next to each other: V is contiguous in them
+        const int ph = pc < hd ? small_div(pc, dh) : 0, pe = pc - ph * dh;
+        float vfirst[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) vfirst[u] = pc < hd && ps + u * S < P.geo.seq_pad ? vc[ph * he + kv_v_idx(P.geo, pe, ps + u * S)] : 0.f;
         __syncthreads();
-        const int G = P.head_threads, hq = small_div(tid, G);
         if (hq < H) {
             const float *kh = kc + hq * he, *qr = y + hq * dh;
 #pragma unroll 1
-            for (int j = tid - hq * G; j < nk; j += G) {
+            for (int j = j0; j < nk; j += G) {
                 const float *kr = kh + (size_t)j * dh;
                 float s = 0.f;
                 if (dh % 16 == 0) {
 #pragma unroll 1
                     for (int e = 0; e < dh; e += 16) {
                         f32x4 kk[4];
+                        if (j == j0 && e == 0) {
 #pragma unroll
-                        for (int u = 0; u < 4; u++) kk[u] = *reinterpret_cast<const f32x4 *>(kr + e + 4 * u);
+                            for (int u = 0; u < 4; u++) kk[u] = kfirst[u];
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < 4; u++) kk[u] = *reinterpret_cast<const f32x4 *>(kr + e + 4 * u);
+                        }
 #pragma unroll
                         for (int u = 0; u < 16; u++) s = fmaf(qr[e + u], kk[u / 4][u % 4], s);
                     }
@@ -330,14 +354,15 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const F32Row P) {
         }
         __syncthreads();
         {
-            const int S = P.pv_slices, c = small_div(tid, S), s = tid - c * S;  // slices of the keys next to each other: V is contiguous in them
             float o = 0.f;
-            if (c < hd) {
-                const int hh = small_div(c, dh), e = c - hh * dh;
-                const float *row = sc + hh * P.keys_pad, *vr = vc + hh * he;
+            if (pc < hd) {
+                const float *row = sc + ph * P.keys_pad, *vr = vc + ph * he;
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if (ps + u * S < nk) o = fmaf(row[ps + u * S], vfirst[u], o);
 #pragma unroll 4
-                for (int j = s; j < nk; j += S) o = fmaf(row[j], vr[kv_v_idx(P.geo, e, j)], o);
-                red[s * hd + c] = o;
+                for (int j = ps + 4 * S; j < nk; j += S) o = fmaf(row[j], vr[kv_v_idx(P.geo, pe, j)], o);
+                red[ps * hd + pc] = o;
             }
             __syncthreads();
             o = 0.f;
@@ -363,11 +388,11 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const F32Row P) {
         wn.load(P.next);
         __syncthreads();
         float f = 0.f;
-        if (tid < P.F) {
-            const float gt = wg.sum(P.gu, red, tid) * rstd, up = wg.sum(P.gu, red, P.F + tid) * rstd;
+        if (tid < F) {
+            const float gt = wg.sum(P.gu, red, tid) * rstd, up = wg.sum(P.gu, red, F + tid) * rstd;
             f = gt / (1.0f + expf(-gt)) * up;
         }
-        put_x(P.F, f);
+        put_x(F, f);
         __syncthreads();
         // ---- down, residual
         wd.apply(P.down, x, red);
@@ -471,10 +496,6 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
     };
     P.head_threads = FR_THREADS / c.n_heads;
     P.pv_slices = FR_THREADS / mod->hd;
-    P.d = d;
-    P.hd = mod->hd;
-    P.F = c.d_ffn;
-    P.m = m;
     P.keys_pad = mod->seq_pad;
     P.eps = c.rms_eps;
     P.scale = 1.0f / sqrtf((float)c.head_dim);
@@ -482,11 +503,8 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
     P.h = mod->h;
     P.q = (float *)mod->qbuf;
     P.kv = (float *)kv;
-    P.cache_len = cache_len;
     P.geo = KvGeom{c.max_batch, c.n_heads, c.head_dim, mod->seq_pad, L, mod->kperm ? 1 : 0};
     P.rope = mod->rope;
-    P.tokens = tokens;
-    P.embed = (const float *)mod->embed;
     P.V = c.vocab;
     P.logits = logits;
     if (mod->tree_call) P.depth = mod->tree_depth, P.anc = mod->tree_anc;
@@ -504,12 +522,16 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
             P.down = product(lw.down);
             P.ffn_gain = lw.ffn_norm;
         }
+        const int hd = mod->hd, F = c.d_ffn;
         if (l < 0)
-            hipLaunchKernelGGL((few ? k_f32_row<true, false, 4, 16> : k_f32_row<true, false, 8, 32>), dim3(M), dim3(FR_THREADS), 0, st, P);
+            hipLaunchKernelGGL((few ? k_f32_row<true, false, 4, 16> : k_f32_row<true, false, 8, 32>), dim3(M), dim3(FR_THREADS), 0, st, P.next.W,
+                               (const float *)nullptr, (const float *)tokens, (const float *)mod->embed, cache_len, d, hd, F, m, P);
         else if (l + 1 < L)
-            hipLaunchKernelGGL((few ? k_f32_row<false, false, 4, 16> : k_f32_row<false, false, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P);
+            hipLaunchKernelGGL((few ? k_f32_row<false, false, 4, 16> : k_f32_row<false, false, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P.o.W,
+                               P.gu.W, P.q, P.h, cache_len, d, hd, F, m, P);
         else
-            hipLaunchKernelGGL((few ? k_f32_row<false, true, 4, 32> : k_f32_row<false, true, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P);
+            hipLaunchKernelGGL((few ? k_f32_row<false, true, 4, 32> : k_f32_row<false, true, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P.o.W,
+                               P.gu.W, P.q, P.h, cache_len, d, hd, F, m, P);
         CSD_LAUNCH_CHECK();
         if (mod->trace)
             CSD_HIP(hipMemcpyAsync(mod->trace + (size_t)(l + 1) * M * d, mod->h, sizeof(float) * (size_t)M * d, hipMemcpyDeviceToDevice, st));
