@@ -441,23 +441,24 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
     const bool last = active && L.old == (unsigned)(nch - 1);
     const float *pbase = A.part + ((size_t)b * geo.H + hh) * A.chunks_max * 16 * PS;
     const __amdgpu_buffer_rsrc_t rm = ch_rsrc(pbase, last ? (size_t)A.chunks_max * 16 * PS * 4 : 0);
-    // out[r][x] = sum_c weight[c][r] * acc_c[r][x] with weight[c][r] = e^(m_c - m*) / sum_c l_c e^(m_c - m*).  A thread
-    // takes feature x of every (256 / DH)-th row; the accumulators of four rows x sixteen chunks are requested
-    // together, and the first such batch before the states, so that the common case is one memory round trip.  Every wave makes all
+    // out[r][x] = sum_c weight[c][r] * acc_c[r][x] with weight[c][r] = e^(m_c - m*) / sum_c l_c e^(m_c - m*).  A thread takes four
+    // features of every RG-th row; the accumulators of sixteen chunks are requested together, and the first such batch before the states, so that
+    // the common case is one memory round trip (one feature of four rows per thread was four times the loads, some 25 cycles of the compute unit each:
+    // 7B shape, 1024 / 2000 cached rows, 2976 -> 2925 and 3479 -> 3342 us per step, 160M shape 393 -> 375, T5 shape, 1500 rows, 2909 -> 2863).  Every wave makes all
     // the weights for itself, lane (c % 4, r): no barrier, and up to 16 chunks without a loop over them.
-    const int x = gtid % DH;
-    constexpr int RG = 256 / DH;
-    const int r_first = gtid / DH;
-    float ac[4][16];
-#define CA_LOAD_ACC(R0, C0)                                                                                          \
-    _Pragma("unroll") for (int rr = 0; rr < 4; rr++) _Pragma("unroll") for (int u = 0; u < 16; u++) {                \
-        const int r_ = (R0) + rr * RG; /* (the scalar offset operand must be uniform: the per-thread part is the vector offset) */ \
-        ac[rr][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(                                  \
-                                                  rm, (r_ < m && (C0) + u < nch) ? ((((C0) + u) * 16 + r_) * PS + x) * 4 : CH_OOB, 0, 0)); \
-    }
+    const int x = gtid % (DH / 4) * 4;
+    constexpr int RG = 256 / (DH / 4);
+    const int r_first = gtid / (DH / 4);
+    f32x4 ac[16];
+    auto load_acc = [&](int r_, int c0) {                    // (the scalar offset operand must be uniform: the per-thread part is the vector offset)
+#pragma unroll
+        for (int u = 0; u < 16; u++)
+            ac[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  rm, (r_ < m && c0 + u < nch) ? (((c0 + u) * 16 + r_) * PS + x) * 4 : CH_OOB, 0, 0));
+    };
     float *wgt_c = L.w[wv];
     if (last) {
-        CA_LOAD_ACC(r_first, 0)
+        load_acc(r_first, 0);
         float mc[4], lc[4], mst = -INFINITY, den = 0.f;
         auto states = [&](int c0) {                              // chunks c0 .. c0 + 15 of row `col`
 #pragma unroll
@@ -489,30 +490,19 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
         const float inv = den > 0.f ? 1.0f / den : 0.f;
         for (int cc = g; cc < nch; cc += 4) wgt_c[cc * 16 + col] *= inv;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // read by the other lanes
-        const __amdgpu_buffer_rsrc_t ro = ch_rsrc(A.out, (size_t)2 * A.out_plane_bytes);
-        for (int r0 = r_first; r0 < m; r0 += 4 * RG) {
-            float num[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int r = r_first; r < m; r += RG) {
+            f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
             for (int c0 = 0; c0 < nch; c0 += 16) {
-                if (r0 != r_first || c0 != 0) CA_LOAD_ACC(r0, c0)
+                if (r != r_first || c0 != 0) load_acc(r, c0);
 #pragma unroll
-                for (int rr = 0; rr < 4; rr++)
-#pragma unroll
-                    for (int u = 0; u < 16; u++)
-                        if (r0 + rr * RG < m && c0 + u < nch) num[rr] += ac[rr][u] * wgt_c[(c0 + u) * 16 + r0 + rr * RG];
+                for (int u = 0; u < 16; u++)
+                    if (c0 + u < nch) num += ac[u] * wgt_c[(c0 + u) * 16 + r];
             }
-#pragma unroll
-            for (int rr = 0; rr < 4; rr++) {
-                const int r = r0 + rr * RG;
-                if (r >= m) break;
-                const bf16_t hi = f32_to_bf16(num[rr]);
-                const int off = (int)(act_tiled_idx(b * stride + r, hh * DH + x, A.mtp) * 2);
-                __builtin_amdgcn_raw_buffer_store_b16(hi, ro, off, 0, CH_SC1);
-                __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(num[rr] - bf16_to_f32(hi)), ro, off + A.out_plane_bytes, 0, CH_SC1);
-            }
+            const float v[4] = {num[0], num[1], num[2], num[3]};
+            store_planes4(A.out, A.out_plane_bytes, A.mtp, b * stride + r, hh * DH + x, v);
         }
         if (gtid == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-#undef CA_LOAD_ACC
 }
 
 // Causal attention of a block of up to 16 rows over the cached prefix, one launch per layer.  A workgroup
