@@ -161,20 +161,29 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
         }
     }
 
-    for (int ks = ks0; ks < ks1; ks += R) {
+    // The last turn of the rings requests nothing: a load that brings nothing still takes some 25 cycles of the compute unit's memory pipeline, and
+    // the rings' depth in loads past the end was 1 us of a launch (160M shape 367 -> 335 us per step, 7B shape 2926 -> 2883, T5 shape
+    // 2565 -> 2518, 7B shape, 20 rows 3678 -> 3536).
+    auto step = [&](int r) {
+#pragma unroll
+        for (int f = 0; f < 2 * MT - HALF; f++)
+#pragma unroll
+            for (int j = 0; j < NT; j++)
+                acc[f / 2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wr[r][j]),
+                                                                        __builtin_bit_cast(bf16x8, Ar[r][f]), acc[f / 2][j], 0, 0, 0);
+    };
+    int ks = ks0;
+    for (; ks + R < ks1; ks += R) {
 #pragma unroll
         for (int r = 0; r < R; r++) {
-#pragma unroll
-            for (int f = 0; f < 2 * MT - HALF; f++)
-#pragma unroll
-                for (int j = 0; j < NT; j++)
-                    acc[f / 2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wr[r][j]),
-                                                                            __builtin_bit_cast(bf16x8, Ar[r][f]), acc[f / 2][j], 0, 0, 0);
+            step(r);
             gemm_load_w<NT>(Wr[r], P, S, rw, ks + r + R, lane);
             gemm_load_a<MT, HALF>(Ar[r], P, S, ra, ks + r + R, voff_a);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+#pragma unroll
+    for (int r = 0; r < R; r++) step(r);                         // (k-steps past the end hold zeros)
 
     // ------------------------------------------------------------------ reduction and epilogue, a row tile at a time:
     // wave e takes unit e
