@@ -172,8 +172,7 @@ __device__ __forceinline__ void gemm_run(u32x4 (&Wr)[R][NT], const ChainGemm &P,
                 acc[f / 2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, Wr[r][j]),
                                                                         __builtin_bit_cast(bf16x8, Ar[r][f]), acc[f / 2][j], 0, 0, 0);
     };
-    int ks = ks0;
-    for (; ks + R < ks1; ks += R) {
+    for (int ks = ks0; ks + R < ks1; ks += R) {
 #pragma unroll
         for (int r = 0; r < R; r++) {
             step(r);
@@ -847,42 +846,51 @@ static int32_t attn_launch_small(const csd_model *mod, AttnArgs A, const GemmW *
 
 #define CH_MT_MAX 2          /* row tiles of 16 rows a launch covers: blocks of up to 32 rows */
 
-template <int NT, int R, int EPI, int MT>
-static hipError_t chain_allow_lds() {
-    const int lds = CH_WAVES * NT * 64 * 16 + CH_WAVES * MT * 16 * 4;
-    auto allow = [&](const void *f) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
-    hipError_t e = allow((const void *)kc_gemm<NT, R, EPI, MT, false, false>);
-    if (e == hipSuccess) e = allow((const void *)kc_gemm<NT, R, EPI, MT, true, false>);
-    if constexpr (MT == 1) {
-        if (e == hipSuccess) e = allow((const void *)kc_gemm<NT, R, EPI, MT, false, true>);
-        if (e == hipSuccess) e = allow((const void *)kc_gemm<NT, R, EPI, MT, true, true>);
-    }
-    return e;
+// Tiles per workgroup.  (The QKV epilogue holds the most state: eight tiles with two row tiles do not fit the registers, and a model
+// whose QKV matrix has more than 6 * 256 column tiles takes the per-operation kernels for such blocks.)
+#define CH_FOR_ALL_NT(X, EPI, MT) X(1, EPI, MT) X(2, EPI, MT) X(3, EPI, MT) X(4, EPI, MT) X(6, EPI, MT) X(8, EPI, MT)
+#define CH_FOR_QKV_TALL(X, MT) X(1, EPI_QKV, MT) X(2, EPI_QKV, MT) X(3, EPI_QKV, MT) X(4, EPI_QKV, MT) X(6, EPI_QKV, MT)
+#define CH_FOR_GU(X, MT) X(2, EPI_GU, MT) X(4, EPI_GU, MT) X(6, EPI_GU, MT) X(8, EPI_GU, MT)
+
+// Depth of the rings.  Two row tiles: the accumulators and the activation ring take more registers.  One row tile of at most eight rows: the
+// activation ring is half as wide.  Per launch of the 7B shape with 6 rows: QKV (3 tiles) 18.6 / 19.0 / 18.1 / 18.8 us with rings of 4 / 6 / 8 / 10, gate|up (6)
+// 31.7 / 31.1 / 31.4 / 31.7 with 2 / 3 / 4 / 5, O and down (1) 13.2 / 13.4 / 13.4 with 4 / 6 / 8, LM head (8) 42.2 to 43 with 2 to 4.
+// Short sums take rings of three at most: a ring deeper than a wave's k-steps requests what is past the end (160M shape: 3 k-steps per wave, 12 for down;
+// QKV 4.6 -> 4.3 us, gate|up 5.2 -> 4.5, the step 338 -> 324).
+#define CH_SHORT_KS (16 * CH_WAVES)
+static constexpr int ch_ring(int nt, int mt, bool half, bool short_k) {
+    const int r = mt == 2 ? (nt == 1 ? 4 : nt == 2 ? 3 : 2) : nt == 3 ? (half ? 8 : 4) : nt == 6 ? (half ? 3 : 2) : nt == 2 ? 6 : nt == 8 ? 2 : 4;
+    return short_k && (r > 3 || (nt == 8 && mt == 1)) ? 3 : r;
 }
 
-#ifndef CH_R1
-#define CH_R1 4
-#endif
-// (tiles per workgroup, ring depth): one row tile; and two row tiles, where the accumulators and the
-// activation ring take more registers and the rings are shallower
-#define CH_FOR_ALL_NT(X, EPI, MT) X(1, CH_R1, EPI, MT) X(2, 6, EPI, MT) X(3, 4, EPI, MT) X(4, 4, EPI, MT) X(6, 2, EPI, MT) X(8, 2, EPI, MT)
-#define CH_FOR_ALL_NT_TALL(X, EPI, MT) X(1, 4, EPI, MT) X(2, 3, EPI, MT) X(3, 2, EPI, MT) X(4, 2, EPI, MT) X(6, 2, EPI, MT) X(8, 2, EPI, MT)
-// (the QKV epilogue holds the most state: eight tiles with two row tiles do not fit the registers, and a model
-// whose QKV matrix has more than 6 * 256 column tiles takes the per-operation kernels for such blocks)
-#define CH_FOR_QKV_TALL(X, MT) X(1, 4, EPI_QKV, MT) X(2, 3, EPI_QKV, MT) X(3, 2, EPI_QKV, MT) X(4, 2, EPI_QKV, MT) X(6, 2, EPI_QKV, MT)
-#define CH_FOR_GU(X, MT) X(2, 6, EPI_GU, MT) X(4, 4, EPI_GU, MT) X(6, 2, EPI_GU, MT) X(8, 2, EPI_GU, MT)
-#define CH_FOR_GU_TALL(X, MT) X(2, 3, EPI_GU, MT) X(4, 2, EPI_GU, MT) X(6, 2, EPI_GU, MT) X(8, 2, EPI_GU, MT)
+template <int NT, int EPI, int MT>
+static constexpr int chain_lds() { return CH_WAVES * NT * 64 * 16 + CH_WAVES * MT * 16 * 4; }
+template <int NT, int EPI, int MT, bool HALF, bool SHORT, bool LIVE>
+static constexpr auto *chain_kernel() { return kc_gemm<NT, ch_ring(NT, MT, HALF, SHORT), EPI, MT, HALF, LIVE>; }
+
+template <int NT, int EPI, int MT, bool HALF, bool SHORT>
+static hipError_t chain_allow_lds() {
+    const hipError_t e = hipFuncSetAttribute((const void *)chain_kernel<NT, EPI, MT, HALF, SHORT, false>(), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             chain_lds<NT, EPI, MT>());
+    if (MT > 1 || e != hipSuccess) return e;
+    return hipFuncSetAttribute((const void *)chain_kernel<NT, EPI, MT, HALF, SHORT, MT == 1>(), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               chain_lds<NT, EPI, MT>());
+}
 
 int32_t csd_chain_setup() {
-#define CH_ALLOW(NT, R, EPI, MT) CSD_HIP((chain_allow_lds<NT, R, EPI, MT>()));
+#define CH_ALLOW(NT, EPI, MT)                                   \
+    CSD_HIP((chain_allow_lds<NT, EPI, MT, false, false>()));    \
+    CSD_HIP((chain_allow_lds<NT, EPI, MT, false, true>()));     \
+    CSD_HIP((chain_allow_lds<NT, EPI, MT, true, false>()));     \
+    CSD_HIP((chain_allow_lds<NT, EPI, MT, true, true>()));
     CH_FOR_ALL_NT(CH_ALLOW, EPI_QKV, 1)
     CH_FOR_ALL_NT(CH_ALLOW, EPI_RESID, 1)
     CH_FOR_ALL_NT(CH_ALLOW, EPI_LOGITS, 1)
     CH_FOR_GU(CH_ALLOW, 1)
     CH_FOR_QKV_TALL(CH_ALLOW, 2)
-    CH_FOR_ALL_NT_TALL(CH_ALLOW, EPI_RESID, 2)
-    CH_FOR_ALL_NT_TALL(CH_ALLOW, EPI_LOGITS, 2)
-    CH_FOR_GU_TALL(CH_ALLOW, 2)
+    CH_FOR_ALL_NT(CH_ALLOW, EPI_RESID, 2)
+    CH_FOR_ALL_NT(CH_ALLOW, EPI_LOGITS, 2)
+    CH_FOR_GU(CH_ALLOW, 2)
 #undef CH_ALLOW
 #define CA_ALLOW_ONE(DH, BIAS, LIVE, WARM)                                                                                         \
     CSD_HIP(hipFuncSetAttribute((const void *)kc_attn_one<DH, CA_ONE_NW, BIAS, LIVE, WARM>, hipFuncAttributeMaxDynamicSharedMemorySize, \
@@ -898,31 +906,31 @@ int32_t csd_chain_setup() {
     return CSD_OK;
 }
 
+template <int NT, int EPI, int MT, bool HALF, bool SHORT>
+static void chain_launch_one(const ChainGemm &P, int G, hipStream_t st) {
+    const bool live = MT == 1 && P.live && P.M == P.m;
+    auto *kernel = live ? chain_kernel<NT, EPI, MT, HALF, SHORT, MT == 1>() : chain_kernel<NT, EPI, MT, HALF, SHORT, false>();
+    hipLaunchKernelGGL(kernel, dim3(G), dim3(CH_THREADS), (chain_lds<NT, EPI, MT>()), st, P.Wp, P.KS, P.n_units, P.wbytes, G, P.a, P.a_plane_bytes, P.mtp,
+                       P.M, P.live, P);
+}
+
 template <int EPI, int MT>
 static int32_t chain_launch_mt(ChainGemm &P, int G, int per, hipStream_t st) {
-#define CH_LAUNCH(NT, R, E, MT_)                                                                                   \
-    if (per <= NT) {                                                                                              \
-        const int lds = CH_WAVES * NT * 64 * 16 + CH_WAVES * MT_ * 16 * 4;                                        \
-        const bool half = (P.M - 1) % 16 < 8, live = MT_ == 1 && P.live && P.M == P.m;                            \
-        hipLaunchKernelGGL((half ? live ? kc_gemm<NT, R, E, MT_, true, MT_ == 1> : kc_gemm<NT, R, E, MT_, true, false>     \
-                                 : live ? kc_gemm<NT, R, E, MT_, false, MT_ == 1> : kc_gemm<NT, R, E, MT_, false, false>), \
-                           dim3(G), dim3(CH_THREADS), lds, st, P.Wp, P.KS, P.n_units, P.wbytes, G, P.a, P.a_plane_bytes, P.mtp, P.M, P.live, P); \
-        return CSD_OK;                                                                                            \
+    const bool half = (P.M - 1) % 16 < 8, short_k = P.KS < CH_SHORT_KS;
+#define CH_LAUNCH(NT, E, MT_)                                                                                                                \
+    if (per <= NT) {                                                                                                                        \
+        if (half)                                                                                                                           \
+            short_k ? chain_launch_one<NT, E, MT_, true, true>(P, G, st) : chain_launch_one<NT, E, MT_, true, false>(P, G, st);             \
+        else                                                                                                                                \
+            short_k ? chain_launch_one<NT, E, MT_, false, true>(P, G, st) : chain_launch_one<NT, E, MT_, false, false>(P, G, st);           \
+        return CSD_OK;                                                                                                                      \
     }
-    if constexpr (MT == 1) {
-        if constexpr (EPI == EPI_GU) {
-            CH_FOR_GU(CH_LAUNCH, MT)
-        } else {
-            CH_FOR_ALL_NT(CH_LAUNCH, EPI, MT)
-        }
+    if constexpr (EPI == EPI_GU) {
+        CH_FOR_GU(CH_LAUNCH, MT)
+    } else if constexpr (EPI == EPI_QKV && MT == 2) {
+        CH_FOR_QKV_TALL(CH_LAUNCH, MT)
     } else {
-        if constexpr (EPI == EPI_GU) {
-            CH_FOR_GU_TALL(CH_LAUNCH, MT)
-        } else if constexpr (EPI == EPI_QKV) {
-            CH_FOR_QKV_TALL(CH_LAUNCH, MT)
-        } else {
-            CH_FOR_ALL_NT_TALL(CH_LAUNCH, EPI, MT)
-        }
+        CH_FOR_ALL_NT(CH_LAUNCH, EPI, MT)
     }
 #undef CH_LAUNCH
     return CSD_ESHAPE;
