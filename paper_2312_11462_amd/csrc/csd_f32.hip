@@ -10,6 +10,8 @@
 // (below; the tiny shape runs here only while the profile is on): 363 -> 67 us.
 #include <cmath>
 
+#include <type_traits>
+
 #include "csd_internal.h"
 
 #define FG_WAVES 8
@@ -235,15 +237,67 @@ struct RowSlice {
     }
 };
 
-// PO, PN: most values per thread of the O projection and of the next product
-template <bool FIRST, bool LAST, int PO, int PN>
+// The same with four columns per thread and a quarter of the values of each: a load brings a kilobyte per wave instead of 256 bytes, and a
+// compute unit's loads are what the wide products take their time for.  N a multiple of 4 and at least 64 (at most 64 slices: x is
+// zero that far past its end), W aligned to 16 bytes; red holds 4 * FR_THREADS floats.  Tiny shape, 5 rows over 32 and 9 over 400 cached: 37.7 -> 36.6 and 48.8
+// -> 47.4 us per step.
+template <int PER>
+struct RowSlice4 {
+    f32x4 w[PER / 4];
+    int k0, c, s;
+    static __device__ __forceinline__ int slices(const RowProduct &Q) { return __builtin_amdgcn_readfirstlane(small_div(FR_THREADS, Q.N / 4)); }
+    static __device__ __forceinline__ int values(const RowProduct &Q) { return __builtin_amdgcn_readfirstlane(small_div(Q.K + slices(Q) - 1, slices(Q))); }
+    __device__ __forceinline__ void load(const RowProduct &Q) {
+        const int N = Q.N, S = slices(Q);
+        s = small_div(threadIdx.x, N / 4);
+        c = (threadIdx.x - s * (N / 4)) * 4;
+        k0 = s * values(Q);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(Q.W), 0, Q.K * N * 4, 0x00020000);
+        int off = s < S ? (k0 * N + c) * 4 : (int)0x80000000;        // (as in RowSlice)
+#pragma unroll
+        for (int j = 0; j < PER / 4; j++) {
+            w[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+            off += N * 4;
+        }
+    }
+    __device__ __forceinline__ void apply(const RowProduct &Q, const float *x, float *red) const {
+        f32x4 a[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+        const int S = slices(Q), n = values(Q);
+        const float *xs = x + (s < S ? k0 : 0);
+#pragma unroll
+        for (int j = 0; j < PER / 4; j++)
+            if (j < n) {                                             // (uniform)
+#pragma unroll
+                for (int i = 0; i < 4; i++) a[j & 1][i] = fmaf(xs[j], w[j][i], a[j & 1][i]);
+            }
+        if (s < S) *reinterpret_cast<f32x4 *>(red + s * Q.N + c) = a[0] + a[1];
+    }
+    static __device__ __forceinline__ float sum(const RowProduct &Q, const float *red, int col) {
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        const int S = slices(Q);
+        int i = 0;
+#pragma unroll 1
+        for (; i + 4 <= S; i += 4)
+#pragma unroll
+            for (int u = 0; u < 4; u++) a[u] += red[(i + u) * Q.N + col];
+#pragma unroll 1
+        for (; i < S; i++) a[i & 1] += red[i * Q.N + col];
+        return (a[0] + a[1]) + (a[2] + a[3]);
+    }
+};
+
+// PO, PN: most values per thread of the O projection and of the next product.  VEC: gate|up and the next product four columns per thread.
 // What the first loads need comes ahead of the structure, in registers when a wave starts (see kc_gemm in csd_chain.hip): w0, w1 the O and
 // gate|up matrices, or (FIRST) w0 the QKV matrix, q the tokens and h the embedding.
+template <bool FIRST, bool LAST, int PO, int PN, bool VEC>
 __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const float *w1, const float *q0, const float *h0, const int32_t *cache_len,
                                                         int d, int hd, int F, int m, const F32Row P) {
     extern __shared__ float fr_smem[];
     __shared__ float x[FR_X], red[FR_THREADS], hs[FR_THREADS], y[FR_THREADS], wave_red[2 * (FR_THREADS / 64)];
-    float *sc = fr_smem;                                         // scores [H][keys_pad]
+    float *sc = fr_smem;                                         // scores [H][keys_pad]; behind the attention, VEC: partial sums
+    float *wide = VEC ? fr_smem : red;
+    using Wide32 = typename std::conditional<VEC, RowSlice4<32>, RowSlice<32>>::type;
+    using WideN = typename std::conditional<VEC, RowSlice4<PN>, RowSlice<PN>>::type;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = blockIdx.x;
     const int dh = P.geo.dh, H = P.geo.H, half = dh / 2;
     const int b = r / m, i = r % m;
@@ -266,7 +320,7 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const f
         return rsqrtf(ss / (float)d + P.eps);
     };
     const int t0 = cache_len[b];
-    RowSlice<PN> wn;
+    WideN wn;
     float hv = 0.f;                                              // this thread's entry of the residual stream
     if constexpr (FIRST) {
         wn.load(product(w0, d, 3 * hd));
@@ -280,7 +334,7 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const f
         }
     } else {
         RowSlice<PO> wo;
-        RowSlice<32> wg;
+        Wide32 wg;
         wo.load(product(w0, hd, d));
         wg.load(product(w1, d, 2 * F));
         // ---- attention of the row, all heads (the keys of a head as k_attn_simple takes them)
@@ -384,12 +438,12 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const f
         put_x(d, tid < d ? hv * P.ffn_gain[tid] : 0.f);
         __syncthreads();
         // ---- gate|up, activation
-        wg.apply(P.gu, x, red);
+        wg.apply(P.gu, x, wide);
         wn.load(P.next);
         __syncthreads();
         float f = 0.f;
         if (tid < F) {
-            const float gt = wg.sum(P.gu, red, tid) * rstd, up = wg.sum(P.gu, red, F + tid) * rstd;
+            const float gt = wg.sum(P.gu, wide, tid) * rstd, up = wg.sum(P.gu, wide, F + tid) * rstd;
             f = gt / (1.0f + expf(-gt)) * up;
         }
         put_x(F, f);
@@ -403,10 +457,10 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const f
     const float rstd = row_rstd(hv);
     put_x(d, tid < d ? hv * P.next_gain[tid] : 0.f);
     __syncthreads();
-    wn.apply(P.next, x, red);
+    wn.apply(P.next, x, wide);
     __syncthreads();
     float v = 0.f;
-    if (tid < P.next.N) v = wn.sum(P.next, red, tid) * rstd;
+    if (tid < P.next.N) v = wn.sum(P.next, wide, tid) * rstd;
     if constexpr (LAST) {
         if (tid < P.next.N) P.logits[(size_t)r * P.next.N + tid] = v;
     } else {
@@ -508,7 +562,7 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
     P.V = c.vocab;
     P.logits = logits;
     if (mod->tree_call) P.depth = mod->tree_depth, P.anc = mod->tree_anc;
-    const size_t lds = sizeof(float) * (size_t)c.n_heads * mod->seq_pad;
+    const size_t scores = sizeof(float) * (size_t)c.n_heads * mod->seq_pad;
     const bool few = row_product_fits(mod->hd, d, 4) && row_product_fits(d, 3 * mod->hd, 16);
     for (int l = -1; l < L; l++) {                               // layer l, and the QKV projection of the next one
         const GemmW &next = l + 1 < L ? mod->layers[l + 1].qkv : mod->lm;
@@ -523,15 +577,22 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
             P.ffn_gain = lw.ffn_norm;
         }
         const int hd = mod->hd, F = c.d_ffn;
+        auto four = [](const RowProduct &Q) { return Q.N % 4 == 0 && Q.N >= 64 && (uintptr_t)Q.W % 16 == 0; };
+        const bool vec = four(P.next) && (l < 0 || four(P.gu));
+        const size_t wide = sizeof(float) * 4 * FR_THREADS, lds = vec && scores < wide ? wide : scores;
+#define FR_LAUNCH(FIRST, LAST, PN, W0, W1, Q0, H0)                                                                                       \
+    {                                                                                                                                    \
+        auto *kernel = few ? (vec ? k_f32_row<FIRST, LAST, 4, PN, true> : k_f32_row<FIRST, LAST, 4, PN, false>)                          \
+                           : (vec ? k_f32_row<FIRST, LAST, 8, 32, true> : k_f32_row<FIRST, LAST, 8, 32, false>);                         \
+        hipLaunchKernelGGL(kernel, dim3(M), dim3(FR_THREADS), lds, st, W0, W1, Q0, H0, cache_len, d, hd, F, m, P);                        \
+    }
         if (l < 0)
-            hipLaunchKernelGGL((few ? k_f32_row<true, false, 4, 16> : k_f32_row<true, false, 8, 32>), dim3(M), dim3(FR_THREADS), 0, st, P.next.W,
-                               (const float *)nullptr, (const float *)tokens, (const float *)mod->embed, cache_len, d, hd, F, m, P);
+            FR_LAUNCH(true, false, 16, P.next.W, (const float *)nullptr, (const float *)tokens, (const float *)mod->embed)
         else if (l + 1 < L)
-            hipLaunchKernelGGL((few ? k_f32_row<false, false, 4, 16> : k_f32_row<false, false, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P.o.W,
-                               P.gu.W, P.q, P.h, cache_len, d, hd, F, m, P);
+            FR_LAUNCH(false, false, 16, P.o.W, P.gu.W, P.q, P.h)
         else
-            hipLaunchKernelGGL((few ? k_f32_row<false, true, 4, 32> : k_f32_row<false, true, 8, 32>), dim3(M), dim3(FR_THREADS), lds, st, P.o.W,
-                               P.gu.W, P.q, P.h, cache_len, d, hd, F, m, P);
+            FR_LAUNCH(false, true, 32, P.o.W, P.gu.W, P.q, P.h)
+#undef FR_LAUNCH
         CSD_LAUNCH_CHECK();
         if (mod->trace)
             CSD_HIP(hipMemcpyAsync(mod->trace + (size_t)(l + 1) * M * d, mod->h, sizeof(float) * (size_t)M * d, hipMemcpyDeviceToDevice, st));
