@@ -461,6 +461,40 @@ __global__ __launch_bounds__(SM_THREADS) void k_softmax(const float *logits, flo
     __shared__ unsigned long long red64[SM_THREADS / 64];
     const float *x = logits + (size_t)blockIdx.x * V;
     float *y = probs + (size_t)blockIdx.x * V;
+    // (four consecutive tokens per thread and load where the rows allow it: a value per load is four times as many loads and stores, and a compute unit
+    // takes one in some 10 cycles at best)
+    if (V <= SM_THREADS * SM_PER && V % 4 == 0 && ((uintptr_t)logits | (uintptr_t)probs) % 16 == 0) {
+        float val[SM_PER];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < SM_PER / 4; i++) {
+            const int v = (i * SM_THREADS + (int)threadIdx.x) * 4;
+            float4 t = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            if (v < V) t = *reinterpret_cast<const float4 *>(x + v);
+            val[4 * i] = t.x, val[4 * i + 1] = t.y, val[4 * i + 2] = t.z, val[4 * i + 3] = t.w;
+        }
+#pragma unroll
+        for (int i = 0; i < SM_PER; i++) {
+            val[i] = scaled_logit(val[i], inv_t);   // (the padding stays -inf: the temperature is positive)
+            mx = fmaxf(mx, val[i]);
+        }
+        mx = block_max<SM_THREADS>(mx, red);
+        uint32_t sh = 0, sl = 0;                    // at most 32 terms of at most 2^20 each
+#pragma unroll
+        for (int i = 0; i < SM_PER; i++) {
+            val[i] = exp_term(val[i], mx);
+            uint32_t h, l;
+            fixed40_parts(val[i], h, l);
+            sh += h, sl += l;
+        }
+        const float r = recip_of_total(block_sum_u64<SM_THREADS>((unsigned long long)sh * (1u << 20) + sl, red64));
+#pragma unroll
+        for (int i = 0; i < SM_PER / 4; i++) {
+            const int v = (i * SM_THREADS + (int)threadIdx.x) * 4;
+            if (v < V) *reinterpret_cast<float4 *>(y + v) = make_float4(val[4 * i] * r, val[4 * i + 1] * r, val[4 * i + 2] * r, val[4 * i + 3] * r);
+        }
+        return;
+    }
     if (V <= SM_THREADS * SM_PER) {
         float val[SM_PER];
         float mx = -INFINITY;

@@ -716,7 +716,9 @@ __global__ __launch_bounds__(NW * 64) void kc_attn_one(const bf16_t *k, const bf
 
 // h[r] = E[token[r]]; (h * gain) as the first GEMM's input, the sums of squares per 16-feature tile, and the
 // rotary table of the call's positions.  One workgroup per block row, one thread per 16-feature tile.
-__global__ __launch_bounds__(256) void kc_embed(const int32_t *__restrict__ tokens, const bf16_t *__restrict__ E, int V, int d,
+// A wave of its own makes the table (double precision, a long chain) while the others take the row.
+#define CE_ROW 256
+__global__ __launch_bounds__(CE_ROW + 64) void kc_embed(const int32_t *__restrict__ tokens, const bf16_t *__restrict__ E, int V, int d,
                                                 const float *__restrict__ gain, float *__restrict__ h, bf16_t *__restrict__ out,
                                                 int out_plane_bytes, int mtp, float *__restrict__ ssq_out,
                                                 int ssq_rows, const int32_t *__restrict__ cache_len, int m, int dh, float theta,
@@ -724,7 +726,7 @@ __global__ __launch_bounds__(256) void kc_embed(const int32_t *__restrict__ toke
     const int r = blockIdx.x;
     const int tok = tokens[r];
     const bool ok = tok >= 0 && tok < V;
-    for (int T = threadIdx.x; T < d / 16; T += blockDim.x) {
+    for (int T = (int)threadIdx.x < CE_ROW ? (int)threadIdx.x : d; T < d / 16; T += CE_ROW) {
         float ss = 0.f;
 #pragma unroll
         for (int c4 = 0; c4 < 4; c4++) {
@@ -741,10 +743,10 @@ __global__ __launch_bounds__(256) void kc_embed(const int32_t *__restrict__ toke
         }
         ssq_out[T * ssq_rows + r] = ss;
     }
-    if (theta > 0.f) {
+    if (theta > 0.f && threadIdx.x >= CE_ROW) {
         // the position of a row: where it sits in a plain block, how far it is from row 0 in a tree block
         const int pos = cache_len[r / m] + (depth ? depth[r] : r % m), half = dh / 2;
-        for (int x = threadIdx.x; x < half; x += blockDim.x) {
+        for (int x = (int)threadIdx.x - CE_ROW; x < half; x += 64) {
             const double ang = (double)pos * pow((double)theta, -2.0 * (double)x / (double)dh);
             rope[(size_t)r * half + x] = float2{(float)cos(ang), (float)sin(ang)};
         }
@@ -981,7 +983,7 @@ int32_t csd_chain_enqueue(csd_model *mod, void *kv, const int32_t *tokens, const
     const int ssq_rows = (M + 15) / 16 * 16;
     {
         ProfScope ps(mod, st, CSD_PROF_OTHER);
-        hipLaunchKernelGGL(kc_embed, dim3(M), dim3(256), 0, st, tokens, (const bf16_t *)mod->embed, V, d, mod->layers[0].attn_norm,
+        hipLaunchKernelGGL(kc_embed, dim3(M), dim3(CE_ROW + 64), 0, st, tokens, (const bf16_t *)mod->embed, V, d, mod->layers[0].attn_norm,
                            mod->h, X1, pb_d, mtp, ssq1, ssq_rows, cache_len, m, c.head_dim, t5 ? 0.f : c.rope_theta, mod->rope,
                            mod->tree_call ? mod->tree_depth : nullptr);
         CSD_LAUNCH_CHECK();
