@@ -34,13 +34,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(TALL_PARAMS) {
     extern __shared__ __align__(16) char rs_smem[];
     constexpr int PW = (CT + NW - 1) / NW;                       // weight loads per wave and k-step
     constexpr int AL = 2 * RW, NA = RS_SETS - 1, NST = RS_SETS + 1;
-    constexpr int RA = 4;                                        // weight fragments read ahead
-    // Every wave issues the same loads in every k-step but the last few, so the waits can count them, and some of them bring nothing that is used:
-    // k-steps past the slice (a turn of k-steps that ends with it requests three or four), and the waves' last tiles where CT is no multiple of the
-    // waves.  With four waves those are out of the buffer, where a load reads no memory; re-reading the slice's last k-step, or the last tile into its own place, cost
-    // 2 to 3 % of a call (7B shape, eight layers and the LM head, 128 rows 1485 -> 1438 us, 64 rows 1124 -> 1103; twelve layers of the 160M shape 809 -> 784 and
-    // 627 -> 614).  With three waves the selects cost as much as that or more (72 rows 1226 against 1232, 160M shape, 136 rows 824 against 835; 40 rows
-    // 1010 against 1002), and everything past an end is read as the last one.
+    constexpr int RA = CT * RW < 48 ? 4 : 3;                     // weight fragments read ahead (48 sums a lane and four spill)
+    // Every wave issues the same loads in every k-step that issues any, so the waits can count them, and some of them bring nothing that is used:
+    // k-steps past the slice, and the waves' last tiles where CT is no multiple of the waves.  With four waves those are out of the buffer, where a
+    // load reads no memory: re-reading the slice's last k-step, or the last tile into its own place, cost more (7B shape, whole steps, 128 rows 5667 us
+    // against 5693).  With three waves the selects cost as much as that (160M shape, 136 rows 824 against 835; 40 rows 1010 against 1002), and
+    // everything past an end is read as the last one.
     constexpr bool SKIP = NW == 4;
     constexpr int TILES = rs_tiles<CT, NW>();
     const ChainGemm &P = A.g;
@@ -98,9 +97,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(TALL_PARAMS) {
 #pragma unroll
     for (int c = 0; c < RA; c++) f[c] = L[c * 64];
     int cur = 0, last = NST - 1, k = ks0;                        // the stages of W(k) and of W(k - 1), the latter free for W(k + NA + 1)
-    // END: how many k-steps behind the last one that issued loads (0: this one issues its own).  The last k-steps of a slice issue none: the
-    // activations would not be used, and the compiler takes such loads out, but not those to LDS; the waits have to count what is issued.
-    auto step = [&](int set, auto END) {
+    // END: how many k-steps behind the last one that issued loads (0: this one issues its own).  The last k-steps of a slice issue none, also where the
+    // slice is whole turns: a load costs its time in the memory pipeline whether its data is used or not (7B shape, whole steps, 40 rows 5196 ->
+    // 5134 us, 136 rows 7983 -> 7755, 128 rows 5689 -> 5667; 160M shape, 136 rows 794 -> 779; T5 shape, 40 rows 3916 -> 3849).  The compiler takes
+    // loads of activations that are not used out by itself, but not those to LDS, and the waits have to count what is issued.  A slice that ends one
+    // or two k-steps after a turn still requests two or one too many: a tail for each remainder spilt registers.
+    auto step = [&](int set, auto END) __attribute__((always_inline)) {
         constexpr int E = decltype(END)::value;
         wait_loads<(E ? NA - E : NA - 1) * (PW + AL)>();         // W(k + 1), this wave's share
         stage_barrier();
@@ -132,14 +134,21 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(TALL_PARAMS) {
         cur = nxt;
         k++;
     };
-    while (k + RS_SETS <= ks1) {
+    while (k + RS_SETS < ks1) {
 #pragma unroll
         for (int u = 0; u < RS_SETS; u++) step(u, std::integral_constant<int, 0>{});
     }
     static_assert(RS_SETS == 4, "a k-step of each remainder");
-    if (k < ks1) step(0, std::integral_constant<int, 1>{});      // uniform over the workgroup
-    if (k < ks1) step(1, std::integral_constant<int, 2>{});
-    if (k < ks1) step(2, std::integral_constant<int, 3>{});
+    if (k + RS_SETS == ks1) {                               // uniform over the workgroup
+        step(0, std::integral_constant<int, 0>{});
+        step(1, std::integral_constant<int, 1>{});
+        step(2, std::integral_constant<int, 2>{});
+        step(3, std::integral_constant<int, 3>{});
+    } else {
+        step(0, std::integral_constant<int, 1>{});
+        if (k < ks1) step(1, std::integral_constant<int, 2>{});
+        if (k < ks1) step(2, std::integral_constant<int, 3>{});
+    }
     wait_loads<0>();                                             // nothing may land in this LDS after the workgroup has ended
 
     const int t = lane & 15, g = lane >> 4;

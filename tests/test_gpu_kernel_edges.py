@@ -352,6 +352,15 @@ def test_row_split_sums(P, K, V, plan, m):
     assert ((got - ref).abs() <= (K + 16) * 2.0 ** -23 * size).all()
 
 
+@pytest.mark.parametrize("steps", [1, 2, 4, 5, 6, 7, 8, 9, 10, 11])
+@pytest.mark.parametrize("m", [40, 64, 72, 96, 104, 136])
+def test_row_split_sums_of_every_remainder(P, steps, m):
+    """Slices of K of every length modulo the four k-steps in flight, from one k-step on, with and without a whole turn before the last."""
+    K = 32 * steps
+    assert _rows_plan(P, 528, K, m) == (6, 1)
+    test_row_split_sums(P, K, 528, (6, 1), m)
+
+
 @pytest.mark.parametrize("K,V", [(64, 528), (768, 4112), (4096, 8208)])
 @pytest.mark.parametrize("m", [1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32])
 def test_few_row_sums(P, K, V, m):
