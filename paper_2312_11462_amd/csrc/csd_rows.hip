@@ -13,8 +13,11 @@
 // the weight stream.  Against the form before it, whose four extra waves carried the weights to LDS through registers
 // and whose compute waves always owned two or three row tiles (33 to 48 rows kept two of four busy, 144 rows three), per launch of the 7B
 // shape in traces of whole steps: 40 rows QKV 24.8 -> 22.6 us, gate|up 37.7 -> 33.8, O and down together 34.0 -> 31.5; 136 rows QKV and
-// gate|up together 98.8 -> 94.4, O and down 53.9 -> 52.0.  The weights are read once, so they pass the caches by (non-temporal: 22.2
-// -> 20.5 us for QKV at 40 rows by itself).  Measured and not taken: 6 to 12 k-steps ahead (no faster), all of K in one workgroup
+// gate|up together 98.8 -> 94.4, O and down 53.9 -> 52.0.  (Today, with the arguments in registers and the last turn without
+// loads: 20.8, 32.4, 29.8; 88.7, 51.2.)  The weights are read once, so they pass the caches by (non-temporal: 22.2
+// -> 20.5 us for QKV at 40 rows by itself).  Measured and not taken: 6 to 12 k-steps ahead (no faster), the fragments of 5, 6 and 9 row
+// tiles dealt to four waves, a tile in two halves (fewer matrix instructions per wave, more loads: 136 rows 7755 -> 8000 us per step), one fragment for both planes
+// of a last tile of up to eight rows (40 rows 5119 -> 5109, 72 rows 4775 -> 4720, 136 rows 7760 -> 7820), all of K in one workgroup
 // and the epilogue inside (40 rows, gate|up by itself 39 to 43 us against 33 and 5 for the epilogue kernel; 136 rows 68.8 against 58.0 and 7.8).
 #include "csd_tall.h"
 
@@ -101,7 +104,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(TALL_PARAMS) {
     // slice is whole turns: a load costs its time in the memory pipeline whether its data is used or not (7B shape, whole steps, 40 rows 5196 ->
     // 5134 us, 136 rows 7983 -> 7755, 128 rows 5689 -> 5667; 160M shape, 136 rows 794 -> 779; T5 shape, 40 rows 3916 -> 3849).  The compiler takes
     // loads of activations that are not used out by itself, but not those to LDS, and the waits have to count what is issued.  A slice that ends one
-    // or two k-steps after a turn still requests two or one too many: a tail for each remainder spilt registers.
+    // or two k-steps after a turn still requests two or one too many: a tail for each remainder spilt registers, and no form of this kernel may spill
+    // (accesses to scratch memory are counted by the same waits).
     auto step = [&](int set, auto END) __attribute__((always_inline)) {
         constexpr int E = decltype(END)::value;
         wait_loads<(E ? NA - E : NA - 1) * (PW + AL)>();         // W(k + 1), this wave's share
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_gemm_rs(TALL_PARAMS) {
         for (int u = 0; u < RS_SETS; u++) step(u, std::integral_constant<int, 0>{});
     }
     static_assert(RS_SETS == 4, "a k-step of each remainder");
-    if (k + RS_SETS == ks1) {                               // uniform over the workgroup
+    if (k + RS_SETS == ks1) {                                    // uniform over the workgroup
         step(0, std::integral_constant<int, 0>{});
         step(1, std::integral_constant<int, 1>{});
         step(2, std::integral_constant<int, 2>{});
