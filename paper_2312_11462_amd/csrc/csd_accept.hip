@@ -619,12 +619,13 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
         mx = block_max<RR_THREADS>(mx, red);
         uint32_t sh = 0, sl = 0;                                 // at most 64 terms of at most 2^20 each
         // e^-28 < 2^-40: groups that far below the maximum have no part in the sum nor, scaled by the lenience, in a draw, and their
-        // probabilities are only needed where the caller wants them all
-        const float cut = mx - 28.0f - logf(lenience);
+        // probabilities are only needed where the caller wants them all.  The line is on the difference that exp_term takes, which is 0 at
+        // the maximum whatever its size: mx - 28 is mx itself from 2^29 on, which a temperature of 1e-8 reaches.
+        const float cut = -28.0f - logf(lenience);
 #pragma unroll
         for (int j = 0; j < NG; j++) {
             // (NaN is no maximum: it carries no weight either)
-            if (!__any(fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3])) > cut) && !probs) {
+            if (!__any(fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3])) - mx > cut) && !probs) {
 #pragma unroll
                 for (int c = 0; c < 4; c++) val[4 * j + c] = 0.f;
                 continue;

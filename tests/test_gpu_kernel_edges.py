@@ -779,3 +779,28 @@ def test_review_of_confident_rows_equals_softmax_then_accept(P, V, mode, std):
             lg, p = gm.verify_block(block, cl, want_probs=True)
             n2, x2 = P.accept(lg if mode and lenience == 1.0 else p, q, block[:, 1:].contiguous(), ua, us, lenience=lenience, mode=mode)
             assert torch.equal(n, n2) and torch.equal(x, x2)
+
+
+@pytest.mark.parametrize("V", [512, 8192, 32000])
+@pytest.mark.parametrize("temperature", [1e-2, 1e-4, 1e-6, 3e-7, 1e-7, 3e-8, 1e-8, 1e-9])
+def test_review_at_small_temperatures_equals_softmax_then_accept(P, V, temperature):
+    """Scaled logits of 2^9 to 2^37, up to where the distance of two neighbouring 32-bit numbers passes every margin below the maximum: with and without
+    drafts, without probabilities asked for, the fused review decides as the two kernels, bit for bit, and emits a token."""
+    shape = I.ModelShape("edge_review", 0, "fp32", 1, 16, 1, 16, 16, V)
+    gm = P.Model(shape, I.make_weights(shape, 43, device="cuda", std=2.0), max_batch=2, max_seq=16, max_block=6)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    cl = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for m in (1, 6):
+        block = torch.randint(0, V, (2, m), generator=g, device="cuda", dtype=torch.int32)
+        for i in range(m):                                   # one sequence's drafts are all kept
+            lg, p = gm.verify_block(block, cl, want_probs=True, temperature=temperature)
+            if i + 1 < m:
+                block[0, i + 1] = lg[0, i].argmax()
+        assert (lg.max(-1).values > 4.0).all() and (lg.max(-1).values < 100.0).all()
+        for lenience in (1.0, 256.0):
+            for dense in (False, True) if m > 1 else (False,):
+                q = torch.softmax(6.0 * torch.randn((2, m - 1, V), generator=g, device="cuda"), -1) if dense else None
+                ua, us = torch.rand((2, m - 1), generator=g, device="cuda"), torch.rand(2, generator=g, device="cuda")
+                n, x = gm.verify_accept(block, cl, ua, us, q=q, lenience=lenience, temperature=temperature)
+                n2, x2 = P.accept(p, q, block[:, 1:].contiguous(), ua, us, lenience=lenience)
+                assert torch.equal(n, n2) and torch.equal(x, x2) and (x >= 0).all()
