@@ -444,8 +444,9 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
     unsigned *cnt = A.counters + b * geo.H + hh;
     if (gtid == 0) L.old = active ? __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0xFFFFFFFFu;
     __syncthreads();
-    // ---- last to arrive: merge the chunk states of this (sequence, head).  They were written through to memory,
-    // and this compute die's L2 (emptied when the kernel started) cannot hold an older copy of them.
+    // ---- last to arrive: merge the chunk states of this (sequence, head).  Workgroups on other compute dies wrote them through to memory
+    // (CH_SC1).  The loads are of device scope too: a line outlives the end of a kernel in an L2 (see csd_warm.h), and a die that merged this
+    // head in an earlier layer has read the same addresses.
     const bool last = active && L.old == (unsigned)(nch - 1);
     const float *pbase = A.part + ((size_t)b * geo.H + hh) * A.chunks_max * 16 * PS;
     const __amdgpu_buffer_rsrc_t rm = ch_rsrc(pbase, last ? (size_t)A.chunks_max * 16 * PS * 4 : 0);
@@ -462,7 +463,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
 #pragma unroll
         for (int u = 0; u < 16; u++)
             ac[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                  rm, (r_ < m && c0 + u < nch) ? (((c0 + u) * 16 + r_) * PS + x) * 4 : CH_OOB, 0, 0));
+                                                  rm, (r_ < m && c0 + u < nch) ? (((c0 + u) * 16 + r_) * PS + x) * 4 : CH_OOB, 0, CH_SC1));
     };
     float *wgt_c = L.w[wv];
     if (last) {
@@ -472,8 +473,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
 #pragma unroll
             for (int j = 0; j < 4; j++) {
                 const int cc = c0 + 4 * j + g, o = cc < nch ? (cc * 16 + col) * PS * 4 : CH_OOB;
-                mc[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, DH * 4, 0));
-                lc[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, (DH + 1) * 4, 0));
+                mc[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, DH * 4, CH_SC1));
+                lc[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, o, (DH + 1) * 4, CH_SC1));
             }
 #pragma unroll
             for (int j = 0; j < 4; j++)

@@ -5,7 +5,7 @@
 #include "csd_internal.h"
 
 #define CH_OOB ((int)0x80000000)     /* buffer offset beyond any buffer: loads give 0 and touch no memory */
-#define CH_SC1 16                    /* write-through stores: the data is for workgroups on other compute dies */
+#define CH_SC1 16                    /* device scope: data for, or from, workgroups on other compute dies (stores write through) */
 
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_GU = 2, EPI_LOGITS = 3 };
 
