@@ -140,16 +140,23 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
-// Most of a row carries no weight at all: what is below 2^-40 after the scaling by the lenience is 0 in 40-bit fixed point, and a
-// confident reviewer leaves nearly every token there.  The work on a thread's values is what the review kernels are bound by, so a group of 256
-// tokens (four per lane) is looked at first, and left out where all of it is that small.
-// Rows with nearly all of their weight on one token, 32000 tokens: eight sequences of k_accept 10.0 -> 8.3 us, nine rows of k_review_rows (160M step)
-// 5 us less; rows whose every group matters 9.7 -> 10.0.
+// What is below 2^-40 after the scaling by the lenience, some 28 below the top logit, is 0 in 40-bit fixed point.  The work on a thread's
+// values is what the review kernels are bound by, so a group of 256 tokens (four per lane) of which all is that small is left out.
+// How many are depends on the rows: the largest of 256 logits is some three times their spread above the rest.  32000 tokens, logits of
+// spread 1.3 and one token that leads them, without / with the look, in us:
+//   eight sequences of k_accept, lead 16 / 24 / 36: 10.0 / 9.9, 9.8 / 9.6, 9.8 / 6.2; against draft distributions 10.5 / 9.8, 10.5 / 7.0, 10.1 / 6.7
+//   k_tree_accept over five rows, lead 16 / 31 / 36: 39.1 / 39.9, 38.6 / 35.4, 39.8 / 22.7; trees of the 160M shape 39.5 / 24.3, of the 7B shape
+//   39.5 / 40.4 (0.02 % of that step, where it is 2.6 % of the other)
+//   k_review_rows: see there
 // (As bits, NaN and whatever is negative are above every small weight: the cheapest look that leaves them in.)
 __device__ __forceinline__ bool group_matters(const float *v) {
     const uint32_t m = max(max(__float_as_uint(v[0]), __float_as_uint(v[1])), max(__float_as_uint(v[2]), __float_as_uint(v[3])));
     return __any(m > __float_as_uint(0x1p-41f));
 }
+
+// Where the first two groups of a wave both matter it takes them all, without looks and branches in between: with a look at each, rows of
+// which every group matters took 10.4 us where they now take 9.9.
+__device__ __forceinline__ bool worth_a_look(const float *v) { return !(group_matters(v) && group_matters(v + 4)); }
 
 // The draw inside the wave that owns T: its values in token order are (group j, lane, position in the group), `run` the weight of
 // all tokens before it.  They go through LDS (`own`, a float4 per lane and group) so that the loop over groups needs no registers
@@ -339,8 +346,8 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
                     val[i] = df > 0.0f ? df : 0.0f;
                 }
             }
-            if (!group_matters(val + 4 * j)) continue;
-            live |= 1u << j;
+        }
+        auto add = [&](int j) {
             uint32_t sh = 0;
 #pragma unroll
             for (int c = 0; c < 4; c++) {
@@ -352,6 +359,18 @@ __device__ __forceinline__ void accept_core(AcceptShared &S, const float *__rest
             }
             mine += sh;
             __builtin_amdgcn_sched_barrier(0);
+        };
+        if (__builtin_expect(worth_a_look(val), 0)) {
+#pragma unroll
+            for (int j = 0; j < ACC_NG; j++)
+                if (group_matters(val + 4 * j)) {
+                    live |= 1u << j;
+                    add(j);
+                }
+        } else {
+            live = (1u << ACC_NG) - 1;
+#pragma unroll
+            for (int j = 0; j < ACC_NG; j++) add(j);
         }
         mine = (mine << 20) + sl;
         const unsigned long long wave_total = wave_sum_u64(mine);
@@ -609,7 +628,9 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             if (val[i] > best.v) best = {val[i], vbase + 256 * (i >> 2) + (i & 3)};
     }
     float px = x_logit, mx = -INFINITY, r = 1.0f;
-    uint32_t live = 0;                                           // bit j: group j of this wave (uniform over it)
+    // bit j: group j of this wave (uniform over it); all: the groups inside the row
+    const uint32_t all = (1u << min(NG, max(0, V - __builtin_amdgcn_readfirstlane(wv) * (64 * RR_PER) + 255) / 256)) - 1;
+    uint32_t live = 0;
     if (!raw || probs) {
 #pragma unroll
         for (int i = 0; i < RR_PER; i++) {
@@ -621,16 +642,14 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
         // e^-28 < 2^-40: groups that far below the maximum have no part in the sum nor, scaled by the lenience, in a draw, and their
         // probabilities are only needed where the caller wants them all.  The line is on the difference that exp_term takes, which is 0 at
         // the maximum whatever its size: mx - 28 is mx itself from 2^29 on, which a temperature of 1e-8 reaches.
+        // All looks first: a wave of which every group matters then does its work without branches.  Five rows of 32000 tokens, whole calls of a
+        // tiny model without / with the looks: every group matters 41.5 / 41.4 us, against draft distributions 41.5 / 41.6, few matter 41.6 / 37.5 and
+        // 41.5 / 37.6 (a look in front of each group's work: 42.1, 43.9, 37.1, 36.8).
         const float cut = -28.0f - logf(lenience);
 #pragma unroll
-        for (int j = 0; j < NG; j++) {
-            // (NaN is no maximum: it carries no weight either)
-            if (!__any(fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3])) - mx > cut) && !probs) {
-#pragma unroll
-                for (int c = 0; c < 4; c++) val[4 * j + c] = 0.f;
-                continue;
-            }
-            live |= 1u << j;
+        for (int j = 0; j < NG; j++)                             // (NaN is no maximum: it carries no weight either)
+            if (__any(fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3])) - mx > cut)) live |= 1u << j;
+        auto add = [&](int j) {
 #pragma unroll
             for (int c = 0; c < 4; c++) {
                 const int i = 4 * j + c;
@@ -638,6 +657,21 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 uint32_t h, l;
                 fixed40_parts(val[i], h, l);
                 sh += h, sl += l;
+            }
+        };
+        if (live == all || probs) {                              // without the branches
+            live = all;
+#pragma unroll
+            for (int j = 0; j < NG; j++) add(j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NG; j++) {
+                if (live >> j & 1) {
+                    add(j);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; c++) val[4 * j + c] = 0.f;
+                }
             }
         }
         r = recip_of_total(block_sum_u64<RR_THREADS>((unsigned long long)sh * (1u << 20) + sl, red64));
@@ -687,7 +721,6 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
             if (residual) {                                  // the weights take the probabilities' place
 #pragma unroll
                 for (int j = 0; j < NG; j++) {
-                    if (!qrow && !(live >> j & 1)) continue;     // nothing is above 0 - q
                     float qv[4] = {0.f, 0.f, 0.f, 0.f};
                     const int v = vbase + 256 * j;
                     if (qrow) {
@@ -704,7 +737,12 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                         const float df = __fsub_rn(__fmul_rn(lenience, val[4 * j + c]), qv[c]);
                         val[4 * j + c] = df > 0.0f ? df : 0.0f;
                     }
-                    if (qrow) live = group_matters(val + 4 * j) ? live | 1u << j : live & ~(1u << j);
+                }
+                if (qrow) {                                  // (behind the loop: in it every group would wait for its own q)
+                    live = 0;
+#pragma unroll
+                    for (int j = 0; j < NG; j++)
+                        if (group_matters(val + 4 * j)) live |= 1u << j;
                 }
             }
             unsigned long long Z = 0ull, before = 0ull, wave_total = 0ull;
@@ -713,10 +751,8 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 // all (at most 2^20 each) add up in 32 bits
                 unsigned long long mine = 0ull;
                 uint32_t sl = 0;
-#pragma unroll
-                for (int j = 0; j < NG; j++) {
+                auto add = [&](int j) {
                     uint32_t sh = 0;
-                    if (!(live >> j & 1)) continue;
 #pragma unroll
                     for (int c = 0; c < 4; c++) {
                         uint32_t h, l;
@@ -724,6 +760,14 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                         sh += h, sl += l;
                     }
                     mine += sh;
+                };
+                if (live == all) {
+#pragma unroll
+                    for (int j = 0; j < NG; j++) add(j);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < NG; j++)
+                        if (live >> j & 1) add(j);
                 }
                 mine = (mine << 20) + sl;
                 wave_total = wave_sum_u64(mine);
@@ -737,7 +781,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 }
                 if (Z != 0ull || !residual) break;
                 residual = false;                            // all-zero residual: draw from the reviewer's row, rebuilt
-                live = NG < 32 ? (1u << NG) - 1 : ~0u;
+                live = all;
 #pragma unroll
                 for (int j = 0; j < NG; j++) {
                     const int v = vbase + 256 * j;
