@@ -292,7 +292,7 @@ struct RowSlice4 {
 template <bool FIRST, bool LAST, int PO, int PN, bool VEC>
 __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const float *w1, const float *q0, const float *h0, const int32_t *cache_len,
                                                         int d, int hd, int F, int m, const F32Row P) {
-    extern __shared__ float fr_smem[];
+    extern __shared__ __align__(16) float fr_smem[];             // (RowSlice4 stores four floats at a time)
     __shared__ float x[FR_X], red[FR_THREADS], hs[FR_THREADS], y[FR_THREADS], wave_red[2 * (FR_THREADS / 64)];
     float *sc = fr_smem;                                         // scores [H][keys_pad]; behind the attention, VEC: partial sums
     float *wide = VEC ? fr_smem : red;
