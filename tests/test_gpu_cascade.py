@@ -273,10 +273,14 @@ def test_resident_cascade_sampling_matches_the_oracle_driver_token_for_token(K, 
     assert len(got) - len(prompt) >= n_steps
 
 
-@pytest.mark.parametrize("B", [1, 2, 3])
+# (sequences, rows a call has room for): one row tile with the two planes in a fragment each, and in one; two row tiles, the last one half
+ROOMS = [(1, 16), (2, 16), (3, 16), (1, 8), (2, 12)]
+
+
+@pytest.mark.parametrize("B,room", ROOMS)
 @pytest.mark.parametrize("H,dh,max_seq", [(4, 64, 192), (4, 64, 1088), (2, 128, 192), (2, 128, 1088)])
-def test_review_of_fewer_rows_than_the_call_has_room_for(H, dh, max_seq, B):
-    """csd_review_ctx with room for 16 rows reviews 6, 1 and 4 of them, after a call in which every sequence is skipped and together with a skipped
+def test_review_of_fewer_rows_than_the_call_has_room_for(H, dh, max_seq, B, room):
+    """csd_review_ctx with room for 8 to 16 rows reviews 6, 1 and 4 of them, after a call in which every sequence is skipped and together with a skipped
     one: what the unused rows and the cache behind the used ones hold (NaN here) reaches nothing, and a plain review of
     exactly those rows decides the same."""
     import paper_2312_11462_amd as P
@@ -295,7 +299,7 @@ def test_review_of_fewer_rows_than_the_call_has_room_for(H, dh, max_seq, B):
     status, n_acc, nxt = (torch.zeros(B, **i32) for _ in range(3))
 
     def review(prefix):
-        gm.review_ctx(ctx, length, cache, prefix, 16, status, n_accepted=n_acc, next_token=nxt, mode=1)
+        gm.review_ctx(ctx, length, cache, prefix, room, status, n_accepted=n_acc, next_token=nxt, mode=1)
 
     for rows in (6, 1, 4):
         start = cache.clone()
@@ -314,14 +318,14 @@ def test_review_of_fewer_rows_than_the_call_has_room_for(H, dh, max_seq, B):
 
 
 @pytest.mark.parametrize("mode,lenience", [(0, 1.0), (0, 2.0), (1, 1.0), (1, 2.0)])
-@pytest.mark.parametrize("B", [1, 2])
+@pytest.mark.parametrize("B,room", [x for x in ROOMS if x[0] < 3])
 @pytest.mark.parametrize("arch,H,dh,max_seq", [(0, 4, 64, 192), (0, 2, 128, 1088), (1, 4, 64, 192), (1, 4, 64, 1088), (1, 2, 128, 192), (1, 2, 128, 1088)])
-def test_review_after_nan_everywhere(arch, H, dh, max_seq, B, mode, lenience):
-    """csd_review_ctx with room for 16 rows after a call that left NaN in every buffer of the model and in the cache behind the kept rows: reviews of
+def test_review_after_nan_everywhere(arch, H, dh, max_seq, B, room, mode, lenience, dims=(256, 512, 1024)):
+    """csd_review_ctx with room for 8 to 16 rows after a call that left NaN in every buffer of the model and in the cache behind the kept rows: reviews of
     fewer rows, after a call in which every sequence is skipped and beside a skipped one, decide as a plain review of exactly those rows does, and the
     rows they hand on are its probabilities.  Both architectures, self- and cross-attention in either form for short blocks."""
     import paper_2312_11462_amd as P
-    shape = I.ModelShape("live", arch, "bf16", 2, 256, H, dh, 512, 1024, rms_eps=1e-6 if arch else 1e-5, enc_len=90 if arch else 0)
+    shape = I.ModelShape("live", arch, "bf16", 2, dims[0], H, dh, dims[1], dims[2], rms_eps=1e-6 if arch else 1e-5, enc_len=90 if arch else 0)
     w = I.make_weights(shape, 5, device="cuda", std=0.05)
     gm = P.Model(shape, w, max_batch=B, max_seq=max_seq, max_block=16)
     ref = P.Model(shape, w, max_batch=B, max_seq=max_seq, max_block=16)
@@ -346,7 +350,7 @@ def test_review_after_nan_everywhere(arch, H, dh, max_seq, B, mode, lenience):
     out_q, base = torch.full((B, 48, V), float("nan"), device="cuda"), torch.zeros(B, **i32)
 
     def review(prefix):
-        gm.review_ctx(ctx, length, cache, prefix, 16, status, u_acc_tab=u_acc, u_samp_tab=u_samp, out_q_tab=out_q, out_base=base, n_accepted=n_acc,
+        gm.review_ctx(ctx, length, cache, prefix, room, status, u_acc_tab=u_acc, u_samp_tab=u_samp, out_q_tab=out_q, out_base=base, n_accepted=n_acc,
                       next_token=nxt, mode=mode, lenience=lenience)
 
     for rows in (6, 1, 4):
@@ -370,3 +374,10 @@ def test_review_after_nan_everywhere(arch, H, dh, max_seq, B, mode, lenience):
         assert torch.equal(cache, start + 1 + n_ref)
     gm.close()
     ref.close()
+
+
+@pytest.mark.parametrize("room", [8, 16])
+@pytest.mark.parametrize("arch,H,dh,dims", [(0, 32, 128, (4096, 11008, 32000)), (1, 64, 64, (4096, 10240, 32128)), (0, 12, 64, (768, 3072, 32000))])
+def test_review_after_nan_everywhere_with_wide_matrices(arch, H, dh, dims, room):
+    """The same for the widths of the benchmark shapes' matrices: two to eight tiles per workgroup, long and short sums."""
+    test_review_after_nan_everywhere(arch, H, dh, 192, 1, room, 0, 1.0, dims)
