@@ -446,7 +446,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &A, AttnLds<DH> &L, boo
     __syncthreads();
     // ---- last to arrive: merge the chunk states of this (sequence, head).  Workgroups on other compute dies wrote them through to memory
     // (CH_SC1).  The loads are of device scope too: a line outlives the end of a kernel in an L2 (see csd_warm.h), and a die that merged this
-    // head in an earlier layer has read the same addresses.
+    // head in an earlier layer has read the same addresses.  (160M shape of 24 layers, 2000 cached rows 625 -> 632 us per step, with an acquire
+    // fence in front of plain loads 654; 700 rows 589 all three.)
     const bool last = active && L.old == (unsigned)(nch - 1);
     const float *pbase = A.part + ((size_t)b * geo.H + hh) * A.chunks_max * 16 * PS;
     const __amdgpu_buffer_rsrc_t rm = ch_rsrc(pbase, last ? (size_t)A.chunks_max * 16 * PS * 4 : 0);
@@ -802,6 +803,10 @@ static int chain_groups(int n_units, int ut) {
 // - else, beside one workgroup per head, as much of the first (and so on) as 30 MB, from 256 cache rows on (T5 shape, 33.6 MB: 14 MB 2612, 24 MB 2570,
 //   30 MB 2551, none 2649; 7B shape, 300 rows 2991 -> 2969), 14 MB with fewer, where the attention is shorter (7B shape, 100 rows 2772 -> 2784, with
 //   30 MB 2836; T5 shape, 20 rows and 40 encoder rows 2529 -> 2493, with 30 MB 2525);
+//   (In between, 27 to 76 MB: models of 1024 to 2048 features, 100 cached rows 1 to 4 % of a step shorter with it, 700 rows 0 to 8 %, 2000 rows the same;
+//   arch 1 of 2048 features 1 % shorter with 100 rows, 1 to 2 % longer with 700 and 2000.  Small layers of a model that does not fit the memory-side
+//   cache lose with a short cache: 24 layers of the 160M shape, 340 MB, 584 -> 611 with 100 rows, 600 -> 608 with 200, 623 -> 614 with 300, 644 -> 614
+//   with 500; 12 layers of it 299 -> 273 with 100.)
 // - beside the chunks of large models nothing: their own loads keep the memory busy (7B shape, 1024 rows 2963 against 2960 with 14 MB, 2967 with
 //   16; two sequences of 700 rows 3198 against 3257).
 // 96 workgroups of 16 waves, 128 of 4: 184 and 224 are no faster, half as many are (T5 shape, 30 MB 2805 us), and no more than fit on the chip with the launch's own.
@@ -860,7 +865,9 @@ static int32_t attn_launch_small(const csd_model *mod, AttnArgs A, const GemmW *
 // activation ring is half as wide.  Per launch of the 7B shape with 6 rows: QKV (3 tiles) 18.6 / 19.0 / 18.1 / 18.8 us with rings of 4 / 6 / 8 / 10, gate|up (6)
 // 31.7 / 31.1 / 31.4 / 31.7 with 2 / 3 / 4 / 5, O and down (1) 13.2 / 13.4 / 13.4 with 4 / 6 / 8, LM head (8) 42.2 to 43 with 2 to 4.
 // Short sums take rings of three at most: a ring deeper than a wave's k-steps requests what is past the end (160M shape: 3 k-steps per wave, 12 for down;
-// QKV 4.6 -> 4.3 us, gate|up 5.2 -> 4.5, the step 338 -> 324).
+// QKV 4.6 -> 4.3 us, gate|up 5.2 -> 4.5, the step 338 -> 324).  The line, K = 4096, is where the 7B shape prefers the deeper rings.  Below it, at 6 to 12
+// k-steps per wave, where nothing is requested past the end, rings of three are 0 to 3 % of a step faster (1536, 2048 and 3072 features, 9 rows 340 -> 334, 292 ->
+// 283, 254 -> 253 us) but with arch 1 of 2048 features, where they are 1 to 2 % slower (9 rows 377 -> 383).
 #define CH_SHORT_KS (16 * CH_WAVES)
 static constexpr int ch_ring(int nt, int mt, bool half, bool short_k) {
     const int r = mt == 2 ? (nt == 1 ? 4 : nt == 2 ? 3 : 2) : nt == 3 ? (half ? 8 : 4) : nt == 6 ? (half ? 3 : 2) : nt == 2 ? 6 : nt == 8 ? 2 : 4;
