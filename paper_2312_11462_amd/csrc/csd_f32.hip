@@ -345,7 +345,8 @@ __global__ __launch_bounds__(FR_THREADS) void k_f32_row(const float *w0, const f
         const float *kc = P.kv + kv_k_off(P.geo, P.layer, b, 0), *vc = P.kv + kv_v_off(P.geo, P.layer, b, 0);
         const size_t he = kv_head_elems(P.geo);
         // the first key of the thread (16 values of it) and its first values, requested before anything is waited for: one trip past the
-        // caches instead of three in a row (rows up to the padded cache exist; those past the last key are not used)
+        // caches instead of three in a row (rows up to the padded cache exist; those past the last key are not used: one row over 8 cached ones is 0.1 us
+        // of 11.3 per layer slower for it, five rows are 0.2 faster, over 200 cached ones all are)
         const int G = P.head_threads, hq = small_div(tid, G), j0 = tid - hq * G;
         f32x4 kfirst[4];
 #pragma unroll
@@ -526,6 +527,12 @@ int32_t csd_f32_part(const csd_model *mod, const GemmW &w, const float *act, int
 // block, full cache: 4 heads of 16, 500 / 2000 / 2600 keys 37 / 48, 73 / 76, 88 / 88; 8 of 16, 120 / 250 / 376 keys 33 / 41, 42 / 43, 51 / 47; 3 of 64,
 // 120 / 376 keys 41 / 49, 71 / 67; 8 of 8, 184 / 376 keys 38 / 40, 51 / 43; 3 of 30, 120 / 376 keys 37 / 45, 63 / 54; 1 of 128, 2600 / 10500 keys
 // 248 / 441, 926 / 1648; 16 of 16 with 5 rows, 56 / 120 keys 42 / 46, 57 / 47.  More rows gain more (256 rows, 4 of 16, 500 / 2600 keys 43 / 82, 98 / 215).
+// Four columns per thread (RowSlice4) where the two wide products of a launch (the first launch has one) come in 36 slices of K together or
+// fewer: the partial sums are added one after the other, and narrow products have many of them.  Forward of four layers, 5 rows over 8 cached, one
+// column / four columns, in us, by gate|up and QKV slices: 32 + 42 (32 features, FFN 64) 47.5 / 50.6; 32 + 21 (64, 64) 47.1 / 48.6; 21 + 21 (64, 96) 47.9 / 48.4;
+// 16 + 28 (48, 128) 47.9 / 47.9; 16 + 21 (64, 128) 47.7 / 48.0; 14 + 21 (64, 144) 49.5 / 48.6; 10 + 21 (64, 192) 50.3 / 48.6; 8 + 21 (32, 256) 49.0 / 48.1; 8 + 21 (64,
+// 256) 50.9 / 48.4; 16 + 10 (64, 128, heads of 128 together) 53.3 / 50.8; 10 + 14 (24, 192) 51.0 / 50.6.
+#define FR_VEC_SLICES 36
 static bool row_product_fits(int K, int N, int per) { return N >= 16 && N <= FR_THREADS && (K + FR_THREADS / N - 1) / (FR_THREADS / N) <= per; }
 static bool row_attention_fits(int H, int dh, int keys) {
     const long long hd = (long long)H * dh;
@@ -578,7 +585,8 @@ static int32_t f32_rows_enqueue(csd_model *mod, void *kv, const int32_t *tokens,
         }
         const int hd = mod->hd, F = c.d_ffn;
         auto four = [](const RowProduct &Q) { return Q.N % 4 == 0 && Q.N >= 64 && (uintptr_t)Q.W % 16 == 0; };
-        const bool vec = four(P.next) && (l < 0 || four(P.gu));
+        auto slices = [](const RowProduct &Q) { return FR_THREADS / (Q.N / 4); };
+        const bool vec = four(P.next) && (l < 0 || four(P.gu)) && slices(P.next) + (l < 0 ? FR_VEC_SLICES / 2 : slices(P.gu)) <= FR_VEC_SLICES;
         const size_t wide = sizeof(float) * 4 * FR_THREADS, lds = vec && scores < wide ? wide : scores;
 #define FR_LAUNCH(FIRST, LAST, PN, W0, W1, Q0, H0)                                                                                       \
     {                                                                                                                                    \

@@ -481,11 +481,13 @@ def test_fp32_forward(P, dims, B, m, t, form):
     ((32, 2, 16, 24, 50), 4, 64, 10, 80), ((32, 2, 16, 24, 50), 4, 65, 10, 80), ((32, 4, 8, 24, 50), 1, 3, 2600, 2688), ((32, 4, 8, 24, 50), 1, 3, 2750, 2816),
     ((40, 1, 130, 9, 129), 1, 3, 50, 64), ((32, 4, 16, 24, 50), 1, 3, 2680, 2688), ((32, 1, 16, 24, 50), 1, 3, 10930, 10944), ((16, 16, 16, 24, 50), 1, 3, 50, 64),
     ((32, 8, 16, 24, 50), 2, 9, 180, 192), ((32, 3, 30, 24, 50), 2, 9, 110, 128),
-    ((64, 1, 24, 32, 64), 1, 3, 20, 64), ((64, 4, 16, 32, 66), 1, 3, 20, 64), ((40, 2, 16, 34, 68), 2, 3, 20, 64), ((96, 4, 16, 31, 60), 1, 3, 20, 64)],
+    ((64, 1, 24, 32, 64), 1, 3, 20, 64), ((64, 4, 16, 32, 66), 1, 3, 20, 64), ((40, 2, 16, 34, 68), 2, 3, 20, 64), ((96, 4, 16, 31, 60), 1, 3, 20, 64),
+    ((64, 3, 20, 146, 512), 1, 3, 20, 64), ((64, 3, 20, 136, 512), 1, 3, 20, 64), ((64, 1, 76, 146, 300), 2, 3, 20, 64), ((16, 1, 6, 256, 512), 1, 3, 20, 64),
+    ((24, 6, 16, 192, 384), 1, 3, 20, 64)],
     ids=lambda x: "-".join(map(str, x)) if isinstance(x, tuple) else None)
 def test_small_fp32_models(P, dims, B, m, t, max_seq):
     """The forward of a workgroup per block row at the edges of what it takes: most values per thread in each product, 1024 and 16 columns, products
-    that are and are not read four columns per thread (64 columns and more, a multiple of 4), heads whose keys are not read 16 values at a time, 256 rows and more, the most scores in LDS, the most features times keys of either kind of head, and more."""
+    that are and are not read four columns per thread (64 columns and more, a multiple of 4, 36 slices of two products or 18 of one), heads whose keys are not read 16 values at a time, 256 rows and more, the most scores in LDS, the most features times keys of either kind of head, and more."""
     from gpu_util import import_synthetic_kv, make_pair, tol_ok
     d, H, dh, F, V = dims
     shape = I.ModelShape("edge_small", 0, "fp32", 2, d, H, dh, F, V)
