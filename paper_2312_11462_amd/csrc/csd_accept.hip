@@ -632,23 +632,26 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
     const uint32_t all = (1u << min(NG, max(0, V - __builtin_amdgcn_readfirstlane(wv) * (64 * RR_PER) + 255) / 256)) - 1;
     uint32_t live = 0;
     if (!raw || probs) {
+        float most[NG];                                          // of a group's four values (NaN is no maximum: it carries no weight either)
 #pragma unroll
-        for (int i = 0; i < RR_PER; i++) {
-            val[i] = scaled_logit(val[i], inv_t);
-            mx = fmaxf(mx, val[i]);
+        for (int j = 0; j < NG; j++) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) val[4 * j + c] = scaled_logit(val[4 * j + c], inv_t);
+            most[j] = fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3]));
+            mx = fmaxf(mx, most[j]);
         }
         mx = block_max<RR_THREADS>(mx, red);
         uint32_t sh = 0, sl = 0;                                 // at most 64 terms of at most 2^20 each
         // e^-28 < 2^-40: groups that far below the maximum have no part in the sum nor, scaled by the lenience, in a draw, and their
         // probabilities are only needed where the caller wants them all.  The line is on the difference that exp_term takes, which is 0 at
         // the maximum whatever its size: mx - 28 is mx itself from 2^29 on, which a temperature of 1e-8 reaches.
-        // All looks first: a wave of which every group matters then does its work without branches.  Five rows of 32000 tokens, whole calls of a
-        // tiny model without / with the looks: every group matters 41.5 / 41.4 us, against draft distributions 41.5 / 41.6, few matter 41.6 / 37.5 and
-        // 41.5 / 37.6 (a look in front of each group's work: 42.1, 43.9, 37.1, 36.8).
+        // All looks first, on maxima that are there already.  Five rows of 32000 tokens, whole calls of a tiny model without / with them: every group
+        // matters 41.5 / 41.5 us, against draft distributions 41.5 / 41.6, few matter 41.5 / 37.4 and 41.5 / 37.4 (with the look in front of each
+        // group's work 42.0, 43.7, 37.5, 37.4; with the work for waves of which every group matters in a copy of its own 41.3, 41.7, 38.5, 38.4).
         const float cut = -28.0f - logf(lenience);
 #pragma unroll
-        for (int j = 0; j < NG; j++)                             // (NaN is no maximum: it carries no weight either)
-            if (__any(fmaxf(fmaxf(val[4 * j], val[4 * j + 1]), fmaxf(val[4 * j + 2], val[4 * j + 3])) - mx > cut)) live |= 1u << j;
+        for (int j = 0; j < NG; j++)
+            if (NG == 1 || __any(most[j] - mx > cut)) live |= 1u << j;
         auto add = [&](int j) {
 #pragma unroll
             for (int c = 0; c < 4; c++) {
@@ -659,19 +662,14 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                 sh += h, sl += l;
             }
         };
-        if (live == all || probs) {                              // without the branches
-            live = all;
+        if (NG == 1 || probs) live = all;
 #pragma unroll
-            for (int j = 0; j < NG; j++) add(j);
-        } else {
+        for (int j = 0; j < NG; j++) {
+            if (NG == 1 || (live >> j & 1)) {
+                add(j);
+            } else {
 #pragma unroll
-            for (int j = 0; j < NG; j++) {
-                if (live >> j & 1) {
-                    add(j);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 4; c++) val[4 * j + c] = 0.f;
-                }
+                for (int c = 0; c < 4; c++) val[4 * j + c] = 0.f;
             }
         }
         r = recip_of_total(block_sum_u64<RR_THREADS>((unsigned long long)sh * (1u << 20) + sl, red64));
@@ -738,7 +736,7 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                         val[4 * j + c] = df > 0.0f ? df : 0.0f;
                     }
                 }
-                if (qrow) {                                  // (behind the loop: in it every group would wait for its own q)
+                if (NG > 1 && qrow) {                        // (behind the loop: in it every group would wait for its own q)
                     live = 0;
 #pragma unroll
                     for (int j = 0; j < NG; j++)
@@ -761,14 +759,9 @@ __global__ __launch_bounds__(RR_THREADS) void k_review_rows(
                     }
                     mine += sh;
                 };
-                if (live == all) {
 #pragma unroll
-                    for (int j = 0; j < NG; j++) add(j);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < NG; j++)
-                        if (live >> j & 1) add(j);
-                }
+                for (int j = 0; j < NG; j++)
+                    if (NG == 1 || (live >> j & 1)) add(j);
                 mine = (mine << 20) + sl;
                 wave_total = wave_sum_u64(mine);
                 __syncthreads();
